@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from oracle import stack as ost
 from oracle import tlq_oracle as orc
 from paper_2602_07899_amd import tlq
 
@@ -19,6 +20,37 @@ def dev(a, gpu, bf16):
 
 def host(t):
     return t.detach().float().cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("seq,heads,samples", [(31, 9, 1), (33, 1, 9), (63, 3, 3), (64, 2, 1), (65, 1, 1), (96, 1, 2),
+                                               (128, 1, 1), (160, 2, 1), (257, 1, 1)])
+def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
+    """64-key steps of two halves, 128-query blocks, eight (sample, head) pairs per grid group."""
+    import torch
+    g = np.random.default_rng([21, seq, heads])
+    n, width = seq * samples, heads * 128
+    rnd = BF if bf16 else F16
+    q, k, v = (np.asarray(rnd(g.standard_normal((n, width)) * 1.5), np.float64) for _ in range(3))
+    want = ost.causal_attention(q, k, v, heads, seq)
+    mag = ost.causal_attention(q, k, np.abs(v), heads, seq)
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    out = torch.empty((n, width), dtype=torch.bfloat16 if bf16 else torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # one rounding of every probability, one of the output
+    assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+
+
+def test_attention_infinite_value_stays_behind_its_key(gpu):
+    """An infinite V row reaches only the queries of its own 32-query block and later ones."""
+    import torch
+    g = np.random.default_rng(22)
+    q, k, v = (F16(g.standard_normal((200, 128))).astype(np.float64) for _ in range(3))
+    v[170] = np.inf
+    out = torch.empty((200, 128), dtype=torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, False), dev(k, gpu, False), dev(v, gpu, False), 1, 200, tlq.params(), out)
+    got = host(out)
+    assert np.all(np.isfinite(got[:160])) and np.all(np.isinf(got[170:]))
 
 
 def test_bf16_results_round_half_to_even(gpu):
