@@ -423,7 +423,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;
   // (with activation quantisation 1/s belongs to Q_a's argument, so the weights stay unfolded)
   q.s_table = s.s_table; q.inv_table = act ? nullptr : s.inv_table; q.n_cand = n_alpha;
-  q.what = s.what; q.what_cand_stride = c_out * c_in; q.what_f16 = true;
+  q.what = s.what; q.what_cand_stride = c_out * c_in;
   q.diff = diff; q.xmax_bits = (diff && bf16) ? s.xmax : nullptr;
   TLQ_HIP(launch_fake_quant(q, st));
   if (diff) {  // D0 = Y_ref - X W^T (exact products of the 16-bit inputs, float accumulation)
@@ -584,7 +584,7 @@ tlq_status tlq_scale_search_gram(const void* gram, int64_t c_in, const void* W, 
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = p->x_dtype == TLQ_BF16;
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;
   q.s_table = s.s_table; q.inv_table = s.inv_table; q.n_cand = n_alpha;
-  q.what = s.dq; q.what_cand_stride = c_out * c_in; q.what_f16 = true;
+  q.what = s.dq; q.what_cand_stride = c_out * c_in;
   q.diff = true; q.xmax_bits = nullptr; q.col_scale = v.col_scale;
   TLQ_HIP(launch_fake_quant(q, st));
   // partial = sum_{o,i} (D'_k C)[o,i] D'_k[o,i]: the weight rows play the tokens, C the weights
@@ -666,7 +666,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;
   q.s_table = s; q.inv_table = act ? nullptr : inv; q.n_cand = 1; q.what = what; q.what_cand_stride = 0;
-  q.what_f16 = true;
+ 
   TLQ_HIP(launch_fake_quant(q, st));
   GemmArgs g{};
   g.X = xh ? (const void*)xh : X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = xh ? c_in : ldx;

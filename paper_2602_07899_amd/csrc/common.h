@@ -82,8 +82,8 @@ __host__ __device__ inline int shift_from_bf16_bits(uint32_t bits) {
 }
 
 // S2.  Quantises W*diag(s_k) for n_cand candidates (s_table row stride c_in).
-// what:  folded operand deq/s as 16-bit [n_cand, c_out, c_in] (row stride c_in) or NULL
-// codes/zp/delta/wdq: single-candidate auxiliary outputs or NULL
+// what:  folded operand deq/s as fp16 [n_cand, c_out, c_in] (row stride c_in), or NULL: then
+// codes/zp/delta/wdq, the single-candidate outputs (each may be NULL), are written instead
 struct QuantArgs {
   const void* W; int64_t c_out, c_in, ldw; bool bf16;
   int bits, group, symmetric;
@@ -91,7 +91,6 @@ struct QuantArgs {
   const float* inv_table; // [n_cand, c_in] or NULL (ones); used only for `what`
   int n_cand;
   void* what; int64_t what_cand_stride;  // elements between candidates
-  bool what_f16;          // round `what` to fp16 even when W is bf16
   uint8_t* codes; uint8_t* zp; float* delta; void* wdq; int64_t ld_dq;
   // difference form: `what` receives deq*inv - W*2^shift (shift from xmax_bits, 0 when NULL)
   bool diff; const uint32_t* xmax_bits;

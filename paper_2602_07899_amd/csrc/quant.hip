@@ -10,6 +10,8 @@
 // the contraction kernel multiplies with the *unscaled* tokens (the smoothing
 // identity of Sec. 2.2 moves diag(s)^-1 from X onto the dequantised weights).
 // HBM traffic per weight element: 2 B read + 2 B written per candidate.
+#include <type_traits>
+
 #include "common.h"
 
 namespace tlq {
@@ -17,166 +19,323 @@ namespace tlq {
 struct QuantDev {
   const uint16_t* W; int64_t c_out, c_in, ldw;
   float qmax, qlo, qhi; int half;  // asym: codes in [0,qmax]; sym: q in [qlo,qhi], half = 2^(bits-1)
-  int group;                        // resolved group size (>= 8)
+  float rq;                        // fl(1 / qmax) or fl(1 / qhi)
+  int64_t group;                   // resolved group size (>= 8)
   const float* s_table; const float* inv_table; int n_cand;
-  uint16_t* what; int64_t what_cand_stride; bool what_f16;
+  int cand_step;                   // candidates per block (blockIdx.y picks the stretch)
+  uint16_t* what; int64_t what_cand_stride;
   uint8_t* codes; uint8_t* zp; float* delta; uint16_t* wdq; int64_t ld_dq;
   bool diff; const uint32_t* xmax_bits;  // what = deq*inv - W*2^shift
   const float* col_scale;                // [c_in] factor on `what` or NULL
 };
 
+// What a launch writes: the folded operands of the candidates, their difference form, or the
+// single-candidate outputs (codes, zero points, steps, dequantised weights).
+enum { Q_FOLD = 0, Q_DIFF = 1, Q_AUX = 2 };
+
+// Grid of one group: step, an approximate reciprocal, zero point; `slow` asks for true divisions.
+struct Grid { float delta, rd, zpf; bool slow; };
+
+// The integer codes need rint(fl(x / delta)).  With rd within one ulp of 1/delta, t = fl(x * rd) lies
+// within 2.4e-7 |t| of the rounded quotient, so rint(t) is that integer unless a half-integer sits inside
+// the gap; `tie_measure` below `kTieLimit` rules that out (with a factor of two to spare), and the rare
+// rest (one element in 10^5 at 4 bits) is divided.
+constexpr float kTieLimit = 0.49999976f;
+__device__ __forceinline__ float tie_measure(float t, float n) { return __builtin_fmaf(fabsf(t), 4.8e-7f, fabsf(t - n)); }
+
+// mx/mn: group maximum and minimum of ws (SYM: mx = max |ws|).  range / (2^b - 1) by a correction step on
+// range * fl(1 / (2^b - 1)): equal to the division for every significand and all eight divisors
+// (checked exhaustively); outside [1e-5, 1e36) and for NaN the division itself is used everywhere.
 template <bool SYM>
-__device__ __forceinline__ void grid_params(float mx, float mn, const QuantDev& a, float& delta,
-                                            float& zpf) {
-  if (!SYM) {
-    float rng = mx - mn;
-    rng = fmaxf(rng, kRangeFloor);
-    delta = rng / a.qmax;
-    float z = rintf((-mn) / delta);
-    zpf = fminf(fmaxf(z, 0.0f), a.qmax);
+__device__ __forceinline__ Grid make_grid(float mx, float mn, const QuantDev& a) {
+  Grid g;
+  const float rng = fmaxf(SYM ? mx : mx - mn, kRangeFloor);
+  const float dv = SYM ? a.qhi : a.qmax;
+  g.slow = !(rng < 1e36f);
+  const float q0 = rng * a.rq;
+  g.delta = __builtin_fmaf(__builtin_fmaf(-q0, dv, rng), a.rq, q0);
+  if (g.slow) {
+    asm volatile("" ::: "memory");     // a branch, not a division that is computed and dropped
+    g.delta = rng / dv;
+  }
+  g.rd = __builtin_amdgcn_rcpf(g.delta);
+  if (SYM) {
+    g.zpf = (float)a.half;
   } else {
-    const float amax = fmaxf(mx, kRangeFloor);  // mx carries max|ws|
-    delta = amax / a.qhi;
-    zpf = (float)a.half;
+    const float x = -mn, t = x * g.rd;
+    float z = rintf(t);
+    if (g.slow || !(tie_measure(t, z) < kTieLimit)) z = rintf(x / g.delta);
+    g.zpf = fminf(fmaxf(z, 0.0f), a.qmax);
+  }
+  return g;
+}
+
+// rint(fl(ws / delta)) of eight values, one test for all of them
+__device__ __forceinline__ void rint_quotient8(const float (&ws)[8], const Grid& g, float (&n)[8]) {
+  float e = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float t = ws[j] * g.rd;
+    n[j] = rintf(t);
+    e = fmaxf(e, tie_measure(t, n[j]));
+  }
+  if (g.slow || !(e < kTieLimit)) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) n[j] = rintf(ws[j] / g.delta);
   }
 }
 
-// rint(fl(ws / delta)) without a division per element.  With r = fl(1/delta),
-// t = fl(ws * r) lies within 3 * 2^-24 * |Q| of the correctly rounded quotient q of
-// Q = ws/delta, so rint(t) == rint(q) unless a half-integer sits inside that gap.  When t is
-// that close to a half-integer (about one element in 10^5) the true division decides.
-__device__ __forceinline__ float rint_quotient(float ws, float delta, float rdelta) {
-  const float t = ws * rdelta;
-  float n = rintf(t);
-  const float gap = 0.5f - fabsf(t - n);                  // distance of t to the nearest tie
-  if (!(gap > fabsf(t) * 4.8e-7f + 2.4e-7f)) n = rintf(ws / delta);   // also taken for NaN/inf
-  return n;
+__device__ __forceinline__ void load8(const float* __restrict__ p, float (&v)[8]) {
+  const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
-
+template <typename T>
+__device__ __forceinline__ void widen8(const uint4& v, float (&w)[8]) {
+  const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) w[j] = T::to_float((uint16_t)(u[j >> 1] >> ((j & 1) * 16)));
+}
 template <bool SYM>
-__device__ __forceinline__ void quant_one(float ws, float delta, float rdelta, float zpf,
-                                          const QuantDev& a, float& code, float& deq) {
-  if (!SYM) {
-    float q = rint_quotient(ws, delta, rdelta) + zpf;
-    q = fminf(fmaxf(q, 0.0f), a.qmax);
-    code = q;
-    deq = (q - zpf) * delta;
-  } else {
-    float q = rint_quotient(ws, delta, rdelta);
-    q = fminf(fmaxf(q, a.qlo), a.qhi);
-    code = q + zpf;
-    deq = q * delta;
+__device__ __forceinline__ void range8(const float (&ws)[8], float& mx, float& mn) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    mx = fmaxf(mx, SYM ? fabsf(ws[j]) : ws[j]);
+    if (!SYM) mn = fminf(mn, ws[j]);
   }
 }
 
-// Fast path: group is a power of two in [8, 512].  A lane owns 8 consecutive
-// input channels; a group is `group/8` adjacent lanes; a wave covers 512
-// channels of one output row.  Min/max go through a butterfly inside the
-// lane group; W stays in registers while the candidates are looped over.
-// AUX = false drops the single-candidate outputs (codes, zero points, steps, dequantised
-// weights) at compile time: the search only needs the folded operands.
-template <typename T, bool SYM, bool AUX>
+// Eight quantised values of row `row`, channels c .. c+7 go to memory (`what`: their place in the operand).
+template <typename T, bool SYM, int MODE>
+__device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const float (&w)[8], const float (&ws)[8],
+                                      const float (&inv)[8], const float (&cs)[8], float wsub, uint16_t* what,
+                                      int64_t row, int64_t c) {
+  float n[8];
+  rint_quotient8(ws, g, n);
+  uint32_t hw[4] = {0, 0, 0, 0}, cw[2] = {0, 0};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if constexpr (MODE == Q_AUX) {
+      float code, deq;
+      if (!SYM) {
+        code = fminf(fmaxf(n[j] + g.zpf, 0.0f), a.qmax);
+        deq = (code - g.zpf) * g.delta;
+      } else {
+        const float q = fminf(fmaxf(n[j], a.qlo), a.qhi);
+        code = q + g.zpf;
+        deq = q * g.delta;
+      }
+      // deq is rounded to float before it is rounded to 16 bits: keep the product and the conversion from
+      // becoming one mixed-precision instruction, which rounds once
+      asm("" : "+v"(deq));
+      cw[j >> 2] |= ((uint32_t)code & 0xffu) << ((j & 3) * 8);
+      hw[j >> 1] |= (uint32_t)T::from_float(deq) << ((j & 1) * 16);
+    } else {
+      // (clip(n + zp, 0, qmax) - zp) of small integers is clip(n, -zp, qmax - zp)
+      const float lo = SYM ? a.qlo : -g.zpf, hi = SYM ? a.qhi : a.qmax - g.zpf;
+      // (a NaN weight quantises to `lo` like in the two-step clip)
+      float f = __builtin_amdgcn_fmed3f(n[j], lo, hi) * g.delta * inv[j];
+      if constexpr (MODE == Q_DIFF) {
+        f -= w[j] * wsub;
+        f *= cs[j];
+      }
+      hw[j >> 1] |= (uint32_t)F16::from_float(f) << ((j & 1) * 16);
+    }
+  }
+  const uint4 out = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+  if constexpr (MODE == Q_AUX) {
+    if (a.codes) *reinterpret_cast<uint2*>(a.codes + row * a.c_in + c) = make_uint2(cw[0], cw[1]);
+    if (a.wdq) *reinterpret_cast<uint4*>(a.wdq + row * a.ld_dq + c) = out;
+  } else {
+    *reinterpret_cast<uint4*>(what) = out;
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+// maximum (MAX) or minimum over aligned runs of `lanes` lanes (a power of two); every lane gets it.  Up to
+// 16 lanes stay inside a DPP row: quad permutes, then the mirrors of 8 and 16 lanes.
+template <bool MAX>
+__device__ __forceinline__ float lanes_reduce(float v, int lanes) {
+  auto op = [](float x, float y) { return MAX ? fmaxf(x, y) : fminf(x, y); };
+  if (lanes >= 2) v = op(v, dpp<0xB1>(v));
+  if (lanes >= 4) v = op(v, dpp<0x4E>(v));
+  if (lanes >= 8) v = op(v, dpp<0x141>(v));
+  if (lanes >= 16) v = op(v, dpp<0x140>(v));
+  if (lanes >= 32) v = op(v, __shfl_xor(v, 16, 64));
+  if (lanes >= 64) v = op(v, __shfl_xor(v, 32, 64));
+  return v;
+}
+
+__device__ __forceinline__ float diff_factor(const QuantDev& a) {
+  return a.xmax_bits ? __builtin_ldexpf(1.0f, shift_from_bf16_bits(*a.xmax_bits)) : 1.0f;
+}
+
+// Groups of a power of two up to 512.  A lane owns 8 consecutive input channels of R rows, a group is
+// `group/8` adjacent lanes, a wave covers 512 channels; W stays in registers while the candidates are
+// walked, a candidate's scales are loaded once for the R rows.  Bound by vector ALU issue: ~130
+// wave instructions per 512 weights and candidate (250 with a division and a tie branch per element,
+// divisions for step and zero point, and shuffles through LDS).  20 candidates of 4096 x 4096 (0.7 GB
+// written): 278 -> 195 us.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).
+template <typename T, bool SYM, int MODE, int R, int LPG>
 __global__ __launch_bounds__(256) void quant_pow2_kernel(QuantDev a) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int64_t cblocks = (a.c_in + 511) / 512;
-  const int64_t row = wave / cblocks;
-  if (row >= a.c_out) return;
+  const int64_t row0 = wave / cblocks * R;
+  if (row0 >= a.c_out) return;
   const int64_t c = (wave % cblocks) * 512 + lane * 8;
   const bool active = c < a.c_in;
-  const int lpg = a.group >> 3;
+  const int lpg = LPG > 0 ? LPG : (int)(a.group >> 3);
 
-  float w[8];
-  {
+  float w[R][8];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
     uint4 v = make_uint4(0, 0, 0, 0);
-    if (active) v = *reinterpret_cast<const uint4*>(a.W + row * a.ldw + c);
-    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) w[j] = T::to_float((uint16_t)(u[j >> 1] >> ((j & 1) * 16)));
+    if (active && row0 + r < a.c_out) v = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + c);
+    widen8<T>(v, w[r]);
   }
-  const int64_t gidx = row * (a.c_in / a.group) + c / a.group;
-
-  const float wsub = a.diff ? (a.xmax_bits ? __builtin_ldexpf(1.0f, shift_from_bf16_bits(*a.xmax_bits)) : 1.0f) : 0.0f;
-  float cs[8];
+  const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
+  float s[8], inv[8], cs[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) cs[j] = 1.0f;
-  if (active && a.col_scale) {
-    const float4 c0 = *reinterpret_cast<const float4*>(a.col_scale + c);
-    const float4 c1 = *reinterpret_cast<const float4*>(a.col_scale + c + 4);
-    cs[0] = c0.x; cs[1] = c0.y; cs[2] = c0.z; cs[3] = c0.w;
-    cs[4] = c1.x; cs[5] = c1.y; cs[6] = c1.z; cs[7] = c1.w;
-  }
-  for (int k = 0; k < a.n_cand; ++k) {
-    float s[8], inv[8];
+  for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; cs[j] = 1.0f; }
+  if (MODE == Q_DIFF && active && a.col_scale) load8(a.col_scale + c, cs);
+  const int k0 = (int)blockIdx.y * a.cand_step;
+  const int k1 = k0 + a.cand_step < a.n_cand ? k0 + a.cand_step : a.n_cand;
+  const float* ps = a.s_table && active ? a.s_table + (int64_t)k0 * a.c_in + c : nullptr;
+  const float* pi = MODE != Q_AUX && a.inv_table && active ? a.inv_table + (int64_t)k0 * a.c_in + c : nullptr;
+  uint16_t* out = MODE != Q_AUX ? a.what + (int64_t)k0 * a.what_cand_stride + row0 * a.c_in + c : nullptr;
+#pragma unroll 1
+  for (int k = k0; k < k1; ++k) {
+    if (ps) { load8(ps, s); ps += a.c_in; }
+    if (pi) { load8(pi, inv); pi += a.c_in; }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; }
-    if (active && a.s_table) {
-      const float4 s0 = *reinterpret_cast<const float4*>(a.s_table + (int64_t)k * a.c_in + c);
-      const float4 s1 = *reinterpret_cast<const float4*>(a.s_table + (int64_t)k * a.c_in + c + 4);
-      s[0] = s0.x; s[1] = s0.y; s[2] = s0.z; s[3] = s0.w;
-      s[4] = s1.x; s[5] = s1.y; s[6] = s1.z; s[7] = s1.w;
-    }
-    if (active && a.inv_table && a.what) {
-      const float4 i0 = *reinterpret_cast<const float4*>(a.inv_table + (int64_t)k * a.c_in + c);
-      const float4 i1 = *reinterpret_cast<const float4*>(a.inv_table + (int64_t)k * a.c_in + c + 4);
-      inv[0] = i0.x; inv[1] = i0.y; inv[2] = i0.z; inv[3] = i0.w;
-      inv[4] = i1.x; inv[5] = i1.y; inv[6] = i1.z; inv[7] = i1.w;
-    }
-    float ws[8];
+    for (int r = 0; r < R; ++r) {
+      float ws[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
-    float mx, mn;
-    if (!SYM) {
-      mx = ws[0]; mn = ws[0];
-#pragma unroll
-      for (int j = 1; j < 8; ++j) { mx = fmaxf(mx, ws[j]); mn = fminf(mn, ws[j]); }
-    } else {
-      mx = fabsf(ws[0]); mn = 0.0f;
-#pragma unroll
-      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, fabsf(ws[j]));
-    }
-    for (int off = 1; off < lpg; off <<= 1) {
-      mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      if (!SYM) mn = fminf(mn, __shfl_xor(mn, off, 64));
-    }
-    float delta, zpf;
-    grid_params<SYM>(mx, mn, a, delta, zpf);
-    const float rdelta = 1.0f / delta;
-
-    uint32_t cw[2] = {0, 0};
-    uint32_t hw[4] = {0, 0, 0, 0}, dw[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float code, deq;
-      quant_one<SYM>(ws[j], delta, rdelta, zpf, a, code, deq);
-      float folded = deq * inv[j];
-      if (a.diff) folded -= w[j] * wsub;
-      if (a.col_scale) folded *= cs[j];
-      hw[j >> 1] |= (uint32_t)(a.what_f16 ? F16::from_float(folded) : T::from_float(folded)) << ((j & 1) * 16);
-      if (AUX) {
-        cw[j >> 2] |= ((uint32_t)code & 0xffu) << ((j & 3) * 8);
-        dw[j >> 1] |= (uint32_t)T::from_float(deq) << ((j & 1) * 16);
+      for (int j = 0; j < 8; ++j) ws[j] = w[r][j] * s[j];
+      float mx = SYM ? fabsf(ws[0]) : ws[0], mn = ws[0];
+      range8<SYM>(ws, mx, mn);
+      mx = lanes_reduce<true>(mx, lpg);
+      if (!SYM) mn = lanes_reduce<false>(mn, lpg);
+      const Grid g = make_grid<SYM>(mx, mn, a);
+      if (!active || row0 + r >= a.c_out) continue;
+      emit8<T, SYM, MODE>(a, g, w[r], ws, inv, cs, wsub, MODE != Q_AUX ? out + r * a.c_in : nullptr, row0 + r, c);
+      if (MODE == Q_AUX && (lane & (lpg - 1)) == 0) {
+        const int64_t gidx = (row0 + r) * (a.c_in / a.group) + c / a.group;
+        if (a.zp) a.zp[gidx] = (uint8_t)g.zpf;
+        if (a.delta) a.delta[gidx] = g.delta;
       }
     }
-    if (!active) continue;
-    if (a.what)
-      *reinterpret_cast<uint4*>(a.what + (int64_t)k * a.what_cand_stride + row * a.c_in + c) =
-          make_uint4(hw[0], hw[1], hw[2], hw[3]);
-    if (AUX && k == 0) {  // auxiliary outputs describe a single candidate
-      if (a.codes) *reinterpret_cast<uint2*>(a.codes + row * a.c_in + c) = make_uint2(cw[0], cw[1]);
-      if (a.wdq)
-        *reinterpret_cast<uint4*>(a.wdq + row * a.ld_dq + c) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
-      if ((lane & (lpg - 1)) == 0) {
-        if (a.zp) a.zp[gidx] = (uint8_t)zpf;
-        if (a.delta) a.delta[gidx] = delta;
+    if (MODE != Q_AUX) out += a.what_cand_stride;
+  }
+}
+
+// Any other group up to 16384 channels, whole rows among them: NWG waves (1 or 4) own one group of R
+// rows, a lane CH chunks of 8 channels, `64 NWG` chunks apart.  The weights stay packed in registers, each
+// candidate's scales are read twice (range, then codes; the second time from L1) for R rows.  20
+// candidates of 4096 x 4096, group = row: 1143 -> 190 us (2-byte loads, two sweeps over W before).
+template <typename T, bool SYM, int MODE, int NWG, int CH, int R>
+__global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
+  __shared__ float red[2][4][2 * R];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t G = a.c_in / a.group;
+  const int64_t unit = NWG == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wv;
+  const int64_t row0 = unit / G * R, gi = unit % G;
+  if (NWG == 1 && row0 >= a.c_out) return;
+  const int64_t cl = ((NWG == 4 ? wv * 64 : 0) + lane) * 8;    // channel of chunk 0 inside the group
+  const int64_t cg = gi * a.group;
+  constexpr int64_t STEP = (int64_t)NWG * 512;
+
+  uint4 wp[R][CH];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      wp[r][i] = make_uint4(0, 0, 0, 0);
+      if (row0 + r < a.c_out && cl + i * STEP < a.group)
+        wp[r][i] = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + cg + cl + i * STEP);
+    }
+  const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
+  float s[8], inv[8], cs[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; cs[j] = 1.0f; }
+  const int k0 = (int)blockIdx.y * a.cand_step;
+  const int k1 = k0 + a.cand_step < a.n_cand ? k0 + a.cand_step : a.n_cand;
+#pragma unroll 1
+  for (int k = k0; k < k1; ++k) {
+    float mx[R], mn[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) { mx[r] = SYM ? 0.0f : -__builtin_inff(); mn[r] = __builtin_inff(); }
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      if (cl + i * STEP >= a.group) continue;
+      if (a.s_table) load8(a.s_table + (int64_t)k * a.c_in + cg + cl + i * STEP, s);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float ws[8];
+        widen8<T>(wp[r][i], ws);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ws[j] *= s[j];
+        range8<SYM>(ws, mx[r], mn[r]);
       }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      mx[r] = lanes_reduce<true>(mx[r], 64);
+      if (!SYM) mn[r] = lanes_reduce<false>(mn[r], 64);
+    }
+    if constexpr (NWG == 4) {
+      // two buffers: the next candidate's writes cannot overtake this one's reads past one barrier
+      float* rb = &red[k & 1][0][0];
+      if (lane == 0)
+#pragma unroll
+        for (int r = 0; r < R; ++r) { rb[wv * 2 * R + 2 * r] = mx[r]; rb[wv * 2 * R + 2 * r + 1] = mn[r]; }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          mx[r] = fmaxf(mx[r], rb[v * 2 * R + 2 * r]);
+          if (!SYM) mn[r] = fminf(mn[r], rb[v * 2 * R + 2 * r + 1]);
+        }
+    }
+    Grid g[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) g[r] = make_grid<SYM>(mx[r], mn[r], a);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int64_t c = cg + cl + i * STEP;
+      if (cl + i * STEP >= a.group) continue;
+      if (a.s_table) load8(a.s_table + (int64_t)k * a.c_in + c, s);
+      if (MODE != Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
+      if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (row0 + r >= a.c_out) continue;
+        float w[8], ws[8];
+        widen8<T>(wp[r][i], w);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
+        emit8<T, SYM, MODE>(a, g[r], w, ws, inv, cs, wsub,
+                            MODE != Q_AUX ? a.what + (int64_t)k * a.what_cand_stride + (row0 + r) * a.c_in + c : nullptr,
+                            row0 + r, c);
+      }
+    }
+    if (MODE == Q_AUX && cl == 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (row0 + r < a.c_out) {
+          if (a.zp) a.zp[(row0 + r) * G + gi] = (uint8_t)g[r].zpf;
+          if (a.delta) a.delta[(row0 + r) * G + gi] = g[r].delta;
+        }
     }
   }
 }
 
-// General path: any group size that is a multiple of 8 (including the whole
-// row).  One wave per (row, group); two sweeps over the group per candidate.
-template <typename T, bool SYM>
+// Groups beyond 16384 channels: one wave per (row, group), two sweeps over the group per candidate.
+template <typename T, bool SYM, int MODE>
 __global__ __launch_bounds__(256) void quant_any_kernel(QuantDev a) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -184,43 +343,38 @@ __global__ __launch_bounds__(256) void quant_any_kernel(QuantDev a) {
   if (wave >= a.c_out * G) return;
   const int64_t row = wave / G;
   const int64_t c0 = (wave % G) * a.group;
-  const float wsub = a.diff ? (a.xmax_bits ? __builtin_ldexpf(1.0f, shift_from_bf16_bits(*a.xmax_bits)) : 1.0f) : 0.0f;
+  const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
+  float s[8], inv[8], cs[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; cs[j] = 1.0f; }
   for (int k = 0; k < a.n_cand; ++k) {
     const float* sk = a.s_table ? a.s_table + (int64_t)k * a.c_in : nullptr;
-    const float* ik = (a.inv_table && a.what) ? a.inv_table + (int64_t)k * a.c_in : nullptr;
     float mx = SYM ? 0.0f : -__builtin_inff(), mn = __builtin_inff();
-    for (int64_t c = c0 + lane; c < c0 + a.group; c += 64) {
-      const float ws = T::to_float(a.W[row * a.ldw + c]) * (sk ? sk[c] : 1.0f);
-      if (!SYM) { mx = fmaxf(mx, ws); mn = fminf(mn, ws); } else mx = fmaxf(mx, fabsf(ws));
-    }
+    for (int64_t c = c0 + lane * 8; c < c0 + a.group; c += 512) {
+      float ws[8];
+      widen8<T>(*reinterpret_cast<const uint4*>(a.W + row * a.ldw + c), ws);
+      if (sk) load8(sk + c, s);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      if (!SYM) mn = fminf(mn, __shfl_xor(mn, off, 64));
+      for (int j = 0; j < 8; ++j) ws[j] *= s[j];
+      range8<SYM>(ws, mx, mn);
     }
-    float delta, zpf;
-    grid_params<SYM>(mx, mn, a, delta, zpf);
-    const float rdelta = 1.0f / delta;
-    for (int64_t c = c0 + lane; c < c0 + a.group; c += 64) {
-      const float ws = T::to_float(a.W[row * a.ldw + c]) * (sk ? sk[c] : 1.0f);
-      float code, deq;
-      quant_one<SYM>(ws, delta, rdelta, zpf, a, code, deq);
-      if (a.what)
-        {
-          float folded = deq * (ik ? ik[c] : 1.0f);
-          if (a.diff) folded -= T::to_float(a.W[row * a.ldw + c]) * wsub;
-          if (a.col_scale) folded *= a.col_scale[c];
-          a.what[(int64_t)k * a.what_cand_stride + row * a.c_in + c] =
-              a.what_f16 ? F16::from_float(folded) : T::from_float(folded);
-        }
-      if (k == 0) {
-        if (a.codes) a.codes[row * a.c_in + c] = (uint8_t)code;
-        if (a.wdq) a.wdq[row * a.ld_dq + c] = T::from_float(deq);
-      }
+    mx = lanes_reduce<true>(mx, 64);
+    if (!SYM) mn = lanes_reduce<false>(mn, 64);
+    const Grid g = make_grid<SYM>(mx, mn, a);
+    for (int64_t c = c0 + lane * 8; c < c0 + a.group; c += 512) {
+      float w[8], ws[8];
+      widen8<T>(*reinterpret_cast<const uint4*>(a.W + row * a.ldw + c), w);
+      if (sk) load8(sk + c, s);
+      if (MODE != Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
+      if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
+      emit8<T, SYM, MODE>(a, g, w, ws, inv, cs, wsub,
+                          MODE != Q_AUX ? a.what + (int64_t)k * a.what_cand_stride + row * a.c_in + c : nullptr, row, c);
     }
-    if (k == 0 && lane == 0) {
-      if (a.zp) a.zp[wave] = (uint8_t)zpf;
-      if (a.delta) a.delta[wave] = delta;
+    if (MODE == Q_AUX && lane == 0) {
+      if (a.zp) a.zp[wave] = (uint8_t)g.zpf;
+      if (a.delta) a.delta[wave] = g.delta;
     }
   }
 }
@@ -238,6 +392,15 @@ __global__ __launch_bounds__(256) void quant_any_kernel(QuantDev a) {
 // path and the per-token step is applied to the accumulators in its epilogue.
 constexpr int kAqRows = 8;      // rows per wave
 constexpr int kAqCols = 512;    // channels per block strip (64 lanes x 8)
+
+// rint(fl(x / sigma)) without a division per element: see tie_measure; rsig = fl(1 / sigma)
+__device__ __forceinline__ float rint_quotient(float x, float sigma, float rsig) {
+  const float t = x * rsig;
+  float n = rintf(t);
+  const float gap = 0.5f - fabsf(t - n);                  // distance of t to the nearest tie
+  if (!(gap > fabsf(t) * 4.8e-7f + 2.4e-7f)) n = rintf(x / sigma);   // also taken for NaN/inf
+  return n;
+}
 
 template <typename T>
 __device__ __forceinline__ void aq_load_tile(const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in,
@@ -351,46 +514,75 @@ hipError_t launch_act_quant(const void* X, int64_t n_tok, int64_t c_in, int64_t 
   return hipGetLastError();
 }
 
+template <typename T, bool SYM, int MODE>
+static void launch_quant(QuantDev d, hipStream_t stream) {
+  // Enough blocks to fill the chip: the candidates of small matrices are split over blockIdx.y (W is
+  // read again per stretch, from L2).  `waves` counts the waves of one stretch; 8192 = 8 per SIMD.
+  auto grid = [&](int64_t blocks, int64_t waves) {
+    int64_t split = waves < 8192 ? 8192 / waves : 1;
+    if (split > d.n_cand) split = d.n_cand;
+    d.cand_step = (int)ceil_div(d.n_cand, split);
+    return dim3((unsigned)blocks, (unsigned)ceil_div(d.n_cand, d.cand_step));
+  };
+  if (d.group <= 512 && (d.group & (d.group - 1)) == 0) {
+    // rows per wave by size: two share the scale loads once there is work for every SIMD anyway
+    constexpr int R = MODE == Q_AUX ? 1 : 2;
+    const int64_t per_row = ceil_div(d.c_in, 512);
+    const bool two = R == 2 && ceil_div(d.c_out, 2) * per_row * d.n_cand >= 8192;
+    const int64_t waves = ceil_div(d.c_out, two ? 2 : 1) * per_row;
+    const dim3 g = grid(ceil_div(waves, 4), waves);
+    if (two && d.group == 128) quant_pow2_kernel<T, SYM, MODE, R, 16><<<g, 256, 0, stream>>>(d);
+    else if (two) quant_pow2_kernel<T, SYM, MODE, R, 0><<<g, 256, 0, stream>>>(d);
+    else if (d.group == 128) quant_pow2_kernel<T, SYM, MODE, 1, 16><<<g, 256, 0, stream>>>(d);
+    else quant_pow2_kernel<T, SYM, MODE, 1, 0><<<g, 256, 0, stream>>>(d);
+    return;
+  }
+  const int64_t G = d.c_in / d.group;
+  auto one = [&](auto kern, int rows) {     // a wave per group
+    const int64_t waves = ceil_div(d.c_out, rows) * G;
+    const dim3 g = grid(ceil_div(waves, 4), waves);
+    kern<<<g, 256, 0, stream>>>(d);
+  };
+  auto four = [&](auto kern, int rows) {    // a block per group
+    const int64_t blocks = ceil_div(d.c_out, rows) * G;
+    const dim3 g = grid(blocks, 4 * blocks);
+    kern<<<g, 256, 0, stream>>>(d);
+  };
+  // rows x chunks = 8 packed registers quads per lane; a block per group from 2048 channels on (a wave alone
+  // would need more than four chunks a lane)
+  if (d.group <= 512) one(quant_row_kernel<T, SYM, MODE, 1, 1, 4>, 4);
+  else if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
+  else if (d.group <= 2048) one(quant_row_kernel<T, SYM, MODE, 1, 4, 2>, 2);
+  else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 4>, 4);
+  else if (d.group <= 8192) four(quant_row_kernel<T, SYM, MODE, 4, 4, 2>, 2);
+  else if (d.group <= 16384) four(quant_row_kernel<T, SYM, MODE, 4, 8, 1>, 1);
+  else quant_any_kernel<T, SYM, MODE><<<(unsigned)ceil_div(d.c_out * G, 4), 256, 0, stream>>>(d);
+}
+
 hipError_t launch_fake_quant(const QuantArgs& q, hipStream_t stream) {
   QuantDev d;
   d.W = (const uint16_t*)q.W; d.c_out = q.c_out; d.c_in = q.c_in; d.ldw = q.ldw;
   d.qmax = (float)((1 << q.bits) - 1);
   d.half = 1 << (q.bits - 1);
   d.qlo = -(float)d.half; d.qhi = (float)(d.half - 1);
-  d.group = q.group == 0 ? (int)q.c_in : q.group;
-  d.s_table = q.s_table; d.inv_table = q.inv_table; d.n_cand = q.n_cand;
-  d.what = (uint16_t*)q.what; d.what_cand_stride = q.what_cand_stride; d.what_f16 = q.what_f16;
+  d.rq = 1.0f / (q.symmetric ? d.qhi : d.qmax);
+  d.group = q.group == 0 ? q.c_in : q.group;
+  d.s_table = q.s_table; d.inv_table = q.inv_table; d.n_cand = q.n_cand; d.cand_step = q.n_cand;
+  d.what = (uint16_t*)q.what; d.what_cand_stride = q.what_cand_stride;
   d.codes = q.codes; d.zp = q.zp; d.delta = q.delta; d.wdq = (uint16_t*)q.wdq; d.ld_dq = q.ld_dq;
   d.diff = q.diff; d.xmax_bits = q.xmax_bits; d.col_scale = q.col_scale;
-  const bool pow2 = d.group >= 8 && d.group <= 512 && (d.group & (d.group - 1)) == 0;
   const double bytes = (double)q.c_out * (double)q.c_in * (2.0 + 2.0 * (q.what ? q.n_cand : 0) +
                                                            (q.codes ? 1.0 : 0.0) + (q.wdq ? 2.0 : 0.0));
   ProfScope ps("fake_quant", stream, bytes);
-  const bool sym = q.symmetric != 0;
-  if (pow2) {
-    const int64_t waves = q.c_out * ceil_div(q.c_in, 512);
-    const unsigned grid = (unsigned)ceil_div(waves, 4);
-    const bool aux = q.codes || q.zp || q.delta || q.wdq;
-    auto go = [&](auto kern) { kern<<<grid, 256, 0, stream>>>(d); };
-    if (aux) {
-      if (!q.bf16 && !sym) go(quant_pow2_kernel<F16, false, true>);
-      else if (!q.bf16) go(quant_pow2_kernel<F16, true, true>);
-      else if (!sym) go(quant_pow2_kernel<BF16, false, true>);
-      else go(quant_pow2_kernel<BF16, true, true>);
-    } else {
-      if (!q.bf16 && !sym) go(quant_pow2_kernel<F16, false, false>);
-      else if (!q.bf16) go(quant_pow2_kernel<F16, true, false>);
-      else if (!sym) go(quant_pow2_kernel<BF16, false, false>);
-      else go(quant_pow2_kernel<BF16, true, false>);
-    }
-  } else {
-    const int64_t waves = q.c_out * (q.c_in / d.group);
-    const unsigned grid = (unsigned)ceil_div(waves, 4);
-    if (!q.bf16 && !sym) quant_any_kernel<F16, false><<<grid, 256, 0, stream>>>(d);
-    else if (!q.bf16) quant_any_kernel<F16, true><<<grid, 256, 0, stream>>>(d);
-    else if (!sym) quant_any_kernel<BF16, false><<<grid, 256, 0, stream>>>(d);
-    else quant_any_kernel<BF16, true><<<grid, 256, 0, stream>>>(d);
-  }
+  auto pick = [&](auto t, auto sym) {
+    using T = decltype(t);
+    constexpr bool SYM = decltype(sym)::value;
+    if (!q.what) launch_quant<T, SYM, Q_AUX>(d, stream);
+    else if (q.diff) launch_quant<T, SYM, Q_DIFF>(d, stream);
+    else launch_quant<T, SYM, Q_FOLD>(d, stream);
+  };
+  if (!q.bf16) q.symmetric ? pick(F16{}, std::true_type{}) : pick(F16{}, std::false_type{});
+  else q.symmetric ? pick(BF16{}, std::true_type{}) : pick(BF16{}, std::false_type{});
   return hipGetLastError();
 }
 

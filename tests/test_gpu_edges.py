@@ -65,3 +65,48 @@ def test_bf16_results_round_half_to_even(gpu):
     want = (ta.float().cpu() + tb.float().cpu()).numpy()
     want = np.where(np.isnan(want), np.nan, BF(np.nan_to_num(want, nan=0.0, posinf=np.inf, neginf=-np.inf)))
     np.testing.assert_array_equal(out.float().cpu().numpy(), want)
+
+
+# one size per kernel and remainder: a wave of 1 / 2 / 4 chunks, a block of 2 / 4 / 8 chunks, the two-sweep
+# kernel beyond 16384 channels, power-of-two groups with and without two rows per wave; odd row counts
+@pytest.mark.parametrize("group,ci,co,sym,bits,bf16", [
+    (24, 240, 5, 0, 4, False), (320, 640, 7, 1, 3, True), (0, 520, 3, 0, 4, True), (0, 1000, 9, 1, 4, False),
+    (0, 1032, 2, 0, 8, False), (1536, 3072, 5, 0, 4, True), (0, 2056, 6, 1, 4, False), (0, 4104, 3, 0, 4, True),
+    (0, 8200, 2, 1, 4, False), (0, 16384, 1, 0, 3, False), (0, 16392, 2, 1, 4, True), (8, 520, 3, 0, 4, False),
+    (512, 1024, 5, 1, 4, False), (128, 1152, 2051, 0, 4, True)])
+def test_quantiser_group_layouts(gpu, group, ci, co, sym, bits, bf16):
+    import torch
+    g = np.random.default_rng([23, group, ci, co])
+    W = g.standard_normal((co, ci)).astype(np.float32) * 0.05
+    W[0, :8] = 0.0
+    W = BF(W) if bf16 else F16(W)
+    s = np.exp(g.standard_normal(ci)).astype(np.float32)
+    G = ci // (group or ci)
+    code = tlq.BF16 if bf16 else tlq.F16
+    p = tlq.params(bits=bits, group=group, symmetric=sym, x_dtype=code, yref_dtype=tlq.F32)
+    tW = dev(W, gpu, bf16)
+    codes = torch.full((co, ci), 99, dtype=torch.uint8, device=gpu)
+    zp, delta = torch.empty((co, G), dtype=torch.uint8, device=gpu), torch.empty((co, G), dtype=torch.float32, device=gpu)
+    wdq = torch.empty((co, ci + 8), dtype=tW.dtype, device=gpu)[:, :ci]
+    tlq.fake_quant(tW, torch.from_numpy(s).to(gpu), p, codes, zp, delta, wdq)
+    rc, rz, rd, rq = orc.fake_quant(W, s, bits, group, symmetric=bool(sym))
+    np.testing.assert_array_equal(codes.cpu().numpy(), rc)
+    np.testing.assert_array_equal(zp.cpu().numpy(), rz)
+    np.testing.assert_array_equal(delta.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+    np.testing.assert_array_equal(host(wdq), (BF(rq) if bf16 else F16(rq)).astype(np.float64))
+    # the candidates' operands (folded from 65536 outputs on at these bits, else the difference form),
+    # stretches of candidates split over the grid
+    n, na = (65536 + co - 1) // co if co > 256 and bits < 6 else 19, 7
+    X = (BF if bf16 else F16)(g.standard_normal((n, ci)))
+    w = np.full(n, 1.0 / n, np.float32)
+    Y = orc.ref_output(X, W).astype(np.float32)
+    al = (np.arange(na) / na).astype(np.float32)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses = torch.empty(na, dtype=torch.float32, device=gpu)
+    ldy = co + -co % 4
+    tY = torch.zeros((n, ldy), dtype=torch.float32, device=gpu)[:, :co]
+    tY.copy_(torch.from_numpy(Y))
+    tlq.scale_search(dev(X, gpu, bf16), tW, tY, torch.from_numpy(w).to(gpu), torch.from_numpy(al).to(gpu), p, best, idx,
+                     losses)
+    ref = orc.scale_search(X, W, Y, w, bits, group, al, symmetric=bool(sym))
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
