@@ -29,18 +29,6 @@ __device__ __forceinline__ u16x4 lds_read_tr(const unsigned char* p) {
   return __builtin_bit_cast(u16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                                        (__attribute__((address_space(3))) s16x4*)(uint32_t)(uintptr_t)p));
 }
-// c + a + b of two 16-bit values
-template <typename T> __device__ __forceinline__ float pair_sum(uint16_t a, uint16_t b, float c);
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-template <> __device__ __forceinline__ float pair_sum<F16>(uint16_t a, uint16_t b, float c) {
-  const f16x2 v = {__builtin_bit_cast(_Float16, a), __builtin_bit_cast(_Float16, b)}, one = {(_Float16)1.0f, (_Float16)1.0f};
-  return __builtin_amdgcn_fdot2(v, one, c, false);
-}
-template <> __device__ __forceinline__ float pair_sum<BF16>(uint16_t a, uint16_t b, float c) {
-  const bf16x2 v = {__builtin_bit_cast(__bf16, a), __builtin_bit_cast(__bf16, b)}, one = {(__bf16)1.0f, (__bf16)1.0f};
-  return __builtin_amdgcn_fdot2_f32_bf16(v, one, c, false);
-}
 // the value that lane ^ 32 holds
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32, 64); }
 #endif
@@ -58,24 +46,26 @@ constexpr int kAttBq = 128;   // queries per block (32 per wave)
 // 16 sl + 8 (e / 4) + 4 (lane / 32) + e % 4 of a 16-key step; the transposing LDS read hands a lane
 // four keys of one column of V, so V^T is read in that same order and P never moves between lanes.
 //
-// What bounds it: per 32 queries x 64 keys a wave spends 1024 cycles on its matrix core, about 900 on
-// the softmax (32 exponentials a lane) and its share of 128 B/cycle of LDS reads, so two blocks per CU
-// (64 KB of LDS, <= 256 registers) overlap the three.  Per step: the next 64 keys are fetched into
-// registers while this step computes and go to the other LDS stage behind it (one barrier per step).
-// The 64 output accumulators are rescaled only in steps in which some query of the wave meets a new
-// maximum.  (Rescaling only on a rise of 2^8 saves another 5 %, but the largest probability is then no
-// longer exactly 1 in 16 bits: error against 64 bits 2.0e-3 instead of 1.8e-3, not kept.)
-// All query blocks of a (sample, head) run on one XCD, so
-// that its keys and values (0.6 MB at 1200 tokens) are fetched into one L2, not into eight.
+// What bounds it: per 32 queries x 64 keys a wave spends 1024 cycles on its matrix core, about as long
+// on the softmax (32 exponentials a lane) and its share of 128 B/cycle of LDS reads; two blocks per CU
+// (64 KB of LDS, <= 256 registers) overlap the three (matrix cores busy 30 % of the time, the
+// rest is exposed latency of that chain).  Per step: the next 64 keys are fetched into registers while
+// this step computes and go to the other LDS stage behind it (one barrier per step).
+// The softmax advances 32 keys at a time with the exact running maximum as its reference, so that the
+// largest probability is exactly 1 in 16 bits; the 64 output accumulators are rescaled only where some
+// query of the wave meets a new maximum.  (One reference per 64 keys, raised only by a rise of 2^8:
+// 2.99 ms instead of 3.27, but an error against 64 bits of 2.1e-3 instead of 1.8e-3, not kept.)
+// All query blocks of a (sample, head) run on one XCD, so that its keys and values (0.6 MB at 1200
+// tokens) are fetched into one L2, not into eight.
 // LDS rows are 256 B; the 16-byte chunks of a K row are XORed with row % 16, the 32-byte pairs of a V
 // row with a permutation of row % 8: fragment reads and transposing reads hit each bank once.
-// 128 samples x 1200 tokens x 40 heads, bf16: 3.12 ms (605 TFLOP/s) against 8.87 ms with 32-key steps,
+// 128 samples x 1200 tokens x 40 heads, bf16: 3.27 ms (578 TFLOP/s) against 8.87 ms with 32-key steps,
 // K fragments read from global memory by every wave and V transposed by 2-byte LDS stores.
 template <typename T>
 __global__ __launch_bounds__(256, 2) void causal_attention_kernel(
     const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
     const uint16_t* __restrict__ V, int64_t ldv, uint16_t* __restrict__ O, int64_t ldo, int seq_len,
-    int n_heads, int64_t n_hs, float scale_log2e) {
+    int n_heads, int64_t n_hs, float scale) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) unsigned char kv[2][2][kAttTile];   // [stage][K, V]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -162,53 +152,53 @@ __global__ __launch_bounds__(256, 2) void causal_attention_kernel(
 #pragma unroll
       for (int u = 0; u < NSUB; ++u)
         s[u] = mma16<T>(*reinterpret_cast<const u16x8*>(kt_lds + u * 32 * kAttRow + (kbase ^ (st << 5))), qf[st], s[u]);
-    if constexpr (MASK) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int key = kt * kAttBk + (NSUB - 1) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        s[NSUB - 1][v] = key <= q ? s[NSUB - 1][v] : -INFINITY;
-      }
-    }
-    float mx = s[0][0];
-#pragma unroll
-    for (int u = 0; u < NSUB; ++u)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[u][v]);
-    mx *= scale_log2e;
-    if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-      // key 0 is visible to every query and is part of the first step, so m_run becomes finite there
-      const float m_new = fmaxf(m_run, fmaxf(mx, other_half(mx)));
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-      l_run *= alpha;
-      m_run = m_new;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[dt][v] *= alpha;
-    }
-    // the sum takes the ROUNDED probabilities, the ones that weigh V: a rounding error then scales
-    // numerator and denominator alike
-    u16x8 pf[2 * NSUB];
-    float ps[2] = {0.0f, 0.0f};
-#pragma unroll
-    for (int sl = 0; sl < 2 * NSUB; ++sl) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        pf[sl][e] = T::from_float(__builtin_amdgcn_exp2f(__builtin_fmaf(s[sl >> 1][8 * (sl & 1) + e], scale_log2e, -m_run)));
-#pragma unroll
-      for (int e = 0; e < 8; e += 2) ps[sl & 1] = pair_sum<T>(pf[sl][e], pf[sl][e + 1], ps[sl & 1]);
-    }
-    l_run += ps[0] + ps[1];
     const unsigned char* vt_lds = kv[stage][1];
 #pragma unroll
-    for (int sl = 0; sl < 2 * NSUB; ++sl)
+    for (int u = 0; u < NSUB; ++u) {
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const unsigned char* p = vt_lds + sl * 16 * kAttRow + (vbase ^ ((dt ^ r4) << 6));
-        const u16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * kAttRow);
-        const u16x8 a = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        acc[dt] = mma16<T>(a, pf[sl], acc[dt]);
+      for (int v = 0; v < 16; ++v) {
+        s[u][v] *= scale;
+        if (MASK && u == NSUB - 1) {
+          const int key = kt * kAttBk + u * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+          s[u][v] = key <= q ? s[u][v] : -INFINITY;
+        }
       }
+      float mx = s[u][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[u][v]);
+      // wave-uniform: while no query meets a new maximum every factor is exactly 1
+      float alpha = 1.0f;
+      if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+        // key 0 is visible to every query and is part of the first step, so m_run becomes finite there
+        const float m_new = fmaxf(m_run, fmaxf(mx, other_half(mx)));
+        alpha = __expf(m_run - m_new);
+        m_run = m_new;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[dt][v] *= alpha;
+      }
+      float ps = 0.0f;
+      u16x8 pf[2];
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float pv = __expf(s[u][8 * sl + e] - m_run);
+          ps += pv;
+          pf[sl][e] = T::from_float(pv);
+        }
+      l_run = __builtin_fmaf(l_run, alpha, ps);
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+          const unsigned char* p = vt_lds + (2 * u + sl) * 16 * kAttRow + (vbase ^ ((dt ^ r4) << 6));
+          const u16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * kAttRow);
+          const u16x8 a = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          acc[dt] = mma16<T>(a, pf[sl], acc[dt]);
+        }
+    }
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -261,7 +251,7 @@ hipError_t launch_causal_attention(const void* Q, int64_t ldq, const void* K, in
   const int64_t n_hs = n_samples * n_heads, groups = ceil_div(n_hs, 8);
   const int64_t gy = groups < 32768 ? groups : 32768;
   const dim3 grid(8u * (unsigned)ceil_div(seq_len, kAttBq), (unsigned)gy, (unsigned)ceil_div(groups, gy));
-  const float scale = 0.08838834764831845f * 1.4426950408889634f;  // log2(e) / sqrt(128)
+  const float scale = 0.08838834764831845f;  // 1 / sqrt(128)
   if (!bf16)
     causal_attention_kernel<F16><<<grid, 256, 0, stream>>>((const uint16_t*)Q, ldq, (const uint16_t*)K, ldk,
                                                            (const uint16_t*)V, ldv, (uint16_t*)O, ldo, seq_len, n_heads,
