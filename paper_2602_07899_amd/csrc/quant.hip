@@ -137,6 +137,8 @@ __device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const fl
       if constexpr (MODE == Q_DIFF) {
         f -= w[j] * wsub;
         f *= cs[j];
+      } else {
+        asm("" : "+v"(f));               // rounded to float, then to 16 bits (see above)
       }
       hw[j >> 1] |= (uint32_t)F16::from_float(f) << ((j & 1) * 16);
     }
@@ -586,35 +588,42 @@ hipError_t launch_fake_quant(const QuantArgs& q, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Wout[o,c] = round16(Win[o,c] * inv_s[c]); dense output, row stride c_in.
+// Wout[o,c] = round16(Win[o,c] * inv_s[c]); dense output, row stride c_in.  A block owns 2048 channels and
+// walks rows, so the eight factors of a lane are loaded once (HBM-bound; with a flat index the 64-bit
+// division and the scalar factor loads took 105 us for 4096 x 11008).
 template <typename T, typename TO>
 __global__ __launch_bounds__(256) void fold_scale_kernel(const uint16_t* __restrict__ Win,
                                                          int64_t c_out, int64_t c_in, int64_t ldw,
                                                          const float* __restrict__ inv_s,
                                                          const uint32_t* __restrict__ xmax_bits,
                                                          uint16_t* __restrict__ Wout) {
-  const int64_t chunks = c_in / 8;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= c_out * chunks) return;
-  const int64_t row = i / chunks, c = (i % chunks) * 8;
-  const uint4 v = *reinterpret_cast<const uint4*>(Win + row * ldw + c);
-  const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-  uint32_t o[4] = {0, 0, 0, 0};
+  const int64_t c = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (c >= c_in) return;
   const float up = xmax_bits
       ? __builtin_bit_cast(float, (uint32_t)(127 + shift_from_bf16_bits(*xmax_bits)) << 23) : 1.0f;
+  float inv[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float f = T::to_float((uint16_t)(u[j >> 1] >> ((j & 1) * 16))) * (inv_s ? inv_s[c + j] : 1.0f);
-    o[j >> 1] |= (uint32_t)TO::from_float(f * up) << ((j & 1) * 16);
+  for (int j = 0; j < 8; ++j) inv[j] = inv_s ? inv_s[c + j] : 1.0f;   // (no alignment promised for inv_s)
+#pragma unroll 2
+  for (int64_t row = blockIdx.y; row < c_out; row += gridDim.y) {
+    float w[8];
+    widen8<T>(*reinterpret_cast<const uint4*>(Win + row * ldw + c), w);
+    uint32_t o[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j >> 1] |= (uint32_t)TO::from_float(w[j] * inv[j] * up) << ((j & 1) * 16);
+    *reinterpret_cast<uint4*>(Wout + row * c_in + c) = make_uint4(o[0], o[1], o[2], o[3]);
   }
-  *reinterpret_cast<uint4*>(Wout + row * c_in + c) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 hipError_t launch_fold_scale(const void* Win, int64_t c_out, int64_t c_in, int64_t ldw, bool bf16,
                              const float* inv_s, const uint32_t* xmax_bits, bool out_f16, void* Wout,
                              hipStream_t stream) {
   ProfScope ps("fold_scale", stream, 4.0 * (double)c_out * (double)c_in);
-  const unsigned grid = (unsigned)ceil_div(c_out * (c_in / 8), 256);
+  // rows per block: enough blocks for the chip first, then up to 16 rows per load of the factors
+  const int64_t bx = ceil_div(c_in, 2048);
+  int64_t by = 4096 / bx;
+  by = by < 1 ? 1 : by;
+  const dim3 grid((unsigned)bx, (unsigned)(c_out < by ? c_out : by));
   const uint16_t* in = (const uint16_t*)Win;
   uint16_t* out = (uint16_t*)Wout;
   if (!bf16) fold_scale_kernel<F16, F16><<<grid, 256, 0, stream>>>(in, c_out, c_in, ldw, inv_s, xmax_bits, out);

@@ -110,3 +110,36 @@ def test_quantiser_group_layouts(gpu, group, ci, co, sym, bits, bf16):
                      losses)
     ref = orc.scale_search(X, W, Y, w, bits, group, al, symmetric=bool(sym))
     np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
+
+
+@pytest.mark.parametrize("n,ci,co,pad", [(1, 8, 1, 0), (3, 520, 2, 8), (4097, 72, 5, 0), (9, 4104, 3, 16)])
+def test_token_preparation_and_folding_edges(gpu, n, ci, co, pad):
+    """bf16 tokens beyond the fp16 range: the exponent shift follows the largest magnitude wherever it is
+    (last row, last chunk), for row counts around the grid and widths around one wave and one block."""
+    import torch
+    g = np.random.default_rng([24, n, ci])
+    X = BF(g.standard_normal((n, ci)) * 3.0)
+    X[n - 1, ci - 1] = BF(np.array([-3.0e5]))[0]
+    W = BF(g.standard_normal((co, ci)) * 0.05)
+    p = tlq.params(bits=4, group=8, x_dtype=tlq.BF16, yref_dtype=tlq.F32)
+    tX = torch.zeros((n, ci + pad), dtype=torch.bfloat16, device=gpu)[:, :ci]
+    tX.copy_(dev(X, gpu, True))
+    prep = torch.zeros(tlq.prepared_tokens_bytes(n, ci, p), dtype=torch.uint8, device=gpu)
+    tlq.prepare_tokens(tX, p, prep)
+    bits = int(prep[:4].view(torch.int32).item())
+    assert bits == int(dev(np.abs(X).max().reshape(1), gpu, True).view(torch.int16).item())
+    shift = max(0, min(24, ((bits >> 7) & 0xff) - 141))
+    got = prep[256:256 + 2 * n * ci].view(torch.float16).float().cpu().numpy().reshape(n, ci)
+    np.testing.assert_array_equal(got, F16(X.astype(np.float64) * 2.0 ** -shift).astype(np.float32))
+    # the folded operand: one output per row, one token per column
+    inv = (1.0 / np.exp(g.standard_normal(ci))).astype(np.float32)
+    Y = np.zeros((n, co + -co % 4), np.float32)
+    w = np.full(n, 1.0 / n, np.float32)
+    loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+    tlq.weighted_layer_err(tX, dev(W, gpu, True), torch.from_numpy(inv).to(gpu), torch.from_numpy(Y).to(gpu)[:, :co],
+                           torch.from_numpy(w).to(gpu), p, loss, per_token_err=err)
+    want = orc.per_token_err(Y[:, :co], orc.quantised_output(X, W, inv_s=inv))
+    # the folded weight is rounded once to fp16: every output within 2^-11 sum |x inv w|, its square twice that
+    mag = (np.abs(X.astype(np.float64) * inv) @ np.abs(W.astype(np.float64)).T)
+    bound = (2.0 ** -10 * mag * mag + 1e-5 * mag * mag).mean(axis=1)
+    assert np.all(np.abs(err.cpu().numpy() - want) <= bound)
