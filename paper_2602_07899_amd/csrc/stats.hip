@@ -15,17 +15,20 @@ namespace tlq {
 constexpr int kXsThreads = 256;
 constexpr int kXsCols = 64 * 8;  // channels per block
 
+// 16 rows per chunk at least (four a wave), 128 chunks at most: 256 tokens in two chunks of 128 rows left
+// two blocks per 512 channels busy for 11 us, sixteen chunks take 5.
 int xstat_chunks(int64_t n_tok) {
-  int64_t c = ceil_div(n_tok, 128);
+  int64_t c = ceil_div(n_tok, 16);
   return (int)(c < 1 ? 1 : (c > 128 ? 128 : c));
 }
 
-template <typename T, int KIND>
+template <typename T, int KIND, bool MASKED>
 __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
     const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx, int rows_per_chunk,
     double* __restrict__ partial, const uint8_t* __restrict__ pos_mask, int64_t period) {
   __shared__ double red[4][kXsCols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t c0 = (int64_t)blockIdx.x * kXsCols + lane * 8;
   const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk;
   int64_t r1 = r0 + rows_per_chunk;
@@ -33,16 +36,38 @@ __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
   double acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.0;
-  if (c0 < c_in) {
-    for (int64_t r = r0 + wave; r < r1; r += 4) {
-      if (pos_mask && !pos_mask[r % period]) continue;   // token position not in the selected set
-      const uint4 v = *reinterpret_cast<const uint4*>(X + r * ldx + c0);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  auto add = [&](const uint4& v) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint16_t b = (uint16_t)((w[j >> 1] >> ((j & 1) * 16)) & 0x7fffu);  // |x|
-        const double a = (double)T::to_float(b);
-        if (KIND == 0) acc[j] += a; else acc[j] = a > acc[j] ? a : acc[j];
+    for (int j = 0; j < 8; ++j) {
+      const uint16_t b = (uint16_t)((w[j >> 1] >> ((j & 1) * 16)) & 0x7fffu);  // |x|
+      const double a = (double)T::to_float(b);
+      if (KIND == 0) acc[j] += a; else acc[j] = a > acc[j] ? a : acc[j];
+    }
+  };
+  if (MASKED || c0 < c_in) {
+    if constexpr (!MASKED) {
+      for (int64_t r = r0 + wave; r < r1; r += 4) add(*reinterpret_cast<const uint4*>(X + r * ldx + c0));
+    } else {
+      const int64_t cr = c0 < c_in ? c0 : 0;     // (every lane takes part in the look-up)
+      // rows that are not selected are not read: the lanes look 64 of the wave's rows up at once, the set
+      // bits are then walked four loads at a time (a mask load and a division per row kept the loads apart)
+      for (int64_t rb = r0 + wave; rb < r1; rb += 4 * 64) {
+        const int64_t row = rb + 4 * (int64_t)lane;
+        uint64_t sel = __builtin_amdgcn_ballot_w64(row < r1 && pos_mask[row % period] != 0);
+        while (sel) {
+          uint4 v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            v[i] = make_uint4(0, 0, 0, 0);       // a zero changes neither the sum nor the maximum
+            if (sel) {
+              v[i] = *reinterpret_cast<const uint4*>(X + (rb + 4 * (int64_t)__builtin_ctzll(sel)) * ldx + cr);
+              sel &= sel - 1;
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) add(v[i]);
+        }
       }
     }
   }
@@ -60,14 +85,32 @@ __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
   }
 }
 
+// 64 channels per block, the chunks in 16 contiguous stretches (one a wave) that are combined in order: one
+// thread per channel walked 128 dependent loads (32 us at 5120 channels; 5 us this way).
+constexpr int kXfWaves = 16;
 template <int KIND>
-__global__ void xstat_final_kernel(const double* __restrict__ partial, int n_chunks, int64_t c_in,
-                                   int64_t n_tok, float* __restrict__ x_stat) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= c_in) return;
+__global__ __launch_bounds__(kXfWaves * 64) void xstat_final_kernel(const double* __restrict__ partial, int n_chunks,
+                                                                    int64_t c_in, int64_t n_tok,
+                                                                    float* __restrict__ x_stat) {
+  __shared__ double red[kXfWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  const int per = (n_chunks + kXfWaves - 1) / kXfWaves;
+  const int i1 = (wave + 1) * per < n_chunks ? (wave + 1) * per : n_chunks;
   double s = 0.0;
-  for (int i = 0; i < n_chunks; ++i) {
-    const double v = partial[(int64_t)i * c_in + c];
+  if (c < c_in) {
+#pragma unroll 8
+    for (int i = wave * per; i < i1; ++i) {
+      const double v = partial[(int64_t)i * c_in + c];
+      if (KIND == 0) s += v; else s = v > s ? v : s;
+    }
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || c >= c_in) return;
+#pragma unroll
+  for (int i = 1; i < kXfWaves; ++i) {
+    const double v = red[i][lane];
     if (KIND == 0) s += v; else s = v > s ? v : s;
   }
   x_stat[c] = (float)(KIND == 0 ? s / (double)n_tok : s);
@@ -82,18 +125,23 @@ hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   const uint16_t* x = (const uint16_t*)X;
   {
     ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
-    if (!bf16 && kind == 0) xstat_partial_kernel<F16, 0><<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
-    else if (!bf16) xstat_partial_kernel<F16, 1><<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
-    else if (kind == 0) xstat_partial_kernel<BF16, 0><<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
-    else xstat_partial_kernel<BF16, 1><<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
+    auto go = [&](auto kern) { kern<<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period); };
+    if (pos_mask) {       // only the maximum has a masked form
+      if (!bf16) go(xstat_partial_kernel<F16, 1, true>);
+      else go(xstat_partial_kernel<BF16, 1, true>);
+    }
+    else if (!bf16 && kind == 0) go(xstat_partial_kernel<F16, 0, false>);
+    else if (!bf16) go(xstat_partial_kernel<F16, 1, false>);
+    else if (kind == 0) go(xstat_partial_kernel<BF16, 0, false>);
+    else go(xstat_partial_kernel<BF16, 1, false>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   {
     ProfScope ps("xstat_final", stream, 8.0 * (double)chunks * (double)c_in);
-    const unsigned g2 = (unsigned)ceil_div(c_in, 256);
-    if (kind == 0) xstat_final_kernel<0><<<g2, 256, 0, stream>>>(partial, chunks, c_in, n_tok, x_stat);
-    else xstat_final_kernel<1><<<g2, 256, 0, stream>>>(partial, chunks, c_in, n_tok, x_stat);
+    const unsigned g2 = (unsigned)ceil_div(c_in, 64);
+    if (kind == 0) xstat_final_kernel<0><<<g2, kXfWaves * 64, 0, stream>>>(partial, chunks, c_in, n_tok, x_stat);
+    else xstat_final_kernel<1><<<g2, kXfWaves * 64, 0, stream>>>(partial, chunks, c_in, n_tok, x_stat);
   }
   return hipGetLastError();
 }
@@ -222,7 +270,8 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
 // One block.  Wave k sums candidate k's tile partials in double in a fixed
 // order (lane-strided, then a fixed butterfly), scales by 1/c_out, and stores
 // the loss as float (+inf if not finite).  Thread 0 then picks the first
-// minimum (Sec. 3.2.1 argmin) and the block copies that row of the table.
+// minimum (Sec. 3.2.1 argmin) and the block copies that row of the table.  The partials are loaded 16 at a
+// time and added in order: latency-bound, 20 candidates of 12000 tiles 167 -> 25 us, of 640 tiles 13 -> 8.
 __global__ __launch_bounds__(1024) void finalize_kernel(
     const float* __restrict__ partial, int n_cand, int64_t tiles_per_cand, double inv_c_out,
     const double* __restrict__ factor, const float* __restrict__ s_table, int64_t c_in, float* __restrict__ losses,
@@ -233,7 +282,13 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
   for (int k = wave; k < n_cand; k += nwaves) {
     double acc = 0.0;
     const float* p = partial + (int64_t)k * tiles_per_cand;
-    for (int64_t i = lane; i < tiles_per_cand; i += 64) acc += (double)p[i];
+    for (int64_t i = lane; i < tiles_per_cand; i += 16 * 64) {   // 16 loads in flight, added in order
+      float v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v[j] = p[i + j * 64 < tiles_per_cand ? i + j * 64 : lane];   // (no branch)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc += i + j * 64 < tiles_per_cand ? (double)v[j] : 0.0;
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane == 0) {
@@ -275,6 +330,7 @@ __global__ void token_err_reduce_kernel(const float* __restrict__ tok_partial, i
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n_tok) return;
   double acc = 0.0;
+#pragma unroll 8
   for (int64_t i = 0; i < tiles_o; ++i) acc += (double)tok_partial[i * n_tok + t];
   out[t] = (float)(acc * inv_c_out);
 }

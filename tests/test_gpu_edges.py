@@ -143,3 +143,58 @@ def test_token_preparation_and_folding_edges(gpu, n, ci, co, pad):
     mag = (np.abs(X.astype(np.float64) * inv) @ np.abs(W.astype(np.float64)).T)
     bound = (2.0 ** -10 * mag * mag + 1e-5 * mag * mag).mean(axis=1)
     assert np.all(np.abs(err.cpu().numpy() - want) <= bound)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,c,pad,two,period", [(1, 8, 0, False, 0), (5, 72, 8, True, 3), (3, 1024, 0, False, 0),
+                                                (3, 1032, 0, True, 0), (4, 5120, 0, False, 2), (2, 5128, 8, True, 0),
+                                                (3, 75, 0, True, 2), (2, 520, 4, False, 0)])
+def test_rmsnorm_row_widths(gpu, bf16, n, c, pad, two, period):
+    """Rows held in registers (2 and 10 stretches), rows read twice, widths and strides that need the
+    element-wise kernel; the second factor and the two multipliers."""
+    import torch
+    g = np.random.default_rng([25, n, c])
+    rnd = BF if bf16 else F16
+    z, zb = np.asarray(rnd(g.standard_normal((n, c)) * 3), np.float64), np.asarray(rnd(g.standard_normal((n, c))), np.float64)
+    ma, mb = (np.float32(g.uniform(0.5, 2.0, c)) for _ in range(2))
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    dt = torch.bfloat16 if bf16 else torch.float16
+    wide = lambda a: torch.zeros((n, c + pad), dtype=dt, device=gpu)[:, :c].copy_(dev(a, gpu, bf16))
+    out = torch.full((n, c + pad), 7.0, dtype=dt, device=gpu)
+    t = lambda a: torch.from_numpy(a).to(gpu)
+    tlq.rmsnorm_mul(wide(z), p, out[:, :c], Zb=wide(zb) if two else None, m_a=t(ma), m_b=t(mb), period=period,
+                    split=1 if period else 0)
+    v = z * zb if two else z
+    m = np.where(((np.arange(n) % period) >= 1)[:, None], mb, ma) if period else ma
+    want = v / np.sqrt((v * v).mean(axis=1, keepdims=True) + 1e-6) * m
+    got = host(out)
+    assert np.all(got[:, c:] == 7.0)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # one rounding of the result, float arithmetic before it
+    assert np.all(np.abs(got[:, :c] - want) <= eps * np.abs(want) * 1.001 + 1e-6 * np.abs(want) + 6e-8)
+
+
+@pytest.mark.parametrize("B,N,C,l2", [(1, 1, 8, 0), (17, 65, 72, 1), (3, 64, 520, 0), (33, 1, 75, 1), (2, 129, 1096, 0)])
+def test_selection_block_edges(gpu, B, N, C, l2):
+    """64 positions a block, sixteen stretches of samples and rivals, 16-byte and 2-byte gradient rows; the
+    masked maximum with a period that four interleaved rows wrap around, and one that is shorter."""
+    import torch
+    g = np.random.default_rng([26, B, N, C])
+    G = F16(g.standard_normal((B * N, C)))
+    p = tlq.params()
+    sum_n = torch.empty(N, dtype=torch.float64, device=gpu)
+    tlq.token_importance(dev(G, gpu, False), B, p, sum_n, l2=bool(l2))
+    want = orc.token_importance(G, B, l2=bool(l2))
+    np.testing.assert_allclose(sum_n.cpu().numpy(), want, rtol=1e-13)     # double sums in another order
+    vals = np.floor(want * 4)                                             # ties
+    mask = torch.empty(N, dtype=torch.uint8, device=gpu)
+    k = (N + 1) // 2
+    tlq.topk_mask(torch.from_numpy(vals).to(gpu), k, mask)
+    rm = orc.top_fraction_mask(vals, k)
+    np.testing.assert_array_equal(mask.cpu().numpy().astype(bool), rm)
+    if C % 8 == 0:
+        X = F16(g.standard_normal((B * N, C)))
+        xs = torch.empty(C, dtype=torch.float32, device=gpu)
+        tlq.x_stat_masked(dev(X, gpu, False), mask, p, xs)
+        np.testing.assert_array_equal(xs.cpu().numpy(), orc.x_stat_topk_max(X, rm))
+        tlq.x_stat(dev(X, gpu, False), p, xs)
+        np.testing.assert_array_equal(xs.cpu().numpy(), orc.x_stat_mean(X))
