@@ -80,14 +80,16 @@ bool use_diff_form(const tlq_params* p, int64_t n_tok, int64_t c_out) {
 struct SearchPlan {
   double* xs_partial; float* x_stat; float* s_table; float* inv_table; float* partial;
   uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; float* rsig; uint16_t* xc; int nb; size_t bytes;
-  int64_t tiles_o, tiles_t;
+  int64_t tiles_o, tiles_t; bool small;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
 };
+// Small tiles write up to four times the loss partials.  The workspace stays what it is with the big ones: the
+// partials of small tiles take the place of the channel sums, which are done with by then, if they fit.
 SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, bool bf16,
-                       bool act, bool diff) {
+                       bool act, bool diff, bool strides_ok = false) {
   SearchPlan s;
   Carver c(ws);
-  gemm_tile_counts(n_tok, c_out, &s.tiles_o, &s.tiles_t);
+  gemm_tile_counts(n_tok, c_out, false, &s.tiles_o, &s.tiles_t);
   s.xs_partial = c.take<double>((size_t)xstat_chunks(n_tok) * c_in);
   s.x_stat = c.take<float>((size_t)c_in);
   s.s_table = c.take<float>((size_t)n_alpha * c_in);
@@ -103,6 +105,13 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   s.ldd = (int64_t)align_up((size_t)c_out, 4);
   s.d0 = diff ? c.take<float>((size_t)n_tok * s.ldd) : nullptr;
   s.bytes = c.off;
+  int64_t to, tt;
+  gemm_tile_counts(n_tok, c_out, true, &to, &tt);
+  s.small = strides_ok && gemm_small_tiles(n_tok, c_out, n_alpha) &&
+            (size_t)n_alpha * to * tt * sizeof(float) <= (size_t)xstat_chunks(n_tok) * c_in * sizeof(double);
+  if (s.small) {
+    s.tiles_o = to; s.tiles_t = tt; s.partial = (float*)s.xs_partial;
+  }
   return s;
 }
 
@@ -113,7 +122,7 @@ struct ErrPlan {
 ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act) {
   ErrPlan e;
   Carver c(ws);
-  gemm_tile_counts(n_tok, c_out, &e.tiles_o, &e.tiles_t);
+  gemm_tile_counts(n_tok, c_out, false, &e.tiles_o, &e.tiles_t);
   e.partial = c.take<float>((size_t)e.tiles_o * e.tiles_t);
   e.tok_partial = c.take<float>((size_t)e.tiles_o * n_tok);
   e.folded = c.take<uint16_t>((size_t)c_out * c_in);
@@ -152,7 +161,7 @@ GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
   GramPlan g;
   Carver c(ws);
   int64_t to, tt;
-  gemm_tile_counts(c_in, c_in, &to, &tt);
+  gemm_tile_counts(c_in, c_in, false, &to, &tt);
   const int64_t live = to * (to + 1) / 2;
   // measured: more, shorter splits run faster up to 16 (5120 channels: 6.0 ms with 4, 3.9 ms with 16;
   // beyond 16 it collapses); 13824 channels: 4 splits 28.2 ms, 5: 29.7, 12 - 16: 27.5 + a longer sum
@@ -175,7 +184,7 @@ struct GramSearchPlan { float* s_table; float* inv_table; float* partial; uint16
 GramSearchPlan plan_gram_search(void* ws, int64_t c_in, int64_t c_out, int n_alpha) {
   GramSearchPlan s;
   Carver c(ws);
-  gemm_tile_counts(c_out, c_in, &s.tiles_o, &s.tiles_t);   // weight rows take the token role
+  gemm_tile_counts(c_out, c_in, false, &s.tiles_o, &s.tiles_t);   // weight rows take the token role
   s.s_table = c.take<float>((size_t)n_alpha * c_in);
   s.inv_table = c.take<float>((size_t)n_alpha * c_in);
   s.partial = c.take<float>((size_t)n_alpha * s.tiles_o * s.tiles_t);
@@ -357,6 +366,14 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   }
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   g.partial = e.partial; g.tok_partial = per_token_err ? e.tok_partial : nullptr;
+  if (!per_token_err && gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1)) {
+    // (without per-token errors their rows hold the partials of small tiles)
+    int64_t to, tt;
+    gemm_tile_counts(n_tok, c_out, true, &to, &tt);
+    if (to * tt <= e.tiles_o * n_tok) {
+      g.small = true; e.tiles_o = to; e.tiles_t = tt; e.partial = g.partial = e.tok_partial;
+    }
+  }
   TLQ_HIP(launch_gemm_loss(g, st));
   TLQ_HIP(launch_finalize(e.partial, 1, e.tiles_o * e.tiles_t, c_out, nullptr, c_in, loss, nullptr,
                           nullptr, st));
@@ -397,7 +414,8 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   const bool bf16 = p->x_dtype == TLQ_BF16;
   const bool act = p->act_bits != 0;
   const bool diff = use_diff_form(p, n_tok, c_out);
-  SearchPlan s = plan_search(workspace, n_tok, c_in, c_out, n_alpha, bf16, act, diff);
+  SearchPlan s = plan_search(workspace, n_tok, c_in, c_out, n_alpha, bf16, act, diff,
+                             gemm_strides_ok(bf16 || act ? c_in : ldx, c_in));
   if (prepared && !aligned(prepared, 256)) return TLQ_ERR_ALIGN;
   const bool use_prep = prepared && needs_prepared(p);
   if (use_prep) {   // the caller's copy replaces the workspace one
@@ -431,6 +449,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     r.X = X; r.n_tok = n_tok; r.c_in = c_in; r.ldx = ldx;
     r.Wh = W; r.c_out = c_out; r.ldw = ldw; r.w_cand_stride = 0; r.n_cand = 1; r.bf16 = bf16;
     r.Yout = s.d0; r.ldo = s.ldd; r.yout_dtype = TLQ_F32;
+    r.small = gemm_strides_ok(ldx, ldw) && gemm_small_tiles(n_tok, c_out, 1);
     TLQ_HIP(launch_gemm_store(r, st));
     TLQ_HIP(launch_sub_from_y(Y_ref, ldy, p->yref_dtype, s.d0, s.ldd, n_tok, c_out, st));
   }
@@ -441,7 +460,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   g.n_cand = n_alpha; g.bf16 = false;
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   if (diff) { g.Yref = s.d0; g.ldy = s.ldd; g.yref_dtype = TLQ_F32; }
-  g.partial = s.partial; g.tok_partial = nullptr;
+  g.partial = s.partial; g.tok_partial = nullptr; g.small = s.small;
   if (!act) {
     // patch shape by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose
     // 0.5 - 3 % on the narrowing, deep ones (down_proj)
@@ -618,6 +637,7 @@ tlq_status tlq_ref_output(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   g.bf16 = p->x_dtype == TLQ_BF16;
   g.Yout = Y; g.ldo = ldy; g.yout_dtype = p->yref_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
+  g.small = gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1);
   return hip_status(launch_gemm_store(g, (hipStream_t)stream));
 }
 
@@ -674,6 +694,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   g.Wh = what; g.c_out = c_out; g.ldw = c_in; g.w_cand_stride = 0; g.n_cand = 1; g.bf16 = false;
   g.Yout = X_next; g.ldo = ld_next; g.yout_dtype = p->x_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
+  g.small = gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1);
   return hip_status(launch_gemm_store(g, st));
 }
 

@@ -124,6 +124,7 @@ struct GemmArgs {
   bool tri;                // launch_gemm_store of a symmetric product (X == Wh): tiles with tile row <= tile column only
   bool cand_outer;         // walk the candidates one after the other instead of inside every patch row
   bool wide_patch;         // L2 patches of 8 x 4 tiles (output rows x tokens) instead of 4 x 8
+  bool small;              // 128 x 128 tiles (not with tri)
   bool sym_k;              // launch_gemm_dot: Wh is symmetric [c_in, c_in] and Y == X (a quadratic form)
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
@@ -131,7 +132,11 @@ struct GemmArgs {
   // store epilogue (n_cand == 1): Y[t,o]
   void* Yout; int64_t ldo; int yout_dtype;
 };
-void gemm_tile_counts(int64_t n_tok, int64_t c_out, int64_t* tiles_o, int64_t* tiles_t);
+// `small`: 128 x 128 output tiles instead of 256 x 256 (gemm_small_tiles says when they are faster)
+void gemm_tile_counts(int64_t n_tok, int64_t c_out, bool small, int64_t* tiles_o, int64_t* tiles_t);
+bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand);
+// row strides that the pipelined kernel (and with it the small tiles) takes
+bool gemm_strides_ok(int64_t ldx, int64_t ldw);
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out);
 hipError_t launch_gemm_loss(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_store(const GemmArgs& a, hipStream_t stream);

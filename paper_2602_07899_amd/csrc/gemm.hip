@@ -19,9 +19,11 @@
 // the squared residual; SYMK: only the upper part of the symmetric operand is contracted).
 //
 // Two kernels share the tile epilogues and the block -> tile map:
-//   gemm_dma_kernel  the pipelined one (c_in % 64 == 0): 16x16x32 MFMA, operands brought
-//                    into LDS by LDS-DMA loads, two 64 KB stages, hand-placed waits;
-//   gemm_kernel      the general one: 32x32x16 MFMA, register-staged loads.
+//   gemm_dma_kernel  the pipelined one: 16x16x32 MFMA, operands brought into LDS by LDS-DMA loads,
+//                    two 64 KB stages, hand-placed waits; a 128 x 128-tile variant serves launches with
+//                    few tiles;
+//   gemm_kernel      for row strides of 2^21 elements and more (beyond the 32-bit offsets of the other):
+//                    32x32x16 MFMA, register-staged loads.
 // Tiling (wave64): block tile 256 x 256 outputs, k-tile 64; waves own 128 x 64
 // sub-tiles.  Both operands are K-contiguous in memory, so a fragment is one
 // 16-byte LDS read per lane.  LDS rows are 128 B (64 halves) and the eight
@@ -125,7 +127,8 @@ struct GemmDev {
   int64_t n_patches;
   int cpt;          // token patches per chunk (see make_dev)
   int rag, rag_pt;  // tile rows of the last, incomplete patch row (0 = none) and its patch width in tiles
-  int po, pt;       // patch shape in tiles (po * pt == PATCH_SLOTS)
+  int po, pt;       // patch shape in tiles (po * pt <= PATCH_SLOTS)
+  int64_t strips;   // > 0: no patches, the launch has this many tiles (see decode_tile)
 };
 
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
@@ -216,12 +219,17 @@ __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, co
   }
 }
 
+// XOR key of the 16-byte chunks of staged token row `row`: rows of 256 B (CPR = 16) or 128 B (two of them
+// span the banks once)
+template <int CPR>
+__device__ __forceinline__ int row_key(int row) { return CPR == 16 ? row & 15 : (row >> 1) & 7; }
+
 // Same sums as loss_rows for an interior wave tile with 16-bit Y_ref, but Y_ref goes through
 // LDS: the wave copies its 64-token x 128-row piece with whole-line loads (each 128-byte line
 // is fetched once, 8 lines per instruction) into `ylds` (WT x WO 16-bit, this wave's own),
 // then every lane picks its values from there.  Reading Y_ref straight from the accumulator
 // layout touches 16 or 32 lines per instruction and each line 8 times.  16-byte chunks of a token
-// row are stored at chunk ^ (token % 16), which makes the 8-byte reads conflict-free.
+// row are stored at chunk ^ row_key(token), which makes the 8-byte reads conflict-free.
 template <typename YT, bool DOT, typename L, typename Acc>
 __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
                                               int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part,
@@ -229,7 +237,7 @@ __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref
   constexpr int WO = L::WO, WT = L::WT;
   constexpr int CPR = WO / 8;              // 16-byte chunks per token row
   constexpr int RPI = 64 / CPR;            // token rows per wave-wide copy
-  static_assert(CPR == 16 && WT % RPI == 0, "copy shape");
+  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
   const int lane = threadIdx.x & 63;
   const uint16_t* Y = (const uint16_t*)Yref;
   {
@@ -243,7 +251,7 @@ __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref
 #pragma unroll
     for (int j = 0; j < WT / RPI; ++j) {
       const int row = j * RPI + cr;
-      *reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((cc ^ (row & 15)) << 4)) = v[j];
+      *reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4)) = v[j];
     }
   }
   // the values are picked up by OTHER lanes of this wave: order the LDS writes before the reads
@@ -259,7 +267,7 @@ __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref
 #pragma unroll
     for (int q = 0; q < L::NQ; ++q) {
       const int o = L::row(q, lane);        // multiple of 4: chunk o / 8, half (o / 4) % 2
-      const uint2 u = *reinterpret_cast<const uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ (tok & 15)) << 4) +
+      const uint2 u = *reinterpret_cast<const uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ row_key<CPR>(tok)) << 4) +
                                                       ((o >> 2) & 1) * 8);
       const float y[4] = {YT::to_float((uint16_t)(u.x & 0xffffu)), YT::to_float((uint16_t)(u.x >> 16)),
                           YT::to_float((uint16_t)(u.y & 0xffffu)), YT::to_float((uint16_t)(u.y >> 16))};
@@ -284,7 +292,7 @@ __device__ __forceinline__ void store_rows_lds(const GemmDev& a, void* Yout, con
                                                int64_t ow, int64_t tw, unsigned char* ylds) {
   constexpr int WO = L::WO, WT = L::WT;
   constexpr int CPR = WO / 8, RPI = 64 / CPR;
-  static_assert(CPR == 16 && WT % RPI == 0, "copy shape");
+  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int tb = 0; tb < L::NTB; ++tb) {
@@ -296,7 +304,7 @@ __device__ __forceinline__ void store_rows_lds(const GemmDev& a, void* Yout, con
       uint2 u;
       u.x = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 0)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 1)) << 16);
       u.y = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 2)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 3)) << 16);
-      *reinterpret_cast<uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ (tok & 15)) << 4) + ((o >> 2) & 1) * 8) = u;
+      *reinterpret_cast<uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ row_key<CPR>(tok)) << 4) + ((o >> 2) & 1) * 8) = u;
     }
   }
   uint16_t* Y = (uint16_t*)Yout;
@@ -308,7 +316,7 @@ __device__ __forceinline__ void store_rows_lds(const GemmDev& a, void* Yout, con
 #pragma unroll
   for (int j = 0; j < WT / RPI; ++j) {
     const int row = j * RPI + cr;
-    const uint4 v = *reinterpret_cast<const uint4*>(ylds + row * (WO * 2) + ((cc ^ (row & 15)) << 4));
+    const uint4 v = *reinterpret_cast<const uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4));
     *reinterpret_cast<uint4*>(Y + (tw + row) * a.ldo + ow + cc * 8) = v;
   }
 }
@@ -416,7 +424,21 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
 // weights are streamed once per chunk.  When tiles_o is not a multiple of po the last patch row
 // has `rag` tile rows and uses patches of rag x rag_pt tiles, so that (nearly) every slot of a patch
 // is a live tile.  Returns false for a slot that has no tile.
+// Launches of few tiles (`strips`) have no use for patches: whole and nearly empty patches would alternate
+// over the XCDs (5 token tiles in patches of 4: every other XCD idle).  There the tiles are
+// numbered along the shorter side first and every XCD takes one eighth of the numbers, a strip.
 __host__ __device__ __forceinline__ bool decode_tile(const GemmDev& a, int64_t bid, int& cand, int& to, int& tt) {
+  if (a.strips > 0) {
+    const int64_t xcd = bid & (kXcd - 1);
+    const int64_t idx = xcd * a.strips / kXcd + bid / kXcd;
+    if (idx >= (xcd + 1) * a.strips / kXcd) return false;
+    const int per = a.tiles_o * a.tiles_t;
+    cand = (int)(idx / per);
+    const int rem = (int)(idx % per);
+    if (a.tiles_t <= a.tiles_o) { to = rem / a.tiles_t; tt = rem % a.tiles_t; }
+    else { tt = rem / a.tiles_o; to = rem % a.tiles_o; }
+    return true;
+  }
   const int PATCH_O = a.po, PATCH_T = a.pt;
   const int64_t round = bid / (kXcd * PATCH_SLOTS);
   const int within = (int)(bid % (kXcd * PATCH_SLOTS));
@@ -564,7 +586,7 @@ __global__ __launch_bounds__((BO / WO) * (BT / WT) * 64) void gemm_kernel(GemmDe
 }
 
 // ---------------------------------------------------------------------------
-// Pipelined variant for c_in % BK == 0 (every group-128 workload).
+// Pipelined variant (every workload with row strides below 2^21 elements).
 //
 // Global -> LDS goes through the buffer-load-to-LDS path (no VGPR staging, no
 // LDS store instructions): each wave-wide load drops 64 x 16 B contiguously at
@@ -636,19 +658,25 @@ __device__ __forceinline__ void wait_vmcnt() {
 // full contraction at about half the flops.  The k-tiles are walked from the END of the rows
 // down to o0, so that the tiles of a patch - which start at different o0 - work on the same
 // k-tile at the same time and share its token panel in L2; the diagonal block comes last.
-template <typename T, int NSTAGE, int EPI, bool SYMK = false>
-__global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
+// TAIL: c_in is not a multiple of the k-tile; the lanes whose chunk lies past the end of the rows fetch
+// nothing for the last k-tile (their offset is out of range, the chunk arrives as zeros).
+// HALVES = 1: a block of 4 waves computes 128 x 128 outputs, a wave 64 x 64 (a phase per k32 step, all of
+// its eight fragments read one phase ahead); two blocks share a CU.  For launches whose 256 x 256 tiles
+// would leave CUs idle, see gemm_small_tiles.
+template <typename T, int NSTAGE, int EPI, bool SYMK, bool TAIL, int HALVES>
+__global__ __launch_bounds__(HALVES * 256) void gemm_dma_kernel(GemmDev a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses gfx950 builtins the host pass cannot parse
-  constexpr int BK_ = 64, BO = 256, BT = 256, NWO = 2, NWT = 4, NW = NWO * NWT, WO = BO / NWO, WT = BT / NWT;
-  constexpr int IA = WO / 16, JB = WT / 16;   // accumulator tiles per wave: 8 x 4
-  static_assert(IA == 8 && JB == 4, "phase structure below is written for 128 x 64 wave tiles");
+  constexpr int BK_ = 64, NWO = 2, NWT = 2 * HALVES, NW = NWO * NWT, WO = 64 * HALVES, WT = 64;
+  constexpr int BO = NWO * WO, BT = NWT * WT;
+  constexpr int IA = WO / 16, JB = WT / 16;   // accumulator tiles per wave: 8 x 4 or 4 x 4
+  static_assert(HALVES == 1 || HALVES == 2, "phase structure below: one or two row halves of 64");
   constexpr int RB = BK_ * 2;             // bytes per LDS row
   constexpr int CPR = BK_ / 8;            // 16-byte chunks per row
   constexpr int STAGE = (BO + BT) * RB;
   constexpr int RPD = 64 / CPR;           // rows covered by one wave-wide load
   constexpr int DPO = BO / RPD / NW;      // loads per wave per operand per k-tile
   constexpr int LPS = 2 * DPO;            // loads per wave per k-tile
-  static_assert(NSTAGE == 2 && LPS == 8, "pipeline shape");
+  static_assert((NSTAGE == 2 || NSTAGE == 4) && LPS == 8, "pipeline shape");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NSTAGE * STAGE];
   __shared__ float red[NW];
 
@@ -689,8 +717,10 @@ __global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
   // issued (the counter bookkeeping stays uniform) but with a per-lane offset
   // that is out of range for any descriptor, which touches no memory and
   // delivers zeros.
-  const int64_t nk = klen / BK_;
+  const int64_t nk = TAIL ? (klen + BK_ - 1) / BK_ : klen / BK_;
   constexpr int kOutOfRange = (int)0x80000000u;
+  // TAIL: the lane's chunk of a k-tile (the same for all of its loads, see voa) lies inside the last one
+  const bool tail_ok = !TAIL || ((lane % CPR) ^ ((wave * (RPD / 2) + (lane / CPR >> 1)) & 7)) * 8 < (int)(klen - (nk - 1) * BK_);
   auto dma1 = [&](auto dc, unsigned char* sbase, bool live, int so) {
     constexpr int d = decltype(dc)::value, j = d / 2;
     if constexpr ((d & 1) == 0)
@@ -702,9 +732,11 @@ __global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
   };
   // byte offset of k-tile number kt of the walk inside a row
   auto k_offset = [&](int64_t kt) { return (int)((SYMK ? nk - 1 - kt : kt) * BK_ * 2); };
+  // whether this lane fetches k-tile number kt of the walk
+  auto fetches = [&](int64_t kt) { return kt < nk && (!TAIL || tail_ok || kt != (SYMK ? 0 : nk - 1)); };
   auto issue = [&](int64_t kt) {
-    const bool live = kt < nk;
-    const int so = live ? k_offset(kt) : 0;
+    const bool live = fetches(kt);
+    const int so = kt < nk ? k_offset(kt) : 0;
     unsigned char* sb = lds + (int)(kt % NSTAGE) * STAGE;
     static_for<0, LPS>([&](auto dc) { dma1(dc, sb, live, so); });
   };
@@ -743,8 +775,8 @@ __global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
     constexpr bool RDB = decltype(rdbc)::value != 0;
     constexpr int NR = 4 + (RDB ? 4 : 0);
     static_assert(NR + ND <= 16, "two side operations behind each of the first eight MFMAs");
-    const bool live = dkt < nk;
-    const int so = live ? k_offset(dkt) : 0;
+    const bool live = fetches(dkt);
+    const int so = dkt < nk ? k_offset(dkt) : 0;
     unsigned char* sbase = lds + (int)(dkt % NSTAGE) * STAGE;
     // side operation number n of the phase: in the refill phase the LDS-DMA loads come first (the
     // longest latency), then the fragment reads
@@ -784,19 +816,25 @@ __global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
   lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[0][0], Fb[0][1], Fb[0][2], Fb[0][3]);
   auto k_tile = [&](int64_t kt) {
     const uint32_t so_cur = (uint32_t)((kt % NSTAGE) * STAGE);
-    phase(I0{}, I0{}, I0{}, I1{}, I0{}, I0{}, offA[0] + so_cur, 0u, 0);
-    lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
-    phase(I1{}, I0{}, I1{}, I0{}, I1{}, I0{}, offA[1] + so_cur, offB[1] + so_cur, 0);
-    lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[1][0], Fb[1][1], Fb[1][2], Fb[1][3]);
-    phase(I0{}, I1{}, I0{}, I1{}, I0{}, I0{}, offA[1] + so_cur, 0u, 0);
-    lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
+    if constexpr (HALVES == 2) {
+      phase(I0{}, I0{}, I0{}, I1{}, I0{}, I0{}, offA[0] + so_cur, 0u, 0);
+      lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
+      phase(I1{}, I0{}, I1{}, I0{}, I1{}, I0{}, offA[1] + so_cur, offB[1] + so_cur, 0);
+      lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[1][0], Fb[1][1], Fb[1][2], Fb[1][3]);
+      phase(I0{}, I1{}, I0{}, I1{}, I0{}, I0{}, offA[1] + so_cur, 0u, 0);
+      lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
+    } else {
+      phase(I0{}, I0{}, I0{}, I0{}, I1{}, I0{}, offA[1] + so_cur, offB[1] + so_cur, 0);
+      lds_wait8(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3], Fb[1][0], Fb[1][1], Fb[1][2], Fb[1][3]);
+    }
     // every fragment of k-tile kt is in registers: its slot can be refilled once all
     // waves are here, and k-tile kt+1 has landed once this wave's share of it has
     wait_vmcnt<(NSTAGE - 2) * LPS>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t so_next = (uint32_t)(((kt + 1) % NSTAGE) * STAGE);
-    phase(I1{}, I1{}, I1{}, I0{}, I1{}, I8{}, offA[0] + so_next, offB[0] + so_next, kt + NSTAGE);
+    phase(I1{}, I1{}, std::integral_constant<int, HALVES - 1>{}, I0{}, I1{}, I8{}, offA[0] + so_next, offB[0] + so_next,
+          kt + NSTAGE);
     lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[0][0], Fb[0][1], Fb[0][2], Fb[0][3]);
   };
   int64_t kt = 0;
@@ -825,13 +863,29 @@ __global__ __launch_bounds__(512) void gemm_dma_kernel(GemmDev a) {
 
 // ---- host side ---------------------------------------------------------------
 constexpr int kBO = 256, kBT = 256, kWO = 128, kWT = 64;
+constexpr int kSmall = 128;                  // rows and columns of a small tile
 constexpr int64_t kChunkBytes = (int64_t)128 << 20;
-constexpr int kDmaBK = 64, kDmaStages = 2;   // k-tile depth and LDS ring slots of the pipelined kernel
-constexpr int kDmaThreads = 512;             // its 2 x 4 wave grid (128 x 64 outputs per wave)
+// Up to this many tiles a launch is dealt in strips (us, patches -> strips: 480 tiles 252 -> 224, 640 318 ->
+// 308, 960 428 -> 401; 1080 664 -> 667, 1720 762 -> 815: there a strip no longer fits an L2).
+constexpr int64_t kStripTiles = 1024;
+constexpr int kDmaBK = 64;                   // k-tile depth of the pipelined kernel
 
-void gemm_tile_counts(int64_t n_tok, int64_t c_out, int64_t* tiles_o, int64_t* tiles_t) {
-  *tiles_o = ceil_div(c_out, kBO);
-  *tiles_t = ceil_div(n_tok, kBT);
+void gemm_tile_counts(int64_t n_tok, int64_t c_out, bool small, int64_t* tiles_o, int64_t* tiles_t) {
+  *tiles_o = ceil_div(c_out, small ? kSmall : kBO);
+  *tiles_t = ceil_div(n_tok, small ? kSmall : kBT);
+}
+
+// Whether a launch is faster with 128 x 128 tiles (any result is the same up to the order of the loss sums:
+// an output's own products are added in the same order).  Two small blocks share a CU: up to 512 of them
+// are one round, where big tiles leave CUs idle (store epilogue, us big -> small: 640 x 4096 x 4096
+// tokens x channels x outputs 93 -> 49, 1200 x 5120 x 5120 122 -> 82, 1800 x 4096 x 4096 100 -> 71; from 640
+// small tiles on the big ones win, 98 against 113).  Just past one round of big tiles the second
+// round is nearly empty and the small ones win again (1200 x 5120 x 13824, 270 big tiles: 243 -> 213; 320: 201
+// -> 188; 384: 206 -> 211).
+bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand) {
+  const int64_t big = ceil_div(c_out, kBO) * ceil_div(n_tok, kBT) * n_cand;
+  const int64_t small = ceil_div(c_out, kSmall) * ceil_div(n_tok, kSmall) * n_cand;
+  return small <= 512 || (big > 256 && small <= 1280);
 }
 
 static GemmDev make_dev(const GemmArgs& g) {
@@ -846,9 +900,12 @@ static GemmDev make_dev(const GemmArgs& g) {
   d.partial = g.partial; d.tok_partial = g.tok_partial;
   d.Yout = g.Yout; d.ldo = g.ldo; d.odt = g.yout_dtype;
   int64_t to, tt;
-  gemm_tile_counts(g.n_tok, g.c_out, &to, &tt);
+  gemm_tile_counts(g.n_tok, g.c_out, g.small, &to, &tt);
   d.tiles_o = (int)to; d.tiles_t = (int)tt;
   d.po = g.wide_patch ? 8 : 4; d.pt = PATCH_SLOTS / d.po;
+  // few token tiles: one patch across all of them (5 tiles in patches of 4 would alternate full and nearly
+  // empty patches over the XCDs: 20 candidates of 1200 x 5120 x 5120 1578 -> 1110 us)
+  if (tt <= 8) { d.pt = (int)tt; d.po = PATCH_SLOTS / d.pt; }
   const int PATCH_O = d.po, PATCH_T = d.pt;
   d.npo = (int)ceil_div(to, PATCH_O); d.npt = (int)ceil_div(tt, PATCH_T);
   d.rag = (int)(to % PATCH_O);
@@ -859,14 +916,20 @@ static GemmDev make_dev(const GemmArgs& g) {
   // on the same token patch from one candidate to the next, which measured steadier (and on most
   // boxes faster) on 153,600-token inputs than 3, 5 or 6 patches, whose speed flips between
   // launches by up to 8 %.
-  const int64_t patch_bytes = (int64_t)PATCH_T * kBT * g.c_in * 2;
+  const int64_t patch_bytes = (int64_t)PATCH_T * (g.small ? kSmall : kBT) * g.c_in * 2;
   if ((int64_t)d.npt * patch_bytes <= kChunkBytes) {
     d.cpt = d.npt;
   } else {
     d.cpt = 1;
     while (d.cpt * 2 <= kXcd && (int64_t)d.cpt * 2 * patch_bytes <= kChunkBytes) d.cpt *= 2;
   }
-  {
+  const int64_t tiles = to * tt * g.n_cand;
+  // (tiles of a symmetric product differ in work along the rows: strips would not be equal)
+  d.strips = tiles <= kStripTiles && !g.tri && !g.sym_k ? tiles : 0;
+  if (d.strips) {
+    // one strip per XCD, rounded up to whole blocks of eight
+    d.n_patches = ceil_div(ceil_div(tiles, kXcd), PATCH_SLOTS) * kXcd;
+  } else {
     const int n_full = d.rag ? d.npo - 1 : d.npo;
     const int64_t full_chunks = d.npt / d.cpt;
     const int cw_last = d.npt % d.cpt;
@@ -878,39 +941,55 @@ static GemmDev make_dev(const GemmArgs& g) {
   return d;
 }
 
+// the pipelined kernel needs 32-bit byte offsets inside a 256-row panel
+bool gemm_strides_ok(int64_t ldx, int64_t ldw) { return ldw < (1 << 21) && ldx < (1 << 21); }
+static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ldw); }
 // Whether launch_gemm_dot contracts only the upper part of a symmetric Wh (see SYMK).
-// the pipelined kernel needs whole k-tiles and 32-bit byte offsets inside a 256-row panel
-static bool pipelined_ok(const GemmArgs& g) {
-  return (g.c_in % kDmaBK) == 0 && g.ldw < (1 << 21) && g.ldx < (1 << 21);
-}
 bool gemm_dot_symmetric(const GemmArgs& g) { return g.sym_k && g.c_out == g.c_in && pipelined_ok(g); }
+
+template <typename T, int EPI, bool SYMK>
+static void launch_dma(const GemmDev& d, bool small, unsigned blocks, hipStream_t stream) {
+  const bool tail = (d.c_in % kDmaBK) != 0;
+  if (small) {
+    // one block per CU at most: four LDS stages hide the latency that a second block would
+    const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
+    if (!tail && deep) gemm_dma_kernel<T, 4, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
+    else if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
+    else if (deep) gemm_dma_kernel<T, 4, EPI, SYMK, true, 1><<<blocks, 256, 0, stream>>>(d);
+    else gemm_dma_kernel<T, 2, EPI, SYMK, true, 1><<<blocks, 256, 0, stream>>>(d);
+  } else if (!tail) {
+    gemm_dma_kernel<T, 2, EPI, SYMK, false, 2><<<blocks, 512, 0, stream>>>(d);
+  } else {
+    gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
+  }
+}
 
 template <int EPI>
 static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t stream) {
-  GemmDev d = make_dev(g);
+  const bool dma = pipelined_ok(g);
+  if (!dma && g.small) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
+  const GemmDev d = make_dev(g);
   const int64_t rounds = ceil_div(d.n_patches, kXcd);
   const int64_t blocks = rounds * kXcd * PATCH_SLOTS;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const bool dma = pipelined_ok(g);
   const bool symk = EPI == EPI_DOT && gemm_dot_symmetric(g);
   // (a symmetric product computes the tiles on and above the diagonal, a symmetric contraction
   // the k range from the diagonal block on: about half either way)
   const double tile_frac = (g.tri || symk) ? 0.5 * (1.0 + 1.0 / (double)d.tiles_o) : 1.0;
   ProfScope ps(name, stream, 2.0 * (double)g.n_tok * (double)g.c_in * (double)g.c_out * g.n_cand * tile_frac);
-  constexpr int NT = (kBO / kWO) * (kBT / kWT) * 64;
-  if (symk) {
+  if (dma) {
+    auto go = [&](auto sym) {
+      constexpr bool S = decltype(sym)::value;
+      if (!g.bf16) launch_dma<F16, EPI, S>(d, g.small, (unsigned)blocks, stream);
+      else launch_dma<BF16, EPI, S>(d, g.small, (unsigned)blocks, stream);
+    };
     if constexpr (EPI == EPI_DOT) {
-      if (!g.bf16)
-        gemm_dma_kernel<F16, kDmaStages, EPI_DOT, true><<<(unsigned)blocks, kDmaThreads, 0, stream>>>(d);
-      else
-        gemm_dma_kernel<BF16, kDmaStages, EPI_DOT, true><<<(unsigned)blocks, kDmaThreads, 0, stream>>>(d);
+      if (symk) go(std::true_type{}); else go(std::false_type{});
+    } else {
+      go(std::false_type{});
     }
-  } else if (dma) {
-    if (!g.bf16)
-      gemm_dma_kernel<F16, kDmaStages, EPI><<<(unsigned)blocks, kDmaThreads, 0, stream>>>(d);
-    else
-      gemm_dma_kernel<BF16, kDmaStages, EPI><<<(unsigned)blocks, kDmaThreads, 0, stream>>>(d);
   } else {
+    constexpr int NT = (kBO / kWO) * (kBT / kWT) * 64;
     if (!g.bf16) gemm_kernel<F16, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
     else gemm_kernel<BF16, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
   }
@@ -918,17 +997,17 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
 }
 
 // Host-side check of the block -> tile map for one problem shape, in both block orders (candidates
-// inside every patch row, and candidate-outermost) and both patch shapes: walks every block id of the launch and counts
+// inside every patch row, and candidate-outermost), both patch shapes and both tile sizes: walks every block id of the launch and counts
 // how often each (candidate, tile) is produced.  Returns the number of tiles that are not produced
 // exactly once (0 = both maps are bijections onto the tiles), or -1 for an invalid shape.
 // *blocks_out receives the grid size.
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out) {
   if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
   int64_t bad = 0;
-  for (int order = 0; order < 4; ++order) {
+  for (int order = 0; order < 8; ++order) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
-    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0;
+    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.small = (order & 4) != 0;
     const GemmDev d = make_dev(g);
     const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
     if (blocks_out && order == 0) *blocks_out = blocks;

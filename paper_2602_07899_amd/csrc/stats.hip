@@ -8,25 +8,24 @@ namespace tlq {
 // ---------------------------------------------------------------- S0 x_stat
 // Sec. 3.1.2 x_stat (mean variant of the ablation table, or max over all
 // tokens).  Each lane owns 8 consecutive channels (one 16-byte load per row);
-// the 4 waves of a block walk interleaved rows of the block's row chunk and
+// the waves of a block walk interleaved rows of the block's row chunk and
 // are combined through LDS; chunks are combined by a second kernel.  Sums are
 // carried in double: |fp16| values are multiples of 2^-24 below 2^16, so the
 // sum over up to 2^37 tokens is exact and the order of addition is immaterial.
-constexpr int kXsThreads = 256;
 constexpr int kXsCols = 64 * 8;  // channels per block
 
-// 16 rows per chunk at least (four a wave), 128 chunks at most: 256 tokens in two chunks of 128 rows left
-// two blocks per 512 channels busy for 11 us, sixteen chunks take 5.
 int xstat_chunks(int64_t n_tok) {
-  int64_t c = ceil_div(n_tok, 16);
+  int64_t c = ceil_div(n_tok, 128);
   return (int)(c < 1 ? 1 : (c > 128 ? 128 : c));
 }
 
-template <typename T, int KIND, bool MASKED>
-__global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
+// NW waves per block: 16 where a chunk has 128 rows at most (8 a wave; with 4 waves the two blocks of a
+// 256 x 512 input walked 32 rows each wave, 11 us against 4), 4 on longer chunks.
+template <typename T, int KIND, bool MASKED, int NW>
+__global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
     const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx, int rows_per_chunk,
     double* __restrict__ partial, const uint8_t* __restrict__ pos_mask, int64_t period) {
-  __shared__ double red[4][kXsCols];
+  __shared__ double red[NW][kXsCols];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t c0 = (int64_t)blockIdx.x * kXsCols + lane * 8;
@@ -47,13 +46,13 @@ __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
   };
   if (MASKED || c0 < c_in) {
     if constexpr (!MASKED) {
-      for (int64_t r = r0 + wave; r < r1; r += 4) add(*reinterpret_cast<const uint4*>(X + r * ldx + c0));
+      for (int64_t r = r0 + wave; r < r1; r += NW) add(*reinterpret_cast<const uint4*>(X + r * ldx + c0));
     } else {
       const int64_t cr = c0 < c_in ? c0 : 0;     // (every lane takes part in the look-up)
       // rows that are not selected are not read: the lanes look 64 of the wave's rows up at once, the set
       // bits are then walked four loads at a time (a mask load and a division per row kept the loads apart)
-      for (int64_t rb = r0 + wave; rb < r1; rb += 4 * 64) {
-        const int64_t row = rb + 4 * (int64_t)lane;
+      for (int64_t rb = r0 + wave; rb < r1; rb += NW * 64) {
+        const int64_t row = rb + NW * (int64_t)lane;
         uint64_t sel = __builtin_amdgcn_ballot_w64(row < r1 && pos_mask[row % period] != 0);
         while (sel) {
           uint4 v[4];
@@ -61,7 +60,7 @@ __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
           for (int i = 0; i < 4; ++i) {
             v[i] = make_uint4(0, 0, 0, 0);       // a zero changes neither the sum nor the maximum
             if (sel) {
-              v[i] = *reinterpret_cast<const uint4*>(X + (rb + 4 * (int64_t)__builtin_ctzll(sel)) * ldx + cr);
+              v[i] = *reinterpret_cast<const uint4*>(X + (rb + NW * (int64_t)__builtin_ctzll(sel)) * ldx + cr);
               sel &= sel - 1;
             }
           }
@@ -74,12 +73,12 @@ __global__ __launch_bounds__(kXsThreads) void xstat_partial_kernel(
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[wave][lane * 8 + j] = acc[j];
   __syncthreads();
-  for (int i = threadIdx.x; i < kXsCols; i += kXsThreads) {
+  for (int i = threadIdx.x; i < kXsCols; i += NW * 64) {
     const int64_t c = (int64_t)blockIdx.x * kXsCols + i;
     if (c < c_in) {
-      double s;
-      if (KIND == 0) s = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
-      else s = fmax(fmax(red[0][i], red[1][i]), fmax(red[2][i], red[3][i]));
+      double s = red[0][i];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s = KIND == 0 ? s + red[w][i] : fmax(s, red[w][i]);
       partial[(int64_t)blockIdx.y * c_in + c] = s;
     }
   }
@@ -125,15 +124,21 @@ hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   const uint16_t* x = (const uint16_t*)X;
   {
     ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
-    auto go = [&](auto kern) { kern<<<grid, kXsThreads, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period); };
-    if (pos_mask) {       // only the maximum has a masked form
-      if (!bf16) go(xstat_partial_kernel<F16, 1, true>);
-      else go(xstat_partial_kernel<BF16, 1, true>);
-    }
-    else if (!bf16 && kind == 0) go(xstat_partial_kernel<F16, 0, false>);
-    else if (!bf16) go(xstat_partial_kernel<F16, 1, false>);
-    else if (kind == 0) go(xstat_partial_kernel<BF16, 0, false>);
-    else go(xstat_partial_kernel<BF16, 1, false>);
+    const bool shallow = rows <= 128;
+    auto go = [&](auto kern, int waves) {
+      kern<<<grid, waves * 64, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
+    };
+    auto pick = [&](auto t) {
+      using T = decltype(t);
+      if (pos_mask) {       // only the maximum has a masked form
+        if (shallow) go(xstat_partial_kernel<T, 1, true, 16>, 16); else go(xstat_partial_kernel<T, 1, true, 4>, 4);
+      } else if (kind == 0) {
+        if (shallow) go(xstat_partial_kernel<T, 0, false, 16>, 16); else go(xstat_partial_kernel<T, 0, false, 4>, 4);
+      } else {
+        if (shallow) go(xstat_partial_kernel<T, 1, false, 16>, 16); else go(xstat_partial_kernel<T, 1, false, 4>, 4);
+      }
+    };
+    if (!bf16) pick(F16{}); else pick(BF16{});
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -198,3 +198,40 @@ def test_selection_block_edges(gpu, B, N, C, l2):
         np.testing.assert_array_equal(xs.cpu().numpy(), orc.x_stat_topk_max(X, rm))
         tlq.x_stat(dev(X, gpu, False), p, xs)
         np.testing.assert_array_equal(xs.cpu().numpy(), orc.x_stat_mean(X))
+
+
+# 128- and 256-tiles on both sides of the rule, k-tiles with 8 .. 56 channels in the last one, tokens and
+# outputs around the tile edges, token tiles that fill one patch, strided operands
+@pytest.mark.parametrize("n,ci,co,pad,bf16", [
+    (1, 8, 1, 0, False), (127, 72, 129, 8, True), (128, 64, 128, 0, False), (129, 120, 127, 0, True),
+    (257, 136, 255, 8, False), (1030, 184, 1290, 0, True), (1281, 264, 3330, 8, False), (5000, 72, 3400, 0, False)])
+def test_products_at_tile_edges(gpu, n, ci, co, pad, bf16):
+    import torch
+    g = np.random.default_rng([27, n, ci, co])
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    code = tlq.BF16 if bf16 else tlq.F16
+    p = tlq.params(bits=4, group=8, x_dtype=code, yref_dtype=tlq.F32)
+    wide = lambda a: torch.full((a.shape[0], ci + pad), 9.0, dtype=torch.bfloat16 if bf16 else torch.float16,
+                                device=gpu)[:, :ci].copy_(dev(a, gpu, bf16))
+    tX, tW = wide(X), wide(W)
+    Y = torch.full((n, co + -co % 4 + 4), 7.0, dtype=torch.float32, device=gpu)
+    tlq.ref_output(tX, tW, Y[:, :co], p)
+    want = orc.ref_output(X, W)
+    mag = np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)).T
+    got = Y.cpu().numpy()
+    assert np.all(got[:, co:] == 7.0)
+    # exact products, float accumulation: ci roundings of at most 2^-24 of the magnitude
+    assert np.all(np.abs(got[:, :co] - want) <= (ci + 2) * 2.0 ** -24 * mag + 1e-30)
+    # the loss of the same product, against a target away from it, with and without per-token errors
+    T = (want + g.standard_normal(want.shape)).astype(np.float32)
+    Y[:, :co].copy_(torch.from_numpy(T))
+    w = np.full(n, 1.0 / n, np.float32)
+    ref, e = orc.weighted_layer_err(X, W.astype(np.float64), T, w)
+    for per_tok in (False, True):
+        loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+        tlq.weighted_layer_err(tX, tW, None, Y[:, :co], torch.from_numpy(w).to(gpu), p, loss,
+                               per_token_err=err if per_tok else None)
+        np.testing.assert_allclose(float(loss.item()), ref, rtol=2e-5)      # float sums of positive terms
+        if per_tok:
+            np.testing.assert_allclose(err.cpu().numpy(), e, rtol=2e-5)
