@@ -366,14 +366,6 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   }
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   g.partial = e.partial; g.tok_partial = per_token_err ? e.tok_partial : nullptr;
-  if (!per_token_err && gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1)) {
-    // (without per-token errors their rows hold the partials of small tiles)
-    int64_t to, tt;
-    gemm_tile_counts(n_tok, c_out, true, &to, &tt);
-    if (to * tt <= e.tiles_o * n_tok) {
-      g.small = true; e.tiles_o = to; e.tiles_t = tt; e.partial = g.partial = e.tok_partial;
-    }
-  }
   TLQ_HIP(launch_gemm_loss(g, st));
   TLQ_HIP(launch_finalize(e.partial, 1, e.tiles_o * e.tiles_t, c_out, nullptr, c_in, loss, nullptr,
                           nullptr, st));
