@@ -157,27 +157,47 @@ GramView view_gram(void* buf, int64_t c_in) {
 // split along the tokens into n_split partial products (summed afterwards in a fixed order) so
 // that the launch has a few thousand workgroups.
 struct GramPlan { float* wmax; int* e; uint16_t* xst; float* H; int64_t kp, kc; int n_split; size_t bytes; };
-GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
+GramPlan lay_out_gram(void* ws, int64_t n_tok, int64_t c_in, int n_split) {
   GramPlan g;
   Carver c(ws);
-  int64_t to, tt;
-  gemm_tile_counts(c_in, c_in, false, &to, &tt);
-  const int64_t live = to * (to + 1) / 2;
-  // measured: more, shorter splits run faster up to 16 (5120 channels: 6.0 ms with 4, 3.9 ms with 16;
-  // beyond 16 it collapses); 13824 channels: 4 splits 28.2 ms, 5: 29.7, 12 - 16: 27.5 + a longer sum
-  int64_t ns = (5000 + live - 1) / live;
-  const int64_t max_ns = n_tok / 4096;                 // at least 4096 tokens (64 k-tiles) per split
-  ns = ns > 16 ? 16 : ns;
-  ns = ns > max_ns ? max_ns : ns;
-  g.n_split = (int)(ns < 1 ? 1 : ns);
-  g.kc = (int64_t)align_up((size_t)((n_tok + g.n_split - 1) / g.n_split), 64);
-  g.kp = g.kc * g.n_split;
+  g.n_split = n_split;
+  g.kc = (int64_t)align_up((size_t)((n_tok + n_split - 1) / n_split), 64);
+  g.kp = g.kc * n_split;
   g.wmax = c.take<float>(1);
   g.e = c.take<int>((size_t)c_in);
   g.xst = c.take<uint16_t>((size_t)c_in * g.kp);
-  g.H = c.take<float>((size_t)g.n_split * c_in * c_in);
+  g.H = c.take<float>((size_t)n_split * c_in * c_in);
   g.bytes = c.off;
   return g;
+}
+GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
+  int64_t to, tt;
+  gemm_tile_counts(c_in, c_in, false, &to, &tt);
+  const int64_t live = to * (to + 1) / 2;
+  // the workspace holds up to 16 partial products of at least 4096 tokens each, 5000 tiles in all
+  int64_t ns = (5000 + live - 1) / live;
+  const int64_t max_ns = n_tok / 4096;
+  ns = ns > 16 ? 16 : ns;
+  ns = ns > max_ns ? max_ns : ns;
+  ns = ns < 1 ? 1 : ns;
+  GramPlan best = lay_out_gram(ws, n_tok, c_in, (int)ns);
+  const size_t have = best.bytes;
+  // Among the splits that fit, the one with the least time in units of a k-tile on all CUs (1.65 us): whole rounds
+  // of 256 tiles, each its k-tiles and six more of prologue and epilogue, and per split one write and one
+  // read of half the float matrix at 4.5 TB/s.  A split's tokens stay in the last-level cache while several
+  // splits are under way (153,600 x 5120: 6 splits of 262 MB 4.2 ms, 12 of 131 MB 3.9, 16 of 98 MB 3.75); a single
+  // one may fill it (12,000 x 11008: 2 splits 1.82 ms with the sum, one 1.68).
+  double best_cost = 0.0;
+  for (int64_t n = ns; n >= 1; --n) {
+    const GramPlan g = lay_out_gram(ws, n_tok, c_in, (int)n);
+    if (g.bytes > have) continue;
+    if (n != ns && g.kc * c_in * 2 > ((int64_t)(n == 1 ? 280 : 100) << 20)) continue;
+    const double cost = (double)((live * n + 255) / 256) * ((double)g.kc / 64 + 6.0) +
+                        (double)n * 4.0 * (double)c_in * (double)c_in / (4.5e12 * 1.65e-6);
+    if (n == ns || cost < best_cost) { best = g; best_cost = cost; }
+  }
+  best.bytes = have;
+  return best;
 }
 struct GramSearchPlan { float* s_table; float* inv_table; float* partial; uint16_t* dq; size_t bytes;
                         int64_t tiles_o, tiles_t; };
@@ -442,8 +462,8 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     r.Wh = W; r.c_out = c_out; r.ldw = ldw; r.w_cand_stride = 0; r.n_cand = 1; r.bf16 = bf16;
     r.Yout = s.d0; r.ldo = s.ldd; r.yout_dtype = TLQ_F32;
     r.small = gemm_strides_ok(ldx, ldw) && gemm_small_tiles(n_tok, c_out, 1);
+    r.Yref = Y_ref; r.ldy = ldy; r.yref_dtype = p->yref_dtype;   // subtracted in the epilogue (float output)
     TLQ_HIP(launch_gemm_store(r, st));
-    TLQ_HIP(launch_sub_from_y(Y_ref, ldy, p->yref_dtype, s.d0, s.ldd, n_tok, c_out, st));
   }
   // S3 + S4: one launch over the stacked candidates (fp16 operands in either case)
   GemmArgs g{};
@@ -557,7 +577,6 @@ tlq_status tlq_token_gram(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   r.X = g.xst; r.n_tok = c_in; r.c_in = g.kc; r.ldx = g.kp; r.x_cand_stride = g.kc;
   r.Wh = g.xst; r.c_out = c_in; r.ldw = g.kp; r.w_cand_stride = g.kc; r.n_cand = g.n_split; r.bf16 = false;
   r.Yout = g.H; r.ldo = c_in; r.yout_dtype = TLQ_F32; r.o_cand_stride = c_in * c_in; r.tri = true;
-  r.cand_outer = true; r.wide_patch = c_in >= 32 * 256;   // measured: 8 x 4 patches pay from ~32 tile rows on
   TLQ_HIP(launch_gemm_store(r, st));
   return hip_status(launch_gram_finish(g.H, c_in, g.n_split, c_in * c_in, g.wmax, g.e, v.factor, v.col_scale,
                                        v.C, st));

@@ -129,7 +129,7 @@ struct GemmArgs {
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
   float* tok_partial;      // [tiles_o, n_tok] float or NULL (single candidate only)
-  // store epilogue (n_cand == 1): Y[t,o]
+  // store epilogue: Y[t,o]; with Yref given (float output only) Yref - Y
   void* Yout; int64_t ldo; int yout_dtype;
 };
 // `small`: 128 x 128 output tiles instead of 256 x 256 (gemm_small_tiles says when they are faster)
@@ -155,10 +155,6 @@ hipError_t launch_gram_operand(const void* X, int64_t n_tok, int64_t c_in, int64
 // d'^T C d' into the loss; e is scratch [c_in].
 hipError_t launch_gram_finish(float* H, int64_t c_in, int n_split, int64_t split_stride, const float* wmax,
                               int* e, double* factor, float* col_scale, void* C, hipStream_t stream);
-
-// D[t,o] = Y[t,o] - D[t,o] (D float, row stride ldd)
-hipError_t launch_sub_from_y(const void* Y, int64_t ldy, int ydt, float* D, int64_t ldd, int64_t n_tok,
-                             int64_t c_out, hipStream_t stream);
 
 // S4 final combine + S5 selection.
 // `factor` (optional): device double multiplied into every loss

@@ -30,6 +30,7 @@
 // 16-byte chunks of a row are XOR-swizzled with (row/2)%8 so that the 16 lanes
 // served together by a 128-bit LDS access touch 16 different bank groups, for
 // the fragment reads and for the tile writes alike.
+#include <cmath>
 #include <cstdlib>
 #include <utility>
 
@@ -128,6 +129,7 @@ struct GemmDev {
   int cpt;          // token patches per chunk (see make_dev)
   int rag, rag_pt;  // tile rows of the last, incomplete patch row (0 = none) and its patch width in tiles
   int po, pt;       // patch shape in tiles (po * pt <= PATCH_SLOTS)
+  int rot;          // XCD rotation from one round of patches to the next (see make_dev)
   int64_t strips;   // > 0: no patches, the launch has this many tiles (see decode_tile)
 };
 
@@ -283,6 +285,38 @@ __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref
   }
 }
 
+// The staging of loss_rows_lds for the store epilogue that subtracts: the wave's piece of Yref into LDS ...
+template <typename L>
+__device__ __forceinline__ void stage_rows(const void* Yref, int64_t ldy, int64_t ow, int64_t tw, unsigned char* ylds) {
+  constexpr int WO = L::WO, WT = L::WT;
+  constexpr int CPR = WO / 8;              // 16-byte chunks per token row
+  constexpr int RPI = 64 / CPR;            // token rows per wave-wide copy
+  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
+  const int lane = threadIdx.x & 63;
+  const uint16_t* Y = (const uint16_t*)Yref;
+  const int cr = lane / CPR, cc = lane % CPR;
+  uint4 v[WT / RPI];
+#pragma unroll
+  for (int j = 0; j < WT / RPI; ++j) v[j] = *reinterpret_cast<const uint4*>(Y + (tw + j * RPI + cr) * ldy + ow + cc * 8);
+#pragma unroll
+  for (int j = 0; j < WT / RPI; ++j) {
+    const int row = j * RPI + cr;
+    *reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4)) = v[j];
+  }
+  // the values are picked up by OTHER lanes of this wave: order the LDS writes before the reads
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// ... and four staged values: token `tok` of the wave tile, output rows o .. o + 3 of it (o a multiple of 4)
+template <typename YT, typename L>
+__device__ __forceinline__ void staged_y4(const unsigned char* ylds, int tok, int o, float (&y)[4]) {
+  const uint2 u = *reinterpret_cast<const uint2*>(ylds + tok * (L::WO * 2) + (((o >> 3) ^ row_key<L::WO / 8>(tok)) << 4) +
+                                                  ((o >> 2) & 1) * 8);
+  y[0] = YT::to_float((uint16_t)(u.x & 0xffffu)); y[1] = YT::to_float((uint16_t)(u.x >> 16));
+  y[2] = YT::to_float((uint16_t)(u.y & 0xffffu)); y[3] = YT::to_float((uint16_t)(u.y >> 16));
+}
+
 // Store epilogue of an interior wave tile with a 16-bit output, through LDS: every lane drops
 // its rounded values into `ylds` (WT x WO 16-bit, this wave's own, same chunk-XOR-token layout
 // as loss_rows_lds), then the wave writes whole 128-byte lines, 8 lines per instruction.
@@ -344,6 +378,14 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
         return;
       }
     }
+    // the subtrahend's place: whole lines through LDS where the tile is inside the matrix (see loss_rows_lds)
+    unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * (WO * WT * 2);
+    bool staged = false;
+    if constexpr (YLDS) {
+      staged = a.Yref && a.ydt != TLQ_F32 && (o0 + NWO * WO <= a.c_out) && (t0 + BT <= a.n_tok) && (a.ldy % 8) == 0 &&
+               ((uintptr_t)a.Yref % 16) == 0;
+      if (staged) stage_rows<L>(a.Yref, a.ldy, o0 + wo * WO, t0 + wt * WT, ylds);
+    }
 #pragma unroll
     for (int tb = 0; tb < L::NTB; ++tb) {
       const int64_t t = t0 + wt * WT + L::tok(tb, lane);
@@ -354,6 +396,18 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
         const int64_t o = o0 + wo * WO + L::row(q, lane);
         float y[4] = {sg * L::get(acc, q, tb, 0), sg * L::get(acc, q, tb, 1), sg * L::get(acc, q, tb, 2),
                       sg * L::get(acc, q, tb, 3)};
+        if (a.Yref) {                     // the output is Yref - product
+          float yr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+          if (staged) {
+            if (a.ydt == TLQ_F16) staged_y4<F16, L>(ylds, L::tok(tb, lane), L::row(q, lane), yr);
+            else staged_y4<BF16, L>(ylds, L::tok(tb, lane), L::row(q, lane), yr);
+          } else if (o + 3 < a.c_out) load_y4(a.Yref, a.ydt, t * a.ldy + o, yr);
+          else
+            for (int r = 0; r < 4; ++r)
+              if (o + r < a.c_out) yr[r] = load_y(a.Yref, a.ydt, t * a.ldy + o + r);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[r] = yr[r] - y[r];
+        }
         if (o + 3 < a.c_out) store_y4(Yo, a.odt, t * a.ldo + o, y);
         else
           for (int r = 0; r < 4; ++r)
@@ -427,6 +481,37 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
 // Launches of few tiles (`strips`) have no use for patches: whole and nearly empty patches would alternate
 // over the XCDs (5 token tiles in patches of 4: every other XCD idle).  There the tiles are
 // numbered along the shorter side first and every XCD takes one eighth of the numbers, a strip.
+// Symmetric products (`tri`) number only the tiles on and above the diagonal: blocks of eight tile columns,
+// in them row by row (32 consecutive tiles: 4 x 8).  Every candidate's numbers are dealt to the XCDs in
+// eight equal strips.  (In patches the dead half of the square left XCDs idle: at 16 x 16 tiles a candidate
+// has eight patches, two of them empty, and each XCD met the same patch of every candidate.)
+__host__ __device__ __forceinline__ bool decode_tri(const GemmDev& a, int64_t bid, int& cand, int& to, int& tt) {
+  const int n = a.tiles_o, live = n * (n + 1) / 2, per = (live + kXcd - 1) / kXcd;
+  const int xcd = (int)(bid & (kXcd - 1));
+  const int64_t i = bid / kXcd;
+  if (i >= (int64_t)per * a.n_cand) return false;
+  cand = (int)(i / per);
+  const int idx = (int)((int64_t)xcd * live / kXcd) + (int)(i % per);
+  if (idx >= (int)((int64_t)(xcd + 1) * live / kXcd)) return false;
+  // the last column block whose first column c0 has c0 (c0 + 1) / 2 tiles to its left
+  int cb = (int)((sqrtf(8.0f * (float)idx + 1.0f) - 1.0f) * 0.5f) / 8;
+  while (cb > 0 && cb * 8 * (cb * 8 + 1) / 2 > idx) --cb;
+  while ((cb + 1) * 8 < n && (cb + 1) * 8 * ((cb + 1) * 8 + 1) / 2 <= idx) ++cb;
+  const int c0 = cb * 8, w = n - c0 < 8 ? n - c0 : 8;
+  int rem = idx - c0 * (c0 + 1) / 2;
+  if (rem < c0 * w) {
+    to = rem / w;
+    tt = c0 + rem % w;
+  } else {
+    rem -= c0 * w;
+    int r = 0;
+    while (rem >= w - r) { rem -= w - r; ++r; }
+    to = c0 + r;
+    tt = to + rem;
+  }
+  return true;
+}
+
 __host__ __device__ __forceinline__ bool decode_tile(const GemmDev& a, int64_t bid, int& cand, int& to, int& tt) {
   if (a.strips > 0) {
     const int64_t xcd = bid & (kXcd - 1);
@@ -442,7 +527,7 @@ __host__ __device__ __forceinline__ bool decode_tile(const GemmDev& a, int64_t b
   const int PATCH_O = a.po, PATCH_T = a.pt;
   const int64_t round = bid / (kXcd * PATCH_SLOTS);
   const int within = (int)(bid % (kXcd * PATCH_SLOTS));
-  int64_t patch = round * kXcd + (within & (kXcd - 1));
+  int64_t patch = round * kXcd + (((within & (kXcd - 1)) + a.rot * (int)(round & (kXcd - 1))) & (kXcd - 1));
   const int slot = within / kXcd;
   if (patch >= a.n_patches) return false;
   // candidate-outermost order: the same walk with one candidate, repeated per candidate
@@ -477,6 +562,20 @@ __host__ __device__ __forceinline__ bool decode_tile(const GemmDev& a, int64_t b
   return to < a.tiles_o && tt < a.tiles_t;
 }
 
+// The tile of this block, in scalar registers: the operand descriptors are built from it, and a descriptor
+// in vector registers puts a loop over its distinct values around every LDS-DMA load.
+template <int EPI>
+__device__ __forceinline__ bool block_tile(const GemmDev& a, int& cand, int& to, int& tt) {
+  bool live;
+  if (EPI == EPI_STORE && a.tri) live = decode_tri(a, blockIdx.x, cand, to, tt);
+  else live = decode_tile(a, blockIdx.x, cand, to, tt);
+  if (!live) return false;
+  cand = __builtin_amdgcn_readfirstlane(cand);
+  to = __builtin_amdgcn_readfirstlane(to);
+  tt = __builtin_amdgcn_readfirstlane(tt);
+  return true;
+}
+
 // General kernel: two LDS stages; the global loads of k-tile i+1 are issued before the MFMAs of
 // k-tile i and written to the other stage afterwards; one barrier per k-tile.
 template <typename T, int BO, int BT, int WO, int WT, int EPI>
@@ -490,8 +589,7 @@ __global__ __launch_bounds__((BO / WO) * (BT / WT) * 64) void gemm_kernel(GemmDe
   __shared__ float red[NW];
 
   int cand, to, tt;
-  if (!decode_tile(a, blockIdx.x, cand, to, tt)) return;
-  if (a.tri && to > tt) return;   // the mirrored tile carries the same values
+  if (!block_tile<EPI>(a, cand, to, tt)) return;
   const int64_t o0 = (int64_t)to * BO, t0 = (int64_t)tt * BT;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -681,8 +779,7 @@ __global__ __launch_bounds__(HALVES * 256) void gemm_dma_kernel(GemmDev a) {
   __shared__ float red[NW];
 
   int cand, to, tt;
-  if (!decode_tile(a, blockIdx.x, cand, to, tt)) return;
-  if (a.tri && to > tt) return;   // the mirrored tile carries the same values
+  if (!block_tile<EPI>(a, cand, to, tt)) return;
   const int64_t o0 = (int64_t)to * BO, t0 = (int64_t)tt * BT;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -905,7 +1002,7 @@ static GemmDev make_dev(const GemmArgs& g) {
   d.po = g.wide_patch ? 8 : 4; d.pt = PATCH_SLOTS / d.po;
   // few token tiles: one patch across all of them (5 tiles in patches of 4 would alternate full and nearly
   // empty patches over the XCDs: 20 candidates of 1200 x 5120 x 5120 1578 -> 1110 us)
-  if (tt <= 8) { d.pt = (int)tt; d.po = PATCH_SLOTS / d.pt; }
+  if (tt < 8 && tt % d.pt && !g.sym_k) { d.pt = (int)tt; d.po = PATCH_SLOTS / d.pt; }
   const int PATCH_O = d.po, PATCH_T = d.pt;
   d.npo = (int)ceil_div(to, PATCH_O); d.npt = (int)ceil_div(tt, PATCH_T);
   d.rag = (int)(to % PATCH_O);
@@ -924,9 +1021,11 @@ static GemmDev make_dev(const GemmArgs& g) {
     while (d.cpt * 2 <= kXcd && (int64_t)d.cpt * 2 * patch_bytes <= kChunkBytes) d.cpt *= 2;
   }
   const int64_t tiles = to * tt * g.n_cand;
-  // (tiles of a symmetric product differ in work along the rows: strips would not be equal)
+  // (tiles of a symmetric contraction differ in work along the rows: strips would not be equal)
   d.strips = tiles <= kStripTiles && !g.tri && !g.sym_k ? tiles : 0;
-  if (d.strips) {
+  if (g.tri) {
+    d.n_patches = ceil_div(ceil_div(to * (to + 1) / 2, kXcd) * g.n_cand, PATCH_SLOTS) * kXcd;
+  } else if (d.strips) {
     // one strip per XCD, rounded up to whole blocks of eight
     d.n_patches = ceil_div(ceil_div(tiles, kXcd), PATCH_SLOTS) * kXcd;
   } else {
@@ -938,6 +1037,11 @@ static GemmDev make_dev(const GemmArgs& g) {
     };
     d.n_patches = (int64_t)g.n_cand * (full_chunks * per_cand(d.cpt) + (cw_last ? per_cand(cw_last) : 0));
   }
+  // Patches of a symmetric contraction differ in work (its upper rows are the long ones).  Where a candidate has a
+  // multiple of eight of them every XCD would meet the same ones each time: turned by five XCDs a round,
+  // long and short ones alternate (16 x 16 tiles, 20 candidates: 1.77 -> 1.40 ms; where the count is no
+  // multiple the turn only costs shared panels, 43 x 16 tiles 8.4 -> 9.4 ms).
+  d.rot = g.sym_k && (d.n_patches / g.n_cand) % kXcd == 0 ? 5 : 0;
   return d;
 }
 
@@ -997,17 +1101,19 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
 }
 
 // Host-side check of the block -> tile map for one problem shape, in both block orders (candidates
-// inside every patch row, and candidate-outermost), both patch shapes and both tile sizes: walks every block id of the launch and counts
+// inside every patch row, and candidate-outermost), both patch shapes and both tile sizes, and those of the
+// symmetric products over c_out and c_in: walks every block id of the launch and counts
 // how often each (candidate, tile) is produced.  Returns the number of tiles that are not produced
 // exactly once (0 = both maps are bijections onto the tiles), or -1 for an invalid shape.
 // *blocks_out receives the grid size.
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out) {
   if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
   int64_t bad = 0;
-  for (int order = 0; order < 8; ++order) {
+  for (int order = 0; order < 10; ++order) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
-    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.small = (order & 4) != 0;
+    if (order >= 8) { g.tri = true; g.n_tok = g.c_out = order == 8 ? c_out : c_in; }
+    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.sym_k = order == 3; g.small = !g.tri && (order & 4) != 0;
     const GemmDev d = make_dev(g);
     const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
     if (blocks_out && order == 0) *blocks_out = blocks;
@@ -1016,12 +1122,15 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand,
     if (!seen) return -1;
     for (int64_t b = 0; b < blocks; ++b) {
       int cand, to, tt;
-      if (!decode_tile(d, b, cand, to, tt)) continue;
+      if (!(g.tri ? decode_tri(d, b, cand, to, tt) : decode_tile(d, b, cand, to, tt))) continue;
       if (cand < 0 || cand >= n_cand || to < 0 || tt < 0) { ++bad; continue; }
       unsigned char& c = seen[((int64_t)cand * d.tiles_o + to) * d.tiles_t + tt];
       if (c < 255) ++c;
     }
-    for (int64_t i = 0; i < tiles; ++i) bad += seen[i] != 1;
+    for (int64_t i = 0; i < tiles; ++i) {
+      const int64_t row = i / d.tiles_t % d.tiles_o, col = i % d.tiles_t;
+      bad += seen[i] != (g.tri && row > col ? 0 : 1);
+    }
     free(seen);
   }
   return bad;

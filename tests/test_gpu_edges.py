@@ -235,3 +235,62 @@ def test_products_at_tile_edges(gpu, n, ci, co, pad, bf16):
         np.testing.assert_allclose(float(loss.item()), ref, rtol=2e-5)      # float sums of positive terms
         if per_tok:
             np.testing.assert_allclose(err.cpu().numpy(), e, rtol=2e-5)
+
+
+@pytest.mark.parametrize("n,co,ydt,bf16", [(300, 520, tlq.F16, False), (257, 264, tlq.BF16, True), (130, 203, tlq.F32, False),
+                                           (8000, 3400, tlq.BF16, True)])
+def test_difference_target_in_the_product_epilogue(gpu, n, co, ydt, bf16):
+    """Eight bits: the target minus the full-precision product is formed where the product is stored - 16-bit
+    targets inside the tiles through LDS, at the edges and in float directly, small and big tiles."""
+    import torch
+    g = np.random.default_rng([28, n, co])
+    ci, na = 64, 2
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    Yd = orc.ref_output(X, W) + 0.01 * g.standard_normal((n, co))
+    tdt = {tlq.F16: torch.float16, tlq.BF16: torch.bfloat16, tlq.F32: torch.float32}[ydt]
+    Y = torch.zeros((n, co + -co % 8 + 8), dtype=tdt, device=gpu)[:, :co]
+    Y.copy_(torch.from_numpy(Yd).to(gpu))
+    Yv = Y.double().cpu().numpy()
+    w = g.uniform(0.1, 1.0, n).astype(np.float32) / n
+    al = np.array([0.0, 0.5], np.float32)
+    p = tlq.params(bits=8, group=32, x_dtype=tlq.BF16 if bf16 else tlq.F16, yref_dtype=ydt)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses = torch.empty(na, dtype=torch.float32, device=gpu)
+    t = lambda a: torch.from_numpy(a).to(gpu)
+    tlq.scale_search(dev(X, gpu, bf16), dev(W, gpu, bf16), Y, t(w), t(al), p, best, idx, losses)
+    ref = orc.scale_search(X, W, Yv, w, 8, 32, al)
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
+
+
+@pytest.mark.parametrize("n,ci,co", [(4500, 2304, 40), (9000, 264, 300), (300, 4096, 2100)])
+def test_symmetric_products_deal_every_tile(gpu, n, ci, co):
+    """9 tile columns (one full block of eight and one over), one column block with a k tail in the loss, eight
+    patches per candidate: every element of the matrix and the losses through it."""
+    import torch
+    g = np.random.default_rng([29, n, ci])
+    X, W = F16(g.standard_normal((n, ci))), F16(g.standard_normal((co, ci)) * 0.05)
+    w = g.uniform(0.1, 1.0, n).astype(np.float32) / n
+    p = tlq.params(bits=3, group=8)
+    tX, tw = dev(X, gpu, False), torch.from_numpy(w).to(gpu)
+    gram = torch.zeros(tlq.token_gram_bytes(ci), dtype=torch.uint8, device=gpu)
+    tlq.token_gram(tX, tw, p, gram)
+    f, cs, C = tlq.gram_views(gram, ci)
+    G = f.double() * cs.double()[:, None] * cs.double()[None, :] * C.double()
+    Xd = tX.double()
+    want = Xd.t().contiguous() @ (Xd * tw.double()[:, None])
+    scale = want.diagonal().sqrt()
+    # tokens times sqrt(w) and the matrix itself are rounded to fp16 once each
+    assert (((G - want).abs() / (scale[:, None] * scale[None, :])).max().item()) <= 3 * 2.0 ** -11
+    al = np.array([0.0, 0.4, 0.8], np.float32)
+    xs = torch.empty(ci, dtype=torch.float32, device=gpu)
+    tlq.x_stat(tX, p, xs)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses, table = torch.empty(3, dtype=torch.float32, device=gpu), torch.empty((3, ci), dtype=torch.float32, device=gpu)
+    tlq.scale_search_gram(gram, dev(W, gpu, False), torch.from_numpy(al).to(gpu), p, xs, best, idx, losses, s_table_out=table)
+    for k in range(3):
+        s = table[k].cpu().numpy()
+        deq = torch.from_numpy(orc.fake_quant(W, s, 3, 8)[3].astype(np.float64)).to(gpu)
+        d = dev(W, gpu, False).double() - deq / table[k].double()[None, :]
+        ref = (((d @ want) * d).sum() / co).item()
+        assert abs(losses[k].item() - ref) <= 1e-3 * ref      # the parity bar of the search
