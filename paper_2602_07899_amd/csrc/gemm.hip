@@ -1037,11 +1037,13 @@ static GemmDev make_dev(const GemmArgs& g) {
     };
     d.n_patches = (int64_t)g.n_cand * (full_chunks * per_cand(d.cpt) + (cw_last ? per_cand(cw_last) : 0));
   }
-  // Patches of a symmetric contraction differ in work (its upper rows are the long ones).  Where a candidate has a
-  // multiple of eight of them every XCD would meet the same ones each time: turned by five XCDs a round,
-  // long and short ones alternate (16 x 16 tiles, 20 candidates: 1.77 -> 1.40 ms; where the count is no
-  // multiple the turn only costs shared panels, 43 x 16 tiles 8.4 -> 9.4 ms).
-  d.rot = g.sym_k && (d.n_patches / g.n_cand) % kXcd == 0 ? 5 : 0;
+  // Where a candidate has a multiple of eight patches and candidates are walked one after the other, every XCD
+  // meets the same patches each time, and they differ in work: the upper rows of a symmetric contraction
+  // are the long ones, the last token patch may be ragged.  Turned by five XCDs a round they
+  // alternate (quadratic form, 16 x 16 tiles, 20 candidates: 1.77 -> 1.40 ms; 16 x 15 tiles with per-candidate
+  // tokens: 2.34 -> 2.29 ms a search).  Where the count is no multiple the turn only costs shared panels (quadratic form,
+  // 43 x 16 tiles: 8.4 -> 9.4 ms).
+  d.rot = g.cand_outer && !g.tri && (d.n_patches / g.n_cand) % kXcd == 0 ? 5 : 0;
   return d;
 }
 
@@ -1113,7 +1115,7 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand,
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
     if (order >= 8) { g.tri = true; g.n_tok = g.c_out = order == 8 ? c_out : c_in; }
-    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.sym_k = order == 3; g.small = !g.tri && (order & 4) != 0;
+    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.sym_k = order == 3;   // (order 1 and 3 turn the XCDs) g.small = !g.tri && (order & 4) != 0;
     const GemmDev d = make_dev(g);
     const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
     if (blocks_out && order == 0) *blocks_out = blocks;

@@ -23,7 +23,13 @@ __global__ __launch_bounds__(1024) void gram_wmax_kernel(const float* __restrict
                                                          float* __restrict__ out) {
   __shared__ float red[16];
   float m = 0.0f;
-  for (int64_t i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, w[i]);
+  for (int64_t i = threadIdx.x; i < n; i += 16 * 1024) {   // 16 loads in flight (one at a time: 67 us for 153,600)
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = w[i + j * 1024 < n ? i + j * 1024 : i];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) m = fmaxf(m, v[j]);
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
