@@ -1102,23 +1102,39 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   return hipGetLastError();
 }
 
-// Host-side check of the block -> tile map for one problem shape, in both block orders (candidates
-// inside every patch row, and candidate-outermost), both patch shapes and both tile sizes, and those of the
-// symmetric products over c_out and c_in: walks every block id of the launch and counts
-// how often each (candidate, tile) is produced.  Returns the number of tiles that are not produced
-// exactly once (0 = both maps are bijections onto the tiles), or -1 for an invalid shape.
-// *blocks_out receives the grid size.
+// Host-side check of the block -> tile map for one problem shape: both block orders (candidates inside every
+// patch row, and candidate-outermost, which may turn the XCDs), both patch shapes and both tile sizes, the
+// quadratic form's map, and those of the symmetric products over c_out and c_in.  Each walk takes every block
+// id of its launch and counts how often each (candidate, tile) is produced; a walk whose tiles are not
+// of the size it is there for counts as a defect too.  Returns the number of tiles that are not produced
+// exactly once (0 = all maps are bijections onto the tiles), or -1 for an invalid shape.
+// *blocks_out receives the grid size of a launch with the tile size that gemm_small_tiles picks.
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out) {
   if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
+  const bool small_launch = gemm_small_tiles(n_tok, c_out, n_cand);
+  if (blocks_out) *blocks_out = 0;
   int64_t bad = 0;
-  for (int order = 0; order < 10; ++order) {
+  // walks 0 - 7: bit 0 the order, bit 1 the patch shape, bit 2 the tile size
+  enum { kQuadratic = 8, kTriOut, kTriIn, kWalks };
+  for (int walk = 0; walk < kWalks; ++walk) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
-    if (order >= 8) { g.tri = true; g.n_tok = g.c_out = order == 8 ? c_out : c_in; }
-    g.cand_outer = (order & 1) != 0; g.wide_patch = (order & 2) != 0; g.sym_k = order == 3;   // (order 1 and 3 turn the XCDs) g.small = !g.tri && (order & 4) != 0;
+    if (walk < kQuadratic) {
+      g.cand_outer = (walk & 1) != 0;
+      g.wide_patch = (walk & 2) != 0;
+      g.small = (walk & 4) != 0;
+    } else if (walk == kQuadratic) {
+      g.cand_outer = g.wide_patch = g.sym_k = true;
+    } else {
+      g.tri = true;
+      g.n_tok = g.c_out = walk == kTriOut ? c_out : c_in;
+    }
     const GemmDev d = make_dev(g);
+    const int64_t side = walk >= 4 && walk < kQuadratic ? 128 : 256;
+    if (d.tiles_o != (g.c_out + side - 1) / side || d.tiles_t != (g.n_tok + side - 1) / side) ++bad;
     const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
-    if (blocks_out && order == 0) *blocks_out = blocks;
+    if (blocks_out && walk < kQuadratic && !g.cand_outer && !g.wide_patch && g.small == small_launch)
+      *blocks_out = blocks;
     const int64_t tiles = (int64_t)n_cand * d.tiles_o * d.tiles_t;
     unsigned char* seen = (unsigned char*)calloc((size_t)tiles, 1);
     if (!seen) return -1;

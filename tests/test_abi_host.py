@@ -161,3 +161,27 @@ def test_block_to_tile_map_covers_every_tile_once(shape):
     if tiles >= 20000:
         assert blocks <= 1.02 * tiles          # the regrouped patch row leaves < 2 % dead slots
     assert tlq.selftest_tile_map(0, 8, 8, 1)[0] == -1
+
+
+# (tokens, channels, outputs, candidates, side of the launch's tiles): both sides of the rule that picks the tile
+# size (512 small tiles; more than 256 big ones and at most 1280 small ones), of the 1024 tiles up to which a
+# launch is dealt in strips, and launches of one to seven token tiles
+@pytest.mark.parametrize("shape", [
+    (2048, 64, 4096, 1, 128), (2048, 64, 4224, 1, 256), (1800, 4096, 4096, 1, 128), (1200, 5120, 13824, 1, 128),
+    (1281, 64, 16384, 1, 256), (256, 512, 512, 20, 128), (1300, 72, 11900, 1, 128), (1300, 72, 12000, 1, 128),
+    (8192, 64, 8192, 1, 256), (8192, 64, 8193, 1, 256), (1, 64, 5000, 9, 128), (300, 64, 3000, 7, 128),
+    (700, 64, 5120, 20, 256), (1200, 5120, 5120, 20, 256), (1500, 64, 5120, 20, 256), (1700, 64, 7000, 20, 256),
+    (1024, 64, 2304, 30, 256)])
+def test_block_to_tile_map_of_both_tile_sizes(shape):
+    """The self check walks the 128 x 128 tiles as well: it reports the workgroups of the launch that the
+    library would make, at least one per tile of that launch's size (and fewer than the small tiles where
+    the big ones are taken)."""
+    n_tok, c_in, c_out, n_cand, side = shape
+    tiles = {s: n_cand * -(-n_tok // s) * -(-c_out // s) for s in (128, 256)}
+    bad, blocks = tlq.selftest_tile_map(n_tok, c_in, c_out, n_cand)
+    assert bad == 0
+    assert blocks % 256 == 0 and blocks >= tiles[side]
+    if side == 256:
+        assert blocks < tiles[128]
+    else:
+        assert blocks > -(-tiles[256] // 256) * 256 or tiles[128] <= 256
