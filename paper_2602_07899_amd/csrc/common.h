@@ -124,7 +124,7 @@ struct GemmArgs {
   bool tri;                // launch_gemm_store of a symmetric product (X == Wh): tiles with tile row <= tile column only
   bool cand_outer;         // walk the candidates one after the other instead of inside every patch row
   bool wide_patch;         // L2 patches of 8 x 4 tiles (output rows x tokens) instead of 4 x 8
-  bool small;              // 128 x 128 tiles (not with tri)
+  bool small;              // 128 x 128 tiles (stores without tri, and fp16 losses without tok_partial)
   bool sym_k;              // launch_gemm_dot: Wh is symmetric [c_in, c_in] and Y == X (a quadratic form)
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
@@ -140,10 +140,9 @@ bool gemm_strides_ok(int64_t ldx, int64_t ldw);
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out);
 hipError_t launch_gemm_loss(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_store(const GemmArgs& a, hipStream_t stream);
-// partial[k, tile] = sum over the tile of (X_k Wh^T)[t,o] * Y_k[t,o]  (no token weights)
+// partial[k, tile] = sum over the tile of (X_k Wh^T)[t,o] * Y_k[t,o]  (no token weights), fp16, for a symmetric
+// Wh (sym_k): about half the flops, same partial sums
 hipError_t launch_gemm_dot(const GemmArgs& a, hipStream_t stream);
-// true when that launch uses the symmetry (sym_k: about half the flops, same partial sums)
-bool gemm_dot_symmetric(const GemmArgs& a);
 
 // Second-moment form (gram.hip).  out[c, t] = fp16(X[t,c] * sqrt(w_t / max w)) as [c_in, kp] with zero
 // columns for n_tok <= t < kp; *wmax receives max_t w_t.

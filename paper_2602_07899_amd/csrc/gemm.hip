@@ -32,6 +32,7 @@
 // the fragment reads and for the tile writes alike.
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 #include <utility>
 
 #include "common.h"
@@ -1050,27 +1051,34 @@ static GemmDev make_dev(const GemmArgs& g) {
 // the pipelined kernel needs 32-bit byte offsets inside a 256-row panel
 bool gemm_strides_ok(int64_t ldx, int64_t ldw) { return ldw < (1 << 21) && ldx < (1 << 21); }
 static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ldw); }
-// Whether launch_gemm_dot contracts only the upper part of a symmetric Wh (see SYMK).
-bool gemm_dot_symmetric(const GemmArgs& g) { return g.sym_k && g.c_out == g.c_in && pipelined_ok(g); }
 
-template <typename T, int EPI, bool SYMK>
-static void launch_dma(const GemmDev& d, bool small, unsigned blocks, hipStream_t stream) {
+// Only the instances that some launch reaches are compiled: the loading of the code object is part of a
+// program's first call.  The searches' operands are fp16 in every form, so bf16 operands meet the loss only
+// in the single-candidate call, which keeps the big tiles (as does its per-token variant); the quadratic
+// form is fp16, big and symmetric.
+template <typename T, int EPI>
+static hipError_t launch_dma(const GemmDev& d, bool small, unsigned blocks, hipStream_t stream) {
+  constexpr bool SYMK = EPI == EPI_DOT;
+  constexpr bool SMALL = EPI == EPI_STORE || (EPI == EPI_LOSS && std::is_same<T, F16>::value);
   const bool tail = (d.c_in % kDmaBK) != 0;
-  if (small) {
+  if (!small) {
+    if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 2><<<blocks, 512, 0, stream>>>(d);
+    else gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
+    return hipGetLastError();
+  }
+  if constexpr (SMALL) {
     // one block per CU at most: four LDS stages hide the latency that a second block would
     const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
     if (!tail && deep) gemm_dma_kernel<T, 4, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
     else if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
     else if (deep) gemm_dma_kernel<T, 4, EPI, SYMK, true, 1><<<blocks, 256, 0, stream>>>(d);
     else gemm_dma_kernel<T, 2, EPI, SYMK, true, 1><<<blocks, 256, 0, stream>>>(d);
-  } else if (!tail) {
-    gemm_dma_kernel<T, 2, EPI, SYMK, false, 2><<<blocks, 512, 0, stream>>>(d);
-  } else {
-    gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
+    return hipGetLastError();
   }
+  return hipErrorInvalidValue;
 }
 
-template <int EPI>
+template <typename T, int EPI>
 static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t stream) {
   const bool dma = pipelined_ok(g);
   if (!dma && g.small) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
@@ -1078,28 +1086,17 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   const int64_t rounds = ceil_div(d.n_patches, kXcd);
   const int64_t blocks = rounds * kXcd * PATCH_SLOTS;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const bool symk = EPI == EPI_DOT && gemm_dot_symmetric(g);
   // (a symmetric product computes the tiles on and above the diagonal, a symmetric contraction
   // the k range from the diagonal block on: about half either way)
-  const double tile_frac = (g.tri || symk) ? 0.5 * (1.0 + 1.0 / (double)d.tiles_o) : 1.0;
+  const double tile_frac = (g.tri || EPI == EPI_DOT) ? 0.5 * (1.0 + 1.0 / (double)d.tiles_o) : 1.0;
   ProfScope ps(name, stream, 2.0 * (double)g.n_tok * (double)g.c_in * (double)g.c_out * g.n_cand * tile_frac);
-  if (dma) {
-    auto go = [&](auto sym) {
-      constexpr bool S = decltype(sym)::value;
-      if (!g.bf16) launch_dma<F16, EPI, S>(d, g.small, (unsigned)blocks, stream);
-      else launch_dma<BF16, EPI, S>(d, g.small, (unsigned)blocks, stream);
-    };
-    if constexpr (EPI == EPI_DOT) {
-      if (symk) go(std::true_type{}); else go(std::false_type{});
-    } else {
-      go(std::false_type{});
-    }
-  } else {
+  if (dma) return launch_dma<T, EPI>(d, g.small, (unsigned)blocks, stream);
+  if constexpr (EPI != EPI_DOT) {
     constexpr int NT = (kBO / kWO) * (kBT / kWT) * 64;
-    if (!g.bf16) gemm_kernel<F16, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
-    else gemm_kernel<BF16, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
+    gemm_kernel<T, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 // Host-side check of the block -> tile map for one problem shape: both block orders (candidates inside every
@@ -1155,16 +1152,21 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand,
 }
 
 hipError_t launch_gemm_loss(const GemmArgs& g, hipStream_t stream) {
-  if (g.tok_partial) return launch_gemm<EPI_LOSS_TOK>(g, "gemm_loss_tok", stream);
-  return launch_gemm<EPI_LOSS>(g, "gemm_loss", stream);
+  if (g.tok_partial)
+    return g.bf16 ? launch_gemm<BF16, EPI_LOSS_TOK>(g, "gemm_loss_tok", stream)
+                  : launch_gemm<F16, EPI_LOSS_TOK>(g, "gemm_loss_tok", stream);
+  return g.bf16 ? launch_gemm<BF16, EPI_LOSS>(g, "gemm_loss", stream) : launch_gemm<F16, EPI_LOSS>(g, "gemm_loss", stream);
 }
 hipError_t launch_gemm_store(const GemmArgs& g, hipStream_t stream) {
   if (g.tri && g.n_tok != g.c_out) return hipErrorInvalidValue;
   if (g.n_cand != 1 && g.o_cand_stride == 0) return hipErrorInvalidValue;
-  return launch_gemm<EPI_STORE>(g, g.tri ? "gemm_gram" : "gemm_store", stream);
+  const char* name = g.tri ? "gemm_gram" : "gemm_store";
+  return g.bf16 ? launch_gemm<BF16, EPI_STORE>(g, name, stream) : launch_gemm<F16, EPI_STORE>(g, name, stream);
 }
 hipError_t launch_gemm_dot(const GemmArgs& g, hipStream_t stream) {
-  return launch_gemm<EPI_DOT>(g, "gemm_gram_loss", stream);
+  // (row strides of 2^21 and more would mean a matrix of 8 TB)
+  if (g.bf16 || g.small || !g.sym_k || g.c_out != g.c_in || !pipelined_ok(g)) return hipErrorInvalidValue;
+  return launch_gemm<F16, EPI_DOT>(g, "gemm_gram_loss", stream);
 }
 
 }  // namespace tlq

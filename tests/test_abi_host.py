@@ -185,3 +185,20 @@ def test_block_to_tile_map_of_both_tile_sizes(shape):
         assert blocks < tiles[128]
     else:
         assert blocks > -(-tiles[256] // 256) * 256 or tiles[128] <= 256
+
+
+def test_only_reachable_contraction_kernels_are_compiled():
+    """The library holds the contraction kernels that some call launches and no others (every one lengthens
+    the loading of the library): operand type, LDS stages, epilogue (loss, loss with per-token
+    errors, store, quadratic form), symmetric form, k tail, 64-row halves of a wave tile."""
+    blob = open(tlq.LIB_PATH, "rb").read()
+    pat = rb"_ZN3tlq15gemm_dma_kernelINS_[34](F16|BF16)ELi(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)EEEvNS_7GemmDevE"
+    have = {(m[0].decode(), *map(int, m[1:])) for m in re.findall(pat, blob)}
+    LOSS, TOK, STORE, DOT = range(4)
+    want = set()
+    for tail in (0, 1):
+        for ty in ("F16", "BF16"):
+            want |= {(ty, 2, epi, 0, tail, 2) for epi in (LOSS, TOK, STORE)}
+            want |= {(ty, st, STORE, 0, tail, 1) for st in (2, 4)}
+        want |= {("F16", st, LOSS, 0, tail, 1) for st in (2, 4)} | {("F16", 2, DOT, 1, tail, 2)}
+    assert have == want, (sorted(have - want), sorted(want - have))
