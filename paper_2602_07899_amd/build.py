@@ -93,7 +93,8 @@ def build_sanitized_driver() -> str:
     exe = os.path.join(OBJ, "abi_validation_driver")
     src = os.path.join(ROOT, "tests", "native", "abi_validation_driver.cpp")
     cmd = [hipcc(), "--offload-arch=gfx950", "-std=c++17", "-g", "-O1", "-fsanitize=address", "-fsanitize=undefined",
-           "-fno-sanitize-recover=undefined", "-fno-gpu-sanitize", "-I", os.path.join(ROOT, "include"),
+           "-fno-sanitize-recover=undefined", "-fno-gpu-sanitize", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(os.path.dirname(os.path.dirname(hipcc())), "include"),
            "-x", "c++", src, "-x", "none", *san, *plain, "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -129,7 +129,7 @@ struct GemmArgs {
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
   float* tok_partial;      // [tiles_o, n_tok] float or NULL (single candidate only)
-  // store epilogue: Y[t,o]; with Yref given (float output only) Yref - Y
+  // store epilogue: Y[t,o]; with Yref given Yref - Y (float output and one candidate only, else an error)
   void* Yout; int64_t ldo; int yout_dtype;
 };
 // `small`: 128 x 128 output tiles instead of 256 x 256 (gemm_small_tiles says when they are faster)

@@ -1160,6 +1160,8 @@ hipError_t launch_gemm_loss(const GemmArgs& g, hipStream_t stream) {
 hipError_t launch_gemm_store(const GemmArgs& g, hipStream_t stream) {
   if (g.tri && g.n_tok != g.c_out) return hipErrorInvalidValue;
   if (g.n_cand != 1 && g.o_cand_stride == 0) return hipErrorInvalidValue;
+  // the 16-bit store through LDS does not subtract, and Yref has no stride per candidate
+  if (g.Yref && (g.yout_dtype != TLQ_F32 || g.n_cand != 1)) return hipErrorInvalidValue;
   const char* name = g.tri ? "gemm_gram" : "gemm_store";
   return g.bf16 ? launch_gemm<BF16, EPI_STORE>(g, name, stream) : launch_gemm<F16, EPI_STORE>(g, name, stream);
 }

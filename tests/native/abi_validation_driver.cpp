@@ -7,6 +7,7 @@
 #include <cstring>
 #include <vector>
 
+#include "common.h"
 #include "tlq.h"
 
 static int g_checks = 0, g_fail = 0;
@@ -191,6 +192,23 @@ int main() {
   EXPECT(tlq_silu_mul(A, 8, nullptr, 8, 8, 8, &p, A, 8, nullptr), TLQ_ERR_NULL);
   EXPECT(tlq_silu_mul(A, 8, A, 8, 8, 12, &p, A, 16, nullptr), TLQ_ERR_SHAPE);
   EXPECT(tlq_residual_add(A, 8, A, 8, 8, 8, &p, ODD, 8, nullptr), TLQ_ERR_ALIGN);
+
+  // ---- forms that the contraction launchers do not serve: an error before any launch, not another result
+  tlq::GemmArgs g{};
+  g.X = g.Wh = A; g.Yout = A; g.n_tok = 512; g.c_in = g.ldx = g.ldw = 512; g.c_out = g.ldo = g.ldy = 512; g.n_cand = 1;
+  tlq::GemmArgs h = g;
+  h.Yref = A; h.yref_dtype = TLQ_F16;       // subtracting into 16 bits; with several candidates
+  h.yout_dtype = TLQ_F16;  EXPECT(tlq::launch_gemm_store(h, nullptr), hipErrorInvalidValue);
+  h.yout_dtype = TLQ_BF16; EXPECT(tlq::launch_gemm_store(h, nullptr), hipErrorInvalidValue);
+  h.yout_dtype = TLQ_F32; h.n_cand = 2; h.o_cand_stride = 512 * 512;
+  EXPECT(tlq::launch_gemm_store(h, nullptr), hipErrorInvalidValue);
+  h = g; h.tri = true; h.c_out = 256;      EXPECT(tlq::launch_gemm_store(h, nullptr), hipErrorInvalidValue);
+  h = g; h.small = true; h.ldx = 1 << 21;  EXPECT(tlq::launch_gemm_store(h, nullptr), hipErrorInvalidValue);
+  h = g; h.small = true; h.bf16 = true;    EXPECT(tlq::launch_gemm_loss(h, nullptr), hipErrorInvalidValue);
+  h = g; h.small = true; h.tok_partial = F; EXPECT(tlq::launch_gemm_loss(h, nullptr), hipErrorInvalidValue);
+  h = g;                                   EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
+  h = g; h.sym_k = true; h.bf16 = true;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
+  h = g; h.sym_k = true; h.c_out = 256;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
 
   // ---- host-side self test of the block -> tile map, and the timing bookkeeping
   int64_t blocks = 0;
