@@ -294,3 +294,113 @@ def test_symmetric_products_deal_every_tile(gpu, n, ci, co):
         d = dev(W, gpu, False).double() - deq / table[k].double()[None, :]
         ref = (((d @ want) * d).sum() / co).item()
         assert abs(losses[k].item() - ref) <= 1e-3 * ref      # the parity bar of the search
+
+
+# Row strides of 2^21 elements and more leave the pipelined kernel's 32-bit offsets: the register-staged kernel
+# serves them.  257 or 300 rows (two tiles, the second ragged) of a matrix that is never allocated densely.
+WIDE = 1 << 21
+
+
+def wide_rows(a, gpu, bf16):
+    import torch
+    n, c = a.shape
+    dt = torch.bfloat16 if bf16 else torch.float16
+    flat = torch.empty((n - 1) * WIDE + c, dtype=dt, device=gpu)
+    return flat.as_strided((n, c), (WIDE, 1)).copy_(dev(a, gpu, bf16))
+
+
+@pytest.mark.parametrize("n,ci,co,side,bf16", [(300, 136, 300, "X", False), (257, 64, 520, "X", True),
+                                               (130, 200, 257, "W", True), (513, 72, 129, "W", False)])
+def test_products_with_very_wide_rows(gpu, n, ci, co, side, bf16):
+    """Full-precision product (float and 16-bit output) and the loss with and without per-token errors."""
+    import torch
+    g = np.random.default_rng([31, n, ci, co])
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    tX = wide_rows(X, gpu, bf16) if side == "X" else dev(X, gpu, bf16)
+    tW = wide_rows(W, gpu, bf16) if side == "W" else dev(W, gpu, bf16)
+    want = orc.ref_output(X, W)
+    mag = np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)).T
+    code = tlq.BF16 if bf16 else tlq.F16
+    p = tlq.params(group=8, x_dtype=code, yref_dtype=tlq.F32)
+    Y = torch.full((n, co + -co % 4 + 4), 7.0, dtype=torch.float32, device=gpu)
+    tlq.ref_output(tX, tW, Y[:, :co], p)
+    got = Y.cpu().numpy()
+    assert np.all(got[:, co:] == 7.0)
+    # exact products, float accumulation: ci roundings of at most 2^-24 of the magnitude
+    assert np.all(np.abs(got[:, :co] - want) <= (ci + 2) * 2.0 ** -24 * mag + 1e-30)
+    H = torch.full((n, co + -co % 8 + 8), 7.0, dtype=tX.dtype, device=gpu)
+    tlq.ref_output(tX, tW, H[:, :co], tlq.params(group=8, x_dtype=code, yref_dtype=code))
+    # ... and one rounding of the result (and at most one float rounding apart from the float output's)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11
+    assert np.all(host(H)[:, co:] == 7.0)
+    assert np.all(np.abs(host(H)[:, :co] - want) <= eps * np.abs(want) * 1.01 + (ci + 2) * 2.0 ** -23 * mag + 2.0 ** -24)
+    T = (want + g.standard_normal(want.shape)).astype(np.float32)
+    Y[:, :co].copy_(torch.from_numpy(T))
+    w = np.full(n, 1.0 / n, np.float32)
+    ref, e = orc.weighted_layer_err(X, W.astype(np.float64), T, w)
+    for per_tok in (False, True):
+        loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+        tlq.weighted_layer_err(tX, tW, None, Y[:, :co], torch.from_numpy(w).to(gpu), p, loss,
+                               per_token_err=err if per_tok else None)
+        np.testing.assert_allclose(float(loss.item()), ref, rtol=2e-5)      # float sums of positive terms
+        if per_tok:
+            np.testing.assert_allclose(err.cpu().numpy(), e, rtol=2e-5)
+
+
+@pytest.mark.parametrize("bits,act,ydt,bf16", [(4, 0, tlq.F16, False), (8, 0, tlq.F16, False), (8, 0, tlq.BF16, True),
+                                               (8, 0, tlq.F32, False), (4, 8, tlq.F16, False)])
+def test_search_and_propagation_with_very_wide_token_rows(gpu, bits, act, ydt, bf16):
+    """Folded and difference form (the target is subtracted where that kernel stores), several candidates,
+    activation quantisation (whose codes are dense again); then the propagated output."""
+    import torch
+    n, ci, co, na = 300, 136, 300, 3
+    g = np.random.default_rng([32, bits, act])
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    tdt = {tlq.F16: torch.float16, tlq.BF16: torch.bfloat16, tlq.F32: torch.float32}[ydt]
+    Y = torch.zeros((n, co + -co % 8), dtype=tdt, device=gpu)[:, :co]
+    Y.copy_(torch.from_numpy(orc.ref_output(X, W) + 0.01 * g.standard_normal((n, co))).to(gpu))
+    w = g.uniform(0.1, 1.0, n).astype(np.float32) / n
+    al = np.array([0.0, 0.4, 0.8], np.float32)
+    code = tlq.BF16 if bf16 else tlq.F16
+    p = tlq.params(bits=bits, group=8, act_bits=act, x_dtype=code, yref_dtype=ydt)
+    tX, tW = wide_rows(X, gpu, bf16), dev(W, gpu, bf16)
+    f = lambda *s: torch.empty(s, dtype=torch.float32, device=gpu)
+    best, idx, losses = f(ci), torch.empty(1, dtype=torch.int32, device=gpu), f(na)
+    t = lambda a: torch.from_numpy(a).to(gpu)
+    tlq.scale_search(tX, tW, Y, t(w), t(al), p, best, idx, losses)
+    ref = orc.scale_search(X, W, Y.double().cpu().numpy(), w, bits, 8, al, act_bits=act)
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
+    # the same call on dense tokens: same operands, the output's products added in the same order
+    Z, Zd = torch.empty((n, co + -co % 8), dtype=tX.dtype, device=gpu), torch.empty((n, co + -co % 8), dtype=tX.dtype, device=gpu)
+    tlq.apply_best(tX, tW, best, p, Z[:, :co])
+    tlq.apply_best(dev(X, gpu, bf16), tW, best, p, Zd[:, :co])
+    eps = 2.0 ** -7 if bf16 else 2.0 ** -10       # float sums in another order: one unit of the 16-bit result
+    a, b = host(Z[:, :co]), host(Zd[:, :co])
+    assert np.all(np.abs(a - b) <= eps * np.abs(b) + 1e-5)
+
+
+def test_token_matrix_of_more_than_two_million_tokens(gpu):
+    """The transposed tokens have rows of 2^21 elements and more: the symmetric product in the same kernel, two
+    tile columns, sixteen splits."""
+    import torch
+    n, ci = WIDE + 5, 264
+    g = torch.Generator(device=gpu)
+    g.manual_seed(33)
+    X = torch.randn((n, ci), generator=g, device=gpu, dtype=torch.float16)
+    X[:, 5] *= 20.0
+    w = torch.rand(n, generator=g, device=gpu) / n
+    p = tlq.params(group=8)
+    gram = torch.zeros(tlq.token_gram_bytes(ci), dtype=torch.uint8, device=gpu)
+    tlq.token_gram(X, w, p, gram)
+    f, cs, C = tlq.gram_views(gram, ci)
+    G = f.double() * cs.double()[:, None] * cs.double()[None, :] * C.double()
+    want = torch.zeros((ci, ci), dtype=torch.float64, device=gpu)
+    for r in range(0, n, 1 << 18):
+        x = X[r:r + (1 << 18)].double()
+        want += x.t().contiguous() @ (x * w[r:r + (1 << 18)].double()[:, None])
+    scale = want.diagonal().sqrt()
+    # tokens times sqrt(w) and the matrix itself are rounded to fp16 once each (three roundings in a product);
+    # an accumulator takes 131,136 / 16 float additions of a split: 8196 * 2^-24 = 2^-11
+    assert (((G - want).abs() / (scale[:, None] * scale[None, :])).max().item()) <= 4 * 2.0 ** -11
