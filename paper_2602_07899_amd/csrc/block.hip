@@ -56,7 +56,9 @@ constexpr int kAttBq = 128;   // queries per block (32 per wave)
 // query of the wave meets a new maximum.  (One reference per 64 keys, raised only by a rise of 2^8:
 // 2.99 ms instead of 3.27, but an error against 64 bits of 2.1e-3 instead of 1.8e-3, not kept.)
 // All query blocks of a (sample, head) run on one XCD, so that its keys and values (0.6 MB at 1200
-// tokens) are fetched into one L2, not into eight.
+// tokens) are fetched into one L2, not into eight.  Fewer than eight pairs would leave XCDs idle that way:
+// their query blocks are dealt over all eight (us, one XCD a pair -> dealt: 32768 tokens, one pair
+// 2156 -> 791, two 2395 -> 943; 8192 tokens, four pairs 228 -> 214).
 // LDS rows are 256 B; the 16-byte chunks of a K row are XORed with row % 16, the 32-byte pairs of a V
 // row with a permutation of row % 8: fragment reads and transposing reads hit each bank once.
 // 128 samples x 1200 tokens x 40 heads, bf16: 3.27 ms (578 TFLOP/s) against 8.87 ms with 32-key steps,
@@ -65,15 +67,21 @@ template <typename T>
 __global__ __launch_bounds__(256, 2) void causal_attention_kernel(
     const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
     const uint16_t* __restrict__ V, int64_t ldv, uint16_t* __restrict__ O, int64_t ldo, int seq_len,
-    int n_heads, int64_t n_hs, float scale) {
+    int n_heads, int64_t n_hs, unsigned ways, float scale) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) unsigned char kv[2][2][kAttTile];   // [stage][K, V]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, h = lane >> 5;
-  // blockIdx.x = 8 * query block + XCD: the 8 XCDs work on 8 different (sample, head) pairs
-  const int64_t hs = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * 8 + (blockIdx.x & 7);
+  // blockIdx.x = ways * query block + pair: with 8 ways the 8 XCDs work on 8 different (sample, head) pairs
+  unsigned pair = blockIdx.x & 7, qblock = blockIdx.x >> 3, n_qblocks = gridDim.x >> 3;
+  if (ways != 8) {
+    qblock = blockIdx.x / ways;
+    pair = blockIdx.x - qblock * ways;
+    n_qblocks = gridDim.x / ways;
+  }
+  const int64_t hs = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * ways + pair;
   if (hs >= n_hs) return;
-  const int qb = (int)(gridDim.x >> 3) - 1 - (int)(blockIdx.x >> 3);  // longest rows first
+  const int qb = (int)(n_qblocks - 1 - qblock);  // longest rows first
   const int64_t row0 = (hs / n_heads) * seq_len;
   const int64_t col0 = (hs % n_heads) * kAttDh;
   const int q0 = qb * kAttBq + wave * 32;
@@ -248,18 +256,20 @@ hipError_t launch_causal_attention(const void* Q, int64_t ldq, const void* K, in
   const int64_t n_samples = n_tok / seq_len;
   // causal: half of the seq_len^2 score matrix; 2 products of 2*128 flop per score
   ProfScope ps("causal_attention", stream, 2.0 * (double)n_samples * n_heads * (double)seq_len * seq_len * kAttDh);
-  const int64_t n_hs = n_samples * n_heads, groups = ceil_div(n_hs, 8);
+  const int64_t n_hs = n_samples * n_heads;
+  const unsigned ways = n_hs < 8 ? (unsigned)n_hs : 8u;    // pairs side by side (see the kernel)
+  const int64_t groups = ceil_div(n_hs, ways);
   const int64_t gy = groups < 32768 ? groups : 32768;
-  const dim3 grid(8u * (unsigned)ceil_div(seq_len, kAttBq), (unsigned)gy, (unsigned)ceil_div(groups, gy));
+  const dim3 grid(ways * (unsigned)ceil_div(seq_len, kAttBq), (unsigned)gy, (unsigned)ceil_div(groups, gy));
   const float scale = 0.08838834764831845f;  // 1 / sqrt(128)
   if (!bf16)
     causal_attention_kernel<F16><<<grid, 256, 0, stream>>>((const uint16_t*)Q, ldq, (const uint16_t*)K, ldk,
                                                            (const uint16_t*)V, ldv, (uint16_t*)O, ldo, seq_len, n_heads,
-                                                           n_hs, scale);
+                                                           n_hs, ways, scale);
   else
     causal_attention_kernel<BF16><<<grid, 256, 0, stream>>>((const uint16_t*)Q, ldq, (const uint16_t*)K, ldk,
                                                             (const uint16_t*)V, ldv, (uint16_t*)O, ldo, seq_len, n_heads,
-                                                            n_hs, scale);
+                                                            n_hs, ways, scale);
   return hipGetLastError();
 }
 

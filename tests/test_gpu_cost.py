@@ -1,0 +1,44 @@
+"""Calls whose cost must not hang on the shape that a kernel was written for: the same work in another shape may
+cost a stated multiple, far from what the dispatch rules give and far from what missing them costs."""
+import statistics
+
+import pytest
+
+from paper_2602_07899_amd import tlq
+
+pytestmark = pytest.mark.gpu
+
+
+def micros(*fns, reps=10, rounds=7):
+    """Median time of each call in microseconds, the calls in turn."""
+    import torch
+    for f in fns:
+        f()
+    torch.cuda.synchronize()
+    times = [[] for _ in fns]
+    for _ in range(rounds):
+        for f, t in zip(fns, times):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(reps):
+                f()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) * 1e3 / reps)
+    return [statistics.median(t) for t in times]
+
+
+def test_attention_of_one_head_uses_the_whole_chip(gpu):
+    """One (sample, head) pair of 32768 tokens is an eighth of eight pairs: 0.3 of their time when its query
+    blocks run on all XCDs, 0.8 on one."""
+    import torch
+    seq, heads = 32768, 8
+    qkv = torch.randn((seq, 3 * heads * 128), device=gpu).to(torch.bfloat16)
+    out = torch.empty((seq, heads * 128), dtype=torch.bfloat16, device=gpu)
+    p = tlq.params(x_dtype=tlq.BF16)
+
+    def run(h):
+        d = h * 128
+        return lambda: tlq.causal_attention(qkv[:, :d], qkv[:, d:2 * d], qkv[:, 2 * d:3 * d], h, seq, p, out)
+    one, eight = micros(run(1), run(8), reps=3)
+    assert one < 0.65 * eight, (one, eight)

@@ -24,9 +24,11 @@ def host(t):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("seq,heads,samples", [(31, 9, 1), (33, 1, 9), (63, 3, 3), (64, 2, 1), (65, 1, 1), (96, 1, 2),
-                                               (128, 1, 1), (160, 2, 1), (257, 1, 1)])
+                                               (128, 1, 1), (160, 2, 1), (257, 1, 1), (1100, 1, 1), (400, 7, 1),
+                                               (300, 2, 3), (140, 4, 2), (513, 1, 9)])
 def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
-    """64-key steps of two halves, 128-query blocks, eight (sample, head) pairs per grid group."""
+    """64-key steps of two halves, 128-query blocks, eight (sample, head) pairs per grid group, or fewer
+    whose query blocks are dealt over the chip."""
     import torch
     g = np.random.default_rng([21, seq, heads])
     n, width = seq * samples, heads * 128
