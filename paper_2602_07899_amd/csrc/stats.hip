@@ -201,18 +201,19 @@ __global__ void zero_u32_kernel(uint32_t* p) { *p = 0u; }
 // magnitude bits is the order of the magnitudes, so an integer atomic max is exact
 // and order independent.  A wave walks whole rows (no index division) and a block ends in ONE atomic on
 // the single result word: with one per wave and four times the blocks the atomics alone took 130 us.
+// blockIdx.y picks the stretch of `per` chunks of a row: the whole row unless the rows are too few for the chip.
 constexpr int kPrepBlocks = 1024;   // 4 per CU
 __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
-                                                          int64_t c_in, int64_t ldx,
+                                                          int64_t c_in, int64_t ldx, int64_t per,
                                                           uint32_t* __restrict__ out) {
   __shared__ uint32_t red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t chunks = c_in / 8;
+  const int64_t chunks = c_in / 8, i0 = blockIdx.y * per, i1 = i0 + per < chunks ? i0 + per : chunks;
   uint32_t m = 0;
   for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n_tok; r += (int64_t)gridDim.x * 4) {
     const uint16_t* row = X + r * ldx;
 #pragma unroll 4
-    for (int64_t i = lane; i < chunks; i += 64) {
+    for (int64_t i = i0 + lane; i < i1; i += 64) {
       const uint4 v = *reinterpret_cast<const uint4*>(row + i * 8);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -237,15 +238,15 @@ __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __rest
 }
 
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
-                                                          int64_t c_in, int64_t ldx,
+                                                          int64_t c_in, int64_t ldx, int64_t per,
                                                           const uint32_t* __restrict__ xmax_bits,
                                                           uint16_t* __restrict__ Xh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t chunks = c_in / 8;
+  const int64_t chunks = c_in / 8, i0 = blockIdx.y * per, i1 = i0 + per < chunks ? i0 + per : chunks;
   const float scale = __builtin_bit_cast(float, (uint32_t)(127 - shift_from_bf16_bits(*xmax_bits)) << 23);
   for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n_tok; r += (int64_t)gridDim.x * 4) {
 #pragma unroll 4
-    for (int64_t i = lane; i < chunks; i += 64) {
+    for (int64_t i = i0 + lane; i < i1; i += 64) {
       const uint4 v = *reinterpret_cast<const uint4*>(X + r * ldx + i * 8);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
       uint32_t o[4];
@@ -263,11 +264,16 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
                         void* Xh, hipStream_t stream) {
   ProfScope ps("bf16_to_f16", stream, 6.0 * (double)n_tok * (double)c_in);
   const int64_t rows = ceil_div(n_tok, 4);
+  // Few rows: split them into as many stretches (of 512 channels at least) as give every CU a block (us for the
+  // three launches, a wave a row -> split: 4 x 131072 45.5 -> 12.6, 1 x 65536 23.7 -> 12.5, 64 x 65536
+  // 26.7 -> 12.3).
+  const int64_t per = ceil_div(ceil_div(c_in, 512), rows < 256 ? 256 / rows : 1) * 64;   // in chunks of 8 channels
+  const unsigned split = (unsigned)ceil_div(c_in / 8, per);
   zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
-  absmax_bits_kernel<<<(unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), 256, 0, stream>>>(
-      (const uint16_t*)X, n_tok, c_in, ldx, xmax_bits);
-  bf16_to_f16_kernel<<<(unsigned)(rows < 8192 ? rows : 8192), 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx,
-                                                                               xmax_bits, (uint16_t*)Xh);
+  absmax_bits_kernel<<<dim3((unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), split), 256, 0, stream>>>(
+      (const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
+  bf16_to_f16_kernel<<<dim3((unsigned)(rows < 8192 ? rows : 8192), split), 256, 0, stream>>>(
+      (const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits, (uint16_t*)Xh);
   return hipGetLastError();
 }
 

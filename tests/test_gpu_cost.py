@@ -42,3 +42,14 @@ def test_attention_of_one_head_uses_the_whole_chip(gpu):
         return lambda: tlq.causal_attention(qkv[:, :d], qkv[:, d:2 * d], qkv[:, 2 * d:3 * d], h, seq, p, out)
     one, eight = micros(run(1), run(8), reps=3)
     assert one < 0.65 * eight, (one, eight)
+
+
+def test_token_preparation_of_few_long_rows(gpu):
+    """One megabyte of tokens in 4 rows or in 128: 1.0 times the cost when long rows are split, 3.4 when a wave
+    walks a row alone."""
+    import torch
+    p = tlq.params(group=8, x_dtype=tlq.BF16)
+    X = torch.randn((4, 131072), device=gpu).to(torch.bfloat16)
+    buf = torch.zeros(tlq.prepared_tokens_bytes(4, 131072, p), dtype=torch.uint8, device=gpu)
+    few, many = micros(lambda: tlq.prepare_tokens(X, p, buf), lambda: tlq.prepare_tokens(X.view(128, 4096), p, buf), reps=30)
+    assert few < 2.0 * many, (few, many)

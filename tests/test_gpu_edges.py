@@ -114,10 +114,12 @@ def test_quantiser_group_layouts(gpu, group, ci, co, sym, bits, bf16):
     np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
 
 
-@pytest.mark.parametrize("n,ci,co,pad", [(1, 8, 1, 0), (3, 520, 2, 8), (4097, 72, 5, 0), (9, 4104, 3, 16)])
+@pytest.mark.parametrize("n,ci,co,pad", [(1, 8, 1, 0), (3, 520, 2, 8), (4097, 72, 5, 0), (9, 4104, 3, 16),
+                                         (1, 131080, 2, 0), (6, 70000, 1, 8), (130, 1544, 2, 0)])
 def test_token_preparation_and_folding_edges(gpu, n, ci, co, pad):
     """bf16 tokens beyond the fp16 range: the exponent shift follows the largest magnitude wherever it is
-    (last row, last chunk), for row counts around the grid and widths around one wave and one block."""
+    (last row, last chunk), for row counts around the grid and widths around one wave and one block, and
+    for rows that are split over the chip."""
     import torch
     g = np.random.default_rng([24, n, ci])
     X = BF(g.standard_normal((n, ci)) * 3.0)
