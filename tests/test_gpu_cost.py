@@ -53,3 +53,24 @@ def test_token_preparation_of_few_long_rows(gpu):
     buf = torch.zeros(tlq.prepared_tokens_bytes(4, 131072, p), dtype=torch.uint8, device=gpu)
     few, many = micros(lambda: tlq.prepare_tokens(X, p, buf), lambda: tlq.prepare_tokens(X.view(128, 4096), p, buf), reps=30)
     assert few < 2.0 * many, (few, many)
+
+
+def shifted(x):
+    """A copy of x that starts one element off the 16-byte alignment of the wide paths."""
+    import torch
+    out = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)[1:1 + x.numel()].view(x.shape)
+    return out.copy_(x)
+
+
+def test_norms_of_narrow_gradient_rows(gpu):
+    """Rows of 8 channels take the element-wise form whatever their alignment: 1.0 times the cost of misaligned
+    ones, 1.6 where alignment alone picked the form."""
+    import torch
+    n_pos = 65536
+    G = torch.randn((16 * n_pos, 8), device=gpu).to(torch.float16)
+    Gs, p = shifted(G), tlq.params()
+    s = torch.empty(n_pos, dtype=torch.float64, device=gpu)
+    ws = torch.empty(16 * n_pos * 8, dtype=torch.uint8, device=gpu)
+    wide, narrow = micros(lambda: tlq.token_importance(G, 16, p, s, workspace=ws),
+                          lambda: tlq.token_importance(Gs, 16, p, s, workspace=ws))
+    assert wide < 1.25 * narrow, (wide, narrow)
