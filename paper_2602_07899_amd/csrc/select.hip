@@ -39,31 +39,43 @@ __global__ __launch_bounds__(256) void row_norm_kernel(const uint16_t* __restric
   if (lane == 0) out[row] = l2 ? sqrt(acc) : acc / (double)c;
 }
 
-// 64 positions per block; 16 waves bring 128 samples at a time into LDS, one adds them in sample order (one
-// thread per position that walked its loads alone: 48 us for 128 x 1200).
-constexpr int kPosWaves = 16, kPosBatch = 128;
-__global__ __launch_bounds__(kPosWaves * 64) void position_sum_kernel(const double* __restrict__ row_norm,
-                                                                      int64_t n_samples, int64_t n_pos,
-                                                                      double* __restrict__ sum_n) {
-  __shared__ double part[kPosBatch][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n = (int64_t)blockIdx.x * 64 + lane;
-  double s = 0.0;
-  for (int64_t b0 = 0; b0 < n_samples; b0 += kPosBatch) {
-#pragma unroll
-    for (int i = 0; i < kPosBatch / kPosWaves; ++i) {
-      const int64_t b = b0 + wave + i * kPosWaves;
-      part[wave + i * kPosWaves][lane] = (n < n_pos && b < n_samples) ? row_norm[b * n_pos + n] : 0.0;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const int m = n_samples - b0 < kPosBatch ? (int)(n_samples - b0) : kPosBatch;
+// Sum over the samples in sample order.  STAGED: 64 positions per block; 16 waves bring 128 samples at a time into
+// LDS, one adds them (one thread per position that walked its loads alone: 48 us for 128 x 1200).  Otherwise a
+// thread per position, for samples that are few enough to be loaded together and for positions that are enough
+// threads (2 samples x 262,144 positions: 11 us staged, 5 this way; 8 x 65,536: 4.7 both).
+constexpr int kPosWaves = 16, kPosBatch = 128, kPosFew = 8, kPosMany = 131072;
+template <bool STAGED>
+__global__ __launch_bounds__(STAGED ? kPosWaves * 64 : 256) void position_sum_kernel(const double* __restrict__ row_norm,
+                                                                                     int64_t n_samples, int64_t n_pos,
+                                                                                     double* __restrict__ sum_n) {
+  if constexpr (!STAGED) {
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n >= n_pos) return;
+    double s = 0.0;
 #pragma unroll 8
-      for (int i = 0; i < m; ++i) s += part[i][lane];
+    for (int64_t b = 0; b < n_samples; ++b) s += row_norm[b * n_pos + n];
+    sum_n[n] = s;
+  } else {
+    __shared__ double part[kPosBatch][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t n = (int64_t)blockIdx.x * 64 + lane;
+    double s = 0.0;
+    for (int64_t b0 = 0; b0 < n_samples; b0 += kPosBatch) {
+#pragma unroll
+      for (int i = 0; i < kPosBatch / kPosWaves; ++i) {
+        const int64_t b = b0 + wave + i * kPosWaves;
+        part[wave + i * kPosWaves][lane] = (n < n_pos && b < n_samples) ? row_norm[b * n_pos + n] : 0.0;
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const int m = n_samples - b0 < kPosBatch ? (int)(n_samples - b0) : kPosBatch;
+#pragma unroll 8
+        for (int i = 0; i < m; ++i) s += part[i][lane];
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    if (wave == 0 && n < n_pos) sum_n[n] = s;
   }
-  if (wave == 0 && n < n_pos) sum_n[n] = s;
 }
 
 hipError_t launch_token_importance(const void* G, int64_t n_samples, int64_t n_pos, int64_t c, int64_t ldg,
@@ -77,7 +89,11 @@ hipError_t launch_token_importance(const void* G, int64_t n_samples, int64_t n_p
   auto go = [&](auto kern) { kern<<<grid, 256, 0, stream>>>((const uint16_t*)G, rows, c, ldg, l2 ? 1 : 0, row_norm); };
   if (!bf16) { if (vec) go(row_norm_kernel<F16, true>); else go(row_norm_kernel<F16, false>); }
   else       { if (vec) go(row_norm_kernel<BF16, true>); else go(row_norm_kernel<BF16, false>); }
-  position_sum_kernel<<<(unsigned)ceil_div(n_pos, 64), kPosWaves * 64, 0, stream>>>(row_norm, n_samples, n_pos, sum_n);
+  if (n_samples < kPosFew || n_pos >= kPosMany)
+    position_sum_kernel<false><<<(unsigned)ceil_div(n_pos, 256), 256, 0, stream>>>(row_norm, n_samples, n_pos, sum_n);
+  else
+    position_sum_kernel<true><<<(unsigned)ceil_div(n_pos, 64), kPosWaves * 64, 0, stream>>>(row_norm, n_samples, n_pos,
+                                                                                           sum_n);
   return hipGetLastError();
 }
 

@@ -74,3 +74,17 @@ def test_norms_of_narrow_gradient_rows(gpu):
     wide, narrow = micros(lambda: tlq.token_importance(G, 16, p, s, workspace=ws),
                           lambda: tlq.token_importance(Gs, 16, p, s, workspace=ws))
     assert wide < 1.25 * narrow, (wide, narrow)
+
+
+def test_position_sums_of_one_sample(gpu):
+    """As many rows in one sample or in 64 (both are mostly the row norms): 1.0 times the cost when one sample is
+    added without staging, 1.2 with it."""
+    import torch
+    n = 1 << 22
+    G = torch.randn((n, 8), device=gpu).to(torch.float16)
+    p = tlq.params()
+    s = torch.empty(n, dtype=torch.float64, device=gpu)
+    ws = torch.empty(n * 8, dtype=torch.uint8, device=gpu)
+    one, many = micros(lambda: tlq.token_importance(G, 1, p, s, workspace=ws),
+                       lambda: tlq.token_importance(G, 64, p, s[:n // 64], workspace=ws), reps=5)
+    assert one < 1.1 * many, (one, many)

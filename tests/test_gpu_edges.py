@@ -178,7 +178,8 @@ def test_rmsnorm_row_widths(gpu, bf16, n, c, pad, two, period):
 
 
 @pytest.mark.parametrize("B,N,C,l2", [(1, 1, 8, 0), (17, 65, 72, 1), (3, 64, 520, 0), (33, 1, 75, 1), (2, 129, 1096, 0),
-                                       (3, 70, 248, 1), (3, 70, 256, 0)])
+                                       (3, 70, 248, 1), (3, 70, 256, 0),
+                                       (7, 257, 8, 0), (8, 300, 8, 1)])
 def test_selection_block_edges(gpu, B, N, C, l2):
     """64 positions a block, sixteen stretches of samples and rivals, 16-byte and 2-byte gradient rows; the
     masked maximum with a period that four interleaved rows wrap around, and one that is shorter."""
