@@ -37,11 +37,13 @@ __global__ __launch_bounds__(256) void rmsnorm_mul_kernel(const uint16_t* __rest
   }
 }
 
-// The same for rows that can be read 16 bytes at a time (c % 8 == 0, aligned rows and factors).  The sum of
+// The same for rows that can be read 16 bytes at a time (c % 8 == 0, aligned rows and factors, kVecWidth
+// channels at least).  The sum of
 // squares keeps the order of the kernel above - lane l adds elements l, l + 64, l + 128, ... - so that the
 // results are bit-equal: each 512-element stretch goes through 1 KB of LDS and is picked up two bytes a
 // lane.  Rows of up to 512 * HOLD elements stay in registers between the sum and the scaling (HOLD = 0: read
 // again, from L2).  40960 x 4096 bf16: 454 -> 167 us (2-byte loads and stores, two passes before).
+constexpr int64_t kVecWidth = 72;
 template <typename T, int HOLD>
 __global__ __launch_bounds__(256) void rmsnorm_mul_vec_kernel(const uint16_t* __restrict__ Z, int64_t ldz,
                                                               const uint16_t* __restrict__ Zb, int64_t ldzb,
@@ -135,7 +137,9 @@ hipError_t launch_rmsnorm_mul(const void* Z, int64_t ldz, const void* Zb, int64_
   ProfScope ps("rmsnorm_mul", stream, (Zb ? 6.0 : 4.0) * (double)n_tok * (double)c);
   const unsigned grid = (unsigned)ceil_div(n_tok, 4);
   auto al = [](const void* p) { return ((uintptr_t)p % 16) == 0; };   // (NULL counts as aligned)
-  const bool vec = (c % 8) == 0 && (ldz % 8) == 0 && (ldo % 8) == 0 && (!Zb || (ldzb % 8) == 0) && al(Z) && al(Zb) &&
+  // (up to 64 channels an element-wise lane has one value, and the 16-byte form leaves most lanes idle: us element-wise and
+  // 16-byte, 1,000,000 x 8 201 and 262, 300,000 x 64 65 and 81, 250,000 x 72 71 and 69, with Zb 94 and 81)
+  const bool vec = c >= kVecWidth && (c % 8) == 0 && (ldz % 8) == 0 && (ldo % 8) == 0 && (!Zb || (ldzb % 8) == 0) && al(Z) && al(Zb) &&
                    al(out) && al(m_a) && al(m_b);
   auto go = [&](auto kern) {
     kern<<<grid, 256, 0, stream>>>((const uint16_t*)Z, ldz, (const uint16_t*)Zb, ldzb, n_tok, c, m_a, m_b, period,

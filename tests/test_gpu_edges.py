@@ -152,7 +152,8 @@ def test_token_preparation_and_folding_edges(gpu, n, ci, co, pad):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("n,c,pad,two,period", [(1, 8, 0, False, 0), (5, 72, 8, True, 3), (3, 1024, 0, False, 0),
                                                 (3, 1032, 0, True, 0), (4, 5120, 0, False, 2), (2, 5128, 8, True, 0),
-                                                (3, 75, 0, True, 2), (2, 520, 4, False, 0)])
+                                                (3, 75, 0, True, 2), (2, 520, 4, False, 0), (5, 64, 0, True, 2),
+                                                (5, 72, 0, False, 2)])
 def test_rmsnorm_row_widths(gpu, bf16, n, c, pad, two, period):
     """Rows held in registers (2 and 10 stretches), rows read twice, widths and strides that need the
     element-wise kernel; the second factor and the two multipliers."""
