@@ -27,6 +27,7 @@ struct QuantDev {
   uint8_t* codes; uint8_t* zp; float* delta; uint16_t* wdq; int64_t ld_dq;
   bool diff; const uint32_t* xmax_bits;  // what = deq*inv - W*2^shift
   const float* col_scale;                // [c_in] factor on `what` or NULL
+  int shift; bool packed;                // quant_pow2_kernel: log2 of a group's lanes; groups that leave lanes over
 };
 
 // What a launch writes: the folded operands of the candidates, their difference form, or the
@@ -174,39 +175,55 @@ __device__ __forceinline__ float diff_factor(const QuantDev& a) {
   return a.xmax_bits ? __builtin_ldexpf(1.0f, shift_from_bf16_bits(*a.xmax_bits)) : 1.0f;
 }
 
-// Groups of a power of two up to 512.  A lane owns 8 consecutive input channels of R rows, a group is
-// `group/8` adjacent lanes, a wave covers 512 channels; W stays in registers while the candidates are
-// walked, a candidate's scales are loaded once for the R rows.  Bound by vector ALU issue: ~130
+// Groups of a power of two up to 512, and any below 64.  A lane owns 8 consecutive input channels of R rows, a
+// group is `group/8` adjacent lanes and a wave covers 512 channels; W stays in registers while the candidates
+// are walked, a candidate's scales are loaded once for the R rows.  `packed`: the lanes of a group are rounded up
+// to a power of two (the spare ones repeat the group's first channels and store nothing) and the groups of all
+// rows fill the waves one after the other.  Bound by vector ALU issue: ~130
 // wave instructions per 512 weights and candidate (250 with a division and a tie branch per element,
 // divisions for step and zero point, and shuffles through LDS).  20 candidates of 4096 x 4096 (0.7 GB
-// written): 278 -> 195 us.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).
+// written): 278 -> 195 us.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).  Groups of 24, 40
+// and 56 of 4096 x 4100 with every output, a wave per group -> this way: 252 -> 22, 153 -> 26, 111 -> 20 us.
 template <typename T, bool SYM, int MODE, int R, int LPG>
 __global__ __launch_bounds__(256) void quant_pow2_kernel(QuantDev a) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t cblocks = (a.c_in + 511) / 512;
-  const int64_t row0 = wave / cblocks * R;
-  if (row0 >= a.c_out) return;
-  const int64_t c = (wave % cblocks) * 512 + lane * 8;
-  const bool active = c < a.c_in;
-  const int lpg = LPG > 0 ? LPG : (int)(a.group >> 3);
+  const int lpg = LPG > 0 ? LPG : 1 << a.shift;
+  int64_t row0, c;
+  bool valid, active;              // the lane's channels exist; it also stores them
+  if (LPG == 0 && a.packed) {
+    const uint32_t groups = (uint32_t)(a.c_in / a.group);
+    const uint32_t unit = (uint32_t)wave * (64u >> a.shift) + (uint32_t)(lane >> a.shift);   // (row, group), flat
+    const int chunk = lane & (lpg - 1);
+    const bool spare = chunk * 8 >= a.group;
+    row0 = (int64_t)(unit / groups) * R;
+    c = (int64_t)(unit % groups) * a.group + (spare ? 0 : chunk * 8);
+    valid = row0 < a.c_out;
+    active = valid && !spare;
+  } else {
+    const int64_t cblocks = (a.c_in + 511) / 512;
+    row0 = wave / cblocks * R;
+    if (row0 >= a.c_out) return;
+    c = (wave % cblocks) * 512 + lane * 8;
+    valid = active = c < a.c_in;
+  }
 
   float w[R][8];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     uint4 v = make_uint4(0, 0, 0, 0);
-    if (active && row0 + r < a.c_out) v = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + c);
+    if (valid && row0 + r < a.c_out) v = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + c);
     widen8<T>(v, w[r]);
   }
   const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
   float s[8], inv[8], cs[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; cs[j] = 1.0f; }
-  if (MODE == Q_DIFF && active && a.col_scale) load8(a.col_scale + c, cs);
+  if (MODE == Q_DIFF && valid && a.col_scale) load8(a.col_scale + c, cs);
   const int k0 = (int)blockIdx.y * a.cand_step;
   const int k1 = k0 + a.cand_step < a.n_cand ? k0 + a.cand_step : a.n_cand;
-  const float* ps = a.s_table && active ? a.s_table + (int64_t)k0 * a.c_in + c : nullptr;
-  const float* pi = MODE != Q_AUX && a.inv_table && active ? a.inv_table + (int64_t)k0 * a.c_in + c : nullptr;
+  const float* ps = a.s_table && valid ? a.s_table + (int64_t)k0 * a.c_in + c : nullptr;
+  const float* pi = MODE != Q_AUX && a.inv_table && valid ? a.inv_table + (int64_t)k0 * a.c_in + c : nullptr;
   uint16_t* out = MODE != Q_AUX ? a.what + (int64_t)k0 * a.what_cand_stride + row0 * a.c_in + c : nullptr;
 #pragma unroll 1
   for (int k = k0; k < k1; ++k) {
@@ -234,7 +251,7 @@ __global__ __launch_bounds__(256) void quant_pow2_kernel(QuantDev a) {
   }
 }
 
-// Any other group up to 16384 channels, whole rows among them: NWG waves (1 or 4) own one group of R
+// Any other group of up to 16384 channels, whole rows among them: NWG waves (1 or 4) own one group of R
 // rows, a lane CH chunks of 8 channels, `64 NWG` chunks apart.  The weights stay packed in registers, each
 // candidate's scales are read twice (range, then codes; the second time from L1) for R rows.  20
 // candidates of 4096 x 4096, group = row: 1143 -> 190 us (2-byte loads, two sweeps over W before).
@@ -526,12 +543,19 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
     d.cand_step = (int)ceil_div(d.n_cand, split);
     return dim3((unsigned)blocks, (unsigned)ceil_div(d.n_cand, d.cand_step));
   };
-  if (d.group <= 512 && (d.group & (d.group - 1)) == 0) {
+  // A group below 64 that is no power of two would have a wave of quant_row_kernel to its 3 to 7 chunks: whole groups
+  // share a wave instead (their number is a 32-bit index there).
+  const bool pow2 = (d.group & (d.group - 1)) == 0;
+  d.packed = !pow2 && d.group < 64 && d.c_out * (d.c_in / d.group) < (1LL << 30);
+  if (d.packed || (pow2 && d.group <= 512)) {
+    for (d.shift = 0; (8LL << d.shift) < d.group;) ++d.shift;
     // rows per wave by size: two share the scale loads once there is work for every SIMD anyway
     constexpr int R = MODE == Q_AUX ? 1 : 2;
-    const int64_t per_row = ceil_div(d.c_in, 512);
-    const bool two = R == 2 && ceil_div(d.c_out, 2) * per_row * d.n_cand >= 8192;
-    const int64_t waves = ceil_div(d.c_out, two ? 2 : 1) * per_row;
+    auto waves_of = [&](int64_t rows) {
+      return d.packed ? ceil_div(rows * (d.c_in / d.group), 64 >> d.shift) : rows * ceil_div(d.c_in, 512);
+    };
+    const bool two = R == 2 && waves_of(ceil_div(d.c_out, 2)) * d.n_cand >= 8192;
+    const int64_t waves = waves_of(ceil_div(d.c_out, two ? 2 : 1));
     const dim3 g = grid(ceil_div(waves, 4), waves);
     if (two && d.group == 128) quant_pow2_kernel<T, SYM, MODE, R, 16><<<g, 256, 0, stream>>>(d);
     else if (two) quant_pow2_kernel<T, SYM, MODE, R, 0><<<g, 256, 0, stream>>>(d);

@@ -99,3 +99,19 @@ def test_normalisation_of_narrow_rows(gpu):
     out, outs, m = torch.empty_like(Z), shifted(Z), torch.rand(8, device=gpu)
     wide, narrow = micros(lambda: tlq.rmsnorm_mul(Z, p, out, m_a=m), lambda: tlq.rmsnorm_mul(Zs, p, outs, m_a=m))
     assert wide < 1.15 * narrow, (wide, narrow)
+
+
+def test_quantiser_groups_of_24_channels(gpu):
+    """The same weights in groups of 24 or of 32 channels: 1.1 times the cost with whole groups packed into a wave,
+    13 with a wave to every group."""
+    import torch
+    co, ci = 4096, 4128
+    W, s = torch.randn((co, ci), device=gpu).to(torch.float16), torch.rand(ci, device=gpu) + 0.5
+    codes, wdq = torch.empty((co, ci), dtype=torch.uint8, device=gpu), torch.empty_like(W)
+
+    def run(group):
+        zp, delta = torch.empty((co, ci // group), dtype=torch.uint8, device=gpu), torch.empty((co, ci // group), device=gpu)
+        p = tlq.params(group=group)
+        return lambda: tlq.fake_quant(W, s, p, codes, zp, delta, wdq)
+    odd, even = micros(run(24), run(32))
+    assert odd < 4.0 * even, (odd, even)

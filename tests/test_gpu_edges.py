@@ -69,10 +69,11 @@ def test_bf16_results_round_half_to_even(gpu):
     np.testing.assert_array_equal(out.float().cpu().numpy(), want)
 
 
-# one size per kernel and remainder: a wave of 1 / 2 / 4 chunks, a block of 2 / 4 / 8 chunks, the two-sweep
+# one size per kernel and remainder: groups of 3, 5, 6 and 7 lanes, a wave of 1 / 2 / 4 chunks, a block of 2 / 4 / 8 chunks, the two-sweep
 # kernel beyond 16384 channels, power-of-two groups with and without two rows per wave; odd row counts
 @pytest.mark.parametrize("group,ci,co,sym,bits,bf16", [
-    (24, 240, 5, 0, 4, False), (320, 640, 7, 1, 3, True), (0, 520, 3, 0, 4, True), (0, 1000, 9, 1, 4, False),
+    (24, 240, 5, 0, 4, False), (24, 24, 3, 1, 4, True), (40, 520, 6, 0, 3, True), (48, 3120, 2051, 1, 4, False),
+    (56, 1064, 9, 0, 8, False), (56, 448, 300, 0, 4, True), (320, 640, 7, 1, 3, True), (0, 520, 3, 0, 4, True), (0, 1000, 9, 1, 4, False),
     (0, 1032, 2, 0, 8, False), (1536, 3072, 5, 0, 4, True), (0, 2056, 6, 1, 4, False), (0, 4104, 3, 0, 4, True),
     (0, 8200, 2, 1, 4, False), (0, 16384, 1, 0, 3, False), (0, 16392, 2, 1, 4, True), (8, 520, 3, 0, 4, False),
     (512, 1024, 5, 1, 4, False), (128, 1152, 2051, 0, 4, True)])
