@@ -115,3 +115,16 @@ def test_quantiser_groups_of_24_channels(gpu):
         return lambda: tlq.fake_quant(W, s, p, codes, zp, delta, wdq)
     odd, even = micros(run(24), run(32))
     assert odd < 4.0 * even, (odd, even)
+
+
+def test_ragged_edge_of_a_one_round_product(gpu):
+    """252 tiles, one a CU: with outputs that end inside a tile the last column's guarded store is on the
+    critical path: 1.07 times the cost of whole tiles, 1.3 while that store carried the subtraction of the
+    difference form."""
+    import torch
+    n, ci = 7168, 256
+    X, W = torch.randn((n, ci), device=gpu).to(torch.float16), torch.randn((2304, ci), device=gpu).to(torch.float16)
+    p = tlq.params()
+    Y, Z = (torch.empty((n, co), dtype=torch.float16, device=gpu) for co in (2304, 2216))
+    whole, ragged = micros(lambda: tlq.ref_output(X, W, Y, p), lambda: tlq.ref_output(X, W[:2216], Z, p), reps=50)
+    assert ragged < 1.15 * whole, (ragged, whole)
