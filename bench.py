@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 
 METRIC = "candidate-scale evals/sec per layer + fused-kernel TFLOP/s (% fp16 MFMA peak)"
 PEAK_FP16_TFLOPS = 2500.0      # MI355X dense fp16 MFMA peak (published)
-HOST_THREADS = 16              # the GPU machine's CPU share
+HOST_THREADS = 16              # CPU threads of the host baseline
 
 
 def log(msg):

@@ -184,9 +184,16 @@ GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
   const size_t have = best.bytes;
   // Among the splits that fit, the one with the least time in units of a k-tile on all CUs (1.65 us): whole rounds
   // of 256 tiles, each its k-tiles and six more of prologue and epilogue, and per split one write and one
-  // read of half the float matrix at 4.5 TB/s.  A split's tokens stay in the last-level cache while several
-  // splits are under way (153,600 x 5120: 6 splits of 262 MB 4.2 ms, 12 of 131 MB 3.9, 16 of 98 MB 3.75); a single
-  // one may fill it (12,000 x 11008: 2 splits 1.82 ms with the sum, one 1.68).
+  // read of half the float matrix at 4.5 TB/s.  Fewer splits than the workspace holds are only looked at while a
+  // split's tokens stay within 100 MiB (one split: 280 MiB) of the 256 MiB last-level cache.  The rounds are what
+  // decides; the limit is a rough line.  us by number of splits (MiB a split):
+  //   153,600 x 5120  8 (188) 4183, 10 (150) 4296, 13 (115) 4121, 15 (100) 4258, 16 (94) 4290   -> 15
+  //   153,600 x 4096  4 (300) 3384, 6 (200) 3091, 10 (120) 2933, 12 (100) 2920, 16 (75) 2929
+  //    40,960 x 4096  1 (320) 1005, 2 (160) 1152, 3 (107) 863, 5 (64) 825, 10 (32) 919         -> 5
+  //    24,000 x 5120  1 (234) 645, 2 (117) 709, 5 (47) 772                                     -> 1
+  //    12,000 x 11008 1 (252) 1592, 2 (126) 1728                                               -> 1
+  // It misses the best where the cost of a round is not that of its k-tiles: 80,000 x 2048 takes 7 (683), 6 are
+  // 488; 16,000 x 11008 takes 3 (2264), one of 336 MiB is 2033; 30,000 x 13824 takes 4 (6087), one 5326.
   double best_cost = 0.0;
   for (int64_t n = ns; n >= 1; --n) {
     const GramPlan g = lay_out_gram(ws, n_tok, c_in, (int)n);
@@ -697,7 +704,6 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;
   q.s_table = s; q.inv_table = act ? nullptr : inv; q.n_cand = 1; q.what = what; q.what_cand_stride = 0;
- 
   TLQ_HIP(launch_fake_quant(q, st));
   GemmArgs g{};
   g.X = xh ? (const void*)xh : X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = xh ? c_in : ldx;

@@ -179,9 +179,9 @@ __device__ __forceinline__ float diff_factor(const QuantDev& a) {
 // group is `group/8` adjacent lanes and a wave covers 512 channels; W stays in registers while the candidates
 // are walked, a candidate's scales are loaded once for the R rows.  `packed`: the lanes of a group are rounded up
 // to a power of two (the spare ones repeat the group's first channels and store nothing) and the groups of all
-// rows fill the waves one after the other.  Bound by vector ALU issue: ~130
-// wave instructions per 512 weights and candidate (250 with a division and a tie branch per element,
-// divisions for step and zero point, and shuffles through LDS).  20 candidates of 4096 x 4096 (0.7 GB
+// rows fill the waves one after the other.  Bound by vector ALU issue: ~135 vector instructions per 512 weights
+// and candidate, ~145 in the difference form (250 with a division and a tie branch per element, divisions for
+// step and zero point, and shuffles through LDS).  20 candidates of 4096 x 4096 (0.7 GB
 // written): 278 -> 195 us.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).  Groups of 24, 40
 // and 56 of 4096 x 4100 with every output, a wave per group -> this way: 252 -> 22, 153 -> 26, 111 -> 20 us.
 template <typename T, bool SYM, int MODE, int R, int LPG>
@@ -574,8 +574,8 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
     const dim3 g = grid(blocks, 4 * blocks);
     kern<<<g, 256, 0, stream>>>(d);
   };
-  // rows x chunks = 8 packed registers quads per lane; a block per group from 2048 channels on (a wave alone
-  // would need more than four chunks a lane)
+  // rows x chunks: up to 8 packed register quads per lane (4 with one chunk); a block per group above 2048 channels
+  // (a wave alone would need more than four chunks a lane)
   if (d.group <= 512) one(quant_row_kernel<T, SYM, MODE, 1, 1, 4>, 4);
   else if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
   else if (d.group <= 2048) one(quant_row_kernel<T, SYM, MODE, 1, 4, 2>, 2);

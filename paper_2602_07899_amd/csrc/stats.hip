@@ -10,8 +10,10 @@ namespace tlq {
 // tokens).  Each lane owns 8 consecutive channels (one 16-byte load per row);
 // the waves of a block walk interleaved rows of the block's row chunk and
 // are combined through LDS; chunks are combined by a second kernel.  Sums are
-// carried in double: |fp16| values are multiples of 2^-24 below 2^16, so the
-// sum over up to 2^37 tokens is exact and the order of addition is immaterial.
+// carried in double, in an order that the shape fixes, so a result is
+// reproducible.  |fp16| values are multiples of 2^-24: a channel's sum is exact
+// in any order while it stays below 2^29; beyond that, and for bf16 channels of
+// wide range, the order shows in the last bits of the double.
 constexpr int kXsCols = 64 * 8;  // channels per block
 
 int xstat_chunks(int64_t n_tok) {

@@ -80,8 +80,8 @@ def check_losses(gl, ol, gbest, where):
     return float(rel.max())
 
 
-# sizes span several 256-tiles with ragged tails in every dimension; c_in = 200 takes the general
-# contraction kernel (c_in % 64 != 0), n_tok = 37 a single partial k-tile of the token product
+# sizes span several 256-tiles with ragged tails in every dimension; c_in = 200 leaves a
+# partial last k-tile of the contraction, n_tok = 37 a single partial k-tile of the token product
 CASES = [
     # n_tok, c_in, c_out, bits, group, symmetric, bf16, weights
     (700, 384, 520, 4, 128, 0, False, "lognormal"),
