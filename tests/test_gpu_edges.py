@@ -27,7 +27,7 @@ def host(t):
                                                (128, 1, 1), (160, 2, 1), (257, 1, 1), (1100, 1, 1), (400, 7, 1),
                                                (300, 2, 3), (140, 4, 2), (513, 1, 9)])
 def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
-    """64-key steps of two halves, 128-query blocks, eight (sample, head) pairs per grid group, or fewer
+    """32-key steps, 128-query blocks, eight (sample, head) pairs per grid group, or fewer
     whose query blocks are dealt over the chip."""
     import torch
     g = np.random.default_rng([21, seq, heads])
@@ -41,6 +41,30 @@ def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
     tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
     eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # one rounding of every probability, one of the output
     assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+
+
+@pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, "")])
+def test_attention_far_rows_and_partial_groups(gpu, bf16, seq, heads, samples, far):
+    """Row strides of 2^27 elements and more (beyond 32-bit offsets inside a wave's rows) give the bits of dense rows;
+    75 (sample, head) pairs leave the second group of pairs partly filled."""
+    import torch
+    g = np.random.default_rng([23, seq, heads])
+    n, width = seq * samples, heads * 128
+    rnd = BF if bf16 else F16
+    q, k, v = (np.asarray(rnd(g.standard_normal((n, width)) * 1.5), np.float64) for _ in range(3))
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    t = {"Q": dev(q, gpu, bf16), "K": dev(k, gpu, bf16), "V": dev(v, gpu, bf16)}
+    out = torch.empty((n, width), dtype=t["Q"].dtype, device=gpu)
+    tlq.causal_attention(t["Q"], t["K"], t["V"], heads, seq, p, out)
+    want, mag = ost.causal_attention(q, k, v, heads, seq), ost.causal_attention(q, k, np.abs(v), heads, seq)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # one rounding of every probability, one of the output
+    assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+    if far:
+        flat = torch.empty((n - 1) * (1 << 27) + width, dtype=out.dtype, device=gpu)
+        t[far] = flat.as_strided((n, width), (1 << 27, 1)).copy_(t[far])
+        again = torch.empty_like(out)
+        tlq.causal_attention(t["Q"], t["K"], t["V"], heads, seq, p, again)
+        assert torch.equal(out.view(torch.int16), again.view(torch.int16))
 
 
 def test_attention_infinite_value_stays_behind_its_key(gpu):
