@@ -78,7 +78,7 @@ bool use_diff_form(const tlq_params* p, int64_t n_tok, int64_t c_out) {
   return p->act_bits == 0 && (p->bits >= 6 || n_tok * c_out < 256 * 256);
 }
 struct SearchPlan {
-  double* xs_partial; float* x_stat; float* s_table; float* inv_table; float* partial;
+  double* xs_partial; float* s_table; float* inv_table; float* partial;
   uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; float* rsig; uint16_t* xc; int nb; size_t bytes;
   int64_t tiles_o, tiles_t; bool small;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
@@ -91,7 +91,6 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   Carver c(ws);
   gemm_tile_counts(n_tok, c_out, false, &s.tiles_o, &s.tiles_t);
   s.xs_partial = c.take<double>((size_t)xstat_chunks(n_tok) * c_in);
-  s.x_stat = c.take<float>((size_t)c_in);
   s.s_table = c.take<float>((size_t)n_alpha * c_in);
   s.inv_table = c.take<float>((size_t)n_alpha * c_in);
   s.partial = c.take<float>((size_t)n_alpha * s.tiles_o * s.tiles_t);
@@ -305,7 +304,7 @@ tlq_status tlq_scale_table(const float* x_stat, int64_t c_in, const float* alpha
                            int32_t n_alpha, float* s_table, void* stream) {
   if (!x_stat || !alpha_grid || !s_table) return TLQ_ERR_NULL;
   if (c_in <= 0 || n_alpha <= 0 || n_alpha > TLQ_MAX_ALPHA) return TLQ_ERR_SHAPE;
-  return hip_status(launch_scale_table(x_stat, c_in, alpha_grid, n_alpha, s_table, nullptr, nullptr,
+  return hip_status(launch_scale_table(x_stat, c_in, alpha_grid, n_alpha, s_table, nullptr, nullptr, nullptr,
                                        (hipStream_t)stream));
 }
 
@@ -442,18 +441,21 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     s.xmax = const_cast<uint32_t*>(v.xmax); s.xh = const_cast<uint16_t*>(v.xh);
   }
 
-  const float* x_stat = x_stat_in;
-  if (!x_stat) {  // S0
-    TLQ_HIP(launch_xstat(X, n_tok, c_in, ldx, bf16, p->xstat_kind, s.xs_partial, s.x_stat, st));
-    x_stat = s.x_stat;
+  // S0, S1
+  const bool prep = bf16 && !act && !use_prep;
+  uint32_t* shift_bits = (bf16 && !act) ? s.xmax : nullptr;
+  if (x_stat_in) {
+    if (prep) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
+    TLQ_HIP(launch_scale_table(x_stat_in, c_in, alpha_grid, n_alpha, s.s_table, s_table_out, s.inv_table, shift_bits, st));
+  } else {
+    // the token maximum comes with the statistic; its per-block words pass through the operands' place, not written yet
+    uint32_t* block_max = prep && xstat_block_max_words(n_tok, c_in) * sizeof(uint32_t) <=
+                                      (size_t)n_alpha * c_out * c_in * sizeof(uint16_t) ? (uint32_t*)s.what : nullptr;
+    if (prep && !block_max) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
+    TLQ_HIP(launch_xstat_table(X, n_tok, c_in, ldx, bf16, p->xstat_kind, s.xs_partial, alpha_grid, n_alpha, s.s_table,
+                               s_table_out, s.inv_table, shift_bits, block_max, s.xmax, st));
+    if (block_max) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st, true));
   }
-  if (bf16 && !act && !use_prep) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
-  // S1
-  TLQ_HIP(launch_scale_table(x_stat, c_in, alpha_grid, n_alpha, s.s_table, s.inv_table,
-                             (bf16 && !act) ? s.xmax : nullptr, st));
-  if (s_table_out)
-    TLQ_HIP(hipMemcpyAsync(s_table_out, s.s_table, (size_t)n_alpha * c_in * sizeof(float),
-                           hipMemcpyDeviceToDevice, st));
   // S2: all candidates' folded operands in one pass over W
   QuantArgs q{};
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;
@@ -612,10 +614,7 @@ tlq_status tlq_scale_search_gram(const void* gram, int64_t c_in, const void* W, 
   hipStream_t st = (hipStream_t)stream;
   const GramView v = view_gram(const_cast<void*>(gram), c_in);
   const GramSearchPlan s = plan_gram_search(workspace, c_in, c_out, n_alpha);
-  TLQ_HIP(launch_scale_table(x_stat, c_in, alpha_grid, n_alpha, s.s_table, s.inv_table, nullptr, st));
-  if (s_table_out)
-    TLQ_HIP(hipMemcpyAsync(s_table_out, s.s_table, (size_t)n_alpha * c_in * sizeof(float),
-                           hipMemcpyDeviceToDevice, st));
+  TLQ_HIP(launch_scale_table(x_stat, c_in, alpha_grid, n_alpha, s.s_table, s_table_out, s.inv_table, nullptr, st));
   // D'_k = (deq_k / s_k - W) * col_scale for every candidate, fp16
   QuantArgs q{};
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = p->x_dtype == TLQ_BF16;

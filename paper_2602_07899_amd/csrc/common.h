@@ -59,10 +59,17 @@ hipError_t launch_token_importance(const void* G, int64_t n_samples, int64_t n_p
                                    bool bf16, bool l2, double* row_norm, double* sum_n, hipStream_t stream);
 hipError_t launch_topk_mask(const double* sum_n, int64_t n_pos, int64_t k, uint8_t* mask, hipStream_t stream);
 // S1
-// inv_table (optional) = 2^shift / s, where shift comes from `xmax_bits` (see launch_xprep) or is 0
+// inv_table (optional) = 2^shift / s, where shift comes from `xmax_bits` (see launch_xprep) or is 0; s_copy
+// (optional): a second place for the table
 hipError_t launch_scale_table(const float* x_stat, int64_t c_in, const float* alpha, int n_alpha,
-                              float* s_table, float* inv_table, const uint32_t* xmax_bits,
+                              float* s_table, float* s_copy, float* inv_table, const uint32_t* xmax_bits,
                               hipStream_t stream);
+// S0 + S1 without the statistic itself.  block_max (bf16 tokens; optional): scratch of xstat_block_max_words words; then
+// max|X| comes from the same pass, goes to *xmax_out and sets the shift instead of xmax_bits
+size_t xstat_block_max_words(int64_t n_tok, int64_t c_in);
+hipError_t launch_xstat_table(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16, int kind, double* partial,
+                              const float* alpha, int n_alpha, float* s_table, float* s_copy, float* inv_table,
+                              const uint32_t* xmax_bits, uint32_t* block_max, uint32_t* xmax_out, hipStream_t stream);
 // inv[c] = 2^shift / s[c]
 hipError_t launch_recip(const float* s, int64_t c_in, const uint32_t* xmax_bits, float* inv,
                         hipStream_t stream);
@@ -74,8 +81,9 @@ hipError_t launch_recip(const float* s, int64_t c_in, const uint32_t* xmax_bits,
 // the same shift from it.  The folded weights carry the factor 2^shift, so the
 // contraction is unchanged while its computed operand is rounded to 11 instead of 8
 // significant bits.
+// have_max: xmax_bits holds the maximum already
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
-                        void* Xh, hipStream_t stream);
+                        void* Xh, hipStream_t stream, bool have_max = false);
 __host__ __device__ inline int shift_from_bf16_bits(uint32_t bits) {
   const int k = (int)((bits >> 7) & 0xffu) - 141;  // |x| < 2^(e-126); want < 2^15
   return k < 0 ? 0 : (k > 24 ? 24 : k);

@@ -1,6 +1,8 @@
 // S0 (x_stat), S1 (scale table), the final loss combine and S5 (selection).
 // All HBM-bound or tiny; none uses floating-point atomics, so results are
 // bit-identical from run to run.
+#include <type_traits>
+
 #include "common.h"
 
 namespace tlq {
@@ -15,6 +17,16 @@ namespace tlq {
 // in any order while it stays below 2^29; beyond that, and for bf16 channels of
 // wide range, the order shows in the last bits of the double.
 constexpr int kXsCols = 64 * 8;  // channels per block
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const uint32_t o = __shfl_xor(m, off, 64);
+    m = m > o ? m : o;
+  }
+  return m;
+}
 
 int xstat_chunks(int64_t n_tok) {
   int64_t c = ceil_div(n_tok, 128);
@@ -23,11 +35,14 @@ int xstat_chunks(int64_t n_tok) {
 
 // NW waves per block: 16 where a chunk has 128 rows at most (8 a wave; with 4 waves the two blocks of a
 // 256 x 512 input walked 32 rows each wave, 11 us against 4), 4 on longer chunks.
-template <typename T, int KIND, bool MASKED, int NW>
+// MAXBITS: every block also leaves the largest magnitude (as bits) that it has seen in block_max, for the fp16
+// re-expression of bf16 tokens, which would read them all once more for it.
+template <typename T, int KIND, bool MASKED, int NW, bool MAXBITS>
 __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
     const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx, int rows_per_chunk,
-    double* __restrict__ partial, const uint8_t* __restrict__ pos_mask, int64_t period) {
+    double* __restrict__ partial, const uint8_t* __restrict__ pos_mask, int64_t period, uint32_t* __restrict__ block_max) {
   __shared__ double red[NW][kXsCols];
+  __shared__ uint32_t redm[NW];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t c0 = (int64_t)blockIdx.x * kXsCols + lane * 8;
@@ -37,8 +52,13 @@ __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
   double acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.0;
+  u16x2 top = {0, 0};
   auto add = [&](const uint4& v) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    if constexpr (MAXBITS) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint16_t b = (uint16_t)((w[j >> 1] >> ((j & 1) * 16)) & 0x7fffu);  // |x|
@@ -74,7 +94,17 @@ __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
   }
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[wave][lane * 8 + j] = acc[j];
+  if constexpr (MAXBITS) {
+    const uint32_t m = wave_max(top[0] > top[1] ? top[0] : top[1]);
+    if (lane == 0) redm[wave] = m;
+  }
   __syncthreads();
+  if (MAXBITS && threadIdx.x == 0) {
+    uint32_t m = redm[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = m > redm[w] ? m : redm[w];
+    block_max[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = m;
+  }
   for (int i = threadIdx.x; i < kXsCols; i += NW * 64) {
     const int64_t c = (int64_t)blockIdx.x * kXsCols + i;
     if (c < c_in) {
@@ -87,13 +117,12 @@ __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
 }
 
 // 64 channels per block, the chunks in 16 contiguous stretches (one a wave) that are combined in order: one
-// thread per channel walked 128 dependent loads (32 us at 5120 channels; 5 us this way).
+// thread per channel walked 128 dependent loads (32 us at 5120 channels; 5 us this way).  Wave 0 returns the
+// statistic of its lane's channel.
 constexpr int kXfWaves = 16;
 template <int KIND>
-__global__ __launch_bounds__(kXfWaves * 64) void xstat_final_kernel(const double* __restrict__ partial, int n_chunks,
-                                                                    int64_t c_in, int64_t n_tok,
-                                                                    float* __restrict__ x_stat) {
-  __shared__ double red[kXfWaves][64];
+__device__ __forceinline__ float xstat_combine(const double* __restrict__ partial, int n_chunks, int64_t c_in,
+                                               int64_t n_tok, double (&red)[kXfWaves][64]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t c = (int64_t)blockIdx.x * 64 + lane;
   const int per = (n_chunks + kXfWaves - 1) / kXfWaves;
@@ -108,42 +137,62 @@ __global__ __launch_bounds__(kXfWaves * 64) void xstat_final_kernel(const double
   }
   red[wave][lane] = s;
   __syncthreads();
-  if (wave != 0 || c >= c_in) return;
+  if (wave != 0) return 0.0f;
 #pragma unroll
   for (int i = 1; i < kXfWaves; ++i) {
     const double v = red[i][lane];
     if (KIND == 0) s += v; else s = v > s ? v : s;
   }
-  x_stat[c] = (float)(KIND == 0 ? s / (double)n_tok : s);
+  return (float)(KIND == 0 ? s / (double)n_tok : s);
+}
+
+template <int KIND>
+__global__ __launch_bounds__(kXfWaves * 64) void xstat_final_kernel(const double* __restrict__ partial, int n_chunks,
+                                                                    int64_t c_in, int64_t n_tok,
+                                                                    float* __restrict__ x_stat) {
+  __shared__ double red[kXfWaves][64];
+  const float xs = xstat_combine<KIND>(partial, n_chunks, c_in, n_tok, red);
+  const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && c < c_in) x_stat[c] = xs;
+}
+
+// Partial sums of every chunk, and with block_max the largest magnitude of every block of the grid.
+static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16, int kind,
+                                       double* partial, hipStream_t stream, const uint8_t* pos_mask, int64_t period,
+                                       uint32_t* block_max) {
+  const int chunks = xstat_chunks(n_tok);
+  const int rows = (int)ceil_div(n_tok, chunks);
+  const dim3 grid((unsigned)ceil_div(c_in, kXsCols), (unsigned)chunks);
+  const uint16_t* x = (const uint16_t*)X;
+  ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
+  const bool shallow = rows <= 128;
+  auto go = [&](auto kern, int waves) {
+    kern<<<grid, waves * 64, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period, block_max);
+  };
+  auto pick = [&](auto t, auto kind_c, auto masked_c, auto max_c) {
+    using T = decltype(t);
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool MASKED = decltype(masked_c)::value, MAXBITS = decltype(max_c)::value;
+    if (shallow) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS>, 16);
+    else go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS>, 4);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  if (pos_mask) bf16 ? pick(BF16{}, I1{}, Yes{}, No{}) : pick(F16{}, I1{}, Yes{}, No{});   // (only the maximum has a masked form)
+  else if (!bf16) kind == 0 ? pick(F16{}, I0{}, No{}, No{}) : pick(F16{}, I1{}, No{}, No{});
+  else if (block_max) kind == 0 ? pick(BF16{}, I0{}, No{}, Yes{}) : pick(BF16{}, I1{}, No{}, Yes{});
+  else kind == 0 ? pick(BF16{}, I0{}, No{}, No{}) : pick(BF16{}, I1{}, No{}, No{});
+  return hipGetLastError();
 }
 
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,
                         const uint8_t* pos_mask, int64_t period) {
-  const int chunks = xstat_chunks(n_tok);
-  const int rows = (int)ceil_div(n_tok, chunks);
-  dim3 grid((unsigned)ceil_div(c_in, kXsCols), (unsigned)chunks);
-  const uint16_t* x = (const uint16_t*)X;
-  {
-    ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
-    const bool shallow = rows <= 128;
-    auto go = [&](auto kern, int waves) {
-      kern<<<grid, waves * 64, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period);
-    };
-    auto pick = [&](auto t) {
-      using T = decltype(t);
-      if (pos_mask) {       // only the maximum has a masked form
-        if (shallow) go(xstat_partial_kernel<T, 1, true, 16>, 16); else go(xstat_partial_kernel<T, 1, true, 4>, 4);
-      } else if (kind == 0) {
-        if (shallow) go(xstat_partial_kernel<T, 0, false, 16>, 16); else go(xstat_partial_kernel<T, 0, false, 4>, 4);
-      } else {
-        if (shallow) go(xstat_partial_kernel<T, 1, false, 16>, 16); else go(xstat_partial_kernel<T, 1, false, 4>, 4);
-      }
-    };
-    if (!bf16) pick(F16{}); else pick(BF16{});
-  }
-  hipError_t e = hipGetLastError();
+  const hipError_t e = launch_xstat_partial(X, n_tok, c_in, ldx, bf16, kind, partial, stream, pos_mask, period, nullptr);
   if (e != hipSuccess) return e;
+  const int chunks = xstat_chunks(n_tok);
   {
     ProfScope ps("xstat_final", stream, 8.0 * (double)chunks * (double)c_in);
     const unsigned g2 = (unsigned)ceil_div(c_in, 64);
@@ -156,31 +205,167 @@ hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
 // ------------------------------------------------------------ S1 scale table
 // Sec. 3.1.2 scale equation: s = x_stat^alpha, evaluated in double and rounded
 // once; the reciprocal table feeds the folded GEMM operand deq / s.
+__device__ __forceinline__ double pow2(int k) { return (double)__builtin_bit_cast(float, (uint32_t)(127 + k) << 23); }
 __device__ __forceinline__ double pow2_shift(const uint32_t* xmax_bits) {
-  const int k = xmax_bits ? shift_from_bf16_bits(*xmax_bits) : 0;
-  return (double)__builtin_bit_cast(float, (uint32_t)(127 + k) << 23);
+  return pow2(xmax_bits ? shift_from_bf16_bits(*xmax_bits) : 0);
+}
+
+// one entry of the table; s_copy and inv_table may be NULL
+__device__ __forceinline__ void table_entry(float xs, float alpha, double up, int64_t at, float* __restrict__ s_table,
+                                            float* __restrict__ s_copy, float* __restrict__ inv_table) {
+  xs = xs > kXstatFloor ? xs : kXstatFloor;  // also maps NaN to the floor
+  const float s = (float)pow((double)xs, (double)alpha);
+  s_table[at] = s;
+  if (s_copy) s_copy[at] = s;
+  if (inv_table) inv_table[at] = (float)(up / (double)s);
 }
 
 __global__ void scale_table_kernel(const float* __restrict__ x_stat, int64_t c_in,
                                    const float* __restrict__ alpha, int n_alpha,
-                                   float* __restrict__ s_table, float* __restrict__ inv_table,
+                                   float* __restrict__ s_table, float* __restrict__ s_copy, float* __restrict__ inv_table,
                                    const uint32_t* __restrict__ xmax_bits) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int k = blockIdx.y;
   if (c >= c_in || k >= n_alpha) return;
-  float xs = x_stat[c];
-  xs = xs > kXstatFloor ? xs : kXstatFloor;  // also maps NaN to the floor
-  const float s = (float)pow((double)xs, (double)alpha[k]);
-  s_table[(int64_t)k * c_in + c] = s;
-  if (inv_table) inv_table[(int64_t)k * c_in + c] = (float)(pow2_shift(xmax_bits) / (double)s);
+  table_entry(x_stat[c], alpha[k], pow2_shift(xmax_bits), (int64_t)k * c_in + c, s_table, s_copy, inv_table);
 }
 
 hipError_t launch_scale_table(const float* x_stat, int64_t c_in, const float* alpha, int n_alpha,
-                              float* s_table, float* inv_table, const uint32_t* xmax_bits,
+                              float* s_table, float* s_copy, float* inv_table, const uint32_t* xmax_bits,
                               hipStream_t stream) {
   ProfScope ps("scale_table", stream, 8.0 * (double)n_alpha * (double)c_in);
   dim3 grid((unsigned)ceil_div(c_in, 256), (unsigned)n_alpha);
-  scale_table_kernel<<<grid, 256, 0, stream>>>(x_stat, c_in, alpha, n_alpha, s_table, inv_table, xmax_bits);
+  scale_table_kernel<<<grid, 256, 0, stream>>>(x_stat, c_in, alpha, n_alpha, s_table, s_copy, inv_table, xmax_bits);
+  return hipGetLastError();
+}
+
+// The statistic of 64 channels over all rows, straight from the tokens: eight lanes read the 128 bytes of a row, a wave
+// eight rows at a time.  The value of its lane's channel arrives in wave 0.
+template <typename T, int KIND>
+__device__ __forceinline__ float xstat_direct(const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx,
+                                              double (&red)[kXfWaves][64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t c0 = (int64_t)blockIdx.x * 64 + (lane & 7) * 8;
+  double acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.0;
+  if (c0 < c_in) {
+#pragma unroll 4
+    for (int64_t r = wave * 8 + (lane >> 3); r < n_tok; r += kXfWaves * 8) {
+      const uint4 v = *reinterpret_cast<const uint4*>(X + r * ldx + c0);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const double a = (double)T::to_float((uint16_t)((w[j >> 1] >> ((j & 1) * 16)) & 0x7fffu));
+        if (KIND == 0) acc[j] += a; else acc[j] = a > acc[j] ? a : acc[j];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+#pragma unroll
+    for (int off = 8; off <= 32; off <<= 1) {
+      const double o = __shfl_xor(acc[j], off, 64);
+      if (KIND == 0) acc[j] += o; else acc[j] = o > acc[j] ? o : acc[j];
+    }
+    if (lane < 8) red[wave][lane * 8 + j] = acc[j];
+  }
+  __syncthreads();
+  if (wave != 0) return 0.0f;
+  double s = red[0][lane];
+#pragma unroll
+  for (int i = 1; i < kXfWaves; ++i) {
+    const double v = red[i][lane];
+    if (KIND == 0) s += v; else s = v > s ? v : s;
+  }
+  return (float)(KIND == 0 ? s / (double)n_tok : s);
+}
+
+struct TableDev {
+  const float* alpha; int n_alpha; int64_t c_in;
+  float* s_table; float* s_copy; float* inv_table;
+  const uint32_t* xmax_bits;                                   // sets the shift of the reciprocals unless block_max does
+  const uint32_t* block_max; int n_max; uint32_t* xmax_out;
+};
+
+// xstat_final_kernel and scale_table_kernel in one launch for a search that computes its own statistic: wave 0
+// hands the 64 channels' statistics to the 16 waves, which take the candidates in turn.  With block_max, the largest
+// magnitude over its n_max words is taken first (by every block: it is part of the reciprocals) and stored in *xmax_out.
+// Latency-bound: two launches of 3 - 5 us each became one of 5.
+template <int KIND>
+__global__ __launch_bounds__(kXfWaves * 64) void xstat_table_kernel(const double* __restrict__ partial, int n_chunks,
+                                                                    int64_t n_tok, TableDev t) {
+  __shared__ double red[kXfWaves][64];
+  __shared__ float stat[64];
+  __shared__ uint32_t redm[kXfWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (t.block_max) {
+    uint32_t m = 0;
+    for (int i = threadIdx.x; i < t.n_max; i += kXfWaves * 64) m = m > t.block_max[i] ? m : t.block_max[i];
+    m = wave_max(m);
+    if (lane == 0) redm[wave] = m;       // (read behind the barriers below)
+  }
+  const float xs = xstat_combine<KIND>(partial, n_chunks, t.c_in, n_tok, red);
+  if (wave == 0) stat[lane] = xs;
+  __syncthreads();
+  uint32_t top = 0;
+  if (t.block_max) {
+#pragma unroll
+    for (int w = 0; w < kXfWaves; ++w) top = top > redm[w] ? top : redm[w];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *t.xmax_out = top;
+  }
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  if (c >= t.c_in) return;
+  const double up = t.block_max ? pow2(shift_from_bf16_bits(top)) : pow2_shift(t.xmax_bits);
+  for (int k = wave; k < t.n_alpha; k += kXfWaves)
+    table_entry(stat[lane], t.alpha[k], up, (int64_t)k * t.c_in + c, t.s_table, t.s_copy, t.inv_table);
+}
+
+// The same for few rows, without partial sums: one launch instead of two.
+template <typename T, int KIND>
+__global__ __launch_bounds__(kXfWaves * 64) void xstat_table_direct_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
+                                                                           int64_t ldx, TableDev t) {
+  __shared__ double red[kXfWaves][64];
+  __shared__ float stat[64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float xs = xstat_direct<T, KIND>(X, n_tok, t.c_in, ldx, red);
+  if (wave == 0) stat[lane] = xs;
+  __syncthreads();
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  if (c >= t.c_in) return;
+  const double up = pow2_shift(t.xmax_bits);
+  for (int k = wave; k < t.n_alpha; k += kXfWaves)
+    table_entry(stat[lane], t.alpha[k], up, (int64_t)k * t.c_in + c, t.s_table, t.s_copy, t.inv_table);
+}
+
+// Rows up to which one launch is faster than two (a whole search of 20 candidates, us two launches -> one, at 512 and at
+// 4096 channels: 256 rows 39.4 -> 37.6 and 86.0 -> 84.0, 1024 rows 40.0 -> 38.8 and 87.9 -> 87.4, 2048 rows
+// 41.2 -> 41.8 and 97.8 -> 100.0).  Not where the token maximum is taken along: a block sees 64 channels only.
+constexpr int64_t kDirectRows = 1024;
+
+size_t xstat_block_max_words(int64_t n_tok, int64_t c_in) { return (size_t)xstat_chunks(n_tok) * (size_t)ceil_div(c_in, kXsCols); }
+
+hipError_t launch_xstat_table(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16, int kind, double* partial,
+                              const float* alpha, int n_alpha, float* s_table, float* s_copy, float* inv_table,
+                              const uint32_t* xmax_bits, uint32_t* block_max, uint32_t* xmax_out, hipStream_t stream) {
+  TableDev t{alpha, n_alpha, c_in, s_table, s_copy, inv_table, xmax_bits, block_max, 0, xmax_out};
+  const double table_bytes = 8.0 * (double)n_alpha * (double)c_in;
+  if (!block_max && n_tok <= kDirectRows) {
+    ProfScope ps("xstat_table", stream, 2.0 * (double)n_tok * (double)c_in + table_bytes);
+    auto go = [&](auto kern) {
+      kern<<<(unsigned)ceil_div(c_in, 64), kXfWaves * 64, 0, stream>>>((const uint16_t*)X, n_tok, ldx, t);
+    };
+    if (!bf16) kind == 0 ? go(xstat_table_direct_kernel<F16, 0>) : go(xstat_table_direct_kernel<F16, 1>);
+    else kind == 0 ? go(xstat_table_direct_kernel<BF16, 0>) : go(xstat_table_direct_kernel<BF16, 1>);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_xstat_partial(X, n_tok, c_in, ldx, bf16, kind, partial, stream, nullptr, 1, block_max);
+  if (e != hipSuccess) return e;
+  const int chunks = xstat_chunks(n_tok);
+  t.n_max = (int)xstat_block_max_words(n_tok, c_in);
+  ProfScope ps("xstat_table", stream, 8.0 * (double)chunks * (double)c_in + table_bytes);
+  auto go = [&](auto kern) { kern<<<(unsigned)ceil_div(c_in, 64), kXfWaves * 64, 0, stream>>>(partial, chunks, n_tok, t); };
+  kind == 0 ? go(xstat_table_kernel<0>) : go(xstat_table_kernel<1>);
   return hipGetLastError();
 }
 
@@ -226,11 +411,7 @@ __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __rest
       }
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint32_t o = __shfl_xor(m, off, 64);
-    m = m > o ? m : o;
-  }
+  m = wave_max(m);
   if (lane == 0) red[wave] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -263,7 +444,7 @@ __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __rest
 }
 
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
-                        void* Xh, hipStream_t stream) {
+                        void* Xh, hipStream_t stream, bool have_max) {
   ProfScope ps("bf16_to_f16", stream, 6.0 * (double)n_tok * (double)c_in);
   const int64_t rows = ceil_div(n_tok, 4);
   // Few rows: split them into as many stretches (of 512 channels at least) as give every CU a block (us for the
@@ -271,9 +452,11 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   // 26.7 -> 12.3).
   const int64_t per = ceil_div(ceil_div(c_in, 512), rows < 256 ? 256 / rows : 1) * 64;   // in chunks of 8 channels
   const unsigned split = (unsigned)ceil_div(c_in / 8, per);
-  zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
-  absmax_bits_kernel<<<dim3((unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), split), 256, 0, stream>>>(
-      (const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
+  if (!have_max) {
+    zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
+    absmax_bits_kernel<<<dim3((unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), split), 256, 0, stream>>>(
+        (const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
+  }
   bf16_to_f16_kernel<<<dim3((unsigned)(rows < 8192 ? rows : 8192), split), 256, 0, stream>>>(
       (const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits, (uint16_t*)Xh);
   return hipGetLastError();

@@ -22,7 +22,8 @@ from . import stack as gstack
 from . import tlq
 from . import workloads as wl
 
-SEARCH_KERNELS = ("xstat_partial", "xstat_final", "scale_table", "fake_quant", "gemm_loss", "finalize", "bf16_to_f16",
+SEARCH_KERNELS = ("xstat_partial", "xstat_final", "xstat_table", "scale_table", "fake_quant", "gemm_loss", "finalize",
+                  "bf16_to_f16",
                   "act_quant", "gram_operand", "gemm_gram", "gram_scale", "gemm_gram_loss")
 BLOCK_KERNELS = ("rmsnorm_mul", "causal_attention", "silu_mul", "residual_add")
 SELECT_KERNELS = ("token_importance", "topk_mask")

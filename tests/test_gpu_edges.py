@@ -328,6 +328,40 @@ def test_symmetric_products_deal_every_tile(gpu, n, ci, co):
         assert abs(losses[k].item() - ref) <= 1e-3 * ref      # the parity bar of the search
 
 
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("n,ci,co,na,bf16", [(1, 8, 1, 1, False), (1024, 72, 3, 20, False), (1025, 72, 3, 20, False),
+                                             (130, 520, 2, 17, False), (1, 8, 1, 1, True), (700, 64, 1, 1, True),
+                                             (3000, 1032, 5, 33, True), (20000, 136, 4, 2, True)])
+def test_table_of_a_search_that_takes_its_own_statistic(gpu, n, ci, co, na, bf16, kind):
+    """The statistic inside a search (one launch up to 1024 rows, else chunks; with bf16 tokens their maximum comes from
+    the same pass if its words fit into the operands' place) gives the table of the two separate calls and the
+    losses of the search that is handed the statistic."""
+    import torch
+    g = torch.Generator(device=gpu)
+    g.manual_seed(41 + n)
+    dt, code = (torch.bfloat16, tlq.BF16) if bf16 else (torch.float16, tlq.F16)
+    X = torch.randn((n, ci), generator=g, device=gpu)
+    X[:, 0] *= 3e5 if bf16 else 30.0             # (the shift of the fp16 re-expression is not zero)
+    X, W = X.to(dt), (torch.randn((co, ci), generator=g, device=gpu) * 0.05).to(dt)
+    Y = torch.randn((n, co + -co % 8), generator=g, device=gpu).to(dt)[:, :co]
+    w, al = torch.rand(n, generator=g, device=gpu) / n, torch.arange(na, device=gpu) / (1.0 * na)
+    p = tlq.params(group=8, xstat_kind=kind, x_dtype=code, yref_dtype=code)
+    f = lambda *s: torch.empty(s, dtype=torch.float32, device=gpu)
+    xs, table, got = f(ci), f(na, ci), f(na * ci + 1)
+    tlq.x_stat(X, p, xs)
+    tlq.scale_table(xs, al, table)
+    res = []
+    for stat in (None, xs):
+        best, idx, losses = f(ci), torch.empty(1, dtype=torch.int32, device=gpu), f(na)
+        tlq.scale_search(X, W, Y, w, al, p, best, idx, losses, x_stat_in=stat, s_table_out=got[1:].view(na, ci))
+        if bf16:      # sums of a wide range in another order: the last bit of a double, seldom one of the float
+            assert torch.allclose(got[1:].view(na, ci), table, rtol=2.0 ** -22, atol=0.0)
+        else:
+            assert torch.equal(got[1:].view(na, ci), table)
+        res.append((losses, idx, best))
+    torch.testing.assert_close(res[0][0], res[1][0], rtol=1e-3 if bf16 else 0.0, atol=0.0)
+
+
 # Row strides of 2^21 elements and more leave the pipelined kernel's 32-bit offsets: the register-staged kernel
 # serves them.  257 or 300 rows (two tiles, the second ragged) of a matrix that is never allocated densely.
 WIDE = 1 << 21
