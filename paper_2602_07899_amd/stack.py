@@ -127,13 +127,16 @@ def run_stack(h0, weights_fn, n_layers, token_w, alpha_grid, p, n_heads, seq_len
     assert y_dt == act, "the full-precision stream is propagated in the activation type"
     na = alpha_grid.numel()
     new = lambda cols, dt=act: torch.empty((n_tok, cols), dtype=dt, device=dev)
-    ws_cache = {}
+    ws_cache, ws_need = {}, {}
 
     def workspace(c_in, c_out):
-        need = max(tlq.scale_search_gram_workspace_bytes(c_in, c_out, na, p) if gram_any else 0,
-                   tlq.scale_search_workspace_bytes(n_tok, c_in, c_out, na, p) if strategy != "gram" else 0,
-                   tlq.token_gram_workspace_bytes(n_tok, c_in) if gram_any else 0,
-                   tlq.apply_best_workspace_bytes(n_tok, c_in, c_out, p), tlq.x_stat_workspace_bytes(n_tok, c_in))
+        need = ws_need.get((c_in, c_out))       # (the queries depend on nothing else within a run)
+        if need is None:
+            need = max(tlq.scale_search_gram_workspace_bytes(c_in, c_out, na, p) if gram_any else 0,
+                       tlq.scale_search_workspace_bytes(n_tok, c_in, c_out, na, p) if strategy != "gram" else 0,
+                       tlq.token_gram_workspace_bytes(n_tok, c_in) if gram_any else 0,
+                       tlq.apply_best_workspace_bytes(n_tok, c_in, c_out, p), tlq.x_stat_workspace_bytes(n_tok, c_in))
+            ws_need[c_in, c_out] = need
         if ws_cache.get("n", 0) < need:
             ws_cache["t"] = None
             ws_cache["t"] = torch.empty(need, dtype=torch.uint8, device=dev)
