@@ -79,7 +79,7 @@ bool use_diff_form(const tlq_params* p, int64_t n_tok, int64_t c_out) {
 }
 struct SearchPlan {
   double* xs_partial; float* s_table; float* inv_table; float* partial;
-  uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; float* rsig; uint16_t* xc; int nb; size_t bytes;
+  uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; uint16_t* xc; int nb; size_t bytes;
   int64_t tiles_o, tiles_t; bool small;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
 };
@@ -99,7 +99,6 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   s.xh = (bf16 && !act) ? c.take<uint16_t>((size_t)n_tok * c_in) : nullptr;
   s.nb = act ? act_batch(n_tok, c_in, n_alpha) : 0;
   s.sig = act ? c.take<float>((size_t)n_alpha * n_tok) : nullptr;
-  s.rsig = act ? c.take<float>((size_t)s.nb * n_tok) : nullptr;
   s.xc = act ? c.take<uint16_t>((size_t)s.nb * n_tok * c_in) : nullptr;
   s.ldd = (int64_t)align_up((size_t)c_out, 4);
   s.d0 = diff ? c.take<float>((size_t)n_tok * s.ldd) : nullptr;
@@ -340,7 +339,7 @@ tlq_status tlq_act_fake_quant(const void* X, int64_t n_tok, int64_t c_in, int64_
   if (!dims_ok(n_tok, c_in, ldx) || (c_in % 8) != 0) return TLQ_ERR_SHAPE;
   if (!mat16_aligned(X, ldx) || !aligned(codes, 16) || (inv_s && !aligned(inv_s, 4))) return TLQ_ERR_ALIGN;
   return hip_status(launch_act_quant(X, n_tok, c_in, ldx, p->x_dtype == TLQ_BF16, inv_s, 0, 1,
-                                     p->act_bits, codes, sigma, nullptr, (hipStream_t)stream));
+                                     p->act_bits, codes, sigma, (hipStream_t)stream));
 }
 
 // -------------------------------------------------------------------- S3 + S4
@@ -374,7 +373,7 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   g.Wh = Wdq; g.c_out = c_out; g.ldw = ldw; g.w_cand_stride = 0; g.n_cand = 1; g.bf16 = bf16;
   if (act) {
     // Q_a(x * inv_s) as exact fp16 integer codes + per-token steps; the weights stay unfolded
-    TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv_s, 0, 1, p->act_bits, e.xh, e.sig, nullptr, st));
+    TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv_s, 0, 1, p->act_bits, e.xh, e.sig, st));
     g.X = e.xh; g.ldx = c_in; g.tok_scale = e.sig; g.bf16 = false;
     if (bf16) {
       TLQ_HIP(launch_fold_scale(Wdq, c_out, c_in, ldw, true, nullptr, nullptr, true, e.folded, st));
@@ -494,7 +493,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     for (int k0 = 0; k0 < n_alpha; k0 += s.nb) {
       const int nb = (n_alpha - k0) < s.nb ? (n_alpha - k0) : s.nb;
       TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, s.inv_table, k0, nb, p->act_bits, s.xc,
-                               s.sig + (size_t)k0 * n_tok, s.rsig, st));
+                               s.sig + (size_t)k0 * n_tok, st));
       GemmArgs b = g;
       b.X = s.xc; b.ldx = c_in; b.x_cand_stride = n_tok * c_in;
       b.cand_outer = true;   // nothing is shared between candidates here: walk them one after the other
@@ -698,7 +697,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
     TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, xmax, xh, st));
   }
   TLQ_HIP(launch_recip(s, c_in, (bf16 && !act) ? xmax : nullptr, inv, st));
-  if (act) TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv, 0, 1, p->act_bits, xh, sig, nullptr, st));
+  if (act) TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv, 0, 1, p->act_bits, xh, sig, st));
   QuantArgs q{};
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;

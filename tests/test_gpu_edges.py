@@ -362,6 +362,50 @@ def test_table_of_a_search_that_takes_its_own_statistic(gpu, n, ci, co, na, bf16
     torch.testing.assert_close(res[0][0], res[1][0], rtol=1e-3 if bf16 else 0.0, atol=0.0)
 
 
+@pytest.mark.parametrize("n,ci,bf16", [(1, 8, False), (7, 512, True), (8, 520, False), (9, 4096, True), (17, 4104, False),
+                                       (10, 8192, True), (3, 9008, False), (70, 1024, True)])
+def test_activation_codes_at_strip_and_block_edges(gpu, n, ci, bf16):
+    """Blocks of eight rows, strips of 512 channels, eight waves: codes and steps bit for bit, infinities and NaN among
+    the tokens, an odd row stride."""
+    import torch
+    g = np.random.default_rng([45, n, ci])
+    X = g.standard_normal((n, ci + 8)).astype(np.float32) * 3.0
+    X[0, ci // 2] = 200.0
+    if n > 2:
+        X[1], X[2, ci - 1] = 0.0, 1e-7
+    X = (BF if bf16 else F16)(X)
+    inv = (1.0 / g.lognormal(0, 0.6, ci)).astype(np.float32)
+    p = tlq.params(group=8, act_bits=6, x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    codes, sigma = torch.empty((n, ci), dtype=torch.float16, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+    tX = dev(X, gpu, bf16)
+    tlq.act_fake_quant(tX[:, :ci], torch.from_numpy(inv).to(gpu), p, codes, sigma)
+    rc, rs = orc.act_quant(np.ascontiguousarray(X[:, :ci]), inv, 6)
+    assert np.array_equal(sigma.cpu().numpy().view(np.uint32), rs.view(np.uint32))
+    assert np.array_equal(codes.cpu().numpy().astype(np.int16), rc)
+    if n > 4:        # a NaN takes the lowest code and does not count for the step; an infinity makes the others zero
+        tX[3, 0], tX[4, ci - 1] = float("nan"), float("inf")
+        tlq.act_fake_quant(tX[:, :ci], torch.from_numpy(inv).to(gpu), p, codes, sigma)
+        c = codes.cpu().numpy()
+        assert c[3, 0] == -32 and np.array_equal(c[:3].astype(np.int16), rc[:3]) and np.array_equal(c[5:].astype(np.int16), rc[5:])
+        assert not c[4, :ci - 1].any() and c[4, ci - 1] == -32 and np.isinf(sigma[4].item())
+
+
+def test_search_over_more_candidates_than_a_block_takes(gpu):
+    """40 candidates with activation codes (a block's maxima hold 32), few rows and many."""
+    import torch
+    for n in (9, 3000):
+        g = np.random.default_rng([46, n])
+        X, W = F16(g.standard_normal((n, 128))), F16(g.standard_normal((24, 128)) * 0.05)
+        Y, w, al = F16(orc.ref_output(X, W)), np.full(n, 1.0 / n, np.float32), (np.arange(40) / 40).astype(np.float32)
+        p = tlq.params(group=0, symmetric=1, act_bits=6)
+        t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu)
+        best, idx = torch.empty(128, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+        losses = torch.empty(40, device=gpu)
+        tlq.scale_search(t(X), t(W), t(Y), t(w), t(al), p, best, idx, losses)
+        ref = orc.scale_search(X, W, Y, w, 4, 0, al, symmetric=True, act_bits=6)
+        np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)     # the parity bar of the search
+
+
 # Row strides of 2^21 elements and more leave the pipelined kernel's 32-bit offsets: the register-staged kernel
 # serves them.  257 or 300 rows (two tiles, the second ragged) of a matrix that is never allocated densely.
 WIDE = 1 << 21
