@@ -77,6 +77,16 @@ int act_batch(int64_t n_tok, int64_t c_in, int n_alpha) {
 bool use_diff_form(const tlq_params* p, int64_t n_tok, int64_t c_out) {
   return p->act_bits == 0 && (p->bits >= 6 || n_tok * c_out < 256 * 256);
 }
+// Activation codes against one step per weight row: both operands are small integers, so the contraction runs on int8 MFMA
+// with exact sums and the steps follow in the epilogue (per-group steps would have to be applied inside the
+// contraction).  The rows are padded to whole k-tiles of 128 codes; from 72 channels on they and the steps, at least 16
+// bytes a row, fit into the place of the 16-bit operands.  Asymmetric differences of 8-bit codes do not fit a byte.
+bool use_int8(const tlq_params* p, int64_t c_in) {
+  return p->act_bits != 0 && (p->group == 0 || p->group == c_in) && c_in >= 72 && c_in <= 16384 &&
+         (p->symmetric || p->bits <= 7);
+}
+int64_t int8_row(int64_t c_in) { return (int64_t)align_up((size_t)c_in, 128); }
+
 struct SearchPlan {
   double* xs_partial; float* s_table; float* inv_table; float* partial;
   uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; uint16_t* xc; int nb; size_t bytes;
@@ -430,7 +440,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = p->x_dtype == TLQ_BF16;
   const bool act = p->act_bits != 0;
-  const bool diff = use_diff_form(p, n_tok, c_out);
+  const bool diff = use_diff_form(p, n_tok, c_out), int8 = use_int8(p, c_in);
   SearchPlan s = plan_search(workspace, n_tok, c_in, c_out, n_alpha, bf16, act, diff,
                              gemm_strides_ok(bf16 || act ? c_in : ldx, c_in));
   if (prepared && !aligned(prepared, 256)) return TLQ_ERR_ALIGN;
@@ -463,6 +473,9 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   q.s_table = s.s_table; q.inv_table = act ? nullptr : s.inv_table; q.n_cand = n_alpha;
   q.what = s.what; q.what_cand_stride = c_out * c_in;
   q.diff = diff; q.xmax_bits = (diff && bf16) ? s.xmax : nullptr;
+  const int64_t ld8 = int8 ? int8_row(c_in) : 0, step_stride = (int64_t)align_up((size_t)c_out, 4);
+  float* steps = (float*)((unsigned char*)s.what + (size_t)n_alpha * c_out * ld8);
+  if (int8) { q.w8 = (int8_t*)s.what; q.ld8 = ld8; q.w8_cand_stride = c_out * ld8; q.steps = steps; q.step_stride = step_stride; }
   TLQ_HIP(launch_fake_quant(q, st));
   if (diff) {  // D0 = Y_ref - X W^T (exact products of the 16-bit inputs, float accumulation)
     GemmArgs r{};
@@ -493,12 +506,18 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     for (int k0 = 0; k0 < n_alpha; k0 += s.nb) {
       const int nb = (n_alpha - k0) < s.nb ? (n_alpha - k0) : s.nb;
       TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, s.inv_table, k0, nb, p->act_bits, s.xc,
-                               s.sig + (size_t)k0 * n_tok, st));
+                               s.sig + (size_t)k0 * n_tok, st, ld8));
       GemmArgs b = g;
       b.X = s.xc; b.ldx = c_in; b.x_cand_stride = n_tok * c_in;
       b.cand_outer = true;   // nothing is shared between candidates here: walk them one after the other
       b.tok_scale = s.sig + (size_t)k0 * n_tok;
       b.Wh = s.what + (size_t)k0 * c_out * c_in; b.n_cand = nb;
+      if (int8) {      // (in units of 16 bits)
+        b.i8_k = c_in; b.c_in = b.ldx = b.ldw = ld8 / 2;
+        b.x_cand_stride = n_tok * ld8 / 2; b.w_cand_stride = c_out * ld8 / 2;
+        b.Wh = s.what + (size_t)k0 * b.w_cand_stride;
+        b.row_scale = steps + (size_t)k0 * step_stride; b.row_scale_stride = step_stride;
+      }
       b.partial = s.partial + (size_t)k0 * tiles;
       TLQ_HIP(launch_gemm_loss(b, st));
     }
@@ -689,6 +708,8 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   const bool act = p->act_bits != 0;
   uint16_t* xh = (bf16 || act) ? c.take<uint16_t>((size_t)n_tok * c_in) : nullptr;
   float* sig = act ? c.take<float>((size_t)n_tok) : nullptr;
+  const int64_t ld8 = use_int8(p, c_in) ? int8_row(c_in) : 0;
+  float* steps = (float*)((unsigned char*)what + (size_t)c_out * ld8);
   if (prepared && !aligned(prepared, 256)) return TLQ_ERR_ALIGN;
   if (prepared && needs_prepared(p)) {
     const Prepared v = view_prepared(prepared);
@@ -697,16 +718,18 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
     TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, xmax, xh, st));
   }
   TLQ_HIP(launch_recip(s, c_in, (bf16 && !act) ? xmax : nullptr, inv, st));
-  if (act) TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv, 0, 1, p->act_bits, xh, sig, st));
+  if (act) TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv, 0, 1, p->act_bits, xh, sig, st, ld8));
   QuantArgs q{};
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;
   q.bits = p->bits; q.group = p->group; q.symmetric = p->symmetric;
   q.s_table = s; q.inv_table = act ? nullptr : inv; q.n_cand = 1; q.what = what; q.what_cand_stride = 0;
+  if (ld8) { q.w8 = (int8_t*)what; q.ld8 = ld8; q.steps = steps; }
   TLQ_HIP(launch_fake_quant(q, st));
   GemmArgs g{};
   g.X = xh ? (const void*)xh : X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = xh ? c_in : ldx;
   g.tok_scale = sig;
   g.Wh = what; g.c_out = c_out; g.ldw = c_in; g.w_cand_stride = 0; g.n_cand = 1; g.bf16 = false;
+  if (ld8) { g.i8_k = c_in; g.c_in = g.ldx = g.ldw = ld8 / 2; g.row_scale = steps; }      // (in units of 16 bits)
   g.Yout = X_next; g.ldo = ld_next; g.yout_dtype = p->x_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
   g.small = gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1);

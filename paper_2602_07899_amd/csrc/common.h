@@ -103,15 +103,19 @@ struct QuantArgs {
   // difference form: `what` receives deq*inv - W*2^shift (shift from xmax_bits, 0 when NULL)
   bool diff; const uint32_t* xmax_bits;
   const float* col_scale;   // [c_in] factor applied to `what` after everything else, or NULL
+  // integer form (w8 given; a group must be a whole row of at most 16384 channels): instead of `what`, the codes less
+  // their zero point as int8 rows of `ld8` bytes (zeros behind c_in) and the steps [n_cand, step_stride]
+  int8_t* w8; int64_t ld8, w8_cand_stride; float* steps; int64_t step_stride;
 };
 hipError_t launch_fake_quant(const QuantArgs& a, hipStream_t stream);
 
 // Q_a: per-token symmetric activation fake-quant of X * diag(inv_k) for candidates k0 .. k0+nb-1.
 // inv_table: [.., c_in] rows (row k used for candidate k) or NULL (ones).
-// codes: fp16 integers [nb, n_tok, c_in]; sigma: float [nb, n_tok] (already offset to k0).
+// codes: fp16 integers [nb, n_tok, c_in], or with ld8 > 0 int8 rows of ld8 bytes, zeros behind c_in; sigma: float
+// [nb, n_tok] (already offset to k0).
 hipError_t launch_act_quant(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                             const float* inv_table, int k0, int nb, int act_bits, void* codes,
-                            float* sigma, hipStream_t stream);
+                            float* sigma, hipStream_t stream, int64_t ld8 = 0);
 
 // Wout[o,c] = round16(Win[o,c] * inv_s[c])
 hipError_t launch_fold_scale(const void* Win, int64_t c_out, int64_t c_in, int64_t ldw, bool bf16,
@@ -136,6 +140,10 @@ struct GemmArgs {
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
   float* tok_partial;      // [tiles_o, n_tok] float or NULL (single candidate only)
+  // integer codes (i8_k = their number per row, 0: floating point): X and Wh hold int8 rows padded with zeros to whole
+  // k-tiles of 128 codes, and c_in, ldx, ldw and the strides count 16-bit units; row_scale [n_cand, c_out] are the
+  // steps of the weight rows.  Losses without tok_partial, and stores
+  int64_t i8_k; const float* row_scale; int64_t row_scale_stride;
   // store epilogue: Y[t,o]; with Yref given Yref - Y (float output and one candidate only, else an error)
   void* Yout; int64_t ldo; int yout_dtype;
 };

@@ -28,11 +28,13 @@ struct QuantDev {
   bool diff; const uint32_t* xmax_bits;  // what = deq*inv - W*2^shift
   const float* col_scale;                // [c_in] factor on `what` or NULL
   int shift; bool packed;                // quant_pow2_kernel: log2 of a group's lanes; groups that leave lanes over
+  int8_t* w8; int64_t ld8, w8_cand_stride; float* steps; int64_t step_stride;   // Q_INT
 };
 
 // What a launch writes: the folded operands of the candidates, their difference form, or the
-// single-candidate outputs (codes, zero points, steps, dequantised weights).
-enum { Q_FOLD = 0, Q_DIFF = 1, Q_AUX = 2 };
+// single-candidate outputs (codes, zero points, steps, dequantised weights), or the candidates' integer codes less
+// their zero points (int8) and steps.
+enum { Q_FOLD = 0, Q_DIFF = 1, Q_AUX = 2, Q_INT = 3 };
 
 // Grid of one group: step, an approximate reciprocal, zero point; `slow` asks for true divisions.
 struct Grid { float delta, rd, zpf; bool slow; };
@@ -105,6 +107,11 @@ __device__ __forceinline__ void range8(const float (&ws)[8], float& mx, float& m
   }
 }
 
+// four small integers as bytes
+__device__ __forceinline__ uint32_t pack_i8(float a, float b, float c, float d) {
+  return ((uint32_t)(int)a & 0xffu) | (((uint32_t)(int)b & 0xffu) << 8) | (((uint32_t)(int)c & 0xffu) << 16) | ((uint32_t)(int)d << 24);
+}
+
 // Eight quantised values of row `row`, channels c .. c+7 go to memory (`what`: their place in the operand).
 template <typename T, bool SYM, int MODE>
 __device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const float (&w)[8], const float (&ws)[8],
@@ -134,6 +141,7 @@ __device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const fl
       // (clip(n + zp, 0, qmax) - zp) of small integers is clip(n, -zp, qmax - zp)
       const float lo = SYM ? a.qlo : -g.zpf, hi = SYM ? a.qhi : a.qmax - g.zpf;
       // (a NaN weight quantises to `lo` like in the two-step clip)
+      if constexpr (MODE == Q_INT) { n[j] = __builtin_amdgcn_fmed3f(n[j], lo, hi); continue; }
       float f = __builtin_amdgcn_fmed3f(n[j], lo, hi) * g.delta * inv[j];
       if constexpr (MODE == Q_DIFF) {
         f -= w[j] * wsub;
@@ -143,6 +151,10 @@ __device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const fl
       }
       hw[j >> 1] |= (uint32_t)F16::from_float(f) << ((j & 1) * 16);
     }
+  }
+  if constexpr (MODE == Q_INT) {
+    *reinterpret_cast<uint2*>(what) = make_uint2(pack_i8(n[0], n[1], n[2], n[3]), pack_i8(n[4], n[5], n[6], n[7]));
+    return;
   }
   const uint4 out = make_uint4(hw[0], hw[1], hw[2], hw[3]);
   if constexpr (MODE == Q_AUX) {
@@ -326,9 +338,18 @@ __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int64_t c = cg + cl + i * STEP;
+      if constexpr (MODE == Q_INT) {       // (the group is the row)
+        if (cl + i * STEP >= a.group) {
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if (row0 + r < a.c_out && c < a.ld8)
+              *reinterpret_cast<uint2*>(a.w8 + (int64_t)k * a.w8_cand_stride + (row0 + r) * a.ld8 + c) = make_uint2(0, 0);
+          continue;
+        }
+      }
       if (cl + i * STEP >= a.group) continue;
       if (a.s_table) load8(a.s_table + (int64_t)k * a.c_in + c, s);
-      if (MODE != Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
+      if (MODE < Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
       if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -337,10 +358,16 @@ __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
         widen8<T>(wp[r][i], w);
 #pragma unroll
         for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
-        emit8<T, SYM, MODE>(a, g[r], w, ws, inv, cs, wsub,
-                            MODE != Q_AUX ? a.what + (int64_t)k * a.what_cand_stride + (row0 + r) * a.c_in + c : nullptr,
-                            row0 + r, c);
+        uint16_t* at = nullptr;
+        if (MODE == Q_INT) at = (uint16_t*)(a.w8 + (int64_t)k * a.w8_cand_stride + (row0 + r) * a.ld8 + c);
+        else if (MODE != Q_AUX) at = a.what + (int64_t)k * a.what_cand_stride + (row0 + r) * a.c_in + c;
+        emit8<T, SYM, MODE>(a, g[r], w, ws, inv, cs, wsub, at, row0 + r, c);
       }
+    }
+    if (MODE == Q_INT && cl == 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (row0 + r < a.c_out) a.steps[(int64_t)k * a.step_stride + row0 + r] = g[r].delta;
     }
     if (MODE == Q_AUX && cl == 0) {
 #pragma unroll
@@ -426,11 +453,12 @@ __device__ __forceinline__ void aq_load_tile(const uint16_t* __restrict__ X, int
   }
 }
 
-template <typename T>
+// INT: int8 codes in rows of ldc bytes (zeros behind c_in) instead of fp16 ones in rows of c_in.
+template <typename T, bool INT>
 __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in,
                                                                   int64_t ldx, const float* __restrict__ inv_table,
                                                                   int nb, int cand_step, float qa, float* __restrict__ sig,
-                                                                  uint16_t* __restrict__ codes) {
+                                                                  uint16_t* __restrict__ codes, int64_t ldc) {
   extern __shared__ __attribute__((aligned(16))) float part[];   // [4 quarter waves of every wave][candidate][row]
   __shared__ __attribute__((aligned(16))) float step[kAqStep][kAqRows];
   const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
@@ -488,11 +516,11 @@ __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t
   __syncthreads();
   for (int strip = wave; strip < strips; strip += nw) {
     const int64_t c = (int64_t)strip * kAqCols + lane * 8;
-    if (c >= c_in) continue;
+    if (c >= (INT ? ldc : c_in)) continue;
     aq_load_tile<T>(X, n_tok, c_in, ldx, r0, c, x);
     for (int k = 0; k < nk; ++k) {
-      if (inv_table) load8(inv_table + (int64_t)(k0 + k) * c_in + c, iv);
-      uint16_t* out = codes + ((int64_t)(k0 + k) * n_tok + r0) * c_in + c;
+      if (inv_table && (!INT || c < c_in)) load8(inv_table + (int64_t)(k0 + k) * c_in + c, iv);
+      const int64_t at = ((int64_t)(k0 + k) * n_tok + r0) * ldc + c;      // (a zero gives the code zero behind c_in)
 #pragma unroll
       for (int r = 0; r < kAqRows; ++r) {
         if (r0 + r >= n_tok) break;
@@ -505,12 +533,19 @@ __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t
 #pragma unroll
         for (int j = 0; j < 8; ++j) xt[j] = x[r][j] * iv[j];
         rint_quotient8(xt, g, n);
+        if constexpr (INT) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) n[j] = __builtin_amdgcn_fmed3f(n[j], -qa - 1.0f, qa);
+          *reinterpret_cast<uint2*>((int8_t*)codes + at + r * ldc) =
+              make_uint2(pack_i8(n[0], n[1], n[2], n[3]), pack_i8(n[4], n[5], n[6], n[7]));
+          continue;
+        }
         uint32_t o[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           o[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_fmed3f(n[2 * j], -qa - 1.0f, qa),
                                                                          __builtin_amdgcn_fmed3f(n[2 * j + 1], -qa - 1.0f, qa)));
-        *reinterpret_cast<uint4*>(out + r * c_in) = make_uint4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<uint4*>(codes + at + r * ldc) = make_uint4(o[0], o[1], o[2], o[3]);
       }
     }
   }
@@ -518,8 +553,8 @@ __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t
 
 hipError_t launch_act_quant(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                             const float* inv_table, int k0, int nb, int act_bits, void* codes,
-                            float* sigma, hipStream_t stream) {
-  ProfScope ps("act_quant", stream, (double)n_tok * (double)c_in * (4.0 + 2.0 * nb));
+                            float* sigma, hipStream_t stream, int64_t ld8) {
+  ProfScope ps("act_quant", stream, (double)n_tok * (double)c_in * (4.0 + (ld8 ? 1.0 : 2.0) * nb));
   const float qa = (float)((1 << (act_bits - 1)) - 1);
   const int64_t strips = ceil_div(c_in, kAqCols), blocks = ceil_div(n_tok, kAqRows);
   const int nw = (int)(strips < kAqWaves ? strips : kAqWaves);
@@ -532,9 +567,11 @@ hipError_t launch_act_quant(const void* X, int64_t n_tok, int64_t c_in, int64_t 
   const size_t lds = (size_t)nw * 4 * cand_step * kAqRows * sizeof(float);
   const float* inv = inv_table ? inv_table + (int64_t)k0 * c_in : nullptr;
   auto go = [&](auto kern) {
-    kern<<<grid, nw * 64, lds, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, inv, nb, cand_step, qa, sigma, (uint16_t*)codes);
+    kern<<<grid, nw * 64, lds, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, inv, nb, cand_step, qa, sigma, (uint16_t*)codes,
+                                  ld8 ? ld8 : c_in);
   };
-  bf16 ? go(act_quant_kernel<BF16>) : go(act_quant_kernel<F16>);
+  if (ld8) bf16 ? go(act_quant_kernel<BF16, true>) : go(act_quant_kernel<F16, true>);
+  else bf16 ? go(act_quant_kernel<BF16, false>) : go(act_quant_kernel<F16, false>);
   return hipGetLastError();
 }
 
@@ -550,9 +587,9 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
   };
   // A group below 64 that is no power of two would have a wave of quant_row_kernel to its 3 to 7 chunks: whole groups
   // share a wave instead (their number is a 32-bit index there).
-  const bool pow2 = (d.group & (d.group - 1)) == 0;
-  d.packed = !pow2 && d.group < 64 && d.c_out * (d.c_in / d.group) < (1LL << 30);
-  if (d.packed || (pow2 && d.group <= 512)) {
+  const bool pow2 = MODE != Q_INT && (d.group & (d.group - 1)) == 0;
+  d.packed = MODE != Q_INT && !pow2 && d.group < 64 && d.c_out * (d.c_in / d.group) < (1LL << 30);
+  if constexpr (MODE != Q_INT) if (d.packed || (pow2 && d.group <= 512)) {
     for (d.shift = 0; (8LL << d.shift) < d.group;) ++d.shift;
     // rows per wave by size: two share the scale loads once there is work for every SIMD anyway
     constexpr int R = MODE == Q_AUX ? 1 : 2;
@@ -581,6 +618,13 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
   };
   // rows x chunks: up to 8 packed register quads per lane (4 with one chunk); a block per group above 2048 channels
   // (a wave alone would need more than four chunks a lane)
+  if constexpr (MODE == Q_INT) {       // (half the shapes: every instance lengthens the loading of the library)
+    if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
+    else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 4>, 4);
+    else if (d.group <= 8192) four(quant_row_kernel<T, SYM, MODE, 4, 4, 2>, 2);
+    else four(quant_row_kernel<T, SYM, MODE, 4, 8, 1>, 1);
+    return;
+  } else {
   if (d.group <= 512) one(quant_row_kernel<T, SYM, MODE, 1, 1, 4>, 4);
   else if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
   else if (d.group <= 2048) one(quant_row_kernel<T, SYM, MODE, 1, 4, 2>, 2);
@@ -588,6 +632,7 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
   else if (d.group <= 8192) four(quant_row_kernel<T, SYM, MODE, 4, 4, 2>, 2);
   else if (d.group <= 16384) four(quant_row_kernel<T, SYM, MODE, 4, 8, 1>, 1);
   else quant_any_kernel<T, SYM, MODE><<<(unsigned)ceil_div(d.c_out * G, 4), 256, 0, stream>>>(d);
+  }
 }
 
 hipError_t launch_fake_quant(const QuantArgs& q, hipStream_t stream) {
@@ -602,13 +647,16 @@ hipError_t launch_fake_quant(const QuantArgs& q, hipStream_t stream) {
   d.what = (uint16_t*)q.what; d.what_cand_stride = q.what_cand_stride;
   d.codes = q.codes; d.zp = q.zp; d.delta = q.delta; d.wdq = (uint16_t*)q.wdq; d.ld_dq = q.ld_dq;
   d.diff = q.diff; d.xmax_bits = q.xmax_bits; d.col_scale = q.col_scale;
-  const double bytes = (double)q.c_out * (double)q.c_in * (2.0 + 2.0 * (q.what ? q.n_cand : 0) +
+  d.w8 = q.w8; d.ld8 = q.ld8; d.w8_cand_stride = q.w8_cand_stride; d.steps = q.steps; d.step_stride = q.step_stride;
+  if (q.w8 && (d.group != q.c_in || d.group > 16384 || (!q.symmetric && q.bits > 7))) return hipErrorInvalidValue;
+  const double bytes = (double)q.c_out * (double)q.c_in * (2.0 + 2.0 * (q.what ? q.n_cand : 0) + 1.0 * (q.w8 ? q.n_cand : 0) +
                                                            (q.codes ? 1.0 : 0.0) + (q.wdq ? 2.0 : 0.0));
   ProfScope ps("fake_quant", stream, bytes);
   auto pick = [&](auto t, auto sym) {
     using T = decltype(t);
     constexpr bool SYM = decltype(sym)::value;
-    if (!q.what) launch_quant<T, SYM, Q_AUX>(d, stream);
+    if (q.w8) launch_quant<T, SYM, Q_INT>(d, stream);
+    else if (!q.what) launch_quant<T, SYM, Q_AUX>(d, stream);
     else if (q.diff) launch_quant<T, SYM, Q_DIFF>(d, stream);
     else launch_quant<T, SYM, Q_FOLD>(d, stream);
   };

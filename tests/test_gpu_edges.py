@@ -390,6 +390,46 @@ def test_activation_codes_at_strip_and_block_edges(gpu, n, ci, bf16):
         assert not c[4, :ci - 1].any() and c[4, ci - 1] == -32 and np.isinf(sigma[4].item())
 
 
+@pytest.mark.parametrize("n,ci,co,bits,sym,abits,bf16", [
+    (1, 72, 1, 4, True, 8, False), (130, 128, 129, 8, True, 8, True), (257, 136, 258, 7, False, 6, False),
+    (300, 1000, 70, 3, True, 8, True), (520, 1096, 261, 4, False, 8, False), (40, 4104, 33, 4, True, 2, False),
+    (64, 8200, 20, 2, False, 8, True), (9, 16384, 10, 4, True, 8, False)])
+def test_integer_contraction_edges(gpu, n, ci, co, bits, sym, abits, bf16):
+    """One step per weight row and activation codes: widths that are no multiple of the 128-code k-tile, each width class
+    of the quantiser, ragged tiles; the losses of a search and the propagated output."""
+    import torch
+    g = np.random.default_rng([47, n, ci])
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci)) * 2.0), rnd(g.standard_normal((co, ci)) * 0.05)
+    code, dt = (tlq.BF16, torch.bfloat16) if bf16 else (tlq.F16, torch.float16)
+    Y = torch.zeros((n, co + -co % 8), dtype=torch.float32, device=gpu)[:, :co]
+    Y.copy_(torch.from_numpy(orc.ref_output(X, W) + 0.05 * g.standard_normal((n, co))).to(gpu))
+    w = g.uniform(0.1, 1.0, n).astype(np.float32) / n
+    al = np.array([0.0, 0.4, 0.8], np.float32)
+    p = tlq.params(bits=bits, group=0, symmetric=int(sym), act_bits=abits, x_dtype=code, yref_dtype=tlq.F32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu)
+    f = lambda *s: torch.empty(s, dtype=torch.float32, device=gpu)
+    best, idx, losses, table = f(ci), torch.empty(1, dtype=torch.int32, device=gpu), f(3), f(3, ci)
+    tlq.scale_search(dev(X, gpu, bf16), dev(W, gpu, bf16), Y, t(w), t(al), p, best, idx, losses, s_table_out=table)
+    ref = orc.scale_search(X, W, Y.double().cpu().numpy(), w, bits, 0, al, s_table=table.cpu().numpy(), symmetric=sym, act_bits=abits)
+    # exact sums of codes; three float roundings of a product, then float sums of squares (n * co / 64 terms a lane at most);
+    # a residual is at least a hundredth of the product's size here: 2 * 100 * 4 * 2^-24
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=5e-5)
+    s = table[1].contiguous()
+    Z = torch.full((n, co + -co % 8 + 8), 7.0, dtype=dt, device=gpu)
+    tlq.apply_best(dev(X, gpu, bf16), dev(W, gpu, bf16), s, p, Z[:, :co])
+    want = orc.apply_best(X, W, s.cpu().numpy(), bits, 0, symmetric=sym, act_bits=abits)
+    got = host(Z)
+    assert np.all(got[:, co:] == 7.0)
+    # one rounding of the result to 16 bits, four float roundings before it; the oracle's dequantised weights are floats,
+    # each 2^-24 of itself away from code times step, which stays where a sum cancels
+    c, sg = orc.act_quant(X, orc.recip_scale(s.cpu().numpy()), abits)
+    deq = orc.fake_quant(W, s.cpu().numpy(), bits, 0, symmetric=sym)[3]
+    mag = (np.abs(c.astype(np.float64)) * sg.astype(np.float64)[:, None]) @ np.abs(deq.astype(np.float64)).T
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11
+    assert np.all(np.abs(got[:, :co] - want) <= (eps + 4 * 2.0 ** -24) * np.abs(want) + 2.0 ** -24 * (mag + 1.0))
+
+
 def test_search_over_more_candidates_than_a_block_takes(gpu):
     """40 candidates with activation codes (a block's maxima hold 32), few rows and many."""
     import torch
