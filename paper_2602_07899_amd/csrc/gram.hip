@@ -44,7 +44,7 @@ __global__ __launch_bounds__(1024) void gram_wmax_kernel(const float* __restrict
 // One block transposes 64 tokens x 64 channels through LDS: 16-byte loads along the channels,
 // 16-byte stores along the tokens.
 constexpr int GT = 64, GLD = GT + 8;   // LDS row stride in halves (keeps 16-byte alignment)
-template <typename T>
+template <typename T, bool NT>
 __global__ __launch_bounds__(256) void gram_operand_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
                                                            int64_t c_in, int64_t ldx,
                                                            const float* __restrict__ w,
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void gram_operand_kernel(const uint16_t* __res
     uint4 v = make_uint4(0, 0, 0, 0);
     float r = 0.0f;
     if (t < n_tok && c < c_in) {
-      v = *reinterpret_cast<const uint4*>(X + t * ldx + c);
+      v = load16<NT>(X + t * ldx + c);
       r = wm > 0.0f ? sqrtf(w[t] / wm) : 0.0f;
     }
     const uint32_t u[4] = {v.x, v.y, v.z, v.w};
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void gram_operand_kernel(const uint16_t* __res
     const int cr = idx >> 3, ch = idx & 7;
     const int64_t c = c0 + cr, t = t0 + ch * 8;
     if (c < c_in && t < kp)
-      *reinterpret_cast<uint4*>(out + c * kp + t) = *reinterpret_cast<const uint4*>(tile + cr * GLD + ch * 8);
+      store16<NT>(out + c * kp + t, *reinterpret_cast<const uint4*>(tile + cr * GLD + ch * 8));
   }
 }
 
@@ -174,12 +174,12 @@ hipError_t launch_gram_operand(const void* X, int64_t n_tok, int64_t c_in, int64
   ProfScope ps("gram_operand", stream, 2.0 * (double)n_tok * (double)c_in + 2.0 * (double)kp * (double)c_in);
   gram_wmax_kernel<<<1, 1024, 0, stream>>>(token_w, n_tok, wmax);
   const dim3 grid((unsigned)bx, (unsigned)by);
-  if (!bf16)
-    gram_operand_kernel<F16><<<grid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, token_w, wmax,
-                                                       (uint16_t*)out, kp);
-  else
-    gram_operand_kernel<BF16><<<grid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, token_w, wmax,
-                                                        (uint16_t*)out, kp);
+  const bool nt = streams_past(4.0 * (double)n_tok * (double)c_in);
+  auto go = [&](auto kern) {
+    kern<<<grid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, token_w, wmax, (uint16_t*)out, kp);
+  };
+  if (!bf16) nt ? go(gram_operand_kernel<F16, true>) : go(gram_operand_kernel<F16, false>);
+  else nt ? go(gram_operand_kernel<BF16, true>) : go(gram_operand_kernel<BF16, false>);
   return hipGetLastError();
 }
 

@@ -8,8 +8,8 @@ namespace tlq {
 
 // One wave per gradient row: mean_c |g| (the reading of the text) or the Euclidean norm.  VEC: 16-byte
 // loads (c % 8 == 0, 16-byte aligned rows of 256 channels and more), four in flight; HBM-bound, 128 x 1200 rows of 5120 channels
-// 805 -> 254 us against 2-byte loads.
-template <typename T, bool VEC>
+// 805 -> 267 us against 2-byte loads, 235 past the caches (NT, 6.7 TB/s).
+template <typename T, bool VEC, bool NT>
 __global__ __launch_bounds__(256) void row_norm_kernel(const uint16_t* __restrict__ G, int64_t rows, int64_t c,
                                                        int64_t ldg, int l2, double* __restrict__ out) {
   const int lane = threadIdx.x & 63;
@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void row_norm_kernel(const uint16_t* __restric
     const uint16_t* g = G + row * ldg;
 #pragma unroll 4
     for (int64_t j = lane * 8; j < c; j += 512) {
-      const uint4 v = *reinterpret_cast<const uint4*>(g + j);
+      const uint4 v = load16<NT>(g + j);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -87,8 +87,14 @@ hipError_t launch_token_importance(const void* G, int64_t n_samples, int64_t n_p
   // row: 524,288 rows of 8 channels 76 us element-wise, 122 wide; of 128 98 and 130; of 256 155 and 138)
   const bool vec = c >= 256 && (c % 8) == 0 && (ldg % 8) == 0 && ((uintptr_t)G % 16) == 0;
   auto go = [&](auto kern) { kern<<<grid, 256, 0, stream>>>((const uint16_t*)G, rows, c, ldg, l2 ? 1 : 0, row_norm); };
-  if (!bf16) { if (vec) go(row_norm_kernel<F16, true>); else go(row_norm_kernel<F16, false>); }
-  else       { if (vec) go(row_norm_kernel<BF16, true>); else go(row_norm_kernel<BF16, false>); }
+  const bool nt = streams_past(2.0 * (double)rows * (double)c);
+  auto pick = [&](auto t) {
+    using T = decltype(t);
+    if (!vec) go(row_norm_kernel<T, false, false>);
+    else if (nt) go(row_norm_kernel<T, true, true>);
+    else go(row_norm_kernel<T, true, false>);
+  };
+  bf16 ? pick(BF16{}) : pick(F16{});
   if (n_samples < kPosFew || n_pos >= kPosMany)
     position_sum_kernel<false><<<(unsigned)ceil_div(n_pos, 256), 256, 0, stream>>>(row_norm, n_samples, n_pos, sum_n);
   else

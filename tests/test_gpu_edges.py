@@ -446,6 +446,61 @@ def test_search_over_more_candidates_than_a_block_takes(gpu):
         np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)     # the parity bar of the search
 
 
+# Streams of more than 320 MB go past the caches by other instructions: the same bits as in pieces that do not.
+def pieces(n, k):
+    return [slice(i * n // k, (i + 1) * n // k) for i in range(k)]
+
+
+@pytest.mark.parametrize("c", [1000, 4096, 5128])      # rows held in 2 and 10 registers quads, and read twice
+def test_long_streams_of_the_glue(gpu, c):
+    import torch
+    n = int(3.4e8) // (4 * c)
+    g = torch.Generator(device=gpu)
+    g.manual_seed(51)
+    A, B = (torch.randn((n, c), generator=g, device=gpu, dtype=torch.bfloat16) for _ in range(2))
+    m, p = torch.rand(c, generator=g, device=gpu), tlq.params(x_dtype=tlq.BF16)
+    for call in (lambda r, o: tlq.rmsnorm_mul(A[r], p, o, m_a=m), lambda r, o: tlq.rmsnorm_mul(A[r], p, o, Zb=B[r]),
+                 lambda r, o: tlq.silu_mul(A[r], B[r], p, o), lambda r, o: tlq.residual_add(A[r], B[r], p, o)):
+        whole, parts = torch.empty_like(A), torch.empty_like(A)
+        call(slice(0, n), whole)
+        for r in pieces(n, 3):
+            call(r, parts[r])
+        assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
+
+
+def test_long_streams_of_statistics_and_codes(gpu):
+    import torch
+    n, c = 42000, 4096
+    g = torch.Generator(device=gpu)
+    g.manual_seed(52)
+    X = torch.randn((n, c), generator=g, device=gpu, dtype=torch.float16)
+    p, f = tlq.params(act_bits=8), lambda *s: torch.empty(s, dtype=torch.float32, device=gpu)
+    norms = [torch.empty(n, dtype=torch.float64, device=gpu) for _ in range(2)]
+    tlq.token_importance(X, 1, p, norms[0])
+    xs, mask = f(c), (torch.rand(700, generator=g, device=gpu) < 0.9).to(torch.uint8)
+    tlq.x_stat(X, p, xs)
+    assert torch.equal(xs, (X.abs().sum(0, dtype=torch.float64) / n).float())       # sums of fp16 are exact in double
+    tlq.x_stat_masked(X, mask, p, xs)
+    assert torch.equal(xs, X.view(-1, 700, c)[:, mask.bool()].abs().amax((0, 1)).float())
+    codes, sg = [torch.empty((n, c), dtype=torch.float16, device=gpu) for _ in range(2)], [f(n), f(n)]
+    tlq.act_fake_quant(X, None, p, codes[0], sg[0])
+    for r in pieces(n, 3):
+        tlq.token_importance(X[r], 1, p, norms[1][r])
+        tlq.act_fake_quant(X[r], None, p, codes[1][r], sg[1][r])
+    for a, b in (norms, codes, sg):
+        assert torch.equal(a, b)
+    # operands of 18 candidates: 755 MB (fp16) or, with one step per row, 377 MB (int8) together
+    W, n = X[:5120], 64
+    Y, w = torch.randn((n, 5120), generator=g, device=gpu, dtype=torch.float16), torch.rand(n, generator=g, device=gpu) / n
+    al = torch.arange(18, device=gpu) / 20.0
+    for q in (tlq.params(), tlq.params(group=0, symmetric=1, act_bits=8)):
+        best, idx, many, one = f(c), torch.empty(1, dtype=torch.int32, device=gpu), f(18), f(18)
+        tlq.scale_search(X[6000:6000 + n], W, Y, w, al, q, best, idx, many)
+        for k in range(18):
+            tlq.scale_search(X[6000:6000 + n], W, Y, w, al[k:k + 1], q, best, idx, one[k:k + 1])
+        torch.testing.assert_close(many, one, rtol=1e-5, atol=0.0)         # (tiles of another size: sums in another order)
+
+
 # Row strides of 2^21 elements and more leave the pipelined kernel's 32-bit offsets: the register-staged kernel
 # serves them.  257 or 300 rows (two tiles, the second ragged) of a matrix that is never allocated densely.
 WIDE = 1 << 21
