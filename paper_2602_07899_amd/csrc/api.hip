@@ -90,16 +90,17 @@ int64_t int8_row(int64_t c_in) { return (int64_t)align_up((size_t)c_in, 128); }
 struct SearchPlan {
   double* xs_partial; float* s_table; float* inv_table; float* partial;
   uint16_t* what; uint32_t* xmax; uint16_t* xh; float* sig; uint16_t* xc; int nb; size_t bytes;
-  int64_t tiles_o, tiles_t; bool small;
+  int64_t tiles_o, tiles_t; GemmTile tile;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
 };
-// Small tiles write up to four times the loss partials.  The workspace stays what it is with the big ones: the
-// partials of small tiles take the place of the channel sums, which are done with by then, if they fit.
+// Smaller tiles write up to four times the loss partials.  The workspace stays what it is with 256 x 256: where there
+// are more of them they take the place of the channel sums, which are done with by then, if they fit.
 SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, bool bf16,
                        bool act, bool diff, bool strides_ok = false) {
   SearchPlan s;
   Carver c(ws);
-  gemm_tile_counts(n_tok, c_out, false, &s.tiles_o, &s.tiles_t);
+  s.tile = GemmTile{};
+  gemm_tile_counts(n_tok, c_out, s.tile, &s.tiles_o, &s.tiles_t);
   s.xs_partial = c.take<double>((size_t)xstat_chunks(n_tok) * c_in);
   s.s_table = c.take<float>((size_t)n_alpha * c_in);
   s.inv_table = c.take<float>((size_t)n_alpha * c_in);
@@ -113,24 +114,25 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   s.ldd = (int64_t)align_up((size_t)c_out, 4);
   s.d0 = diff ? c.take<float>((size_t)n_tok * s.ldd) : nullptr;
   s.bytes = c.off;
-  int64_t to, tt;
-  gemm_tile_counts(n_tok, c_out, true, &to, &tt);
-  s.small = strides_ok && gemm_small_tiles(n_tok, c_out, n_alpha) &&
-            (size_t)n_alpha * to * tt * sizeof(float) <= (size_t)xstat_chunks(n_tok) * c_in * sizeof(double);
-  if (s.small) {
-    s.tiles_o = to; s.tiles_t = tt; s.partial = (float*)s.xs_partial;
-  }
+  if (!strides_ok) return s;
+  const int64_t room = (int64_t)((size_t)xstat_chunks(n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
+  const int64_t big = s.tiles_o * s.tiles_t;
+  // (the differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us)
+  s.tile = gemm_tile(n_tok, c_out, act ? s.nb : n_alpha, diff ? kTileSmall | kTileNarrow : kTileAll, room > big ? room : big);
+  gemm_tile_counts(n_tok, c_out, s.tile, &s.tiles_o, &s.tiles_t);
+  if (s.tiles_o * s.tiles_t > big) s.partial = (float*)s.xs_partial;
   return s;
 }
 
 struct ErrPlan {
   float* partial; float* tok_partial; uint16_t* folded; uint32_t* xmax; uint16_t* xh; float* sig;
-  size_t bytes; int64_t tiles_o, tiles_t;   // xh doubles as the code matrix in act mode
+  size_t bytes; int64_t tiles_o, tiles_t; GemmTile tile;   // xh doubles as the code matrix in act mode
 };
-ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act) {
+// fp16: fp16 operands for the pipelined kernel
+ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act, bool fp16 = false) {
   ErrPlan e;
   Carver c(ws);
-  gemm_tile_counts(n_tok, c_out, false, &e.tiles_o, &e.tiles_t);
+  gemm_tile_counts(n_tok, c_out, GemmTile{}, &e.tiles_o, &e.tiles_t);
   e.partial = c.take<float>((size_t)e.tiles_o * e.tiles_t);
   e.tok_partial = c.take<float>((size_t)e.tiles_o * n_tok);
   e.folded = c.take<uint16_t>((size_t)c_out * c_in);
@@ -138,6 +140,9 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   e.xh = (bf16 || act) ? c.take<uint16_t>((size_t)n_tok * c_in) : nullptr;
   e.sig = act ? c.take<float>((size_t)n_tok) : nullptr;
   e.bytes = c.off;
+  e.tile = GemmTile{};
+  if (fp16) e.tile = gemm_tile(n_tok, c_out, 1, kTileWide, e.tiles_o * e.tiles_t);
+  gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
   return e;
 }
 
@@ -180,7 +185,7 @@ GramPlan lay_out_gram(void* ws, int64_t n_tok, int64_t c_in, int n_split) {
 }
 GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
   int64_t to, tt;
-  gemm_tile_counts(c_in, c_in, false, &to, &tt);
+  gemm_tile_counts(c_in, c_in, GemmTile{}, &to, &tt);
   const int64_t live = to * (to + 1) / 2;
   // the workspace holds up to 16 partial products of at least 4096 tokens each, 5000 tiles in all
   int64_t ns = (5000 + live - 1) / live;
@@ -215,16 +220,18 @@ GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
   return best;
 }
 struct GramSearchPlan { float* s_table; float* inv_table; float* partial; uint16_t* dq; size_t bytes;
-                        int64_t tiles_o, tiles_t; };
+                        int64_t tiles_o, tiles_t; GemmTile tile; };
 GramSearchPlan plan_gram_search(void* ws, int64_t c_in, int64_t c_out, int n_alpha) {
   GramSearchPlan s;
   Carver c(ws);
-  gemm_tile_counts(c_out, c_in, false, &s.tiles_o, &s.tiles_t);   // weight rows take the token role
+  gemm_tile_counts(c_out, c_in, GemmTile{}, &s.tiles_o, &s.tiles_t);   // weight rows take the token role
   s.s_table = c.take<float>((size_t)n_alpha * c_in);
   s.inv_table = c.take<float>((size_t)n_alpha * c_in);
   s.partial = c.take<float>((size_t)n_alpha * s.tiles_o * s.tiles_t);
   s.dq = c.take<uint16_t>((size_t)n_alpha * c_out * c_in);
   s.bytes = c.off;
+  s.tile = gemm_tile(c_out, c_in, n_alpha, kTileWide, s.tiles_o * s.tiles_t);
+  gemm_tile_counts(c_out, c_in, s.tile, &s.tiles_o, &s.tiles_t);
   return s;
 }
 }  // namespace
@@ -377,7 +384,7 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = p->x_dtype == TLQ_BF16;
   const bool act = p->act_bits != 0;
-  ErrPlan e = plan_err(workspace, n_tok, c_in, c_out, bf16, act);
+  ErrPlan e = plan_err(workspace, n_tok, c_in, c_out, bf16, act, gemm_strides_ok(ldx, ldw) && (!bf16 || act || inv_s));
   GemmArgs g{};
   g.X = X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = ldx;
   g.Wh = Wdq; g.c_out = c_out; g.ldw = ldw; g.w_cand_stride = 0; g.n_cand = 1; g.bf16 = bf16;
@@ -400,7 +407,7 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
     g.Wh = e.folded; g.ldw = c_in;
   }
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
-  g.partial = e.partial; g.tok_partial = per_token_err ? e.tok_partial : nullptr;
+  g.tile() = e.tile; g.partial = e.partial; g.tok_partial = per_token_err ? e.tok_partial : nullptr;
   TLQ_HIP(launch_gemm_loss(g, st));
   TLQ_HIP(launch_finalize(e.partial, 1, e.tiles_o * e.tiles_t, c_out, nullptr, c_in, loss, nullptr,
                           nullptr, st));
@@ -482,7 +489,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     r.X = X; r.n_tok = n_tok; r.c_in = c_in; r.ldx = ldx;
     r.Wh = W; r.c_out = c_out; r.ldw = ldw; r.w_cand_stride = 0; r.n_cand = 1; r.bf16 = bf16;
     r.Yout = s.d0; r.ldo = s.ldd; r.yout_dtype = TLQ_F32;
-    r.small = gemm_strides_ok(ldx, ldw) && gemm_small_tiles(n_tok, c_out, 1);
+    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
     r.Yref = Y_ref; r.ldy = ldy; r.yref_dtype = p->yref_dtype;   // subtracted in the epilogue (float output)
     TLQ_HIP(launch_gemm_store(r, st));
   }
@@ -493,7 +500,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   g.n_cand = n_alpha; g.bf16 = false;
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   if (diff) { g.Yref = s.d0; g.ldy = s.ldd; g.yref_dtype = TLQ_F32; }
-  g.partial = s.partial; g.tok_partial = nullptr; g.small = s.small;
+  g.partial = s.partial; g.tok_partial = nullptr; g.tile() = s.tile;
   if (!act) {
     // patch shape by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose
     // 0.5 - 3 % on the narrowing, deep ones (down_proj)
@@ -646,7 +653,7 @@ tlq_status tlq_scale_search_gram(const void* gram, int64_t c_in, const void* W, 
   g.X = s.dq; g.n_tok = c_out; g.c_in = c_in; g.ldx = c_in; g.x_cand_stride = c_out * c_in;
   g.Wh = v.C; g.c_out = c_in; g.ldw = c_in; g.w_cand_stride = 0; g.n_cand = n_alpha; g.bf16 = false;
   g.Yref = s.dq; g.ldy = c_in; g.yref_dtype = TLQ_F16; g.y_cand_stride = c_out * c_in;
-  g.partial = s.partial; g.cand_outer = true;   // D'_k and C stay cache-resident for one candidate at a time
+  g.partial = s.partial; g.tile() = s.tile; g.cand_outer = true;   // D'_k and C stay cache-resident for one candidate at a time
   g.wide_patch = true;   // consecutive patches keep their 8 panels of C and fetch 4 new ones of D'_k
   g.sym_k = true;        // C is symmetric: contract from each tile's diagonal block on, the rest counted twice
   TLQ_HIP(launch_gemm_dot(g, st));
@@ -672,7 +679,7 @@ tlq_status tlq_ref_output(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   g.bf16 = p->x_dtype == TLQ_BF16;
   g.Yout = Y; g.ldo = ldy; g.yout_dtype = p->yref_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  g.small = gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
   return hip_status(launch_gemm_store(g, (hipStream_t)stream));
 }
 
@@ -732,7 +739,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   if (ld8) { g.i8_k = c_in; g.c_in = g.ldx = g.ldw = ld8 / 2; g.row_scale = steps; }      // (in units of 16 bits)
   g.Yout = X_next; g.ldo = ld_next; g.yout_dtype = p->x_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  g.small = gemm_strides_ok(g.ldx, g.ldw) && gemm_small_tiles(n_tok, c_out, 1);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
   return hip_status(launch_gemm_store(g, st));
 }
 

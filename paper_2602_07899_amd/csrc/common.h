@@ -157,8 +157,12 @@ hipError_t launch_fold_scale(const void* Win, int64_t c_out, int64_t c_in, int64
                              const float* inv_s, const uint32_t* xmax_bits, bool out_f16, void* Wout,
                              hipStream_t stream);
 
+// Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
+// or 128 x 128 (stores without tri, and fp16 losses without tok_partial).  gemm_tile says which is the fastest.
+struct GemmTile { bool small; int tok_blocks; };
 // S3+S4 / plain GEMM with store epilogue.
-struct GemmArgs {
+struct GemmArgs : GemmTile {
+  GemmTile& tile() { return *this; }
   const void* X; int64_t n_tok, c_in, ldx;     // tokens  [n_tok, c_in]
   int64_t x_cand_stride;                        // elements between per-candidate token matrices (0 = shared)
   const float* tok_scale;                       // [n_cand, n_tok] factor on the accumulators or NULL
@@ -170,7 +174,6 @@ struct GemmArgs {
   bool tri;                // launch_gemm_store of a symmetric product (X == Wh): tiles with tile row <= tile column only
   bool cand_outer;         // walk the candidates one after the other instead of inside every patch row
   bool wide_patch;         // L2 patches of 8 x 4 tiles (output rows x tokens) instead of 4 x 8
-  bool small;              // 128 x 128 tiles (stores without tri, and fp16 losses without tok_partial)
   bool sym_k;              // launch_gemm_dot: Wh is symmetric [c_in, c_in] and Y == X (a quadratic form)
   int64_t o_cand_stride;   // launch_gemm_store with n_cand > 1: elements between per-candidate outputs
   float* partial;          // [n_cand, tiles_o, tiles_t] float
@@ -182,10 +185,13 @@ struct GemmArgs {
   // store epilogue: Y[t,o]; with Yref given Yref - Y (float output and one candidate only, else an error)
   void* Yout; int64_t ldo; int yout_dtype;
 };
-// `small`: 128 x 128 output tiles instead of 256 x 256 (gemm_small_tiles says when they are faster)
-void gemm_tile_counts(int64_t n_tok, int64_t c_out, bool small, int64_t* tiles_o, int64_t* tiles_t);
-bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand);
-// row strides that the pipelined kernel (and with it the small tiles) takes
+void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tiles_o, int64_t* tiles_t);
+// kinds: tiles besides 256 x 256 that the launch has (stores and fp16 losses: all; fp16 losses with tok_partial and the
+// quadratic form: the wide one); max_tiles: tiles per candidate that the caller has room for, at least those of
+// 256 x 256
+enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7 };
+GemmTile gemm_tile(int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles);
+// row strides that the pipelined kernel (and with it any tile but 256 x 256) takes
 bool gemm_strides_ok(int64_t ldx, int64_t ldw);
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out);
 hipError_t launch_gemm_loss(const GemmArgs& a, hipStream_t stream);

@@ -20,8 +20,8 @@
 //
 // Two kernels share the tile epilogues and the block -> tile map:
 //   gemm_dma_kernel  the pipelined one: 16x16x32 MFMA, operands brought into LDS by LDS-DMA loads,
-//                    two 64 KB stages, hand-placed waits; a 128 x 128-tile variant serves launches with
-//                    few tiles;
+//                    two 64 KB stages, hand-placed waits; variants of 128 x 128, 256 x 192 and 256 x 320 outputs
+//                    serve the launches whose count of tiles they suit better (gemm_tile);
 //   gemm_kernel      for row strides of 2^21 elements and more (beyond the 32-bit offsets of the other):
 //                    32x32x16 MFMA, register-staged loads.
 // Tiling (wave64): block tile 256 x 256 outputs, k-tile 64; waves own 128 x 64
@@ -96,7 +96,7 @@ template <> struct Mma16<Int8> {
 //   get(acc, q, tb, r)  the accumulator of row(q) + r and tok(tb),
 //   tok_sum(v)     sum of v over the lanes that hold the same token.
 template <int FA, int FB> struct Acc32 {   // acc[FA][FB] of f32x16 (32x32x16)
-  static constexpr int NQ = FA * 4, NTB = FB, WO = FA * 32, WT = FB * 32;
+  static constexpr int NQ = FA * 4, NTB = FB, WO = FA * 32, WT = FB * 32, STG = FB;
   static __device__ __forceinline__ int tok(int tb, int lane) { return tb * 32 + (lane & 31); }
   static __device__ __forceinline__ int row(int q, int lane) { return (q >> 2) * 32 + (q & 3) * 8 + (lane >> 5) * 4; }
   template <typename A> static __device__ __forceinline__ float get(const A& acc, int q, int tb, int r) {
@@ -105,7 +105,7 @@ template <int FA, int FB> struct Acc32 {   // acc[FA][FB] of f32x16 (32x32x16)
   static __device__ __forceinline__ float tok_sum(float v) { return v + __shfl_xor(v, 32, 64); }
 };
 template <int IA, int JB> struct Acc16 {   // acc[IA][JB] of f32x4 (16x16x32)
-  static constexpr int NQ = IA, NTB = JB, WO = IA * 16, WT = JB * 16;
+  static constexpr int NQ = IA, NTB = JB, WO = IA * 16, WT = JB * 16, STG = JB > 4 ? 2 : JB;
   static __device__ __forceinline__ int tok(int tb, int lane) { return tb * 16 + (lane & 15); }
   static __device__ __forceinline__ int row(int q, int lane) { return q * 16 + (lane >> 4) * 4; }
   template <typename A> static __device__ __forceinline__ float get(const A& acc, int q, int tb, int r) {
@@ -190,6 +190,14 @@ __device__ __forceinline__ void store_y1(void* Y, int odt, int64_t idx, float y)
 
 
 
+template <int I, int N, typename Fn>
+__device__ __forceinline__ void static_for(Fn&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
 // Per-lane part of the loss of one wave tile whose first output row is `ow` and first
 // token is `tw`: sq[tb] = sum over this lane's rows of (Y_ref - acc)^2 for its token of
 // token block tb; part = sum_tb token_w * sq[tb].  YDT >= 0 fixes the Y_ref type at
@@ -236,138 +244,136 @@ __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, co
   }
 }
 
-// XOR key of the 16-byte chunks of staged token row `row`: rows of 256 B (CPR = 16) or 128 B (two of them
-// span the banks once)
-template <int CPR>
+// A wave tile passes through LDS L::STG token blocks at a time, in this wave's own piece of WO x 16 STG 16-bit values
+// (all of it at once up to 64 tokens; 80 would not fit beside each other's).  16-byte chunks of a token row are stored
+// at chunk ^ row_key(token), which makes the 8-byte accesses conflict-free.
+template <int CPR>   // rows of 256 B (CPR = 16) or 128 B (two of them span the banks once)
 __device__ __forceinline__ int row_key(int row) { return CPR == 16 ? row & 15 : (row >> 1) & 7; }
 
-// Same sums as loss_rows for an interior wave tile with 16-bit Y_ref, but Y_ref goes through
-// LDS: the wave copies its 64-token x 128-row piece with whole-line loads (each 128-byte line
-// is fetched once, 8 lines per instruction) into `ylds` (WT x WO 16-bit, this wave's own),
-// then every lane picks its values from there.  Reading Y_ref straight from the accumulator
-// layout touches 16 or 32 lines per instruction and each line 8 times.  16-byte chunks of a token
-// row are stored at chunk ^ row_key(token), which makes the 8-byte reads conflict-free.
-template <typename YT, bool DOT, typename L, typename Acc>
-__device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
-                                              int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part,
-                                              unsigned char* ylds) {
-  constexpr int WO = L::WO, WT = L::WT;
-  constexpr int CPR = WO / 8;              // 16-byte chunks per token row
-  constexpr int RPI = 64 / CPR;            // token rows per wave-wide copy
-  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
-  const int lane = threadIdx.x & 63;
-  const uint16_t* Y = (const uint16_t*)Yref;
-  {
-    const int cr = lane / CPR, cc = lane % CPR;
-    uint4 v[WT / RPI];
-#pragma unroll
-    for (int j = 0; j < WT / RPI; ++j) {
-      const int row = j * RPI + cr;
-      v[j] = *reinterpret_cast<const uint4*>(Y + (tw + row) * a.ldy + ow + cc * 8);
-    }
-#pragma unroll
-    for (int j = 0; j < WT / RPI; ++j) {
-      const int row = j * RPI + cr;
-      *reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4)) = v[j];
-    }
-  }
-  // the values are picked up by OTHER lanes of this wave: order the LDS writes before the reads
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-  for (int tb = 0; tb < L::NTB; ++tb) {
-    const int tok = L::tok(tb, lane);
-    const int64_t t = tw + tok;
-    const float nsg = tsc ? -tsc[t] : -1.0f;
-    float sumsq = 0.0f;
-#pragma unroll
-    for (int q = 0; q < L::NQ; ++q) {
-      const int o = L::row(q, lane);        // multiple of 4: chunk o / 8, half (o / 4) % 2
-      const uint2 u = *reinterpret_cast<const uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ row_key<CPR>(tok)) << 4) +
-                                                      ((o >> 2) & 1) * 8);
-      const float y[4] = {YT::to_float((uint16_t)(u.x & 0xffffu)), YT::to_float((uint16_t)(u.x >> 16)),
-                          YT::to_float((uint16_t)(u.y & 0xffffu)), YT::to_float((uint16_t)(u.y >> 16))};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (DOT) { sumsq += L::get(acc, q, tb, r) * y[r]; continue; }
-        const float d = __builtin_fmaf(nsg, L::get(acc, q, tb, r), y[r]);
-        sumsq += d * d;
-      }
-    }
-    part += DOT ? sumsq : a.token_w[t] * sumsq;
-    sq[tb] = sumsq;
-  }
-}
-
-// The staging of loss_rows_lds for the store epilogue that subtracts: the wave's piece of Yref into LDS ...
-template <typename L>
-__device__ __forceinline__ void stage_rows(const void* Yref, int64_t ldy, int64_t ow, int64_t tw, unsigned char* ylds) {
-  constexpr int WO = L::WO, WT = L::WT;
-  constexpr int CPR = WO / 8;              // 16-byte chunks per token row
-  constexpr int RPI = 64 / CPR;            // token rows per wave-wide copy
-  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
-  const int lane = threadIdx.x & 63;
-  const uint16_t* Y = (const uint16_t*)Yref;
-  const int cr = lane / CPR, cc = lane % CPR;
-  uint4 v[WT / RPI];
-#pragma unroll
-  for (int j = 0; j < WT / RPI; ++j) v[j] = *reinterpret_cast<const uint4*>(Y + (tw + j * RPI + cr) * ldy + ow + cc * 8);
-#pragma unroll
-  for (int j = 0; j < WT / RPI; ++j) {
-    const int row = j * RPI + cr;
-    *reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4)) = v[j];
-  }
-  // the values are picked up by OTHER lanes of this wave: order the LDS writes before the reads
+// The LDS accesses of a wave are executed in order; this keeps the compiler from moving those of one lane across
+// those of OTHER lanes of the wave
+__device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-// ... and four staged values: token `tok` of the wave tile, output rows o .. o + 3 of it (o a multiple of 4)
-template <typename YT, typename L>
-__device__ __forceinline__ void staged_y4(const unsigned char* ylds, int tok, int o, float (&y)[4]) {
-  const uint2 u = *reinterpret_cast<const uint2*>(ylds + tok * (L::WO * 2) + (((o >> 3) ^ row_key<L::WO / 8>(tok)) << 4) +
-                                                  ((o >> 2) & 1) * 8);
+template <typename L> struct Staged {
+  static constexpr int WO = L::WO, TBW = L::WT / L::NTB, CPR = WO / 8, RPI = 64 / CPR;   // RPI: rows per wave-wide copy
+  static constexpr int GROUPS = (L::NTB + L::STG - 1) / L::STG;
+  static_assert((CPR == 16 || CPR == 8) && TBW % RPI == 0, "copy shape");
+  // token blocks of group G, and its 16-byte copies per lane
+  template <int G> static constexpr int blocks() { return L::NTB - G * L::STG < L::STG ? L::NTB - G * L::STG : L::STG; }
+  template <int G> static constexpr int copies() { return blocks<G>() * TBW / RPI; }
+  // Four values of token block `b` of the group, quad `q` of the lane; and eight of copy number `j`.  The keys repeat
+  // every 16 rows, so b and j only add constants
+  static __device__ __forceinline__ uint2* at4(unsigned char* ylds, int b, int q) {
+    const int lane = threadIdx.x & 63, tok = L::tok(0, lane), o = L::row(q, lane);   // (o a multiple of 4)
+    return reinterpret_cast<uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ row_key<CPR>(tok)) << 4) + ((o >> 2) & 1) * 8 +
+                                    b * TBW * (WO * 2));
+  }
+  static __device__ __forceinline__ uint4* at8(unsigned char* ylds, int j) {
+    constexpr int PER = 16 / RPI;
+    const int lane = threadIdx.x & 63, row = (j % PER) * RPI + lane / CPR, chunk = lane % CPR;
+    return reinterpret_cast<uint4*>(ylds + row * (WO * 2) + ((chunk ^ row_key<CPR>(row)) << 4) + j / PER * 16 * (WO * 2));
+  }
+  // group G of the wave's piece of a 16-bit matrix into LDS: whole-line loads (each 128-byte line is fetched once, 8
+  // lines per instruction)
+  template <int G>
+  static __device__ __forceinline__ void fill(const void* Yref, int64_t ldy, int64_t ow, int64_t tw, unsigned char* ylds) {
+    const int lane = threadIdx.x & 63, cr = lane / CPR, cc = lane % CPR;
+    const uint16_t* Y = (const uint16_t*)Yref + (tw + G * L::STG * TBW + cr) * ldy + ow + cc * 8;
+    if (G > 0) wave_lds_order();
+    uint4 v[copies<G>()];
+#pragma unroll
+    for (int j = 0; j < copies<G>(); ++j) v[j] = *reinterpret_cast<const uint4*>(Y + j * RPI * ldy);
+#pragma unroll
+    for (int j = 0; j < copies<G>(); ++j) *at8(ylds, j) = v[j];
+    wave_lds_order();
+  }
+  // ... and back out of LDS, whole lines again
+  template <int G>
+  static __device__ __forceinline__ void drain(void* Yout, int64_t ldo, int64_t ow, int64_t tw, unsigned char* ylds) {
+    const int lane = threadIdx.x & 63, cr = lane / CPR, cc = lane % CPR;
+    uint16_t* Y = (uint16_t*)Yout + (tw + G * L::STG * TBW + cr) * ldo + ow + cc * 8;
+#pragma unroll
+    for (int j = 0; j < copies<G>(); ++j) *reinterpret_cast<uint4*>(Y + j * RPI * ldo) = *at8(ylds, j);
+  }
+};
+template <typename YT>
+__device__ __forceinline__ void unpack4(uint2 u, float (&y)[4]) {
   y[0] = YT::to_float((uint16_t)(u.x & 0xffffu)); y[1] = YT::to_float((uint16_t)(u.x >> 16));
   y[2] = YT::to_float((uint16_t)(u.y & 0xffffu)); y[3] = YT::to_float((uint16_t)(u.y >> 16));
 }
 
-// Store epilogue of an interior wave tile with a 16-bit output, through LDS: every lane drops
-// its rounded values into `ylds` (WT x WO 16-bit, this wave's own, same chunk-XOR-token layout
-// as loss_rows_lds), then the wave writes whole 128-byte lines, 8 lines per instruction.
-// Storing straight from the accumulator layout writes 8-byte pieces of 16 or 32 lines per instruction.
+// Same sums as loss_rows for an interior wave tile with 16-bit Y_ref, but Y_ref goes through LDS and every lane picks
+// its values from there.  Reading Y_ref straight from the accumulator layout touches 16 or 32 lines per
+// instruction and each line 8 times.
+template <typename YT, bool DOT, typename L, typename Acc>
+__device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
+                                              int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part,
+                                              unsigned char* ylds) {
+  using S = Staged<L>;
+  const int lane = threadIdx.x & 63;
+  // the bodies of the two types stay apart: merged, with a branch at every value, they need more registers than there are
+  asm volatile("; values of type %0" ::"n"(std::is_same<YT, F16>::value ? TLQ_F16 : TLQ_BF16));
+  float nsg[L::NTB];
+#pragma unroll
+  for (int tb = 0; tb < L::NTB; ++tb) nsg[tb] = -1.0f;
+  if (tsc) {
+#pragma unroll
+    for (int tb = 0; tb < L::NTB; ++tb) nsg[tb] = -tsc[tw + L::tok(tb, lane)];
+  }
+  static_for<0, S::GROUPS>([&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    S::template fill<G>(Yref, a.ldy, ow, tw, ylds);
+#pragma unroll
+    for (int b = 0; b < S::template blocks<G>(); ++b) {
+      const int tb = G * L::STG + b;
+      float sumsq = 0.0f;
+#pragma unroll
+      for (int q = 0; q < L::NQ; ++q) {
+        float y[4];
+        unpack4<YT>(*S::at4(ylds, b, q), y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (DOT) { sumsq += L::get(acc, q, tb, r) * y[r]; continue; }
+          const float d = __builtin_fmaf(nsg[tb], L::get(acc, q, tb, r), y[r]);
+          sumsq += d * d;
+        }
+      }
+      part += DOT ? sumsq : a.token_w[tw + L::tok(tb, lane)] * sumsq;
+      sq[tb] = sumsq;
+      if (L::NTB > 4) __builtin_amdgcn_sched_barrier(0);
+    }
+  });
+}
+
+// Store epilogue of an interior wave tile with a 16-bit output, through LDS: every lane drops its rounded values there,
+// then the wave writes whole lines.  Storing straight from the accumulator layout writes 8-byte pieces of
+// 16 or 32 lines per instruction.
 template <typename YT, typename L, typename Acc>
 __device__ __forceinline__ void store_rows_lds(const GemmDev& a, void* Yout, const Acc& acc, const float* tsc,
                                                int64_t ow, int64_t tw, unsigned char* ylds) {
-  constexpr int WO = L::WO, WT = L::WT;
-  constexpr int CPR = WO / 8, RPI = 64 / CPR;
-  static_assert((CPR == 16 || CPR == 8) && WT % RPI == 0, "copy shape");
+  using S = Staged<L>;
   const int lane = threadIdx.x & 63;
+  static_for<0, S::GROUPS>([&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    if (G > 0) wave_lds_order();
 #pragma unroll
-  for (int tb = 0; tb < L::NTB; ++tb) {
-    const int tok = L::tok(tb, lane);
-    const float sg = tsc ? tsc[tw + tok] : 1.0f;
+    for (int b = 0; b < S::template blocks<G>(); ++b) {
+      const int tb = G * L::STG + b;
+      const float sg = tsc ? tsc[tw + L::tok(tb, lane)] : 1.0f;
 #pragma unroll
-    for (int q = 0; q < L::NQ; ++q) {
-      const int o = L::row(q, lane);
-      uint2 u;
-      u.x = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 0)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 1)) << 16);
-      u.y = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 2)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 3)) << 16);
-      *reinterpret_cast<uint2*>(ylds + tok * (WO * 2) + (((o >> 3) ^ row_key<CPR>(tok)) << 4) + ((o >> 2) & 1) * 8) = u;
+      for (int q = 0; q < L::NQ; ++q) {
+        uint2 u;
+        u.x = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 0)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 1)) << 16);
+        u.y = (uint32_t)YT::from_float(sg * L::get(acc, q, tb, 2)) | ((uint32_t)YT::from_float(sg * L::get(acc, q, tb, 3)) << 16);
+        *S::at4(ylds, b, q) = u;
+      }
     }
-  }
-  uint16_t* Y = (uint16_t*)Yout;
-  const int cr = lane / CPR, cc = lane % CPR;
-  // whole lines are read back by OTHER lanes of this wave: order the LDS writes before the reads
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-  for (int j = 0; j < WT / RPI; ++j) {
-    const int row = j * RPI + cr;
-    const uint4 v = *reinterpret_cast<const uint4*>(ylds + row * (WO * 2) + ((cc ^ row_key<CPR>(row)) << 4));
-    *reinterpret_cast<uint4*>(Y + (tw + row) * a.ldo + ow + cc * 8) = v;
-  }
+    wave_lds_order();
+    S::template drain<G>(Yout, a.ldo, ow, tw, ylds);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -380,6 +386,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
                                               int tt, int64_t o0, int64_t t0, int wo, int wt,
                                               float* red, float* rows) {
   constexpr int WO = L::WO, WT = L::WT, NW = NWO * NWT, NT = NW * 64;
+  constexpr int kStage = WO * L::STG * (WT / L::NTB) * 2;   // bytes of LDS per wave, see Staged
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* tsc = a.tok_scale ? a.tok_scale + (int64_t)cand * a.n_tok : nullptr;
   if (EPI == EPI_STORE) {
@@ -387,7 +394,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
     if constexpr (YLDS) {
       if (a.odt != TLQ_F32 && (o0 + NWO * WO <= a.c_out) && (t0 + BT <= a.n_tok) && (a.ldo % 8) == 0 &&
           ((uintptr_t)Yo % 16) == 0) {
-        unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * (WO * WT * 2);
+        unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * kStage;
         if (a.odt == TLQ_F16) store_rows_lds<F16, L>(a, Yo, acc, tsc, o0 + wo * WO, t0 + wt * WT, ylds);
         else store_rows_lds<BF16, L>(a, Yo, acc, tsc, o0 + wo * WO, t0 + wt * WT, ylds);
         return;
@@ -396,11 +403,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
     // the guarded body, written out once for the plain store and once for the subtraction: the checks are a long
     // straight piece of code that an edge tile fetches cold, so the plain one carries nothing of the other
     // (6981 x 256 x 2216 tokens x channels x outputs, 252 tiles, 16-bit output: 20.3 us in one body, 16.3 in two)
-    auto rows_out = [&](auto emit) {
-#pragma unroll
-      for (int tb = 0; tb < L::NTB; ++tb) {
+    auto rows_out = [&](auto before, auto emit) {
+      static_for<0, L::NTB>([&](auto tbc) {
+        constexpr int tb = decltype(tbc)::value;
+        before(tbc);
         const int64_t t = t0 + wt * WT + L::tok(tb, lane);
-        if (t >= a.n_tok) continue;
+        if (t >= a.n_tok) return;
         const float sg = tsc ? tsc[t] : 1.0f;
 #pragma unroll
         for (int q = 0; q < L::NQ; ++q) {
@@ -408,10 +416,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
                         sg * L::get(acc, q, tb, 3)};
           emit(tb, q, t, o0 + wo * WO + L::row(q, lane), y);
         }
-      }
+      });
     };
     if (!a.Yref) {
-      rows_out([&](int, int, int64_t t, int64_t o, const float (&y)[4]) {
+      rows_out([](auto) {}, [&](int, int, int64_t t, int64_t o, const float (&y)[4]) {
         if (o + 3 < a.c_out) store_y4(Yo, a.odt, t * a.ldo + o, y);
         else
           for (int r = 0; r < 4; ++r)
@@ -421,18 +429,22 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
     }
     // Yref - product, as float; Yref comes in whole lines through LDS where the tile is inside the matrix (see
     // loss_rows_lds)
-    unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * (WO * WT * 2);
+    unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * kStage;
     bool staged = false;
     if constexpr (YLDS) {
       staged = a.ydt != TLQ_F32 && (o0 + NWO * WO <= a.c_out) && (t0 + BT <= a.n_tok) && (a.ldy % 8) == 0 &&
                ((uintptr_t)a.Yref % 16) == 0;
-      if (staged) stage_rows<L>(a.Yref, a.ldy, o0 + wo * WO, t0 + wt * WT, ylds);
     }
-    rows_out([&](int tb, int q, int64_t t, int64_t o, const float (&y)[4]) {
+    rows_out([&](auto tbc) {
+      constexpr int tb = decltype(tbc)::value;
+      if constexpr (YLDS && tb % L::STG == 0)
+        if (staged) Staged<L>::template fill<tb / L::STG>(a.Yref, a.ldy, o0 + wo * WO, t0 + wt * WT, ylds);
+    }, [&](int tb, int q, int64_t t, int64_t o, const float (&y)[4]) {
       float yr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
       if (staged) {
-        if (a.ydt == TLQ_F16) staged_y4<F16, L>(ylds, L::tok(tb, lane), L::row(q, lane), yr);
-        else staged_y4<BF16, L>(ylds, L::tok(tb, lane), L::row(q, lane), yr);
+        const uint2 u = *Staged<L>::at4(ylds, tb % L::STG, q);
+        if (a.ydt == TLQ_F16) unpack4<F16>(u, yr);
+        else unpack4<BF16>(u, yr);
       } else if (o + 3 < a.c_out) load_y4(a.Yref, a.ydt, t * a.ldy + o, yr);
       else
         for (int r = 0; r < 4; ++r)
@@ -458,13 +470,14 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
   bool done = false;
   if constexpr (YLDS && (EPI == EPI_LOSS || DOT)) {
     if (interior && a.ydt != TLQ_F32 && (a.ldy % 8) == 0 && ((uintptr_t)Yc % 16) == 0) {
-      unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * (WO * WT * 2);
+      unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * kStage;
       if (a.ydt == TLQ_F16) loss_rows_lds<F16, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part, ylds);
       else loss_rows_lds<BF16, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part, ylds);
       done = true;
     }
   }
   if (done) {}
+  else if (L::NTB > 4) loss_rows<-1, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);   // (few registers, little code)
   else if (interior && a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
   else if (interior && a.ydt == TLQ_F32) loss_rows<TLQ_F32, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
   else if (interior) loss_rows<TLQ_BF16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
@@ -742,22 +755,23 @@ __device__ __forceinline__ void lds_read128(u32x4& v, uint32_t addr) {
 }
 // Wait for every outstanding LDS read; the fragments are tied through the
 // statement so that nothing consuming them can be scheduled above it.
-__device__ __forceinline__ void lds_wait4(u32x4& f0, u32x4& f1, u32x4& f2, u32x4& f3) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3) : : "memory");
+__device__ __forceinline__ void lds_wait(u32x4 (&a)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]) : : "memory");
 }
-__device__ __forceinline__ void lds_wait8(u32x4& f0, u32x4& f1, u32x4& f2, u32x4& f3, u32x4& f4,
-                                          u32x4& f5, u32x4& f6, u32x4& f7) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3), "+v"(f4), "+v"(f5), "+v"(f6), "+v"(f7)
-               :
-               : "memory");
-}
-template <int I, int N, typename Fn>
-__device__ __forceinline__ void static_for(Fn&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
+template <int N>
+__device__ __forceinline__ void lds_wait(u32x4 (&a)[4], u32x4 (&b)[N]) {
+  static_assert(N >= 3 && N <= 5, "token fragments of a wave tile");
+  if constexpr (N == 3)
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]) : : "memory");
+  else if constexpr (N == 4)
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3])
+                 : : "memory");
+  else
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]),
+                   "+v"(b[4]) : : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -788,23 +802,25 @@ __device__ __forceinline__ void wait_vmcnt() {
 // k-tile at the same time and share its token panel in L2; the diagonal block comes last.
 // TAIL: c_in is not a multiple of the k-tile; the lanes whose chunk lies past the end of the rows fetch
 // nothing for the last k-tile (their offset is out of range, the chunk arrives as zeros).
+// JB = 3 or 5: the wave tile is 128 x 48 or 128 x 80 tokens (twelve or twenty MFMAs a phase); 80 take 252 registers and 144 KB
+// of LDS, the most that two waves a SIMD and one block a CU can have.
 // HALVES = 1: a block of 4 waves computes 128 x 128 outputs, a wave 64 x 64 (a phase per k32 step, all of
 // its eight fragments read one phase ahead); two blocks share a CU.  For launches whose 256 x 256 tiles
 // would leave CUs idle, see gemm_small_tiles.
-template <typename T, int NSTAGE, int EPI, bool SYMK, bool TAIL, int HALVES>
+template <typename T, int NSTAGE, int EPI, bool SYMK, bool TAIL, int HALVES, int JB>
 __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses gfx950 builtins the host pass cannot parse
-  constexpr int BK_ = 64, NWO = 2, NWT = 2 * HALVES, NW = NWO * NWT, WO = 64 * HALVES, WT = 64;
+  constexpr int BK_ = 64, NWO = 2, NWT = 2 * HALVES, NW = NWO * NWT, WO = 64 * HALVES, WT = 16 * JB;
   constexpr int BO = NWO * WO, BT = NWT * WT;
-  constexpr int IA = WO / 16, JB = WT / 16;   // accumulator tiles per wave: 8 x 4 or 4 x 4
+  constexpr int IA = WO / 16;                 // accumulator tiles per wave: IA x JB
   static_assert(HALVES == 1 || HALVES == 2, "phase structure below: one or two row halves of 64");
   constexpr int RB = BK_ * 2;             // bytes per LDS row
   constexpr int CPR = BK_ / 8;            // 16-byte chunks per row
   constexpr int STAGE = (BO + BT) * RB;
   constexpr int RPD = 64 / CPR;           // rows covered by one wave-wide load
-  constexpr int DPO = BO / RPD / NW;      // loads per wave per operand per k-tile
-  constexpr int LPS = 2 * DPO;            // loads per wave per k-tile
-  static_assert((NSTAGE == 2 || NSTAGE == 4) && LPS == 8, "pipeline shape");
+  constexpr int DPA = BO / RPD / NW, DPB = BT / RPD / NW;   // loads per wave per k-tile: weights, tokens
+  constexpr int LPS = DPA + DPB, DPM = DPA < DPB ? DPA : DPB;
+  static_assert((NSTAGE == 2 || NSTAGE == 4) && DPA * RPD * NW == BO && DPB * RPD * NW == BT, "pipeline shape");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NSTAGE * STAGE];
   __shared__ float red[NW];
 
@@ -830,14 +846,14 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
 
   // per-lane global byte offsets of the chunks this lane fetches: LDS slot `p` of row r holds
   // chunk p ^ ((r / 2) % 8)
-  int voa[DPO], vob[DPO];
+  int voa[DPA], vob[DPB];
 #pragma unroll
-  for (int j = 0; j < DPO; ++j) {
+  for (int j = 0; j < (DPA > DPB ? DPA : DPB); ++j) {
     const int r = (j * NW + wave) * RPD + lane / CPR;
     const int p = lane % CPR;
     const int c = p ^ ((r >> 1) & 7);
-    voa[j] = r * (int)a.ldw * 2 + c * 16;
-    vob[j] = r * (int)a.ldx * 2 + c * 16;
+    if (j < DPA) voa[j] = r * (int)a.ldw * 2 + c * 16;
+    if (j < DPB) vob[j] = r * (int)a.ldx * 2 + c * 16;
   }
   // The scalar offset is not part of the descriptor's range check, so a k-tile
   // past the end of the rows must not be fetched at all: its loads are still
@@ -849,8 +865,9 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
   // TAIL: the lane's chunk of a k-tile (the same for all of its loads, see voa) lies inside the last one
   const bool tail_ok = !TAIL || ((lane % CPR) ^ ((wave * (RPD / 2) + (lane / CPR >> 1)) & 7)) * 8 < (int)(klen - (nk - 1) * BK_);
   auto dma1 = [&](auto dc, unsigned char* sbase, bool live, int so) {
-    constexpr int d = decltype(dc)::value, j = d / 2;
-    if constexpr ((d & 1) == 0)
+    // the operands take turns while both have loads left
+    constexpr int d = decltype(dc)::value, j = d < 2 * DPM ? d / 2 : d - DPM;
+    if constexpr (d < 2 * DPM ? (d & 1) == 0 : DPA > DPB)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr_t)(sbase + (j * NW + wave) * 1024), 16,
                                                live ? voa[j] : kOutOfRange, so, 0, 0);
     else
@@ -882,7 +899,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
     offA[st] = lds0 + o + (wo * WO) * RB;
     offB[st] = lds0 + o + BO * RB + (wt * WT) * RB;
   }
-  u32x4 Fa[2][4], Fb[2][4];   // weight fragments (double-buffered per phase), token fragments (per k32 step)
+  u32x4 Fa[2][4], Fb[2][JB];   // weight fragments (double-buffered per phase), token fragments (per k32 step)
   f32x4 acc[IA][JB];
 #pragma unroll
   for (int i = 0; i < IA; ++i)
@@ -891,8 +908,8 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
 
-  // One phase: the 16 MFMAs of weight buffer AB x token buffer BB into output rows HALF, with the
-  // side operations behind the first eight: the weight fragments of half RH into buffer AB ^ 1
+  // One phase: the 4 x JB MFMAs of weight buffer AB x token buffer BB into output rows HALF, with the
+  // side operations behind the first of them: the weight fragments of half RH into buffer AB ^ 1
   // (from `ra`), - if RDB - the token fragments into buffer BB ^ 1 (from `rb`), and ND LDS-DMA
   // loads of k-tile `dkt`.
   auto phase = [&](auto abc, auto bbc, auto halfc, auto rhc, auto rdbc, auto ndc, uint32_t ra, uint32_t rb,
@@ -900,8 +917,8 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
     constexpr int AB = decltype(abc)::value, BB = decltype(bbc)::value, HALF = decltype(halfc)::value;
     constexpr int RH = decltype(rhc)::value, ND = decltype(ndc)::value;
     constexpr bool RDB = decltype(rdbc)::value != 0;
-    constexpr int NR = 4 + (RDB ? 4 : 0);
-    static_assert(NR + ND <= 16, "two side operations behind each of the first eight MFMAs");
+    constexpr int NR = 4 + (RDB ? JB : 0);
+    static_assert(NR + ND <= 8 * JB, "two side operations behind an MFMA");
     const bool live = fetches(dkt);
     const int so = dkt < nk ? k_offset(dkt) : 0;
     unsigned char* sbase = lds + (int)(dkt % NSTAGE) * STAGE;
@@ -914,12 +931,12 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
       else if constexpr (n < NR) lds_read128<(n - 4) * 16 * RB>(Fb[BB ^ 1][n - 4], rb);
       else if constexpr (n < NR + ND) dma1(std::integral_constant<int, n - NR>{}, sbase, live, so);
     };
-    static_for<0, 16>([&](auto mc) {
-      // boustrophedon over the 4 x 4 fragment pairs: consecutive MFMAs share one operand register set
-      constexpr int m = decltype(mc)::value, ib = m / 4, jb = (ib & 1) ? 3 - m % 4 : m % 4;
+    static_for<0, 4 * JB>([&](auto mc) {
+      // boustrophedon over the 4 x JB fragment pairs: consecutive MFMAs share one operand register set
+      constexpr int m = decltype(mc)::value, ib = m / JB, jb = (ib & 1) ? JB - 1 - m % JB : m % JB;
       acc[HALF * 4 + ib][jb] = Mma16<T>::run(__builtin_bit_cast(uint4, Fa[AB][ib]),
                                              __builtin_bit_cast(uint4, Fb[BB][jb]), acc[HALF * 4 + ib][jb]);
-      if constexpr (m < 8) {   // two side operations behind each of the first eight MFMAs
+      if constexpr (2 * m < NR + ND) {
         side(std::integral_constant<int, 2 * m>{});
         side(std::integral_constant<int, 2 * m + 1>{});
       }
@@ -928,31 +945,31 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  using I8 = std::integral_constant<int, LPS>;
+  using ILoads = std::integral_constant<int, LPS>;
 
   // prologue: fill the whole ring, wait for k-tile 0, fetch its first fragments
 #pragma unroll
   for (int s = 0; s < NSTAGE; ++s) issue(s);
   wait_vmcnt<(NSTAGE - 1) * LPS>();
   __builtin_amdgcn_s_barrier();
-  static_for<0, 4>([&](auto mc) {
+  static_for<0, (JB > 4 ? JB : 4)>([&](auto mc) {
     constexpr int m = decltype(mc)::value;
-    lds_read128<m * 16 * RB>(Fa[0][m], offA[0]);
-    lds_read128<m * 16 * RB>(Fb[0][m], offB[0]);
+    if constexpr (m < 4) lds_read128<m * 16 * RB>(Fa[0][m], offA[0]);
+    if constexpr (m < JB) lds_read128<m * 16 * RB>(Fb[0][m], offB[0]);
   });
-  lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[0][0], Fb[0][1], Fb[0][2], Fb[0][3]);
+  lds_wait(Fa[0], Fb[0]);
   auto k_tile = [&](int64_t kt) {
     const uint32_t so_cur = (uint32_t)((kt % NSTAGE) * STAGE);
     if constexpr (HALVES == 2) {
       phase(I0{}, I0{}, I0{}, I1{}, I0{}, I0{}, offA[0] + so_cur, 0u, 0);
-      lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
+      lds_wait(Fa[1]);
       phase(I1{}, I0{}, I1{}, I0{}, I1{}, I0{}, offA[1] + so_cur, offB[1] + so_cur, 0);
-      lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[1][0], Fb[1][1], Fb[1][2], Fb[1][3]);
+      lds_wait(Fa[0], Fb[1]);
       phase(I0{}, I1{}, I0{}, I1{}, I0{}, I0{}, offA[1] + so_cur, 0u, 0);
-      lds_wait4(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3]);
+      lds_wait(Fa[1]);
     } else {
       phase(I0{}, I0{}, I0{}, I0{}, I1{}, I0{}, offA[1] + so_cur, offB[1] + so_cur, 0);
-      lds_wait8(Fa[1][0], Fa[1][1], Fa[1][2], Fa[1][3], Fb[1][0], Fb[1][1], Fb[1][2], Fb[1][3]);
+      lds_wait(Fa[1], Fb[1]);
     }
     // every fragment of k-tile kt is in registers: its slot can be refilled once all
     // waves are here, and k-tile kt+1 has landed once this wave's share of it has
@@ -960,9 +977,9 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t so_next = (uint32_t)(((kt + 1) % NSTAGE) * STAGE);
-    phase(I1{}, I1{}, std::integral_constant<int, HALVES - 1>{}, I0{}, I1{}, I8{}, offA[0] + so_next, offB[0] + so_next,
+    phase(I1{}, I1{}, std::integral_constant<int, HALVES - 1>{}, I0{}, I1{}, ILoads{}, offA[0] + so_next, offB[0] + so_next,
           kt + NSTAGE);
-    lds_wait8(Fa[0][0], Fa[0][1], Fa[0][2], Fa[0][3], Fb[0][0], Fb[0][1], Fb[0][2], Fb[0][3]);
+    lds_wait(Fa[0], Fb[0]);
   };
   int64_t kt = 0;
   if constexpr (SYMK) {
@@ -998,50 +1015,85 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
   }
   // every LDS-DMA write has landed and every wave is past its last fragment read:
   // the tile memory is free for the per-token row sums and the Y_ref / output staging
-  tile_epilogue<EPI, Acc16<IA, JB>, NWO, NWT, BT, (NSTAGE * STAGE >= NW * WO * WT * 2)>(
+  tile_epilogue<EPI, Acc16<IA, JB>, NWO, NWT, BT, (NSTAGE * STAGE >= NW * WO * Acc16<IA, JB>::STG * 32)>(
       a, acc, cand, to, tt, o0, t0, wo, wt, red, reinterpret_cast<float*>(lds));
 #endif
 }
 
 template <typename T, int NSTAGE, int EPI, bool SYMK, bool TAIL, int HALVES>
 __global__ __launch_bounds__(HALVES * 256) void gemm_dma_kernel(GemmDev a) {
-  gemm_dma_body<T, NSTAGE, EPI, SYMK, TAIL, HALVES>(a);
+  gemm_dma_body<T, NSTAGE, EPI, SYMK, TAIL, HALVES, 4>(a);
+}
+// 256 output rows x 64 JB tokens, JB = 3 or 5
+template <typename T, int EPI, bool SYMK, bool TAIL, int JB>
+__global__ __launch_bounds__(512) void gemm_width_kernel(GemmDev a) {
+  gemm_dma_body<T, 2, EPI, SYMK, TAIL, 2, JB>(a);
 }
 // Integer codes on both sides (per-token activation codes, per-row weight codes): twice the multiplications per
 // MFMA cycle and per byte moved of the fp16 form of the same codes, exact sums, one rounding less (the dequantised
 // weight's).  The rows of both operands are padded with zeros to whole k-tiles.  20 candidates of 3678 x 4096 x 4096,
 // W4A8: contraction 2.1 -> 1.2 ms, the whole search 2.19 -> 1.31 ms; relative error of the losses against 64
 // bits 5e-6 -> 3e-8.
-template <int NSTAGE, int EPI, int HALVES>
+template <int NSTAGE, int EPI, int HALVES, int JB>
 __global__ __launch_bounds__(HALVES * 256) void gemm_i8_kernel(GemmDev a) {
-  gemm_dma_body<Int8, NSTAGE, EPI, false, false, HALVES>(a);
+  gemm_dma_body<Int8, NSTAGE, EPI, false, false, HALVES, JB>(a);
 }
 
 // ---- host side ---------------------------------------------------------------
-constexpr int kBO = 256, kBT = 256, kWO = 128, kWT = 64;
+constexpr int kBO = 256, kBT = 256, kWO = 128, kWT = 64;   // (the general kernel has this tile only)
 constexpr int kSmall = 128;                  // rows and columns of a small tile
 constexpr int64_t kChunkBytes = (int64_t)128 << 20;
-// Up to this many tiles a launch is dealt in strips (us, patches -> strips: 480 tiles 252 -> 224, 640 318 ->
+// Up to this many tiles (of 256 tokens, or small ones) a launch is dealt in strips (us, patches -> strips: 480 tiles 252 -> 224, 640 318 ->
 // 308, 960 428 -> 401; 1080 664 -> 667, 1720 762 -> 815: there a strip no longer fits an L2).
 constexpr int64_t kStripTiles = 1024;
 constexpr int kDmaBK = 64;                   // k-tile depth of the pipelined kernel
 
-void gemm_tile_counts(int64_t n_tok, int64_t c_out, bool small, int64_t* tiles_o, int64_t* tiles_t) {
-  *tiles_o = ceil_div(c_out, small ? kSmall : kBO);
-  *tiles_t = ceil_div(n_tok, small ? kSmall : kBT);
+static int64_t tile_tokens(GemmTile t) { return t.small ? kSmall : 64 * (t.tok_blocks ? t.tok_blocks : 4); }
+void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tiles_o, int64_t* tiles_t) {
+  *tiles_o = ceil_div(c_out, tile.small ? kSmall : kBO);
+  *tiles_t = ceil_div(n_tok, tile_tokens(tile));
 }
 
-// Whether a launch is faster with 128 x 128 tiles (any result is the same up to the order of the loss sums:
-// an output's own products are added in the same order).  Two small blocks share a CU: up to 512 of them
+// Of the square tiles, whether the small one is faster.  Two small blocks share a CU: up to 512 of them
 // are one round, where big tiles leave CUs idle (store epilogue, us big -> small: 640 x 4096 x 4096
 // tokens x channels x outputs 93 -> 49, 1200 x 5120 x 5120 122 -> 82, 1800 x 4096 x 4096 100 -> 71; from 640
 // small tiles on the big ones win, 98 against 113).  Just past one round of big tiles the second
 // round is nearly empty and the small ones win again (1200 x 5120 x 13824, 270 big tiles: 243 -> 213; 320: 201
 // -> 188; 384: 206 -> 211).
-bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand) {
+static bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand) {
   const int64_t big = ceil_div(c_out, kBO) * ceil_div(n_tok, kBT) * n_cand;
   const int64_t small = ceil_div(c_out, kSmall) * ceil_div(n_tok, kSmall) * n_cand;
   return small <= 512 || (big > 256 && small <= 1280);
+}
+
+// The tile that takes the least time (any result is the same up to the order of the loss sums: an output's own
+// products are added in the same order).  A launch of up to eight rounds takes whole rounds of one block per
+// CU (small tiles: two), longer ones drift apart and pay for their tiles.  The cost of a round, in rounds of 256 x 256,
+// from store launches of one round with 4096 channels (us): 128 x 128 59, 192 tokens 79, 256 97, 320 114.  The wide tile reads
+// fewer fragments and fetches fewer panels per product, so it is ahead of the square one also where the count of rounds
+// does not decide.  us by tile (128, 192, 256, 320), tokens x channels x outputs [x candidates]:
+//   store   1200 x 5120 x 13824 207 185 214 140      search  10,240 x 4096 x 4096 x 20  6241 5797 5213 5031
+//   store   2500 x 4096 x 4096   99  74  88 101      search  40,000 x 5120 x 5120 x 20   41.1  37.9  33.1  30.7 ms
+//   store   3678 x 4096 x 4096  111 137  96 110      search     640 x 4096 x 4096 x 20   690  632  594  550
+//   store   4800 x 4096 x 4096  151 146 171 114      search  W4A8 3678 x 4096 x 4096    1499 1370 1277 1218
+//   store  10,240 x 11008 x 4096 833 959 805 642     search    1839 x 1152 x 1400 x 12   129  125  133  128
+//   store  40,960 x 4096 x 11008  3.28 2.94 2.77 2.61 ms   quadratic form 5120 x 5120 - - 2824 2654; 4096 x 1024 - - 448 523
+GemmTile gemm_tile(int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles) {
+  GemmTile best{false, 4};
+  double best_cost = 1e300;
+  auto consider = [&](GemmTile t, double slots, double first, double each) {
+    int64_t to, tt;
+    gemm_tile_counts(n_tok, c_out, t, &to, &tt);
+    if (to * tt > max_tiles) return;
+    const double rounds = (double)(to * tt) * n_cand / slots;
+    const double cost = first + each * (rounds <= 8.0 ? std::ceil(rounds) : rounds + 0.5);
+    if (cost < best_cost) { best = t; best_cost = cost; }
+  };
+  if ((kinds & kTileSmall) && gemm_small_tiles(n_tok, c_out, n_cand)) consider(GemmTile{true, 0}, 512, 0.12, 0.5);
+  if (best_cost == 1e300) consider(GemmTile{false, 4}, 256, 0.0, 1.0);
+  if (kinds & kTileNarrow) consider(GemmTile{false, 3}, 256, 0.0, 0.8);
+  if (kinds & kTileWide) consider(GemmTile{false, 5}, 256, 0.0, 1.19);
+  return best;
 }
 
 static GemmDev make_dev(const GemmArgs& g) {
@@ -1057,7 +1109,7 @@ static GemmDev make_dev(const GemmArgs& g) {
   d.Yout = g.Yout; d.ldo = g.ldo; d.odt = g.yout_dtype;
   d.row_scale = g.row_scale; d.row_scale_stride = g.row_scale_stride;
   int64_t to, tt;
-  gemm_tile_counts(g.n_tok, g.c_out, g.small, &to, &tt);
+  gemm_tile_counts(g.n_tok, g.c_out, g, &to, &tt);
   d.tiles_o = (int)to; d.tiles_t = (int)tt;
   d.po = g.wide_patch ? 8 : 4; d.pt = PATCH_SLOTS / d.po;
   // few token tiles: one patch across all of them (5 tiles in patches of 4 would alternate full and nearly
@@ -1073,7 +1125,7 @@ static GemmDev make_dev(const GemmArgs& g) {
   // on the same token patch from one candidate to the next, which measured steadier (and on most
   // boxes faster) on 153,600-token inputs than 3, 5 or 6 patches, whose speed flips between
   // launches by up to 8 %.
-  const int64_t patch_bytes = (int64_t)PATCH_T * (g.small ? kSmall : kBT) * g.c_in * 2;
+  const int64_t patch_bytes = (int64_t)PATCH_T * tile_tokens(g) * g.c_in * 2;
   if ((int64_t)d.npt * patch_bytes <= kChunkBytes) {
     d.cpt = d.npt;
   } else {
@@ -1082,7 +1134,7 @@ static GemmDev make_dev(const GemmArgs& g) {
   }
   const int64_t tiles = to * tt * g.n_cand;
   // (tiles of a symmetric contraction differ in work along the rows: strips would not be equal)
-  d.strips = tiles <= kStripTiles && !g.tri && !g.sym_k ? tiles : 0;
+  d.strips = (g.small ? tiles : tiles * tile_tokens(g) / kBT) <= kStripTiles && !g.tri && !g.sym_k ? tiles : 0;
   if (g.tri) {
     d.n_patches = ceil_div(ceil_div(to * (to + 1) / 2, kXcd) * g.n_cand, PATCH_SLOTS) * kXcd;
   } else if (d.strips) {
@@ -1116,12 +1168,25 @@ static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ld
 // in the single-candidate call, which keeps the big tiles (as does its per-token variant); the quadratic
 // form is fp16, big and symmetric.
 template <typename T, int EPI>
-static hipError_t launch_dma(const GemmDev& d, bool small, unsigned blocks, hipStream_t stream) {
+static hipError_t launch_dma(const GemmDev& d, GemmTile tile, unsigned blocks, hipStream_t stream) {
   constexpr bool SYMK = EPI == EPI_DOT;
   constexpr bool SMALL = EPI == EPI_STORE || (EPI == EPI_LOSS && std::is_same<T, F16>::value);
   const bool tail = (d.c_in % kDmaBK) != 0;
-  if (!small) {
-    if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 2><<<blocks, 512, 0, stream>>>(d);
+  if (!tile.small) {
+    auto run = [&](auto jb) {
+      constexpr int JB = decltype(jb)::value;
+      if (!tail) gemm_width_kernel<T, EPI, SYMK, false, JB><<<blocks, 512, 0, stream>>>(d);
+      else gemm_width_kernel<T, EPI, SYMK, true, JB><<<blocks, 512, 0, stream>>>(d);
+    };
+    constexpr bool F = std::is_same<T, F16>::value, NARROW = EPI == EPI_STORE || (EPI == EPI_LOSS && F);
+    constexpr bool WIDE = EPI == EPI_STORE || F;
+    if (tile.tok_blocks == 3) {
+      if constexpr (!NARROW) return hipErrorInvalidValue;
+      else run(std::integral_constant<int, 3>{});
+    } else if (tile.tok_blocks == 5) {
+      if constexpr (!WIDE) return hipErrorInvalidValue;
+      else run(std::integral_constant<int, 5>{});
+    } else if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 2><<<blocks, 512, 0, stream>>>(d);
     else gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
     return hipGetLastError();
   }
@@ -1138,10 +1203,12 @@ static hipError_t launch_dma(const GemmDev& d, bool small, unsigned blocks, hipS
 }
 
 template <int EPI>
-static hipError_t launch_i8(const GemmDev& d, bool small, unsigned blocks, hipStream_t stream) {
-  if (!small) gemm_i8_kernel<2, EPI, 2><<<blocks, 512, 0, stream>>>(d);
-  else if ((int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256) gemm_i8_kernel<4, EPI, 1><<<blocks, 256, 0, stream>>>(d);
-  else gemm_i8_kernel<2, EPI, 1><<<blocks, 256, 0, stream>>>(d);
+static hipError_t launch_i8(const GemmDev& d, GemmTile tile, unsigned blocks, hipStream_t stream) {
+  if (!tile.small && tile.tok_blocks == 3) gemm_i8_kernel<2, EPI, 2, 3><<<blocks, 512, 0, stream>>>(d);
+  else if (!tile.small && tile.tok_blocks == 5) gemm_i8_kernel<2, EPI, 2, 5><<<blocks, 512, 0, stream>>>(d);
+  else if (!tile.small) gemm_i8_kernel<2, EPI, 2, 4><<<blocks, 512, 0, stream>>>(d);
+  else if ((int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256) gemm_i8_kernel<4, EPI, 1, 4><<<blocks, 256, 0, stream>>>(d);
+  else gemm_i8_kernel<2, EPI, 1, 4><<<blocks, 256, 0, stream>>>(d);
   return hipGetLastError();
 }
 
@@ -1150,7 +1217,7 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   const bool dma = pipelined_ok(g);
   constexpr bool kHasInt = std::is_same<T, F16>::value && (EPI == EPI_LOSS || EPI == EPI_STORE);
   if (g.i8_k && (!kHasInt || !dma || !g.row_scale || (g.c_in % kDmaBK) != 0)) return hipErrorInvalidValue;
-  if (!dma && g.small) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
+  if (!dma && (g.small || (g.tok_blocks && g.tok_blocks != 4))) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
   const GemmDev d = make_dev(g);
   const int64_t rounds = ceil_div(d.n_patches, kXcd);
   const int64_t blocks = rounds * kXcd * PATCH_SLOTS;
@@ -1161,9 +1228,9 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   const double k = (double)(g.i8_k ? g.i8_k : g.c_in);
   ProfScope ps(name, stream, 2.0 * (double)g.n_tok * k * (double)g.c_out * g.n_cand * tile_frac);
   if constexpr (kHasInt) {
-    if (g.i8_k) return launch_i8<EPI>(d, g.small, (unsigned)blocks, stream);
+    if (g.i8_k) return launch_i8<EPI>(d, g, (unsigned)blocks, stream);
   }
-  if (dma) return launch_dma<T, EPI>(d, g.small, (unsigned)blocks, stream);
+  if (dma) return launch_dma<T, EPI>(d, g, (unsigned)blocks, stream);
   if constexpr (EPI != EPI_DOT) {
     constexpr int NT = (kBO / kWO) * (kBT / kWT) * 64;
     gemm_kernel<T, kBO, kBT, kWO, kWT, EPI><<<(unsigned)blocks, NT, 0, stream>>>(d);
@@ -1173,26 +1240,28 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
 }
 
 // Host-side check of the block -> tile map for one problem shape: both block orders (candidates inside every
-// patch row, and candidate-outermost, which may turn the XCDs), both patch shapes and both tile sizes, the
+// patch row, and candidate-outermost, which may turn the XCDs), both patch shapes and all tile sizes, the
 // quadratic form's map, and those of the symmetric products over c_out and c_in.  Each walk takes every block
 // id of its launch and counts how often each (candidate, tile) is produced; a walk whose tiles are not
 // of the size it is there for counts as a defect too.  Returns the number of tiles that are not produced
 // exactly once (0 = all maps are bijections onto the tiles), or -1 for an invalid shape.
-// *blocks_out receives the grid size of a launch with the tile size that gemm_small_tiles picks.
+// *blocks_out receives the grid size of a launch with the square tile that gemm_small_tiles picks.
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out) {
   if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
   const bool small_launch = gemm_small_tiles(n_tok, c_out, n_cand);
   if (blocks_out) *blocks_out = 0;
   int64_t bad = 0;
-  // walks 0 - 7: bit 0 the order, bit 1 the patch shape, bit 2 the tile size
-  enum { kQuadratic = 8, kTriOut, kTriIn, kWalks };
+  // walks 0 - 15: bit 0 the order, bit 1 the patch shape, bits 2 and 3 the tile
+  const GemmTile tiles_of[4] = {{false, 0}, {true, 0}, {false, 3}, {false, 5}};
+  const int side_of[4] = {256, 128, 192, 320};
+  enum { kQuadratic = 16, kTriOut, kTriIn, kWalks };
   for (int walk = 0; walk < kWalks; ++walk) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
     if (walk < kQuadratic) {
       g.cand_outer = (walk & 1) != 0;
       g.wide_patch = (walk & 2) != 0;
-      g.small = (walk & 4) != 0;
+      g.tile() = tiles_of[walk >> 2];
     } else if (walk == kQuadratic) {
       g.cand_outer = g.wide_patch = g.sym_k = true;
     } else {
@@ -1200,10 +1269,10 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand,
       g.n_tok = g.c_out = walk == kTriOut ? c_out : c_in;
     }
     const GemmDev d = make_dev(g);
-    const int64_t side = walk >= 4 && walk < kQuadratic ? 128 : 256;
-    if (d.tiles_o != (g.c_out + side - 1) / side || d.tiles_t != (g.n_tok + side - 1) / side) ++bad;
+    const int64_t side_t = walk < kQuadratic ? side_of[walk >> 2] : 256, side_o = g.small ? 128 : 256;
+    if (d.tiles_o != (g.c_out + side_o - 1) / side_o || d.tiles_t != (g.n_tok + side_t - 1) / side_t) ++bad;
     const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
-    if (blocks_out && walk < kQuadratic && !g.cand_outer && !g.wide_patch && g.small == small_launch)
+    if (blocks_out && walk < kQuadratic && !g.cand_outer && !g.wide_patch && g.small == small_launch && !g.tok_blocks)
       *blocks_out = blocks;
     const int64_t tiles = (int64_t)n_cand * d.tiles_o * d.tiles_t;
     unsigned char* seen = (unsigned char*)calloc((size_t)tiles, 1);

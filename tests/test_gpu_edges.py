@@ -609,3 +609,57 @@ def test_token_matrix_of_more_than_two_million_tokens(gpu):
     # tokens times sqrt(w) and the matrix itself are rounded to fp16 once each (three roundings in a product);
     # an accumulator takes 131,136 / 16 float additions of a split: 8196 * 2^-24 = 2^-11
     assert (((G - want).abs() / (scale[:, None] * scale[None, :])).max().item()) <= 4 * 2.0 ** -11
+
+
+# (tokens, channels, outputs, candidates): launches of tiles of 192 and of 320 tokens, with remainders on both sides, a
+# k tail, one candidate and several
+@pytest.mark.parametrize("n,ci,co,na,act,bf16", [
+    (760, 136, 770, 16, 0, False), (1270, 136, 776, 16, 0, True), (760, 264, 776, 16, 8, True), (1270, 264, 776, 16, 6, False),
+    (2560, 64, 1792, 6, 0, False), (1280, 192, 1024, 16, 8, False)])
+def test_losses_of_narrow_and_wide_tiles(gpu, n, ci, co, na, act, bf16):
+    import torch
+    g = np.random.default_rng([41, n, ci, co])
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    code = tlq.BF16 if bf16 else tlq.F16
+    p = tlq.params(bits=4, group=0 if act else 8, symmetric=1, act_bits=act, x_dtype=code, yref_dtype=code)
+    Y = torch.zeros((n, co + -co % 8), dtype=torch.bfloat16 if bf16 else torch.float16, device=gpu)[:, :co]
+    tlq.ref_output(dev(X, gpu, bf16), dev(W, gpu, bf16), Y, p)
+    w = g.uniform(0.1, 1.0, n).astype(np.float32) / n
+    al = np.array([k / na for k in range(na)], np.float32)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses, table = torch.empty(na, dtype=torch.float32, device=gpu), torch.empty((na, ci), dtype=torch.float32, device=gpu)
+    t = lambda a: torch.from_numpy(a).to(gpu)
+    tlq.scale_search(dev(X, gpu, bf16), dev(W, gpu, bf16), Y, t(w), t(al), p, best, idx, losses, s_table_out=table)
+    ref = orc.scale_search(X, W, Y.double().cpu().numpy(), w, 4, 0 if act else 8, al, s_table=table.cpu().numpy(),
+                           symmetric=True, act_bits=act)
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
+
+
+@pytest.mark.parametrize("n,co,bf16", [(2500, 4104, True), (2496, 4096, False), (4700, 4104, False), (4800, 4096, True)])
+def test_stores_and_token_errors_of_narrow_and_wide_tiles(gpu, n, co, bf16):
+    import torch
+    g = np.random.default_rng([42, n, co])
+    ci = 72
+    rnd = BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
+    code, dt = (tlq.BF16, torch.bfloat16) if bf16 else (tlq.F16, torch.float16)
+    tX, tW = dev(X, gpu, bf16), dev(W, gpu, bf16)
+    want = tX.double() @ tW.double().t()
+    mag = tX.double().abs() @ tW.double().abs().t()
+    for ydt, ycode, eps in ((torch.float32, tlq.F32, 0.0), (dt, code, 2.0 ** -8 if bf16 else 2.0 ** -11)):
+        Y = torch.full((n, co + 8), 7.0, dtype=ydt, device=gpu)
+        tlq.ref_output(tX, tW, Y[:, :co], tlq.params(x_dtype=code, yref_dtype=ycode))
+        assert bool((Y[:, co:] == 7.0).all())
+        # ci roundings of at most 2^-24 of the magnitude, then one to the type of the output (subnormal steps of fp16)
+        bound = (ci + 2) * 2.0 ** -24 * mag + eps * want.abs() + 2.0 ** -25
+        assert bool(((Y[:, :co].double() - want).abs() <= bound).all())
+    target = (want + torch.randn(want.shape, generator=torch.Generator(device=gpu).manual_seed(1), device=gpu)).to(dt)
+    s = np.exp2(g.integers(-2, 3, ci)).astype(np.float32)          # powers of two: folding them in is exact
+    w = torch.from_numpy(g.uniform(0.1, 1.0, n).astype(np.float32) / n).to(gpu)
+    loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+    tlq.weighted_layer_err(tX, tW, torch.from_numpy(s).to(gpu), target, w, tlq.params(x_dtype=code, yref_dtype=code), loss,
+                           per_token_err=err)
+    e = ((target.double() - (tX.double() * torch.from_numpy(s).to(gpu).double()) @ tW.double().t()) ** 2).mean(1)
+    np.testing.assert_allclose(err.cpu().numpy(), e.cpu().numpy(), rtol=2e-5)      # float sums of positive terms
+    np.testing.assert_allclose(float(loss.item()), float((e * w.double()).sum()), rtol=2e-5)
