@@ -200,46 +200,63 @@ __device__ __forceinline__ void static_for(Fn&& f) {
 
 // Per-lane part of the loss of one wave tile whose first output row is `ow` and first
 // token is `tw`: sq[tb] = sum over this lane's rows of (Y_ref - acc)^2 for its token of
-// token block tb; part = sum_tb token_w * sq[tb].  YDT >= 0 fixes the Y_ref type at
-// compile time; FULL promises that the whole wave tile lies inside the matrix.
+// token block tb; part = sum_tb token_w * sq[tb].  YDT is the type of Y_ref, k16Bit either 16-bit type; FULL promises that
+// the whole wave tile lies inside the matrix.  Otherwise loads past it go to a valid place and their terms are dropped:
+// a branch around each would put their latencies one after the other, and the tiles at the edges are the last ones of a
+// launch that fits the chip in a few rounds.
 // DOT replaces the squared residual by the product acc * y and drops the token weight.
+constexpr int k16Bit = -1;
 template <int YDT, bool FULL, bool DOT, typename L, typename Acc>
 __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
                                           int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part) {
   const int lane = threadIdx.x & 63;
-  const int ydt = YDT >= 0 ? YDT : a.ydt;
+  const bool quads = FULL || a.c_out >= 4, ragged = !FULL && (!quads || (a.c_out & 3) != 0);
 #pragma unroll
   for (int tb = 0; tb < L::NTB; ++tb) {
-    const int64_t t = tw + L::tok(tb, lane);
+    const int64_t tl = tw + L::tok(tb, lane);
+    const bool t_ok = FULL || tl < a.n_tok;
+    const int64_t t = t_ok ? tl : a.n_tok - 1;
     float sumsq = 0.0f;
-    if (FULL || t < a.n_tok) {
-      // residual = y - sg * acc as one fused multiply-add; sg = 1 gives y - acc exactly
-      const float nsg = tsc ? -tsc[t] : -1.0f;
+    // residual = y - sg * acc as one fused multiply-add; sg = 1 gives y - acc exactly
+    const float nsg = tsc ? -tsc[t] : -1.0f;
+    auto term = [&](int q, int r, float y) {
+      if (DOT) { sumsq += L::get(acc, q, tb, r) * y; return; }
+      const float d = __builtin_fmaf(nsg, L::get(acc, q, tb, r), y);
+      sumsq += d * d;
+    };
+    if (quads) {
 #pragma unroll
       for (int q = 0; q < L::NQ; ++q) {
         const int64_t o = ow + L::row(q, lane);
-        if (FULL || o + 3 < a.c_out) {
-          float y[4];
-          load_y4(Yref, ydt, t * a.ldy + o, y);
+        const bool whole = FULL || o + 3 < a.c_out;
+        float y[4];
+        if constexpr (YDT == k16Bit) {
+          const uint2 u = *reinterpret_cast<const uint2*>((const uint16_t*)Yref + t * a.ldy + (whole ? o : 0));
+          const uint16_t h[4] = {(uint16_t)u.x, (uint16_t)(u.x >> 16), (uint16_t)u.y, (uint16_t)(u.y >> 16)};
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (DOT) { sumsq += L::get(acc, q, tb, r) * y[r]; continue; }
-            const float d = __builtin_fmaf(nsg, L::get(acc, q, tb, r), y[r]);
-            sumsq += d * d;
-          }
+          for (int r = 0; r < 4; ++r) y[r] = a.ydt == TLQ_F16 ? F16::to_float(h[r]) : BF16::to_float(h[r]);
         } else {
+          load_y4(Yref, YDT, t * a.ldy + (whole ? o : 0), y);
+        }
+        const float before = sumsq;
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (o + r < a.c_out) {
-              const float y = load_y(Yref, ydt, t * a.ldy + o + r);
-              if (DOT) { sumsq += L::get(acc, q, tb, r) * y; continue; }
-              const float d = __builtin_fmaf(nsg, L::get(acc, q, tb, r), y);
-              sumsq += d * d;
-            }
+        for (int r = 0; r < 4; ++r) term(q, r, y[r]);
+        if (!whole) sumsq = before;
+      }
+    }
+    if (ragged) {   // the last rows of a matrix whose height is no multiple of four
+#pragma unroll
+      for (int q = 0; q < L::NQ; ++q) {
+        const int64_t o = ow + L::row(q, lane);
+        if (o < a.c_out && o + 3 >= a.c_out) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            if (o + r < a.c_out) term(q, r, load_y(Yref, a.ydt, t * a.ldy + o + r));
         }
       }
-      part += DOT ? sumsq : a.token_w[t] * sumsq;
     }
+    if (!t_ok) sumsq = 0.0f;
+    part += DOT ? sumsq : t_ok ? a.token_w[t] * sumsq : 0.0f;
     sq[tb] = sumsq;
   }
 }
@@ -477,11 +494,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
     }
   }
   if (done) {}
-  else if (L::NTB > 4) loss_rows<-1, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);   // (few registers, little code)
-  else if (interior && a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-  else if (interior && a.ydt == TLQ_F32) loss_rows<TLQ_F32, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-  else if (interior) loss_rows<TLQ_BF16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-  else loss_rows<-1, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
+  else if (a.ydt == TLQ_F32) {
+    if (L::NTB <= 4 && interior) loss_rows<TLQ_F32, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
+    else loss_rows<TLQ_F32, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
+  } else if (L::NTB > 4 || !interior) loss_rows<k16Bit, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);   // (few registers there)
+  else if (a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
+  else loss_rows<TLQ_BF16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
   if (EPI == EPI_LOSS_TOK) {
 #pragma unroll
     for (int tb = 0; tb < L::NTB; ++tb) {
