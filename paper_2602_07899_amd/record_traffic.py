@@ -39,7 +39,7 @@ def _read(dirname, counter):
 
 
 # the fused contraction + weighted-loss instantiation (epilogue 0) of the pipelined kernel
-_LOSS_KERNEL = re.compile(r"gemm_dma_kernel<tlq::\w+, \d+, 0[,>]")
+_LOSS_KERNEL = re.compile(r"gemm_(dma_kernel<tlq::\w+, \d+|width_kernel<tlq::\w+), 0[,>]")
 
 
 def main(prof_dir):
