@@ -328,11 +328,13 @@ tlq_status tlq_residual_add(const void* H, int64_t ldh, const void* Z, int64_t l
 
 /* ---- host-side self check (no GPU work, no device memory): walks the block -> tile map that
  * the contraction kernels (S3/S4, f_fp, S6) would use for this problem shape, in both of its
- * orders (candidates inside every patch row / candidate-outermost), both patch shapes and both tile
- * sizes (256 x 256 and 128 x 128 outputs), the quadratic form's and the symmetric products' maps, and
- * returns how many (candidate, output tile) pairs are NOT produced exactly once - 0 for correct maps,
- * -1 for an invalid shape.  *blocks (may be NULL) receives the number of workgroups of a launch with
- * the tile size that the library picks for the shape. */
+ * orders (candidates inside every patch row / candidate-outermost), both patch shapes and all tile
+ * sizes (128 x 128 outputs, and 256 outputs x 192, 256 or 320 tokens), the quadratic form's and the
+ * symmetric products' maps, and returns how many (candidate, output tile) pairs are NOT produced exactly
+ * once - 0 for correct maps, -1 for an invalid shape.  *blocks (may be NULL) receives the number of
+ * workgroups of the launch that the library makes for the shape, with the tile size that it picks: with one
+ * candidate the product of tlq_ref_output and tlq_apply_best, with several the contraction of a search in
+ * 4 bits without activation codes. */
 int64_t tlq_selftest_tile_map(int64_t n_tok, int64_t c_in, int64_t c_out, int32_t n_cand,
                               int64_t* blocks);
 

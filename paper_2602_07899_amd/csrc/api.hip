@@ -93,8 +93,19 @@ struct SearchPlan {
   int64_t tiles_o, tiles_t; GemmTile tile;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
 };
-// Smaller tiles write up to four times the loss partials.  The workspace stays what it is with 256 x 256: where there
-// are more of them they take the place of the channel sums, which are done with by then, if they fit.
+// Tile of a search's contraction, n_launch candidates a launch.  Smaller tiles write up to four times the loss partials.
+// The workspace stays what it is with 256 x 256: where there are more of them they take the place of the channel
+// sums, which are done with by then, if they fit.
+GemmTile search_tile(int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, int n_launch, bool diff) {
+  int64_t to, tt;
+  gemm_tile_counts(n_tok, c_out, GemmTile{}, &to, &tt);
+  const int64_t room = (int64_t)((size_t)xstat_chunks(n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
+  // (the differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us)
+  return gemm_tile(n_tok, c_out, n_launch, diff ? kTileSmall | kTileNarrow : kTileAll, room > to * tt ? room : to * tt);
+}
+// Patch shape of a search's contraction, by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose
+// 0.5 - 3 % on the narrowing, deep ones (down_proj)
+bool search_wide_patch(int64_t c_in, int64_t c_out) { return c_in <= 2 * c_out; }
 SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, bool bf16,
                        bool act, bool diff, bool strides_ok = false) {
   SearchPlan s;
@@ -115,10 +126,8 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   s.d0 = diff ? c.take<float>((size_t)n_tok * s.ldd) : nullptr;
   s.bytes = c.off;
   if (!strides_ok) return s;
-  const int64_t room = (int64_t)((size_t)xstat_chunks(n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
   const int64_t big = s.tiles_o * s.tiles_t;
-  // (the differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us)
-  s.tile = gemm_tile(n_tok, c_out, act ? s.nb : n_alpha, diff ? kTileSmall | kTileNarrow : kTileAll, room > big ? room : big);
+  s.tile = search_tile(n_tok, c_in, c_out, n_alpha, act ? s.nb : n_alpha, diff);
   gemm_tile_counts(n_tok, c_out, s.tile, &s.tiles_o, &s.tiles_t);
   if (s.tiles_o * s.tiles_t > big) s.partial = (float*)s.xs_partial;
   return s;
@@ -255,7 +264,18 @@ int tlq_version(void) { return TLQ_VERSION; }
 
 // host-side self check of the contraction kernels' block -> tile map (no GPU work)
 int64_t tlq_selftest_tile_map(int64_t n_tok, int64_t c_in, int64_t c_out, int32_t n_cand, int64_t* blocks) {
-  return tile_map_defects(n_tok, c_in, c_out, n_cand, blocks);
+  if (blocks) *blocks = 0;
+  if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
+  // the launch that *blocks is about: the product of tlq_ref_output and tlq_apply_best, or a 4-bit weight-only search's
+  GemmArgs g{};
+  g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
+  tlq_params p{};
+  p.bits = 4;
+  g.tile() = n_cand == 1 ? gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX)
+                         : search_tile(n_tok, c_in, c_out, n_cand, n_cand, use_diff_form(&p, n_tok, c_out));
+  g.wide_patch = n_cand == 1 || search_wide_patch(c_in, c_out);
+  if (blocks) *blocks = gemm_blocks(g);
+  return tile_map_defects(n_tok, c_in, c_out, n_cand);
 }
 
 // ------------------------------------------------------------------------ S0
@@ -502,9 +522,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   if (diff) { g.Yref = s.d0; g.ldy = s.ldd; g.yref_dtype = TLQ_F32; }
   g.partial = s.partial; g.tok_partial = nullptr; g.tile() = s.tile;
   if (!act) {
-    // patch shape by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose
-    // 0.5 - 3 % on the narrowing, deep ones (down_proj)
-    g.wide_patch = c_in <= 2 * c_out;
+    g.wide_patch = search_wide_patch(c_in, c_out);
     TLQ_HIP(launch_gemm_loss(g, st));
   } else {
     // Q_a(x / s_k) differs per candidate: quantise the tokens for a batch of candidates,

@@ -193,7 +193,8 @@ enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7 };
 GemmTile gemm_tile(int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles);
 // row strides that the pipelined kernel (and with it any tile but 256 x 256) takes
 bool gemm_strides_ok(int64_t ldx, int64_t ldw);
-int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out);
+int64_t gemm_blocks(const GemmArgs& g);   // workgroups of the launch (sizes, tile and order are read, no pointer)
+int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand);
 hipError_t launch_gemm_loss(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_store(const GemmArgs& a, hipStream_t stream);
 // partial[k, tile] = sum over the tile of (X_k Wh^T)[t,o] * Y_k[t,o]  (no token weights), fp16, for a symmetric

@@ -1177,6 +1177,9 @@ static GemmDev make_dev(const GemmArgs& g) {
   return d;
 }
 
+static int64_t dev_blocks(const GemmDev& d) { return ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS; }
+int64_t gemm_blocks(const GemmArgs& g) { return dev_blocks(make_dev(g)); }
+
 // the pipelined kernel needs 32-bit byte offsets inside a 256-row panel
 bool gemm_strides_ok(int64_t ldx, int64_t ldw) { return ldw < (1 << 21) && ldx < (1 << 21); }
 static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ldw); }
@@ -1237,8 +1240,7 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   if (g.i8_k && (!kHasInt || !dma || !g.row_scale || (g.c_in % kDmaBK) != 0)) return hipErrorInvalidValue;
   if (!dma && (g.small || (g.tok_blocks && g.tok_blocks != 4))) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
   const GemmDev d = make_dev(g);
-  const int64_t rounds = ceil_div(d.n_patches, kXcd);
-  const int64_t blocks = rounds * kXcd * PATCH_SLOTS;
+  const int64_t blocks = dev_blocks(d);
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   // (a symmetric product computes the tiles on and above the diagonal, a symmetric contraction
   // the k range from the diagonal block on: about half either way)
@@ -1262,12 +1264,8 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
 // quadratic form's map, and those of the symmetric products over c_out and c_in.  Each walk takes every block
 // id of its launch and counts how often each (candidate, tile) is produced; a walk whose tiles are not
 // of the size it is there for counts as a defect too.  Returns the number of tiles that are not produced
-// exactly once (0 = all maps are bijections onto the tiles), or -1 for an invalid shape.
-// *blocks_out receives the grid size of a launch with the square tile that gemm_small_tiles picks.
-int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int64_t* blocks_out) {
-  if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || n_cand <= 0) return -1;
-  const bool small_launch = gemm_small_tiles(n_tok, c_out, n_cand);
-  if (blocks_out) *blocks_out = 0;
+// exactly once (0 = all maps are bijections onto the tiles), or -1 if memory runs out.
+int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand) {
   int64_t bad = 0;
   // walks 0 - 15: bit 0 the order, bit 1 the patch shape, bits 2 and 3 the tile
   const GemmTile tiles_of[4] = {{false, 0}, {true, 0}, {false, 3}, {false, 5}};
@@ -1289,9 +1287,7 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand,
     const GemmDev d = make_dev(g);
     const int64_t side_t = walk < kQuadratic ? side_of[walk >> 2] : 256, side_o = g.small ? 128 : 256;
     if (d.tiles_o != (g.c_out + side_o - 1) / side_o || d.tiles_t != (g.n_tok + side_t - 1) / side_t) ++bad;
-    const int64_t blocks = ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS;
-    if (blocks_out && walk < kQuadratic && !g.cand_outer && !g.wide_patch && g.small == small_launch && !g.tok_blocks)
-      *blocks_out = blocks;
+    const int64_t blocks = dev_blocks(d);
     const int64_t tiles = (int64_t)n_cand * d.tiles_o * d.tiles_t;
     unsigned char* seen = (unsigned char*)calloc((size_t)tiles, 1);
     if (!seen) return -1;

@@ -210,6 +210,23 @@ int main() {
   h = g; h.sym_k = true; h.bf16 = true;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
   h = g; h.sym_k = true; h.c_out = 256;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
 
+  // ---- the tile of a launch: tokens of a tile, 128 for the small one
+  auto tile = [](int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles) {
+    const tlq::GemmTile t = tlq::gemm_tile(n_tok, c_out, n_cand, kinds, max_tiles);
+    return t.small ? 128 : t.tok_blocks * 64;
+  };
+  EXPECT(tile(2048, 4096, 1, tlq::kTileAll, INT64_MAX), 128);    // 512 small tiles, and one row of them more
+  EXPECT(tile(2048, 4097, 1, tlq::kTileAll, INT64_MAX), 192);
+  EXPECT(tile(3072, 4096, 1, tlq::kTileAll, INT64_MAX), 192);    // one round of 256 blocks, and one token more
+  EXPECT(tile(3073, 4096, 1, tlq::kTileAll, INT64_MAX), 256);
+  EXPECT(tile(5120, 4096, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(1200, 13824, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(1200, 13824, 1, 0, INT64_MAX), 256);               // kinds that the launch does not have
+  EXPECT(tile(1200, 13824, 1, tlq::kTileNarrow, INT64_MAX), 192);
+  EXPECT(tile(256, 512, 20, tlq::kTileAll, 8), 128);             // 2 x 4 small tiles, room for them and for one less
+  EXPECT(tile(256, 512, 20, tlq::kTileAll, 7), 192);
+  EXPECT(tile(256, 512, 20, tlq::kTileAll, 3), 256);             // 2 x 2 narrow ones do not fit either
+
   // ---- host-side self test of the block -> tile map, and the timing bookkeeping
   int64_t blocks = 0;
   EXPECT(tlq_selftest_tile_map(10240, 4096, 11008, 20, &blocks), 0);
