@@ -134,9 +134,10 @@ def _ptr(t):
 
 
 def _stream():
-    """Handle of torch's current stream on the current device."""
+    """Handle of torch's current stream on the current device.  current_device() initialises torch's GPU state, or
+    raises: also in a forked child of a process that has used the GPU, where nothing may be launched."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ws(nbytes, like):

@@ -191,6 +191,17 @@ def test_self_check_reports_the_launch_of_the_library(shape):
         assert blocks % 256 == 0 and tiles <= blocks < 2 * tiles
 
 
+def test_no_launch_in_a_forked_child(monkeypatch):
+    """A forked child has its parent's GPU tensors but no usable GPU state: torch refuses there, before the library is
+    called with a stream."""
+    import torch
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    with pytest.raises(RuntimeError, match="fork"):
+        tlq._stream()
+
+
 def test_only_reachable_contraction_kernels_are_compiled():
     """The library holds the contraction kernels that some call launches and no others (every one lengthens
     the loading of the library): operand type, LDS stages, epilogue (loss, loss with per-token
