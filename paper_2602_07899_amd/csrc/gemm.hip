@@ -203,10 +203,13 @@ __device__ __forceinline__ void static_for(Fn&& f) {
 // token block tb; part = sum_tb token_w * sq[tb].  YDT is the type of Y_ref, k16Bit either 16-bit type; FULL promises that
 // the whole wave tile lies inside the matrix.  Otherwise loads past it go to a valid place and their terms are dropped:
 // a branch around each would put their latencies one after the other, and the tiles at the edges are the last ones of a
-// launch that fits the chip in a few rounds.
+// launch that fits the chip in a few rounds.  NQ: the quads that hold live rows, straight code for half of them where the
+// other half lies past the edge (and none for a wave that does as a whole): with 64 outputs in tiles of 256 the reads
+// for nothing cost more than the product (100,000 x 64 x 64, us with a branch around each read, all reads, live halves:
+// loss 24.7, 28.9, 19.0; 20 candidates 427, 458, 324; with 136 outputs the loss 36.0, 24.3, 24.1).
 // DOT replaces the squared residual by the product acc * y and drops the token weight.
 constexpr int k16Bit = -1;
-template <int YDT, bool FULL, bool DOT, typename L, typename Acc>
+template <int YDT, bool FULL, bool DOT, typename L, int NQ, typename Acc>
 __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
                                           int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part) {
   const int lane = threadIdx.x & 63;
@@ -226,7 +229,7 @@ __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, co
     };
     if (quads) {
 #pragma unroll
-      for (int q = 0; q < L::NQ; ++q) {
+      for (int q = 0; q < NQ; ++q) {
         const int64_t o = ow + L::row(q, lane);
         const bool whole = FULL || o + 3 < a.c_out;
         float y[4];
@@ -246,7 +249,7 @@ __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, co
     }
     if (ragged) {   // the last rows of a matrix whose height is no multiple of four
 #pragma unroll
-      for (int q = 0; q < L::NQ; ++q) {
+      for (int q = 0; q < NQ; ++q) {
         const int64_t o = ow + L::row(q, lane);
         if (o < a.c_out && o + 3 >= a.c_out) {
 #pragma unroll
@@ -478,7 +481,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
   // Interior tiles (the common case) take a branch-free body specialised on the Y_ref
   // type; edge tiles and odd strides take the guarded one.
   float part = 0.0f;
-  float sq[L::NTB];
+  float sq[L::NTB] = {};
   const bool interior = (o0 + NWO * WO <= a.c_out) && (t0 + BT <= a.n_tok);
   const int64_t ow = o0 + wo * WO, tw = t0 + wt * WT;
   constexpr bool DOT = EPI == EPI_DOT;
@@ -493,13 +496,16 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
       done = true;
     }
   }
-  if (done) {}
+  const bool half = L::WO == 128 && !DOT && ow + WO / 2 >= a.c_out;   // (the other tiles are small)
+  if (done || ow >= a.c_out || tw >= a.n_tok) {}
   else if (a.ydt == TLQ_F32) {
-    if (L::NTB <= 4 && interior) loss_rows<TLQ_F32, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-    else loss_rows<TLQ_F32, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-  } else if (L::NTB > 4 || !interior) loss_rows<k16Bit, false, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);   // (few registers there)
-  else if (a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
-  else loss_rows<TLQ_BF16, true, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part);
+    if (L::NTB <= 4 && interior) loss_rows<TLQ_F32, true, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
+    else if (half) loss_rows<TLQ_F32, false, DOT, L, L::NQ / 2>(a, Yc, acc, tsc, ow, tw, sq, part);
+    else loss_rows<TLQ_F32, false, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
+  } else if (half) loss_rows<k16Bit, false, DOT, L, L::NQ / 2>(a, Yc, acc, tsc, ow, tw, sq, part);
+  else if (L::NTB > 4 || !interior) loss_rows<k16Bit, false, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);   // (few registers there)
+  else if (a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
+  else loss_rows<TLQ_BF16, true, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
   if (EPI == EPI_LOSS_TOK) {
 #pragma unroll
     for (int tb = 0; tb < L::NTB; ++tb) {

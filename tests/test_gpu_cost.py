@@ -128,3 +128,20 @@ def test_ragged_edge_of_a_one_round_product(gpu):
     Y, Z = (torch.empty((n, co), dtype=torch.float16, device=gpu) for co in (2304, 2216))
     whole, ragged = micros(lambda: tlq.ref_output(X, W, Y, p), lambda: tlq.ref_output(X, W[:2216], Z, p), reps=50)
     assert ragged < 1.18 * whole, (ragged, whole)
+
+
+def test_loss_of_few_outputs(gpu):
+    """64 outputs in tiles of 256: 0.73 times the cost of 256 outputs when the rows past the edge are left out, 1.11
+    when their target is read for nothing."""
+    import torch
+    n, ci = 100000, 64
+    X, W = torch.randn((n, ci), device=gpu).to(torch.float16), torch.randn((256, ci), device=gpu).to(torch.float16)
+    w, loss = torch.full((n,), 1.0 / n, device=gpu), torch.empty(1, device=gpu)
+    p = tlq.params(group=8)
+
+    def run(co):
+        Y = torch.zeros((n, co), dtype=torch.float16, device=gpu)
+        ws = torch.empty(tlq.weighted_layer_err_workspace_bytes(n, ci, co, p), dtype=torch.uint8, device=gpu)
+        return lambda: tlq.weighted_layer_err(X, W[:co], None, Y, w, p, loss, workspace=ws)
+    few, whole = micros(run(64), run(256), reps=50)
+    assert few < 0.9 * whole, (few, whole)

@@ -663,3 +663,32 @@ def test_stores_and_token_errors_of_narrow_and_wide_tiles(gpu, n, co, bf16):
     e = ((target.double() - (tX.double() * torch.from_numpy(s).to(gpu).double()) @ tW.double().t()) ** 2).mean(1)
     np.testing.assert_allclose(err.cpu().numpy(), e.cpu().numpy(), rtol=2e-5)      # float sums of positive terms
     np.testing.assert_allclose(float(loss.item()), float((e * w.double()).sum()), rtol=2e-5)
+
+
+# outputs on both sides of half a tile (128), of a quad (4) and of the first quad; tokens in one and in several waves and
+# tiles, square and wide ones
+@pytest.mark.parametrize("co", [1, 3, 4, 66, 124, 128, 129, 380, 386])
+@pytest.mark.parametrize("n,fl", [(1, False), (130, True), (700, False), (33000, False), (33000, True)])
+def test_losses_where_half_a_tile_lies_past_the_edge(gpu, n, co, fl):
+    import torch
+    g = torch.Generator(device=gpu).manual_seed(n * 512 + co)
+    ci = 64
+    X = torch.randn((n, ci), generator=g, device=gpu).half()
+    W = (torch.randn((co, ci), generator=g, device=gpu) * 0.05).half()
+    prod = X.double() @ W.double().t()
+    dt = torch.float32 if fl else torch.float16
+    Y = torch.full((n, co + -co % 8 + 8), float("nan"), dtype=dt, device=gpu)     # what lies beside the target is not used
+    Y[:, :co] = (prod + torch.randn(prod.shape, generator=g, device=gpu)).to(dt)
+    w = torch.rand(n, generator=g, device=gpu) / n
+    p = tlq.params(group=8, yref_dtype=tlq.F32 if fl else tlq.F16)
+    e = ((Y[:, :co].double() - prod) ** 2).mean(1)
+    want = float((e * w.double()).sum())
+    for tok in (False, True):
+        loss, err = torch.empty(1, device=gpu), torch.empty(n, device=gpu) if tok else None
+        tlq.weighted_layer_err(X, W, None, Y[:, :co], w, p, loss, per_token_err=err)
+        # products of 64 terms are off by 64 roundings of 2^-24 of a magnitude of about three residuals, the sums of
+        # positive terms by a few more: below 2e-5
+        np.testing.assert_allclose(float(loss), want, rtol=2e-5)
+        if tok:
+            # one output: a residual near zero keeps the absolute error of its product
+            np.testing.assert_allclose(err.cpu().numpy(), e.cpu().numpy(), rtol=2e-5, atol=2e-6)
