@@ -93,21 +93,29 @@ struct SearchPlan {
   int64_t tiles_o, tiles_t; GemmTile tile;
   float* d0; int64_t ldd;   // difference form: Y_ref - X W^T as float
 };
-// Tile of a search's contraction, n_launch candidates a launch.  Smaller tiles write up to four times the loss partials.
+// Tile of a search's contraction.  Smaller tiles write up to four times the loss partials.
 // The workspace stays what it is with 256 x 256: where there are more of them they take the place of the channel
 // sums, which are done with by then, if they fit.
-GemmTile search_tile(int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, int n_launch, bool diff) {
+GemmTile search_tile(const GemmArgs& g, int64_t c_in, int n_alpha, bool diff) {
   int64_t to, tt;
-  gemm_tile_counts(n_tok, c_out, GemmTile{}, &to, &tt);
-  const int64_t room = (int64_t)((size_t)xstat_chunks(n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
+  gemm_tile_counts(g.n_tok, g.c_out, GemmTile{}, &to, &tt);
+  const int64_t room = (int64_t)((size_t)xstat_chunks(g.n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
   // (the differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us)
-  return gemm_tile(n_tok, c_out, n_launch, diff ? kTileSmall | kTileNarrow : kTileAll, room > to * tt ? room : to * tt);
+  return gemm_tile(g, diff ? kTileSmall | kTileNarrow : kTileAll, room > to * tt ? room : to * tt);
 }
-// Patch shape of a search's contraction, by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose
-// 0.5 - 3 % on the narrowing, deep ones (down_proj)
-bool search_wide_patch(int64_t c_in, int64_t c_out) { return c_in <= 2 * c_out; }
+// Sizes and order of a search's contraction, n_launch candidates a launch.
+GemmArgs search_args(int64_t n_tok, int64_t c_in, int64_t c_out, int n_launch, bool act, bool int8) {
+  GemmArgs g{};
+  g.n_tok = n_tok; g.c_out = c_out; g.n_cand = n_launch;
+  g.c_in = int8 ? int8_row(c_in) / 2 : c_in;    // (codes in units of 16 bits)
+  g.cand_outer = act;    // with activation codes nothing is shared between candidates: walk them one after the other
+  // patch shape by measurement: 8 x 4 tiles gain ~1 % on square and widening layers and lose 0.5 - 3 % on the
+  // narrowing, deep ones (down_proj)
+  g.wide_patch = !act && c_in <= 2 * c_out;
+  return g;
+}
 SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int n_alpha, bool bf16,
-                       bool act, bool diff, bool strides_ok = false) {
+                       bool act, bool diff, bool int8 = false, bool strides_ok = false) {
   SearchPlan s;
   Carver c(ws);
   s.tile = GemmTile{};
@@ -127,7 +135,7 @@ SearchPlan plan_search(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, int
   s.bytes = c.off;
   if (!strides_ok) return s;
   const int64_t big = s.tiles_o * s.tiles_t;
-  s.tile = search_tile(n_tok, c_in, c_out, n_alpha, act ? s.nb : n_alpha, diff);
+  s.tile = search_tile(search_args(n_tok, c_in, c_out, act ? s.nb : n_alpha, act, int8), c_in, n_alpha, diff);
   gemm_tile_counts(n_tok, c_out, s.tile, &s.tiles_o, &s.tiles_t);
   if (s.tiles_o * s.tiles_t > big) s.partial = (float*)s.xs_partial;
   return s;
@@ -150,7 +158,11 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   e.sig = act ? c.take<float>((size_t)n_tok) : nullptr;
   e.bytes = c.off;
   e.tile = GemmTile{};
-  if (fp16) e.tile = gemm_tile(n_tok, c_out, 1, kTileWide, e.tiles_o * e.tiles_t);
+  if (fp16) {
+    GemmArgs g{};
+    g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
+    e.tile = gemm_tile(g, kTileWide, e.tiles_o * e.tiles_t);
+  }
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
   return e;
 }
@@ -230,6 +242,15 @@ GramPlan plan_gram(void* ws, int64_t n_tok, int64_t c_in) {
 }
 struct GramSearchPlan { float* s_table; float* inv_table; float* partial; uint16_t* dq; size_t bytes;
                         int64_t tiles_o, tiles_t; GemmTile tile; };
+// Sizes and order of the quadratic form: weight rows take the token role.
+GemmArgs gram_search_args(int64_t c_in, int64_t c_out, int n_alpha) {
+  GemmArgs g{};
+  g.n_tok = c_out; g.c_in = g.c_out = c_in; g.n_cand = n_alpha;
+  g.cand_outer = true;   // D'_k and C stay cache-resident for one candidate at a time
+  g.wide_patch = true;   // consecutive patches keep their 8 panels of C and fetch 4 new ones of D'_k
+  g.sym_k = true;        // C is symmetric: contract from each tile's diagonal block on, the rest counted twice
+  return g;
+}
 GramSearchPlan plan_gram_search(void* ws, int64_t c_in, int64_t c_out, int n_alpha) {
   GramSearchPlan s;
   Carver c(ws);
@@ -239,7 +260,7 @@ GramSearchPlan plan_gram_search(void* ws, int64_t c_in, int64_t c_out, int n_alp
   s.partial = c.take<float>((size_t)n_alpha * s.tiles_o * s.tiles_t);
   s.dq = c.take<uint16_t>((size_t)n_alpha * c_out * c_in);
   s.bytes = c.off;
-  s.tile = gemm_tile(c_out, c_in, n_alpha, kTileWide, s.tiles_o * s.tiles_t);
+  s.tile = gemm_tile(gram_search_args(c_in, c_out, n_alpha), kTileWide, s.tiles_o * s.tiles_t);
   gemm_tile_counts(c_out, c_in, s.tile, &s.tiles_o, &s.tiles_t);
   return s;
 }
@@ -271,9 +292,9 @@ int64_t tlq_selftest_tile_map(int64_t n_tok, int64_t c_in, int64_t c_out, int32_
   g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
   tlq_params p{};
   p.bits = 4;
-  g.tile() = n_cand == 1 ? gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX)
-                         : search_tile(n_tok, c_in, c_out, n_cand, n_cand, use_diff_form(&p, n_tok, c_out));
-  g.wide_patch = n_cand == 1 || search_wide_patch(c_in, c_out);
+  if (n_cand > 1) g = search_args(n_tok, c_in, c_out, n_cand, false, false);
+  else g.wide_patch = true;
+  g.tile() = n_cand > 1 ? search_tile(g, c_in, n_cand, use_diff_form(&p, n_tok, c_out)) : gemm_tile(g, kTileAll, INT64_MAX);
   if (blocks) *blocks = gemm_blocks(g);
   return tile_map_defects(n_tok, c_in, c_out, n_cand);
 }
@@ -468,7 +489,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   const bool bf16 = p->x_dtype == TLQ_BF16;
   const bool act = p->act_bits != 0;
   const bool diff = use_diff_form(p, n_tok, c_out), int8 = use_int8(p, c_in);
-  SearchPlan s = plan_search(workspace, n_tok, c_in, c_out, n_alpha, bf16, act, diff,
+  SearchPlan s = plan_search(workspace, n_tok, c_in, c_out, n_alpha, bf16, act, diff, int8,
                              gemm_strides_ok(bf16 || act ? c_in : ldx, c_in));
   if (prepared && !aligned(prepared, 256)) return TLQ_ERR_ALIGN;
   const bool use_prep = prepared && needs_prepared(p);
@@ -509,20 +530,18 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     r.X = X; r.n_tok = n_tok; r.c_in = c_in; r.ldx = ldx;
     r.Wh = W; r.c_out = c_out; r.ldw = ldw; r.w_cand_stride = 0; r.n_cand = 1; r.bf16 = bf16;
     r.Yout = s.d0; r.ldo = s.ldd; r.yout_dtype = TLQ_F32;
-    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
+    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(r, kTileAll, INT64_MAX);
     r.Yref = Y_ref; r.ldy = ldy; r.yref_dtype = p->yref_dtype;   // subtracted in the epilogue (float output)
     TLQ_HIP(launch_gemm_store(r, st));
   }
   // S3 + S4: one launch over the stacked candidates (fp16 operands in either case)
-  GemmArgs g{};
-  g.X = bf16 ? (const void*)s.xh : X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = bf16 ? c_in : ldx;
-  g.Wh = s.what; g.c_out = c_out; g.ldw = c_in; g.w_cand_stride = c_out * c_in;
-  g.n_cand = n_alpha; g.bf16 = false;
+  GemmArgs g = search_args(n_tok, c_in, c_out, act ? s.nb : n_alpha, act, int8);
+  g.X = bf16 ? (const void*)s.xh : X; g.ldx = bf16 ? c_in : ldx;
+  g.Wh = s.what; g.ldw = c_in; g.w_cand_stride = c_out * c_in; g.bf16 = false;
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   if (diff) { g.Yref = s.d0; g.ldy = s.ldd; g.yref_dtype = TLQ_F32; }
   g.partial = s.partial; g.tok_partial = nullptr; g.tile() = s.tile;
   if (!act) {
-    g.wide_patch = search_wide_patch(c_in, c_out);
     TLQ_HIP(launch_gemm_loss(g, st));
   } else {
     // Q_a(x / s_k) differs per candidate: quantise the tokens for a batch of candidates,
@@ -534,11 +553,10 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
                                s.sig + (size_t)k0 * n_tok, st, ld8));
       GemmArgs b = g;
       b.X = s.xc; b.ldx = c_in; b.x_cand_stride = n_tok * c_in;
-      b.cand_outer = true;   // nothing is shared between candidates here: walk them one after the other
       b.tok_scale = s.sig + (size_t)k0 * n_tok;
       b.Wh = s.what + (size_t)k0 * c_out * c_in; b.n_cand = nb;
       if (int8) {      // (in units of 16 bits)
-        b.i8_k = c_in; b.c_in = b.ldx = b.ldw = ld8 / 2;
+        b.i8_k = c_in; b.ldx = b.ldw = ld8 / 2;
         b.x_cand_stride = n_tok * ld8 / 2; b.w_cand_stride = c_out * ld8 / 2;
         b.Wh = s.what + (size_t)k0 * b.w_cand_stride;
         b.row_scale = steps + (size_t)k0 * step_stride; b.row_scale_stride = step_stride;
@@ -667,13 +685,11 @@ tlq_status tlq_scale_search_gram(const void* gram, int64_t c_in, const void* W, 
   q.diff = true; q.xmax_bits = nullptr; q.col_scale = v.col_scale;
   TLQ_HIP(launch_fake_quant(q, st));
   // partial = sum_{o,i} (D'_k C)[o,i] D'_k[o,i]: the weight rows play the tokens, C the weights
-  GemmArgs g{};
-  g.X = s.dq; g.n_tok = c_out; g.c_in = c_in; g.ldx = c_in; g.x_cand_stride = c_out * c_in;
-  g.Wh = v.C; g.c_out = c_in; g.ldw = c_in; g.w_cand_stride = 0; g.n_cand = n_alpha; g.bf16 = false;
+  GemmArgs g = gram_search_args(c_in, c_out, n_alpha);
+  g.X = s.dq; g.ldx = c_in; g.x_cand_stride = c_out * c_in;
+  g.Wh = v.C; g.ldw = c_in; g.w_cand_stride = 0; g.bf16 = false;
   g.Yref = s.dq; g.ldy = c_in; g.yref_dtype = TLQ_F16; g.y_cand_stride = c_out * c_in;
-  g.partial = s.partial; g.tile() = s.tile; g.cand_outer = true;   // D'_k and C stay cache-resident for one candidate at a time
-  g.wide_patch = true;   // consecutive patches keep their 8 panels of C and fetch 4 new ones of D'_k
-  g.sym_k = true;        // C is symmetric: contract from each tile's diagonal block on, the rest counted twice
+  g.partial = s.partial; g.tile() = s.tile;
   TLQ_HIP(launch_gemm_dot(g, st));
   TLQ_HIP(launch_finalize(s.partial, n_alpha, s.tiles_o * s.tiles_t, c_out, s.s_table, c_in, losses,
                           best_idx, best_scales, st, v.factor));
@@ -697,7 +713,7 @@ tlq_status tlq_ref_output(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   g.bf16 = p->x_dtype == TLQ_BF16;
   g.Yout = Y; g.ldo = ldy; g.yout_dtype = p->yref_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, kTileAll, INT64_MAX);
   return hip_status(launch_gemm_store(g, (hipStream_t)stream));
 }
 
@@ -757,7 +773,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   if (ld8) { g.i8_k = c_in; g.c_in = g.ldx = g.ldw = ld8 / 2; g.row_scale = steps; }      // (in units of 16 bits)
   g.Yout = X_next; g.ldo = ld_next; g.yout_dtype = p->x_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(n_tok, c_out, 1, kTileAll, INT64_MAX);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, kTileAll, INT64_MAX);
   return hip_status(launch_gemm_store(g, st));
 }
 

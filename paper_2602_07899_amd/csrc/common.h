@@ -186,11 +186,11 @@ struct GemmArgs : GemmTile {
   void* Yout; int64_t ldo; int yout_dtype;
 };
 void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tiles_o, int64_t* tiles_t);
-// kinds: tiles besides 256 x 256 that the launch has (stores and fp16 losses: all; fp16 losses with tok_partial and the
-// quadratic form: the wide one); max_tiles: tiles per candidate that the caller has room for, at least those of
-// 256 x 256
+// The tile for a launch of g's sizes, candidates and order.  kinds: tiles besides 256 x 256 that the launch has (stores and
+// fp16 losses: all; fp16 losses with tok_partial and the quadratic form: the wide one); max_tiles: tiles per candidate
+// that the caller has room for, at least those of 256 x 256
 enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7 };
-GemmTile gemm_tile(int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles);
+GemmTile gemm_tile(const GemmArgs& g, int kinds, int64_t max_tiles);
 // row strides that the pipelined kernel (and with it any tile but 256 x 256) takes
 bool gemm_strides_ok(int64_t ldx, int64_t ldw);
 int64_t gemm_blocks(const GemmArgs& g);   // workgroups of the launch (sizes, tile and order are read, no pointer)

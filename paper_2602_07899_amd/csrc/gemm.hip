@@ -1090,36 +1090,6 @@ static bool gemm_small_tiles(int64_t n_tok, int64_t c_out, int n_cand) {
   return small <= 512 || (big > 256 && small <= 1280);
 }
 
-// The tile that takes the least time (any result is the same up to the order of the loss sums: an output's own
-// products are added in the same order).  A launch of up to eight rounds takes whole rounds of one block per
-// CU (small tiles: two), longer ones drift apart and pay for their tiles.  The cost of a round, in rounds of 256 x 256,
-// from store launches of one round with 4096 channels (us): 128 x 128 59, 192 tokens 79, 256 97, 320 114.  The wide tile reads
-// fewer fragments and fetches fewer panels per product, so it is ahead of the square one also where the count of rounds
-// does not decide.  us by tile (128, 192, 256, 320), tokens x channels x outputs [x candidates]:
-//   store   1200 x 5120 x 13824 207 185 214 140      search  10,240 x 4096 x 4096 x 20  6241 5797 5213 5031
-//   store   2500 x 4096 x 4096   99  74  88 101      search  40,000 x 5120 x 5120 x 20   41.1  37.9  33.1  30.7 ms
-//   store   3678 x 4096 x 4096  111 137  96 110      search     640 x 4096 x 4096 x 20   690  632  594  550
-//   store   4800 x 4096 x 4096  151 146 171 114      search  W4A8 3678 x 4096 x 4096    1499 1370 1277 1218
-//   store  10,240 x 11008 x 4096 833 959 805 642     search    1839 x 1152 x 1400 x 12   129  125  133  128
-//   store  40,960 x 4096 x 11008  3.28 2.94 2.77 2.61 ms   quadratic form 5120 x 5120 - - 2824 2654; 4096 x 1024 - - 448 523
-GemmTile gemm_tile(int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles) {
-  GemmTile best{false, 4};
-  double best_cost = 1e300;
-  auto consider = [&](GemmTile t, double slots, double first, double each) {
-    int64_t to, tt;
-    gemm_tile_counts(n_tok, c_out, t, &to, &tt);
-    if (to * tt > max_tiles) return;
-    const double rounds = (double)(to * tt) * n_cand / slots;
-    const double cost = first + each * (rounds <= 8.0 ? std::ceil(rounds) : rounds + 0.5);
-    if (cost < best_cost) { best = t; best_cost = cost; }
-  };
-  if ((kinds & kTileSmall) && gemm_small_tiles(n_tok, c_out, n_cand)) consider(GemmTile{true, 0}, 512, 0.12, 0.5);
-  if (best_cost == 1e300) consider(GemmTile{false, 4}, 256, 0.0, 1.0);
-  if (kinds & kTileNarrow) consider(GemmTile{false, 3}, 256, 0.0, 0.8);
-  if (kinds & kTileWide) consider(GemmTile{false, 5}, 256, 0.0, 1.19);
-  return best;
-}
-
 static GemmDev make_dev(const GemmArgs& g) {
   GemmDev d;
   d.X = (const uint16_t*)g.X; d.n_tok = g.n_tok; d.c_in = g.c_in; d.ldx = g.ldx;
@@ -1181,6 +1151,77 @@ static GemmDev make_dev(const GemmArgs& g) {
   // 43 x 16 tiles: 8.4 -> 9.4 ms).
   d.rot = g.cand_outer && !g.tri && (d.n_patches / g.n_cand) % kXcd == 0 ? 5 : 0;
   return d;
+}
+
+// Rounds of 256 tiles that a launch takes.  An XCD works on its own patches only, and where every candidate (or every
+// second one) has as many patches as there are XCDs, the short patches at the end of the tokens always meet the same
+// ones: 13 token tiles in patches of four leave two XCDs a quarter of the work of the others.  An idle XCD leaves
+// power to the busy ones, so that the time lies halfway between the average and the busiest XCD's work (4096 x 4096 x
+// 4096 x 20 with 320-token tiles: 16.25 and 20 rounds, and the time of 18).
+static double launch_rounds(const GemmDev& d, bool sym) {
+  const int64_t tiles = (int64_t)d.tiles_o * d.tiles_t * d.n_cand;
+  if (d.strips) return (double)tiles / (kXcd * PATCH_SLOTS);
+  // (in a symmetric contraction the tile row r contracts tiles_o - r of the tiles_o blocks along k)
+  auto rows = [&](int first, int n) { return sym ? (int64_t)n * (d.tiles_o - first) - (int64_t)n * (n - 1) / 2 : n; };
+  int64_t load[kXcd] = {}, p = 0;
+  auto deal = [&](int64_t live) {
+    const int64_t round = p / kXcd;
+    load[(p - d.rot * (round & (kXcd - 1))) & (kXcd - 1)] += live;
+    ++p;
+  };
+  const int n_full = d.rag ? d.npo - 1 : d.npo, inner = d.cand_outer ? 1 : d.n_cand;
+  for (int k = 0; k < (d.cand_outer ? d.n_cand : 1); ++k)      // (the walk of decode_tile, patch by patch)
+    for (int64_t t0 = 0; t0 < d.tiles_t; t0 += (int64_t)d.cpt * d.pt) {
+      const int64_t chunk = (int64_t)d.cpt * d.pt, end = t0 + chunk < d.tiles_t ? t0 + chunk : d.tiles_t;
+      auto row_of_patches = [&](int64_t high, int wide) {
+        for (int c = 0; c < inner; ++c)
+          for (int64_t t = t0; t < end; t += wide) deal(high * (end - t < wide ? end - t : wide));
+      };
+      for (int r = 0; r < n_full; ++r) row_of_patches(rows(r * d.po, d.po), d.pt);
+      if (d.rag) row_of_patches(rows(n_full * d.po, d.rag), d.rag_pt);
+    }
+  double most = 0.0, sum = 0.0;
+  for (int64_t l : load) { sum += (double)l; most = (double)l > most ? (double)l : most; }
+  return 0.5 * (most / PATCH_SLOTS + sum / (kXcd * PATCH_SLOTS)) / (sym ? 0.5 * (d.tiles_o + 1) : 1.0);
+}
+
+// The tile that takes the least time (any result is the same up to the order of the loss sums: an output's own
+// products are added in the same order).  A launch of up to eight rounds takes whole rounds of one block per
+// CU (small tiles: two), longer ones drift apart and pay for their tiles.  The cost of a round, in rounds of 256 x 256,
+// from store launches of one round with 4096 channels (us): 128 x 128 59, 192 tokens 79, 256 97, 320 114.  Over several
+// rounds the narrow one comes to 0.80 - 0.91; two rounds of small ones cost what one of wide ones does (1300 x 1024 x
+// 11904 35 and 36 us, 1300 x 4096 x 11904 117 and 114), three a little more than two of narrow ones.  The wide tile
+// reads fewer fragments and fetches fewer panels per product, so it is ahead of the square one also where the
+// count of rounds does not decide, unless its last token tile is short or its patches meet the XCDs unevenly.
+// us by tile (128, 192, 256, 320), tokens x channels x outputs [x candidates]:
+//   store   1200 x 5120 x 13824 207 185 214 140      search  10,240 x 4096 x 4096 x 20  6241 5797 5213 5031
+//   store   2500 x 4096 x 4096   99  74  88 101      search  40,000 x 5120 x 5120 x 20   41.1  37.9  33.1  30.7 ms
+//   store   3678 x 4096 x 4096  111 137  96 110      search     640 x 4096 x 4096 x 20   690  632  594  550
+//   store   4800 x 4096 x 4096  151 146 171 114      search  W4A8 3678 x 4096 x 4096    1499 1370 1277 1218
+//   store  10,240 x 11008 x 4096 833 959 805 642     search    1839 x 1152 x 1400 x 12   129  125  133  128
+//   store  40,960 x 4096 x 11008  3.28 2.94 2.77 2.61 ms   quadratic form 5120 x 5120 - - 2824 2654; 4096 x 1024 - - 448 523
+//   store  6144 x 5120 x 13824    -  850 702 686     search    4096 x 4096 x 4096 x 20     -  2588 2370 2591
+//   quadratic form 5120 x 4096 - - 2327 2586         search    8192 x 4096 x 1024 x 20     -  1237 1119 1255
+// Over 228 launches of three rounds and more the choice costs 0.2 % against the best of the three (1.0 % with
+// the plain count of tiles, whose worst cases were 21 % and 12 %).
+GemmTile gemm_tile(const GemmArgs& args, int kinds, int64_t max_tiles) {
+  GemmArgs g = args;
+  GemmTile best{false, 4};
+  double best_cost = 1e300;
+  auto consider = [&](GemmTile t, double first, double each) {
+    int64_t to, tt;
+    gemm_tile_counts(g.n_tok, g.c_out, t, &to, &tt);
+    if (to * tt > max_tiles) return;
+    g.tile() = t;
+    const double rounds = t.small ? (double)(to * tt) * g.n_cand / 512 : launch_rounds(make_dev(g), g.sym_k);
+    const double cost = first + each * (rounds <= 8.0 ? std::ceil(rounds - 1e-9) : rounds + 0.5);
+    if (cost < best_cost) { best = t; best_cost = cost; }
+  };
+  if ((kinds & kTileSmall) && gemm_small_tiles(g.n_tok, g.c_out, g.n_cand)) consider(GemmTile{true, 0}, 0.06, 0.56);
+  if (best_cost == 1e300) consider(GemmTile{false, 4}, 0.0, 1.0);
+  if (kinds & kTileNarrow) consider(GemmTile{false, 3}, 0.0, 0.86);
+  if (kinds & kTileWide) consider(GemmTile{false, 5}, 0.0, 1.19);
+  return best;
 }
 
 static int64_t dev_blocks(const GemmDev& d) { return ceil_div(d.n_patches, kXcd) * kXcd * PATCH_SLOTS; }

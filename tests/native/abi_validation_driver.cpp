@@ -211,21 +211,33 @@ int main() {
   h = g; h.sym_k = true; h.c_out = 256;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
 
   // ---- the tile of a launch: tokens of a tile, 128 for the small one
-  auto tile = [](int64_t n_tok, int64_t c_out, int n_cand, int kinds, int64_t max_tiles) {
-    const tlq::GemmTile t = tlq::gemm_tile(n_tok, c_out, n_cand, kinds, max_tiles);
+  auto tile = [](int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int kinds, int64_t max_tiles, bool quadratic = false) {
+    tlq::GemmArgs a{};
+    a.n_tok = n_tok; a.c_in = c_in; a.c_out = c_out; a.n_cand = n_cand;
+    a.wide_patch = true; a.cand_outer = a.sym_k = quadratic;
+    const tlq::GemmTile t = tlq::gemm_tile(a, kinds, max_tiles);
     return t.small ? 128 : t.tok_blocks * 64;
   };
-  EXPECT(tile(2048, 4096, 1, tlq::kTileAll, INT64_MAX), 128);    // 512 small tiles, and one row of them more
-  EXPECT(tile(2048, 4097, 1, tlq::kTileAll, INT64_MAX), 192);
-  EXPECT(tile(3072, 4096, 1, tlq::kTileAll, INT64_MAX), 192);    // one round of 256 blocks, and one token more
-  EXPECT(tile(3073, 4096, 1, tlq::kTileAll, INT64_MAX), 256);
-  EXPECT(tile(5120, 4096, 1, tlq::kTileAll, INT64_MAX), 320);
-  EXPECT(tile(1200, 13824, 1, tlq::kTileAll, INT64_MAX), 320);
-  EXPECT(tile(1200, 13824, 1, 0, INT64_MAX), 256);               // kinds that the launch does not have
-  EXPECT(tile(1200, 13824, 1, tlq::kTileNarrow, INT64_MAX), 192);
-  EXPECT(tile(256, 512, 20, tlq::kTileAll, 8), 128);             // 2 x 4 small tiles, room for them and for one less
-  EXPECT(tile(256, 512, 20, tlq::kTileAll, 7), 192);
-  EXPECT(tile(256, 512, 20, tlq::kTileAll, 3), 256);             // 2 x 2 narrow ones do not fit either
+  EXPECT(tile(2048, 64, 4096, 1, tlq::kTileAll, INT64_MAX), 128);    // 512 small tiles, and one row of them more
+  EXPECT(tile(2048, 64, 4097, 1, tlq::kTileAll, INT64_MAX), 192);
+  EXPECT(tile(3072, 64, 4096, 1, tlq::kTileAll, INT64_MAX), 192);    // one round of 256 blocks, and one token more
+  EXPECT(tile(3073, 64, 4096, 1, tlq::kTileAll, INT64_MAX), 256);
+  EXPECT(tile(5120, 64, 4096, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(1200, 64, 13824, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(1200, 64, 13824, 1, 0, INT64_MAX), 256);               // kinds that the launch does not have
+  EXPECT(tile(1200, 64, 13824, 1, tlq::kTileNarrow, INT64_MAX), 192);
+  EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 8), 128);            // 2 x 4 small tiles, room for them and for one less
+  EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 7), 192);
+  EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 3), 256);            // 2 x 2 narrow ones do not fit either
+  // long launches: as many wide tiles as fill the patches; a short last column of patches that always meets the same XCDs;
+  // many rounds of narrow tiles
+  EXPECT(tile(5120, 4096, 4096, 20, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(4096, 4096, 4096, 20, tlq::kTileAll, INT64_MAX), 256);
+  EXPECT(tile(8192, 4096, 1024, 20, tlq::kTileAll, INT64_MAX), 256);
+  EXPECT(tile(6144, 5120, 13824, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(153600, 5120, 13824, 20, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(5120, 5120, 5120, 20, tlq::kTileWide, INT64_MAX, true), 320);
+  EXPECT(tile(4096, 5120, 5120, 20, tlq::kTileWide, INT64_MAX, true), 256);
 
   // ---- host-side self test of the block -> tile map, and the timing bookkeeping
   int64_t blocks = 0;

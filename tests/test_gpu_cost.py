@@ -145,3 +145,22 @@ def test_loss_of_few_outputs(gpu):
         return lambda: tlq.weighted_layer_err(X, W[:co], None, Y, w, p, loss, workspace=ws)
     few, whole = micros(run(64), run(256), reps=50)
     assert few < 0.9 * whole, (few, whole)
+
+
+def test_search_whose_last_patches_are_short(gpu):
+    """20 candidates over 8192 and over 10,240 tokens: 0.84 times the cost when the tile is chosen by the busiest XCD's
+    work, 0.95 with wide tiles, whose 26 columns leave the short patches of every candidate to the same two XCDs."""
+    import torch
+    ci, co, na = 4096, 1024, 20
+    X, W = torch.randn((10240, ci), device=gpu).to(torch.float16), (torch.randn((co, ci), device=gpu) * 0.02).to(torch.float16)
+    p, al = tlq.params(), torch.tensor([k / na for k in range(na)], device=gpu)
+    best, idx, losses = torch.empty(ci, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu), torch.empty(na, device=gpu)
+    Y = torch.empty((10240, co), dtype=torch.float16, device=gpu)
+    tlq.ref_output(X, W, Y, p)
+    ws = torch.empty(tlq.scale_search_workspace_bytes(10240, ci, co, na, p), dtype=torch.uint8, device=gpu)
+
+    def run(n):
+        w = torch.full((n,), 1.0 / n, device=gpu)
+        return lambda: tlq.scale_search(X[:n], W, Y[:n], w, al, p, best, idx, losses, workspace=ws)
+    few, more = micros(run(8192), run(10240))
+    assert few < 0.9 * more, (few, more)
