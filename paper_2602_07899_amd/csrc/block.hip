@@ -306,9 +306,9 @@ hipError_t launch_causal_attention(const void* Q, int64_t ldq, const void* K, in
   return hipGetLastError();
 }
 
-// MODE 0: out = SiLU(a) * b;  MODE 1: out = a + b.  8 elements per thread; c % 8 == 0.  HBM-bound; NT (see streams_past):
-// gate of 40960 x 11008 477 -> 426 us (6.3 TB/s), sum of 40960 x 4096 171 -> 154 (6.5 TB/s).
-template <typename T, int MODE, bool NT>
+// MODE 0: out = SiLU(a) * b;  MODE 1: out = a + b.  8 elements per thread; c % 8 == 0.  HBM-bound; NT, NTS: loads and stores past
+// the caches: gate of 40960 x 11008 477 -> 426 us (6.3 TB/s), sum of 40960 x 4096 171 -> 154 (6.5 TB/s).
+template <typename T, int MODE, bool NT, bool NTS>
 __global__ __launch_bounds__(256) void pairwise_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                        const uint16_t* __restrict__ B, int64_t ldb, int64_t n_tok,
                                                        int64_t c8, uint16_t* __restrict__ out, int64_t ldo) {
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256) void pairwise_kernel(const uint16_t* __restric
     const float x = T::to_float(a[e]), y = T::to_float(b[e]);
     o[e] = T::from_float(MODE == 0 ? x / (1.0f + __expf(-x)) * y : x + y);
   }
-  store16<NT>(out + row * ldo + col, __builtin_bit_cast(uint4, o));
+  store16<NTS>(out + row * ldo + col, __builtin_bit_cast(uint4, o));
 }
 
 hipError_t launch_pairwise(int mode, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t n_tok,
@@ -331,14 +331,21 @@ hipError_t launch_pairwise(int mode, const void* A, int64_t lda, const void* B, 
   ProfScope ps(mode == 0 ? "silu_mul" : "residual_add", stream, 6.0 * (double)n_tok * (double)c);
   const int64_t c8 = c / 8;
   const unsigned grid = (unsigned)ceil_div(n_tok * c8, 256);
-  const bool nt = streams_past(6.0 * (double)n_tok * (double)c);
+  const double bytes = (double)n_tok * (double)c;
+  const bool nt = streams_past(6.0 * bytes), nts = nt && outgrows_cache(2.0 * bytes);
   auto go = [&](auto kern) {
     kern<<<grid, 256, 0, stream>>>((const uint16_t*)A, lda, (const uint16_t*)B, ldb, n_tok, c8, (uint16_t*)out, ldo);
   };
   auto pick = [&](auto t) {
     using T = decltype(t);
-    if (mode == 0) nt ? go(pairwise_kernel<T, 0, true>) : go(pairwise_kernel<T, 0, false>);
-    else nt ? go(pairwise_kernel<T, 1, true>) : go(pairwise_kernel<T, 1, false>);
+    auto of = [&](auto m) {
+      constexpr int MODE = decltype(m)::value;
+      if (!nt) go(pairwise_kernel<T, MODE, false, false>);
+      else if (!nts) go(pairwise_kernel<T, MODE, true, false>);
+      else go(pairwise_kernel<T, MODE, true, true>);
+    };
+    if (mode == 0) of(std::integral_constant<int, 0>{});
+    else of(std::integral_constant<int, 1>{});
   };
   bf16 ? pick(BF16{}) : pick(F16{});
   return hipGetLastError();

@@ -65,10 +65,17 @@ __device__ __forceinline__ void store16(void* p, const uint4& v, bool nt) {
 __device__ __forceinline__ void store8(void* p, uint32_t a, uint32_t b, bool nt) {
   if (nt) { asm volatile("" ::: "memory"); store8<true>(p, a, b); asm volatile("" ::: "memory"); } else store8<false>(p, a, b);
 }
-// Bytes from which a stream is better off past the 256 MB last-level cache, us plain -> past it: the residual sum, 288 MB read
-// and written 43.8 -> 44.8, 384 MB 65.7 -> 57.8, 1152 MB 194 -> 175; gradient norms, 256 MB 46.7 -> 46.8, 320 MB
-// 62 -> 58, 1500 MB 306 -> 263; the statistic, 256 MB 40.9 -> 49.4, 320 MB 63.4 -> 60.5, 1500 MB 279 -> 267.
+// Bytes of a call from which what it only reads is better off past the 256 MB last-level cache, us plain -> past it: the residual
+// sum, 288 MB read and written 43.8 -> 44.8, 384 MB 65.7 -> 57.8, 1152 MB 194 -> 175; gradient norms, 256 MB 46.7 ->
+// 46.8, 320 MB 62 -> 58, 1500 MB 306 -> 263; the statistic, 256 MB 40.9 -> 49.4, 320 MB 63.4 -> 60.5, 1500 MB 279 -> 267.
 inline bool streams_past(double bytes) { return bytes > 320e6; }
+// Bytes of an output from which it is: below, the call that reads it next finds it there, all the more if the inputs went
+// past.  Two calls in a row, us all plain, loads past, loads and stores past: residual sum and norm with an output of
+// 107 MB 94, 92, 99, of 168 MB 137, 132, 147; gate of 113 MB and the product behind it 222, 183, 253, of 224 MB 323, 301, 313,
+// of 252 MB 342, 331, 338; norm and product, 200 MB 273, 232, 265, 240 MB 310, 302, 300; bf16 tokens to fp16 and a loss, 201 MB
+// 235, 197, 210, 224 MB 253, 216, 223, 240 MB 262, 234, 231, 252 MB 269, 247, 237.  (A producer alone, over and over the same
+// buffers, has no reader: there the conversion of 200 MB takes 110 us with plain stores, 95 with stores past.)
+inline bool outgrows_cache(double bytes) { return bytes > 230e6; }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

@@ -45,9 +45,9 @@ __global__ __launch_bounds__(256) void rmsnorm_mul_kernel(const uint16_t* __rest
 // results are bit-equal: each 512-element stretch goes through 1 KB of LDS and is picked up two bytes a
 // lane.  Rows of up to 512 * HOLD elements stay in registers between the sum and the scaling (HOLD = 0: read
 // again, from L2).  40960 x 4096 bf16: 454 -> 146 us (2-byte loads and stores, two passes before),
-// 138 past the caches (NT).
+// 138 past the caches (NT loads, NTS stores).
 constexpr int64_t kVecWidth = 72;
-template <typename T, int HOLD, bool NT>
+template <typename T, int HOLD, bool NT, bool NTS>
 __global__ __launch_bounds__(256) void rmsnorm_mul_vec_kernel(const uint16_t* __restrict__ Z, int64_t ldz,
                                                               const uint16_t* __restrict__ Zb, int64_t ldzb,
                                                               int64_t n_tok, int64_t c, const float* __restrict__ m_a,
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void rmsnorm_mul_vec_kernel(const uint16_t* __
       if (zb) x *= T::to_float((uint16_t)(b[e >> 1] >> ((e & 1) * 16)));
       o[e >> 1] |= (uint32_t)T::from_float(x * inv * f[e]) << ((e & 1) * 16);
     }
-    store16<NT>(out + row * ldo + j, make_uint4(o[0], o[1], o[2], o[3]));
+    store16<NTS>(out + row * ldo + j, make_uint4(o[0], o[1], o[2], o[3]));
   };
   if constexpr (HOLD > 0) {
 #pragma unroll
@@ -150,15 +150,16 @@ hipError_t launch_rmsnorm_mul(const void* Z, int64_t ldz, const void* Zb, int64_
   };
   auto pick = [&](auto t) {
     using T = decltype(t);
-    auto vec_of = [&](auto nt_c) {
-      constexpr bool NT = decltype(nt_c)::value;
-      if (c <= 1024) go(rmsnorm_mul_vec_kernel<T, 2, NT>);
-      else if (c <= 5120) go(rmsnorm_mul_vec_kernel<T, 10, NT>);
-      else go(rmsnorm_mul_vec_kernel<T, 0, NT>);
+    auto vec_of = [&](auto nt_c, auto nts_c) {
+      constexpr bool NT = decltype(nt_c)::value, NTS = decltype(nts_c)::value;
+      if (c <= 1024) go(rmsnorm_mul_vec_kernel<T, 2, NT, NTS>);
+      else if (c <= 5120) go(rmsnorm_mul_vec_kernel<T, 10, NT, NTS>);
+      else go(rmsnorm_mul_vec_kernel<T, 0, NT, NTS>);
     };
     if (!vec) go(rmsnorm_mul_kernel<T>);
-    else if (streams_past((Zb ? 6.0 : 4.0) * (double)n_tok * (double)c)) vec_of(std::true_type{});
-    else vec_of(std::false_type{});
+    else if (!streams_past((Zb ? 6.0 : 4.0) * (double)n_tok * (double)c)) vec_of(std::false_type{}, std::false_type{});
+    else if (!outgrows_cache(2.0 * (double)n_tok * (double)c)) vec_of(std::true_type{}, std::false_type{});
+    else vec_of(std::true_type{}, std::true_type{});
   };
   if (!bf16) pick(F16{}); else pick(BF16{});
   return hipGetLastError();

@@ -33,8 +33,9 @@ int xstat_chunks(int64_t n_tok) {
   return (int)(c < 1 ? 1 : (c > 128 ? 128 : c));
 }
 
-// NW waves per block: NT: rows that come past the caches (153,600 x 5120: 265 -> 244 us, 6.4 TB/s).  16 where a chunk has 128 rows at most (8 a wave; with 4 waves the two blocks of a
+// NW waves per block: 16 where a chunk has 128 rows at most (8 a wave; with 4 waves the two blocks of a
 // 256 x 512 input walked 32 rows each wave, 11 us against 4), 4 on longer chunks.
+// NT: rows that come past the caches (153,600 x 5120: 265 -> 244 us, 6.4 TB/s).
 // MAXBITS: every block also leaves the largest magnitude (as bits) that it has seen in block_max, for the fp16
 // re-expression of bf16 tokens, which would read them all once more for it.
 template <typename T, int KIND, bool MASKED, int NW, bool MAXBITS, bool NT>
@@ -390,8 +391,9 @@ __global__ void zero_u32_kernel(uint32_t* p) { *p = 0u; }
 // and order independent.  A wave walks whole rows (no index division) and a block ends in ONE atomic on
 // the single result word: with one per wave and four times the blocks the atomics alone took 130 us.
 // blockIdx.y picks the stretch of `per` chunks of a row: the whole row unless the rows are too few for the chip.
+// (The tokens stay in the caches here, whatever their size: the conversion reads them once more.  Both passes over
+// 40,960 x 4096 bf16, conversion past the caches: 152 us, with this one past them too 164; 65,536 x 4096 240 and 262.)
 constexpr int kPrepBlocks = 1024;   // 4 per CU
-template <bool NT>
 __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
                                                           int64_t c_in, int64_t ldx, int64_t per,
                                                           uint32_t* __restrict__ out) {
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __rest
     const uint16_t* row = X + r * ldx;
 #pragma unroll 4
     for (int64_t i = i0 + lane; i < i1; i += 64) {
-      const uint4 v = load16<NT>(row + i * 8);
+      const uint4 v = *reinterpret_cast<const uint4*>(row + i * 8);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -422,7 +424,8 @@ __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __rest
   }
 }
 
-template <bool NT>
+// NT, NTS: loads and stores past the caches
+template <bool NT, bool NTS>
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
                                                           int64_t c_in, int64_t ldx, int64_t per,
                                                           const uint32_t* __restrict__ xmax_bits,
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __rest
         const float lo = BF16::to_float((uint16_t)w[j]) * scale, hi = BF16::to_float((uint16_t)(w[j] >> 16)) * scale;
         o[j] = (uint32_t)F16::from_float(lo) | ((uint32_t)F16::from_float(hi) << 16);
       }
-      store16<NT>(Xh + r * c_in + i * 8, make_uint4(o[0], o[1], o[2], o[3]));
+      store16<NTS>(Xh + r * c_in + i * 8, make_uint4(o[0], o[1], o[2], o[3]));
     }
   }
 }
@@ -456,16 +459,17 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   const int64_t per = ceil_div(ceil_div(c_in, 512), rows < 256 ? 256 / rows : 1) * 64;   // in chunks of 8 channels
   const unsigned split = (unsigned)ceil_div(c_in / 8, per);
   const dim3 mgrid((unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), split), cgrid((unsigned)(rows < 8192 ? rows : 8192), split);
-  auto go = [&](auto nt) {
-    constexpr bool NT = decltype(nt)::value;
-    if (!have_max) {
-      zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
-      absmax_bits_kernel<NT><<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
-    }
-    bf16_to_f16_kernel<NT><<<cgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits, (uint16_t*)Xh);
+  if (!have_max) {
+    zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
+    absmax_bits_kernel<<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
+  }
+  auto go = [&](auto kern) {
+    kern<<<cgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits, (uint16_t*)Xh);
   };
-  if (streams_past(4.0 * (double)n_tok * (double)c_in)) go(std::true_type{});
-  else go(std::false_type{});
+  const double bytes = (double)n_tok * (double)c_in;
+  if (!streams_past(4.0 * bytes)) go(bf16_to_f16_kernel<false, false>);
+  else if (!outgrows_cache(2.0 * bytes)) go(bf16_to_f16_kernel<true, false>);
+  else go(bf16_to_f16_kernel<true, true>);
   return hipGetLastError();
 }
 

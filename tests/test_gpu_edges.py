@@ -446,15 +446,17 @@ def test_search_over_more_candidates_than_a_block_takes(gpu):
         np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)     # the parity bar of the search
 
 
-# Streams of more than 320 MB go past the caches by other instructions: the same bits as in pieces that do not.
+# What is read of more than 320 MB, and outputs of more than 230 MB, go past the caches by other instructions: the same
+# bits as in pieces that do not.
 def pieces(n, k):
     return [slice(i * n // k, (i + 1) * n // k) for i in range(k)]
 
 
+@pytest.mark.parametrize("mb", [170, 240])             # of one matrix: loads past the caches, and stores too
 @pytest.mark.parametrize("c", [1000, 4096, 5128])      # rows held in 2 and 10 registers quads, and read twice
-def test_long_streams_of_the_glue(gpu, c):
+def test_long_streams_of_the_glue(gpu, c, mb):
     import torch
-    n = int(3.4e8) // (4 * c)
+    n = int(mb * 1e6) // (2 * c)
     g = torch.Generator(device=gpu)
     g.manual_seed(51)
     A, B = (torch.randn((n, c), generator=g, device=gpu, dtype=torch.bfloat16) for _ in range(2))
@@ -466,6 +468,15 @@ def test_long_streams_of_the_glue(gpu, c):
         for r in pieces(n, 3):
             call(r, parts[r])
         assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
+    # the tokens in fp16, behind 256 bytes that hold the maximum: the same one in every piece
+    for r in pieces(n, 3):
+        A[r.start] = 9.0
+    ready = lambda r: tlq.prepare_tokens(A[r], p, torch.zeros(tlq.prepared_tokens_bytes(r.stop - r.start, c, p),
+                                                              dtype=torch.uint8, device=gpu))
+    p = tlq.params(group=8, x_dtype=tlq.BF16)
+    whole = ready(slice(0, n))[256:256 + 2 * n * c].view(torch.int16)
+    parts = [ready(r)[256:256 + 2 * (r.stop - r.start) * c].view(torch.int16) for r in pieces(n, 3)]
+    assert torch.equal(whole, torch.cat(parts)) and int(whole.abs().max()) > 0
 
 
 def test_long_streams_of_statistics_and_codes(gpu):
