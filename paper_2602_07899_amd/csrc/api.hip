@@ -100,7 +100,9 @@ GemmTile search_tile(const GemmArgs& g, int64_t c_in, int n_alpha, bool diff) {
   int64_t to, tt;
   gemm_tile_counts(g.n_tok, g.c_out, GemmTile{}, &to, &tt);
   const int64_t room = (int64_t)((size_t)xstat_chunks(g.n_tok) * c_in * sizeof(double) / ((size_t)n_alpha * sizeof(float)));
-  // (the differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us)
+  // (The differences' target is float, which the wide tile reads without staging: 1839 x 1096 x 1400 179 -> 184 us.  A
+  // caller's float target is read the same way, but there the wide tile is ahead, us 256 -> 320: 4-bit searches of 20
+  // candidates over 1839 x 1096 x 1400 180 -> 172, 10,240 x 1024 x 4096 1764 -> 1710, 10,240 x 4096 x 4096 5598 -> 5466.)
   return gemm_tile(g, diff ? kTileSmall | kTileNarrow : kTileAll, room > to * tt ? room : to * tt);
 }
 // Sizes and order of a search's contraction, n_launch candidates a launch.
@@ -161,6 +163,8 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   if (fp16) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
+    // (also with a float target, and with the token errors, whose epilogue never stages the target: 10,240 x 4096 x 4096
+    // fp16 us 256 -> 320: 338 -> 297 float, 318 -> 288 16-bit; 20,000 x 512 x 2048 76 -> 66 and 74 -> 65)
     e.tile = gemm_tile(g, kTileWide, e.tiles_o * e.tiles_t);
   }
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
@@ -530,7 +534,10 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     r.X = X; r.n_tok = n_tok; r.c_in = c_in; r.ldx = ldx;
     r.Wh = W; r.c_out = c_out; r.ldw = ldw; r.w_cand_stride = 0; r.n_cand = 1; r.bf16 = bf16;
     r.Yout = s.d0; r.ldo = s.ldd; r.yout_dtype = TLQ_F32;
-    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(r, kTileAll, INT64_MAX);
+    // few channels: the wide tile's subtraction, which stages the target in three goes, outweighs its products (two
+    // candidates' searches without and with it, us: 5000 x 128 x 13824 292 and 328, 20,000 x 512 x 2048 with a 16-bit
+    // target 243 and 252, a float one 293 and 285, 40,000 x 768 x 1000 381 and 363)
+    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(r, c_in >= 512 ? kTileAll : kTileSmall | kTileNarrow, INT64_MAX);
     r.Yref = Y_ref; r.ldy = ldy; r.yref_dtype = p->yref_dtype;   // subtracted in the epilogue (float output)
     TLQ_HIP(launch_gemm_store(r, st));
   }
