@@ -44,7 +44,7 @@ def source_fingerprint():
     readings describe): those readings are only quoted for the build they were taken from."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2602_07899_amd", "csrc")
-    files = [os.path.join(csrc, "gemm.hip"), os.path.join(csrc, "common.h")]
+    files = [os.path.join(csrc, f) for f in ("gemm.hip", "gemm_width.hip", "contraction.h", "common.h")]
     for f in files:
         h.update(os.path.basename(f).encode())
         h.update(open(f, "rb").read())

@@ -6,7 +6,7 @@
 //   G = sum_t w_t x_t x_t^T   (C_in x C_in, independent of the candidate and of the linear).
 // G costs one pass of 2 N C_in^2 flops (half of it: G is symmetric) and every candidate
 // 2 C_out C_in^2 instead of 2 N C_in C_out: N / C_in times fewer.  The kernels here prepare the
-// operands; the two contractions run on the tile kernels of gemm.hip.
+// operands; the two contractions run on the tile kernels of contraction.h.
 //
 // Conditioning.  G is held in fp16 as C[i,j] = G'[i,j] 2^-(e_i + e_j) with G' = G / max_t w_t and
 // e_c = round(log2(G'[c,c]) / 2): |C| <= 2 whatever the spread of the channel magnitudes, and the

@@ -4,6 +4,7 @@ anything could be launched."""
 import ctypes as C
 import os
 import re
+import struct
 
 import pytest
 
@@ -202,18 +203,59 @@ def test_no_launch_in_a_forked_child(monkeypatch):
         tlq._stream()
 
 
+def code_objects(blob):
+    """The device code objects of the library: entries of its offload bundles."""
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := blob.find(magic, at)) >= 0:
+        p = at + len(magic)
+        (n,) = struct.unpack_from("<Q", blob, p)
+        p += 8
+        for _ in range(n):
+            offset, size, name = struct.unpack_from("<QQQ", blob, p)
+            triple = blob[p + 24:p + 24 + name]
+            p += 24 + name
+            if triple.startswith(b"hip") and size:
+                yield blob[at + offset:at + offset + size]
+        at += len(magic)
+
+
+LOSS, TOK, STORE, DOT = range(4)
+
+
 def test_only_reachable_contraction_kernels_are_compiled():
     """The library holds the contraction kernels that some call launches and no others (every one lengthens
     the loading of the library): operand type, LDS stages, epilogue (loss, loss with per-token
-    errors, store, quadratic form), symmetric form, k tail, 64-row halves of a wave tile."""
+    errors, store, quadratic form), symmetric form, k tail, 64-row halves of a wave tile; of the wider and narrower tiles
+    operand type, epilogue, symmetric form, k tail and token blocks; of the integer ones LDS stages, epilogue, halves
+    and token blocks."""
     blob = open(tlq.LIB_PATH, "rb").read()
-    pat = rb"_ZN3tlq15gemm_dma_kernelINS_[34](F16|BF16)ELi(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)EEEvNS_7GemmDevE"
-    have = {(m[0].decode(), *map(int, m[1:])) for m in re.findall(pat, blob)}
-    LOSS, TOK, STORE, DOT = range(4)
+
+    def found(pattern):
+        names = {m for m in re.findall(rb"_ZN3tlq\d+" + pattern + rb"EEEvNS_7GemmDevE", blob)}
+        return {tuple(int(v) if v.isdigit() else v.decode() for v in m) for m in names}
+    ty = rb"INS_[34](F16|BF16)E"
+    have = found(rb"gemm_dma_kernel" + ty + rb"Li(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)")
     want = set()
     for tail in (0, 1):
-        for ty in ("F16", "BF16"):
-            want |= {(ty, 2, epi, 0, tail, 2) for epi in (LOSS, TOK, STORE)}
-            want |= {(ty, st, STORE, 0, tail, 1) for st in (2, 4)}
+        for t in ("F16", "BF16"):
+            want |= {(t, 2, epi, 0, tail, 2) for epi in (LOSS, TOK, STORE)}
+            want |= {(t, st, STORE, 0, tail, 1) for st in (2, 4)}
         want |= {("F16", st, LOSS, 0, tail, 1) for st in (2, 4)} | {("F16", 2, DOT, 1, tail, 2)}
     assert have == want, (sorted(have - want), sorted(want - have))
+    have = found(rb"gemm_width_kernel" + ty + rb"Li(\d)ELb(\d)ELb(\d)ELi(\d)")
+    want = {(t, STORE, 0, tail, jb) for t in ("F16", "BF16") for tail in (0, 1) for jb in (3, 5)}
+    want |= {("F16", epi, 0, tail, jb) for tail in (0, 1) for epi, jb in ((LOSS, 3), (LOSS, 5), (TOK, 5))}
+    want |= {("F16", DOT, 1, tail, 5) for tail in (0, 1)}
+    assert have == want, (sorted(have - want), sorted(want - have))
+    have = found(rb"gemm_i8_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)")
+    want = {(2, epi, 2, jb) for epi in (LOSS, STORE) for jb in (3, 4, 5)} | {(st, epi, 1, 4) for epi in (LOSS, STORE) for st in (2, 4)}
+    assert have == want, (sorted(have - want), sorted(want - have))
+
+
+def test_contraction_kernels_are_loaded_in_three_parts():
+    """A code object is loaded as a whole by the first call that needs one of its kernels: square, wider and narrower, and
+    integer tiles are one each, and the other kernels of the library are in none of them."""
+    families = [rb"gemm_dma_kernel", rb"gemm_width_kernel", rb"gemm_i8_kernel", rb"quant_row_kernel", rb"xstat_partial_kernel"]
+    objects = list(code_objects(open(tlq.LIB_PATH, "rb").read()))
+    where = [[i for i, o in enumerate(objects) if f in o] for f in families]
+    assert all(len(w) == 1 for w in where) and len({w[0] for w in where}) == len(families), where
