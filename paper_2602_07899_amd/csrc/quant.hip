@@ -521,7 +521,9 @@ __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t
     aq_load_tile<T>(X, n_tok, c_in, ldx, r0, c, x);
     for (int k = 0; k < nk; ++k) {
       if (inv_table && (!INT || c < c_in)) load8(inv_table + (int64_t)(k0 + k) * c_in + c, iv);
-      const int64_t at = ((int64_t)(k0 + k) * n_tok + r0) * ldc + c;      // (a zero gives the code zero behind c_in)
+      // (behind c_in any code will do, the weights are zeros there: a zero gives the code zero, unless the lane's last
+      // factor was infinite)
+      const int64_t at = ((int64_t)(k0 + k) * n_tok + r0) * ldc + c;
 #pragma unroll
       for (int r = 0; r < kAqRows; ++r) {
         if (r0 + r >= n_tok) break;

@@ -211,10 +211,11 @@ int main() {
   h = g; h.sym_k = true; h.c_out = 256;    EXPECT(tlq::launch_gemm_dot(h, nullptr), hipErrorInvalidValue);
 
   // ---- the tile of a launch: tokens of a tile, 128 for the small one
-  auto tile = [](int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int kinds, int64_t max_tiles, bool quadratic = false) {
+  auto tile = [](int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand, int kinds, int64_t max_tiles, bool quadratic = false,
+                 bool codes = false) {
     tlq::GemmArgs a{};
     a.n_tok = n_tok; a.c_in = c_in; a.c_out = c_out; a.n_cand = n_cand;
-    a.wide_patch = true; a.cand_outer = a.sym_k = quadratic;
+    a.wide_patch = !codes; a.cand_outer = quadratic || codes; a.sym_k = quadratic;
     const tlq::GemmTile t = tlq::gemm_tile(a, kinds, max_tiles);
     return t.small ? 128 : t.tok_blocks * 64;
   };
@@ -229,6 +230,14 @@ int main() {
   EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 8), 128);            // 2 x 4 small tiles, room for them and for one less
   EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 7), 192);
   EXPECT(tile(256, 512, 512, 20, tlq::kTileAll, 3), 256);            // 2 x 2 narrow ones do not fit either
+  // the products of codes whose tiles the GPU tests are about
+  EXPECT(tile(2500, 128, 4101, 1, tlq::kTileAll, INT64_MAX), 192);
+  EXPECT(tile(2496, 128, 4096, 1, tlq::kTileAll, INT64_MAX), 192);
+  EXPECT(tile(4000, 128, 4002, 1, tlq::kTileAll, INT64_MAX), 256);
+  EXPECT(tile(4700, 128, 4090, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(4800, 128, 4096, 1, tlq::kTileAll, INT64_MAX), 320);
+  EXPECT(tile(2000, 128, 3001, 1, tlq::kTileAll, INT64_MAX), 128);
+  EXPECT(tile(250, 64, 1000, 40, tlq::kTileAll, 7, false, true), 256);
   // long launches: as many wide tiles as fill the patches; a short last column of patches that always meets the same XCDs;
   // many rounds of narrow tiles
   EXPECT(tile(5120, 4096, 4096, 20, tlq::kTileAll, INT64_MAX), 320);

@@ -393,7 +393,7 @@ def test_activation_codes_at_strip_and_block_edges(gpu, n, ci, bf16):
 @pytest.mark.parametrize("n,ci,co,bits,sym,abits,bf16", [
     (1, 72, 1, 4, True, 8, False), (130, 128, 129, 8, True, 8, True), (257, 136, 258, 7, False, 6, False),
     (300, 1000, 70, 3, True, 8, True), (520, 1096, 261, 4, False, 8, False), (40, 4104, 33, 4, True, 2, False),
-    (64, 8200, 20, 2, False, 8, True), (9, 16384, 10, 4, True, 8, False)])
+    (64, 8200, 20, 2, False, 8, True), (9, 16384, 10, 4, True, 8, False), (1000, 136, 2001, 4, True, 8, False)])
 def test_integer_contraction_edges(gpu, n, ci, co, bits, sym, abits, bf16):
     """One step per weight row and activation codes: widths that are no multiple of the 128-code k-tile, each width class
     of the quantiser, ragged tiles; the losses of a search and the propagated output."""
@@ -428,6 +428,48 @@ def test_integer_contraction_edges(gpu, n, ci, co, bits, sym, abits, bf16):
     mag = (np.abs(c.astype(np.float64)) * sg.astype(np.float64)[:, None]) @ np.abs(deq.astype(np.float64)).T
     eps = 2.0 ** -8 if bf16 else 2.0 ** -11
     assert np.all(np.abs(got[:, :co] - want) <= (eps + 4 * 2.0 ** -24) * np.abs(want) + 2.0 ** -24 * (mag + 1.0))
+
+
+# (tokens, outputs): products of codes in tiles of 192, 256 and 320 tokens, more than 256 of 128 x 128 and fewer, each with
+# whole tiles and with remainders on both sides
+@pytest.mark.parametrize("n,co,bf16", [(2500, 4101, True), (2496, 4096, False), (4000, 4002, False), (4096, 4096, True),
+                                       (4700, 4090, True), (4800, 4096, False), (2000, 3001, False), (2048, 3072, True), (1000, 2001, True)])
+def test_integer_products_in_every_tile(gpu, n, co, bf16):
+    import torch
+    g = np.random.default_rng([48, n, co])
+    ci, rnd = 136, BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci)) * 2.0), rnd(g.standard_normal((co, ci)) * 0.05)
+    code, dt = (tlq.BF16, torch.bfloat16) if bf16 else (tlq.F16, torch.float16)
+    s = np.exp(g.uniform(-1.0, 1.0, ci)).astype(np.float32)
+    p = tlq.params(bits=4, group=0, symmetric=1, act_bits=8, x_dtype=code, yref_dtype=code)
+    Z = torch.full((n, co + -co % 8 + 8), 7.0, dtype=dt, device=gpu)
+    tlq.apply_best(dev(X, gpu, bf16), dev(W, gpu, bf16), torch.from_numpy(s).to(gpu), p, Z[:, :co])
+    assert bool((Z[:, co:] == 7.0).all())
+    c, sg = orc.act_quant(X, orc.recip_scale(s), 8)
+    deq = orc.fake_quant(W, s, 4, 0, symmetric=True)[3]
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to(gpu)
+    tc, td, ts = t(c), t(deq), t(sg)[:, None]
+    want, mag = (tc @ td.t()) * ts, (tc.abs() @ td.abs().t()) * ts
+    # the bound of test_integer_contraction_edges
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11
+    assert bool(((Z[:, :co].double() - want).abs() <= (eps + 4 * 2.0 ** -24) * want.abs() + 2.0 ** -24 * (mag + 1.0)).all())
+
+
+def test_integer_losses_in_square_tiles(gpu):
+    """40 candidates of 250 x 72 x 1000: 160 tiles of 256 x 256, one round; the partial sums of smaller ones would not fit."""
+    import torch
+    n, ci, co, na = 250, 72, 1000, 40
+    g = np.random.default_rng(49)
+    X, W = F16(g.standard_normal((n, ci)) * 2.0), F16(g.standard_normal((co, ci)) * 0.05)
+    Y = F16(orc.ref_output(X, W) + 0.05 * g.standard_normal((n, co)))
+    w, al = g.uniform(0.1, 1.0, n).astype(np.float32) / n, (np.arange(na) / na).astype(np.float32)
+    p = tlq.params(bits=4, group=0, symmetric=1, act_bits=8)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu)
+    f = lambda *s: torch.empty(s, dtype=torch.float32, device=gpu)
+    best, idx, losses, table = f(ci), torch.empty(1, dtype=torch.int32, device=gpu), f(na), f(na, ci)
+    tlq.scale_search(t(X), t(W), t(Y), t(w), t(al), p, best, idx, losses, s_table_out=table)
+    ref = orc.scale_search(X, W, Y, w, 4, 0, al, s_table=table.cpu().numpy(), symmetric=True, act_bits=8)
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=5e-5)      # the bound of test_integer_contraction_edges
 
 
 def test_search_over_more_candidates_than_a_block_takes(gpu):
@@ -648,10 +690,10 @@ def test_losses_of_narrow_and_wide_tiles(gpu, n, ci, co, na, act, bf16):
 
 
 @pytest.mark.parametrize("n,co,bf16", [(2500, 4104, True), (2496, 4096, False), (4700, 4104, False), (4800, 4096, True)])
-def test_stores_and_token_errors_of_narrow_and_wide_tiles(gpu, n, co, bf16):
+@pytest.mark.parametrize("ci", [72, 128])      # with and without a k tail
+def test_stores_and_token_errors_of_narrow_and_wide_tiles(gpu, n, co, bf16, ci):
     import torch
     g = np.random.default_rng([42, n, co])
-    ci = 72
     rnd = BF if bf16 else F16
     X, W = rnd(g.standard_normal((n, ci))), rnd(g.standard_normal((co, ci)) * 0.05)
     code, dt = (tlq.BF16, torch.bfloat16) if bf16 else (tlq.F16, torch.float16)
