@@ -134,10 +134,12 @@ def _ptr(t):
 
 
 def _stream():
-    """Handle of torch's current stream on the current device.  current_device() initialises torch's GPU state, or
-    raises: also in a forked child of a process that has used the GPU, where nothing may be launched."""
+    """Handle of torch's current stream on the current device.  In a forked child of a process that has used the GPU,
+    where nothing may be launched, init() raises."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if torch._C._cuda_isInBadFork():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ws(nbytes, like):
