@@ -61,7 +61,7 @@ constexpr int64_t kAttWide = 1LL << 27;   // row strides from which eight rows n
 // waves per SIMD (<= 168 registers, 32 KB of LDS a block) overlap the two.  The next 32 keys go from global memory
 // to the other LDS stage without registers (the 32 registers of a staged tile were what held it to two waves),
 // four K fragments are read ahead of the score product and the first V fragments before the softmax.
-// 128 samples x 1200 tokens x 40 heads, bf16: 3.35 -> 2.68 ms, 7.0 -> 5.0 million cycles; the clock falls from 2.14 to
+// 128 samples x 1200 tokens x 40 heads, bf16: 3.35 -> 2.73 ms, 7.0 -> 5.0 million cycles; the clock falls from 2.14 to
 // 1.90 GHz as the chip gets busier, so further overlap pays less than it saves.  (Two waves per SIMD with the
 // score product of the next half beside the softmax of this one: no faster than before, or spilled.)
 // The softmax advances 32 keys at a time with the exact running maximum as its reference, so that the

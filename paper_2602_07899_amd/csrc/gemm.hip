@@ -6,6 +6,7 @@
 #include "contraction.h"
 
 namespace tlq {
+
 // General kernel: two LDS stages; the global loads of k-tile i+1 are issued before the MFMAs of
 // k-tile i and written to the other stage afterwards; one barrier per k-tile.
 template <typename T, int BO, int BT, int WO, int WT, int EPI>
