@@ -163,8 +163,8 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   if (fp16) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
-    // (also with a float target, and with the token errors, whose epilogue never stages the target: 10,240 x 4096 x 4096
-    // fp16 us 256 -> 320: 338 -> 297 float, 318 -> 288 16-bit; 20,000 x 512 x 2048 76 -> 66 and 74 -> 65)
+    // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
+    // 2048 76 -> 66)
     e.tile = gemm_tile(g, kTileWide, e.tiles_o * e.tiles_t);
   }
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);

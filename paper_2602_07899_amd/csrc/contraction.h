@@ -330,7 +330,8 @@ __device__ __forceinline__ void unpack4(uint2 u, float (&y)[4]) {
 
 // Same sums as loss_rows for an interior wave tile with 16-bit Y_ref, but Y_ref goes through LDS and every lane picks
 // its values from there.  Reading Y_ref straight from the accumulator layout touches 16 or 32 lines per
-// instruction and each line 8 times.
+// instruction and each line 8 times (losses with token errors, us that way -> through LDS: 14,000 x 64 x 6144 with
+// 256-token tiles 81, with 320 89 -> 64; 27,730 x 2048 x 10,728 1054 and 1048 -> 999).
 template <typename YT, bool DOT, typename L, typename Acc>
 __device__ __forceinline__ void loss_rows_lds(const GemmDev& a, const void* Yref, const Acc& acc, const float* tsc,
                                               int64_t ow, int64_t tw, float (&sq)[L::NTB], float& part,
@@ -491,7 +492,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
   const void* Yc = a.Yref;
   if (DOT) Yc = (const unsigned char*)a.Yref + (int64_t)cand * a.y_cand_stride * (a.ydt == TLQ_F32 ? 4 : 2);
   bool done = false;
-  if constexpr (YLDS && (EPI == EPI_LOSS || DOT)) {
+  if constexpr (YLDS) {
     if (interior && a.ydt != TLQ_F32 && (a.ldy % 8) == 0 && ((uintptr_t)Yc % 16) == 0) {
       unsigned char* ylds = reinterpret_cast<unsigned char*>(rows) + wave * kStage;
       if (a.ydt == TLQ_F16) loss_rows_lds<F16, DOT, L>(a, Yc, acc, tsc, ow, tw, sq, part, ylds);
@@ -510,6 +511,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& a, const Acc& acc, 
   else if (a.ydt == TLQ_F16) loss_rows<TLQ_F16, true, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
   else loss_rows<TLQ_BF16, true, DOT, L, L::NQ>(a, Yc, acc, tsc, ow, tw, sq, part);
   if (EPI == EPI_LOSS_TOK) {
+    if (done) __syncthreads();       // (`done` is the same for the block; the row sums take the place of all waves' staging)
 #pragma unroll
     for (int tb = 0; tb < L::NTB; ++tb) {
       const float both = L::tok_sum(sq[tb]);

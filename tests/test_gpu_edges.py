@@ -721,19 +721,19 @@ def test_stores_and_token_errors_of_narrow_and_wide_tiles(gpu, n, co, bf16, ci):
 # outputs on both sides of half a tile (128), of a quad (4) and of the first quad; tokens in one and in several waves and
 # tiles, square and wide ones
 @pytest.mark.parametrize("co", [1, 3, 4, 66, 124, 128, 129, 380, 386])
-@pytest.mark.parametrize("n,fl", [(1, False), (130, True), (700, False), (33000, False), (33000, True)])
-def test_losses_where_half_a_tile_lies_past_the_edge(gpu, n, co, fl):
+@pytest.mark.parametrize("n,kind", [(1, "f16"), (130, "f32"), (700, "f16"), (700, "bf16"), (33000, "f16"), (33000, "f32")])
+def test_losses_where_half_a_tile_lies_past_the_edge(gpu, n, co, kind):
     import torch
     g = torch.Generator(device=gpu).manual_seed(n * 512 + co)
     ci = 64
-    X = torch.randn((n, ci), generator=g, device=gpu).half()
-    W = (torch.randn((co, ci), generator=g, device=gpu) * 0.05).half()
+    dt, act = {"f16": torch.float16, "f32": torch.float32, "bf16": torch.bfloat16}[kind], torch.bfloat16 if kind == "bf16" else torch.float16
+    X = torch.randn((n, ci), generator=g, device=gpu).to(act)
+    W = (torch.randn((co, ci), generator=g, device=gpu) * 0.05).to(act)
     prod = X.double() @ W.double().t()
-    dt = torch.float32 if fl else torch.float16
     Y = torch.full((n, co + -co % 8 + 8), float("nan"), dtype=dt, device=gpu)     # what lies beside the target is not used
     Y[:, :co] = (prod + torch.randn(prod.shape, generator=g, device=gpu)).to(dt)
     w = torch.rand(n, generator=g, device=gpu) / n
-    p = tlq.params(group=8, yref_dtype=tlq.F32 if fl else tlq.F16)
+    p = tlq.params(group=8, x_dtype=tlq.BF16 if kind == "bf16" else tlq.F16, yref_dtype={"f16": tlq.F16, "f32": tlq.F32, "bf16": tlq.BF16}[kind])
     e = ((Y[:, :co].double() - prod) ** 2).mean(1)
     want = float((e * w.double()).sum())
     for tok in (False, True):
