@@ -209,7 +209,8 @@ __device__ __forceinline__ void static_for(Fn&& f) {
 // launch that fits the chip in a few rounds.  NQ: the quads that hold live rows, straight code for half of them where the
 // other half lies past the edge (and none for a wave that does as a whole): with 64 outputs in tiles of 256 the reads
 // for nothing cost more than the product (100,000 x 64 x 64, us with a branch around each read, all reads, live halves:
-// loss 24.7, 28.9, 19.0; 20 candidates 427, 458, 324; with 136 outputs the loss 36.0, 24.3, 24.1).
+// loss 24.7, 28.9, 19.0; 20 candidates 427, 458, 324; with 136 outputs the loss 36.0, 24.3, 24.1).  Token blocks past the
+// edge end the walk (one token of 256 x 256: 14.3, 16.0, 13.4).
 // DOT replaces the squared residual by the product acc * y and drops the token weight.
 constexpr int k16Bit = -1;
 template <int YDT, bool FULL, bool DOT, typename L, int NQ, typename Acc>
@@ -219,6 +220,7 @@ __device__ __forceinline__ void loss_rows(const GemmDev& a, const void* Yref, co
   const bool quads = FULL || a.c_out >= 4, ragged = !FULL && (!quads || (a.c_out & 3) != 0);
 #pragma unroll
   for (int tb = 0; tb < L::NTB; ++tb) {
+    if (!FULL && tw + L::tok(tb, 0) >= a.n_tok) break;      // (sq is zero there)
     const int64_t tl = tw + L::tok(tb, lane);
     const bool t_ok = FULL || tl < a.n_tok;
     const int64_t t = t_ok ? tl : a.n_tok - 1;
