@@ -185,21 +185,28 @@ def test_gate_and_the_product_behind_it(gpu):
 
 
 def test_difference_form_of_few_channels(gpu):
-    """An 8-bit search of two candidates over 128 channels against one over 4 bits, which has no difference to subtract:
-    2.6 times the cost, 2.9 when the difference is formed in 320-token tiles."""
+    """The product that leaves the differences of 5000 x 128 x 13824 as floats: 0.89 times the contraction of two candidates
+    with them, 1.11 in 320-token tiles."""
     import torch
     n, ci, co, na = 5000, 128, 13824, 2
     X, W = torch.randn((n, ci), device=gpu).to(torch.bfloat16), (torch.randn((co, ci), device=gpu) * 0.02).to(torch.bfloat16)
     Y, w, al = torch.empty((n, co), dtype=torch.bfloat16, device=gpu), torch.full((n,), 1.0 / n, device=gpu), torch.tensor([0.0, 0.5], device=gpu)
     best, idx, losses = torch.empty(ci, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu), torch.empty(na, device=gpu)
-
-    def run(bits):
-        p = tlq.params(bits=bits, group=0, symmetric=1, x_dtype=tlq.BF16, yref_dtype=tlq.BF16)
-        tlq.ref_output(X, W, Y, p)
-        ws = torch.empty(tlq.scale_search_workspace_bytes(n, ci, co, na, p), dtype=torch.uint8, device=gpu)
-        return lambda: tlq.scale_search(X, W, Y, w, al, p, best, idx, losses, workspace=ws)
-    eight, four = micros(run(8), run(4))
-    assert eight < 2.8 * four, (eight, four)
+    p = tlq.params(bits=8, group=0, symmetric=1, x_dtype=tlq.BF16, yref_dtype=tlq.BF16)
+    tlq.ref_output(X, W, Y, p)
+    ws = torch.empty(tlq.scale_search_workspace_bytes(n, ci, co, na, p), dtype=torch.uint8, device=gpu)
+    run = lambda: tlq.scale_search(X, W, Y, w, al, p, best, idx, losses, workspace=ws)
+    run()
+    torch.cuda.synchronize()
+    tlq.profile_enable(True)
+    try:
+        tlq.profile_reset()
+        for _ in range(20):
+            run()
+        ms = {k.name: k.total_ms for k in tlq.profile_read()}
+    finally:
+        tlq.profile_enable(False)
+    assert ms["gemm_store"] < ms["gemm_loss"], ms
 
 
 def test_token_errors_beside_the_loss(gpu):
