@@ -366,9 +366,12 @@ __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
       }
     }
     if (MODE == Q_INT && cl == 0) {
+      // an infinite weight gives an infinite step, and the finite weights beside it 0 times infinity: NaN, which the
+      // integers cannot carry
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        if (row0 + r < a.c_out) a.steps[(int64_t)k * a.step_stride + row0 + r] = g[r].delta;
+        if (row0 + r < a.c_out)
+          a.steps[(int64_t)k * a.step_stride + row0 + r] = g[r].delta < __builtin_inff() ? g[r].delta : __builtin_nanf("");
     }
     if (MODE == Q_AUX && cl == 0) {
 #pragma unroll

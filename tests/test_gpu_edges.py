@@ -455,6 +455,31 @@ def test_integer_products_in_every_tile(gpu, n, co, bf16):
     assert bool(((Z[:, :co].double() - want).abs() <= (eps + 4 * 2.0 ** -24) * want.abs() + 2.0 ** -24 * (mag + 1.0)).all())
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("sym,inf", [(1, np.inf), (1, -np.inf), (0, np.inf), (0, -np.inf)])
+def test_integer_products_of_an_infinite_weight(gpu, bf16, sym, inf):
+    """The step of its row is infinite and the codes beside it are zero: NaN for every token, like the oracle's dequantised
+    weights, and nothing of it in the other rows."""
+    import torch
+    g = np.random.default_rng(50)
+    n, ci, co, rnd = 130, 136, 72, BF if bf16 else F16
+    X, W = rnd(g.standard_normal((n, ci)) * 2.0), rnd(g.standard_normal((co, ci)) * 0.05)
+    bad = W.copy()
+    bad[3, 7] = inf
+    with np.errstate(invalid="ignore"):
+        assert np.isnan(np.delete(orc.fake_quant(bad[3:4], None, 4, 0, symmetric=bool(sym))[3], 7)).all()
+    code, dt = (tlq.BF16, torch.bfloat16) if bf16 else (tlq.F16, torch.float16)
+    p = tlq.params(bits=4, group=0, symmetric=sym, act_bits=8, x_dtype=code, yref_dtype=code)
+    tX, s = dev(X, gpu, bf16), torch.ones(ci, device=gpu)
+    out = [torch.empty((n, co), dtype=dt, device=gpu) for _ in range(2)]
+    tlq.apply_best(tX, dev(W, gpu, bf16), s, p, out[0])
+    tW = dev(W, gpu, bf16)
+    tW[3, 7] = float(inf)
+    tlq.apply_best(tX, tW, s, p, out[1])
+    rest = [r for r in range(co) if r != 3]
+    assert bool(out[1][:, 3].isnan().all()) and torch.equal(out[0][:, rest].view(torch.int16), out[1][:, rest].view(torch.int16))
+
+
 def test_integer_losses_in_square_tiles(gpu):
     """40 candidates of 250 x 72 x 1000: 160 tiles of 256 x 256, one round; the partial sums of smaller ones would not fit."""
     import torch
