@@ -259,17 +259,26 @@ static double launch_rounds(const GemmDev& d, bool sym) {
 //   quadratic form 5120 x 4096 - - 2327 2586         search    8192 x 4096 x 1024 x 20     -  1237 1119 1255
 // Over 228 launches of three rounds and more the choice costs 0.2 % against the best of the three (1.0 % with
 // the plain count of tiles, whose worst cases were 21 % and 12 %).
+// The tiles of a symmetric contraction differ in length and fill each other's rounds: beyond two tiles a CU they are not
+// rounded up (4416 x 1057 and 2624 x 1061, channels x rows, 7 and 11 candidates, us 256 and 320: 215 and 178, 139 and 188);
+// up to there the plain count is the better guess (768 x 2840 x 7 45 and 58, 1408 x 528 x 20 58 and 51).  Over 220 quadratic
+// forms of 0.4 to 20 rounds the choice costs 2.5 % against the better of the two, 4.9 % by the plain count throughout
+// and 2.7 % with the XCDs' shares rounded up, 12 to 28 % behind the plain count in eight of those below two rounds.
 GemmTile gemm_tile(const GemmArgs& args, int kinds, int64_t max_tiles) {
   GemmArgs g = args;
   GemmTile best{false, 4};
   double best_cost = 1e300;
+  int64_t to, tt;
+  gemm_tile_counts(g.n_tok, g.c_out, best, &to, &tt);
+  const bool few = to * tt * g.n_cand <= 512;
   auto consider = [&](GemmTile t, double first, double each) {
-    int64_t to, tt;
     gemm_tile_counts(g.n_tok, g.c_out, t, &to, &tt);
     if (to * tt > max_tiles) return;
     g.tile() = t;
-    const double rounds = t.small ? (double)(to * tt) * g.n_cand / 512 : launch_rounds(make_dev(g), g.sym_k);
-    const double cost = first + each * (rounds <= 8.0 ? std::ceil(rounds - 1e-9) : rounds + 0.5);
+    const double even = (double)(to * tt) * g.n_cand / (t.small ? 512 : 256);
+    const double rounds = t.small || (g.sym_k && few) ? even : launch_rounds(make_dev(g), g.sym_k);
+    const double whole = rounds <= 8.0 ? std::ceil(rounds - 1e-9) : rounds + 0.5;
+    const double cost = first + each * (g.sym_k && !few ? rounds : whole);
     if (cost < best_cost) { best = t; best_cost = cost; }
   };
   if ((kinds & kTileSmall) && gemm_small_tiles(g.n_tok, g.c_out, g.n_cand)) consider(GemmTile{true, 0}, 0.06, 0.56);

@@ -247,6 +247,11 @@ int main() {
   EXPECT(tile(153600, 5120, 13824, 20, tlq::kTileAll, INT64_MAX), 320);
   EXPECT(tile(5120, 5120, 5120, 20, tlq::kTileWide, INT64_MAX, true), 320);
   EXPECT(tile(4096, 5120, 5120, 20, tlq::kTileWide, INT64_MAX, true), 256);
+  // quadratic forms of up to two square tiles a CU: whole rounds of all tiles; of more: the XCDs' shares as they are
+  EXPECT(tile(2840, 768, 768, 7, tlq::kTileWide, INT64_MAX, true), 256);
+  EXPECT(tile(528, 1408, 1408, 20, tlq::kTileWide, INT64_MAX, true), 320);
+  EXPECT(tile(1061, 2624, 2624, 11, tlq::kTileWide, INT64_MAX, true), 256);
+  EXPECT(tile(1057, 4416, 4416, 7, tlq::kTileWide, INT64_MAX, true), 320);
 
   // ---- host-side self test of the block -> tile map, and the timing bookkeeping
   int64_t blocks = 0;
