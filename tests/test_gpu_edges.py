@@ -43,6 +43,26 @@ def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
     assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("seq,heads,samples", [(1, 1, 1), (15, 2, 1), (17, 1, 5), (48, 1, 2), (79, 3, 1), (80, 1, 1), (95, 1, 1),
+                                               (97, 2, 1), (127, 1, 2), (129, 1, 1), (191, 1, 1), (193, 2, 1), (321, 1, 1)])
+def test_attention_tile_remainders(gpu, bf16, seq, heads, samples):
+    """64-key tiles of two 32-key blocks, of which a wave's last may be the first or the second; 16-query tiles that are
+    rescaled apart: scores that grow with the key make every step meet new maxima in some queries."""
+    import torch
+    g = np.random.default_rng([24, seq, heads])
+    n, width = seq * samples, heads * 128
+    rnd = BF if bf16 else F16
+    grow = 1.0 + 2.0 * (np.arange(n) % seq)[:, None] / seq
+    q, k, v = (np.asarray(rnd(g.standard_normal((n, width)) * f), np.float64) for f in (1.5, grow, 1.0))
+    want, mag = ost.causal_attention(q, k, v, heads, seq), ost.causal_attention(q, k, np.abs(v), heads, seq)
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    out = torch.empty((n, width), dtype=torch.bfloat16 if bf16 else torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # one rounding of every probability, one of the output
+    assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+
+
 @pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, "")])
 def test_attention_far_rows_and_partial_groups(gpu, bf16, seq, heads, samples, far):
     """Row strides of 2^27 elements and more (beyond 32-bit offsets inside a wave's rows) give the bits of dense rows;
