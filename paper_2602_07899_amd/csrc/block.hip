@@ -253,8 +253,13 @@ __global__ __launch_bounds__(256, 3) void causal_attention_kernel(
       const u16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 1024);
       vf[i % RING] = u16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     };
-    if (mine == 2) mask(1, s);
-    else if (mine == 1) mask(0, s);
+    if (mine <= 2) {      // (asked for in this order the steps without a mask keep all their values in registers)
+      if (mine == 2) {
+        mask(1, s);
+      } else {
+        mask(0, s);
+      }
+    }
     float mx[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
