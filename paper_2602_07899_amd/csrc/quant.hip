@@ -37,55 +37,66 @@ struct QuantDev {
 // their zero points (int8) and steps.
 enum { Q_FOLD = 0, Q_DIFF = 1, Q_AUX = 2, Q_INT = 3 };
 
-// Grid of one group: step, an approximate reciprocal, zero point; `slow` asks for true divisions.
-struct Grid { float delta, rd, zpf; bool slow; };
+// Grid of one group: step, an approximate reciprocal, zero point, and how near to a tie the reciprocal may be used.
+struct Grid { float delta, rd, zpf, lim; };
 
 // The integer codes need rint(fl(x / delta)).  With rd within one ulp of 1/delta, t = fl(x * rd) lies
 // within 2.4e-7 |t| of the rounded quotient, so rint(t) is that integer unless a half-integer sits inside
-// the gap; `tie_measure` below `kTieLimit` rules that out (with a factor of two to spare), and the rare
-// rest (one element in 10^5 at 4 bits) is divided.
-constexpr float kTieLimit = 0.49999976f;
-__device__ __forceinline__ float tie_measure(float t, float n) { return __builtin_fmaf(fabsf(t), 4.8e-7f, fabsf(t - n)); }
-
-// mx/mn: group maximum and minimum of ws (SYM: mx = max |ws|).  range / (2^b - 1) by a correction step on
-// range * fl(1 / (2^b - 1)): equal to the division for every significand and all eight divisors
-// (checked exhaustively); outside [1e-5, 1e36) and for NaN the division itself is used everywhere.
+// the gap; |t - rint(t)| < lim = 0.49999976 - 4.8e-7 max|t| rules that out for a whole group (with a factor of two to
+// spare), and the rare rest (one element in 10^5 at 4 bits) is divided, eight elements at a time.
+// Outside [1e-5, 1e36) and for NaN lim is negative or NaN: everything is divided.
 template <bool SYM>
-__device__ __forceinline__ Grid make_grid(float mx, float mn, const QuantDev& a) {
+__device__ __forceinline__ Grid make_grid(float mx, float mn, const QuantDev& a, float& tie) {
   Grid g;
   const float rng = fmaxf(SYM ? mx : mx - mn, kRangeFloor);
   const float dv = SYM ? a.qhi : a.qmax;
-  g.slow = !(rng < 1e36f);
+  // range / (2^b - 1) by a correction step on range * fl(1 / (2^b - 1)): equal to the division for every significand and
+  // all eight divisors (checked exhaustively)
   const float q0 = rng * a.rq;
   g.delta = __builtin_fmaf(__builtin_fmaf(-q0, dv, rng), a.rq, q0);
-  if (g.slow) {
-    asm volatile("" ::: "memory");     // a branch, not a division that is computed and dropped
-    g.delta = rng / dv;
-  }
   g.rd = __builtin_amdgcn_rcpf(g.delta);
+  const float top = (SYM ? mx : __builtin_amdgcn_fmed3f(mx, -mn, __builtin_inff())) * g.rd;     // (the larger of the two)
+  g.lim = rng < 1e36f ? __builtin_fmaf(top, -4.8e-7f, 0.49999976f) : -1.0f;
   if (SYM) {
     g.zpf = (float)a.half;
+    tie = 0.0f;
   } else {
-    const float x = -mn, t = x * g.rd;
-    float z = rintf(t);
-    if (g.slow || !(tie_measure(t, z) < kTieLimit)) z = rintf(x / g.delta);
-    g.zpf = fminf(fmaxf(z, 0.0f), a.qmax);
+    const float t = -mn * g.rd, z = rintf(t);
+    tie = fabsf(t - z);
+    g.zpf = __builtin_amdgcn_fmed3f(z, 0.0f, a.qmax);
   }
   return g;
 }
+// the same with divisions
+template <bool SYM>
+__device__ __forceinline__ void divide_grid(float mx, float mn, const QuantDev& a, Grid& g) {
+  const float rng = fmaxf(SYM ? mx : mx - mn, kRangeFloor);
+  if (!(rng < 1e36f)) g.delta = rng / (SYM ? a.qhi : a.qmax);
+  if (!SYM) g.zpf = fminf(fmaxf(rintf(-mn / g.delta), 0.0f), a.qmax);
+}
+template <bool SYM>
+__device__ __forceinline__ Grid grid_of(float mx, float mn, const QuantDev& a) {
+  float tie;
+  Grid g = make_grid<SYM>(mx, mn, a, tie);
+  if (!(tie < g.lim)) divide_grid<SYM>(mx, mn, a, g);
+  return g;
+}
 
-// rint(fl(ws / delta)) of eight values, one test for all of them
-__device__ __forceinline__ void rint_quotient8(const float (&ws)[8], const Grid& g, float (&n)[8]) {
-  float e = 0.0f;
+// rint(fl(ws / delta)) of eight values unless the result, or `tie` from before, reaches lim; the larger of the two measures
+__device__ __forceinline__ float rint_quotient8(const float (&ws)[8], const Grid& g, float tie, float (&n)[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const float t = ws[j] * g.rd;
     n[j] = rintf(t);
-    e = fmaxf(e, tie_measure(t, n[j]));
+    tie = fmaxf(tie, fabsf(t - n[j]));
   }
-  if (g.slow || !(e < kTieLimit)) {
+  return tie;
+}
+__device__ __forceinline__ void divide8(const float (&ws)[8], const Grid& g, float (&n)[8]) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) n[j] = rintf(ws[j] / g.delta);
+  for (int j = 0; j < 8; ++j) {
+    n[j] = rintf(ws[j] / g.delta);
+    asm volatile("" : "+v"(n[j]) :: "memory");     // one after the other, and in a branch, not computed and dropped
   }
 }
 
@@ -99,6 +110,12 @@ __device__ __forceinline__ void widen8(const uint4& v, float (&w)[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) w[j] = T::to_float((uint16_t)(u[j >> 1] >> ((j & 1) * 16)));
 }
+__device__ __forceinline__ void times8(const float (&w)[8], const float (&s)[8], float (&ws)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
+}
+// what is worked out from v is worked out again, not held in registers from before
+__device__ __forceinline__ void anew(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 template <bool SYM>
 __device__ __forceinline__ void range8(const float (&ws)[8], float& mx, float& mn) {
 #pragma unroll
@@ -108,18 +125,23 @@ __device__ __forceinline__ void range8(const float (&ws)[8], float& mx, float& m
   }
 }
 
-// four small integers as bytes
+// two floats rounded to fp16 (one instruction; bit-equal to two conversions for all 2^32 floats)
+__device__ __forceinline__ uint32_t pack_f16(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), f16x2));
+}
+// four small integers as bytes: beside 1.5 * 2^23 the low byte of the float is the integer's
 __device__ __forceinline__ uint32_t pack_i8(float a, float b, float c, float d) {
-  return ((uint32_t)(int)a & 0xffu) | (((uint32_t)(int)b & 0xffu) << 8) | (((uint32_t)(int)c & 0xffu) << 16) | ((uint32_t)(int)d << 24);
+  auto bits = [](float v) { return __builtin_bit_cast(uint32_t, v + 12582912.0f); };
+  return __builtin_amdgcn_perm(bits(b), bits(a), 0x0c0c0400u) | __builtin_amdgcn_perm(bits(d), bits(c), 0x04000c0cu);
 }
 
 // Eight quantised values of row `row`, channels c .. c+7 go to memory (`what`: their place in the operand).
 template <typename T, bool SYM, int MODE>
-__device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const float (&w)[8], const float (&ws)[8],
+__device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const float (&w)[8], float (&n)[8],
                                       const float (&inv)[8], const float (&cs)[8], float wsub, uint16_t* what,
                                       int64_t row, int64_t c) {
-  float n[8];
-  rint_quotient8(ws, g, n);
   uint32_t hw[4] = {0, 0, 0, 0}, cw[2] = {0, 0};
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -150,12 +172,16 @@ __device__ __forceinline__ void emit8(const QuantDev& a, const Grid& g, const fl
       } else {
         asm("" : "+v"(f));               // rounded to float, then to 16 bits (see above)
       }
-      hw[j >> 1] |= (uint32_t)F16::from_float(f) << ((j & 1) * 16);
+      n[j] = f;
     }
   }
   if constexpr (MODE == Q_INT) {
     store8(what, pack_i8(n[0], n[1], n[2], n[3]), pack_i8(n[4], n[5], n[6], n[7]), a.nt);
     return;
+  }
+  if constexpr (MODE != Q_AUX) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hw[j] = pack_f16(n[2 * j], n[2 * j + 1]);
   }
   const uint4 out = make_uint4(hw[0], hw[1], hw[2], hw[3]);
   if constexpr (MODE == Q_AUX) {
@@ -184,6 +210,34 @@ __device__ __forceinline__ float lanes_reduce(float v, int lanes) {
   return v;
 }
 
+// mx and mn of R rows over 16 lanes each, every lane gets them.  In assembly: the exchange is part of the maximum
+// (the compiler moves first and then makes sure that the moved value is no signalling NaN, three instructions for one);
+// a value is read by another lane's instruction two wait states behind its write at the earliest.
+template <bool SYM, int R>
+__device__ __forceinline__ void row_ranges(float (&mx)[R], float (&mn)[R]) {
+#define TLQ_STEP(op, reg, how) "v_" op "_f32_dpp %" reg ", %" reg ", %" reg " " how " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define TLQ_FOUR(m) m("quad_perm:[1,0,3,2]") m("quad_perm:[2,3,0,1]") m("row_half_mirror") m("row_mirror")
+  if constexpr (R == 2 && !SYM) {
+#define TLQ_ALL(how) TLQ_STEP("max", "0", how) TLQ_STEP("min", "1", how) TLQ_STEP("max", "2", how) TLQ_STEP("min", "3", how)
+    asm("s_nop 1\n\t" TLQ_FOUR(TLQ_ALL) : "+v"(mx[0]), "+v"(mn[0]), "+v"(mx[1]), "+v"(mn[1]));
+#undef TLQ_ALL
+  } else if constexpr (R == 2) {
+#define TLQ_ALL(how) TLQ_STEP("max", "0", how) TLQ_STEP("max", "1", how) "s_nop 0\n\t"
+    asm("s_nop 1\n\t" TLQ_FOUR(TLQ_ALL) : "+v"(mx[0]), "+v"(mx[1]));
+#undef TLQ_ALL
+  } else if constexpr (!SYM) {
+#define TLQ_ALL(how) TLQ_STEP("max", "0", how) TLQ_STEP("min", "1", how) "s_nop 0\n\t"
+    asm("s_nop 1\n\t" TLQ_FOUR(TLQ_ALL) : "+v"(mx[0]), "+v"(mn[0]));
+#undef TLQ_ALL
+  } else {
+#define TLQ_ALL(how) TLQ_STEP("max", "0", how) "s_nop 1\n\t"
+    asm("s_nop 1\n\t" TLQ_FOUR(TLQ_ALL) : "+v"(mx[0]));
+#undef TLQ_ALL
+  }
+#undef TLQ_FOUR
+#undef TLQ_STEP
+}
+
 __device__ __forceinline__ float diff_factor(const QuantDev& a) {
   return a.xmax_bits ? __builtin_ldexpf(1.0f, shift_from_bf16_bits(*a.xmax_bits)) : 1.0f;
 }
@@ -192,72 +246,103 @@ __device__ __forceinline__ float diff_factor(const QuantDev& a) {
 // group is `group/8` adjacent lanes and a wave covers 512 channels; W stays in registers while the candidates
 // are walked, a candidate's scales are loaded once for the R rows.  `packed`: the lanes of a group are rounded up
 // to a power of two (the spare ones repeat the group's first channels and store nothing) and the groups of all
-// rows fill the waves one after the other.  Bound by vector ALU issue: ~135 vector instructions per 512 weights
-// and candidate, ~145 in the difference form (250 with a division and a tie branch per element, divisions for
-// step and zero point, and shuffles through LDS).  20 candidates of 4096 x 4096 (0.7 GB
-// written): 278 -> 195 us.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).  Groups of 24, 40
-// and 56 of 4096 x 4100 with every output, a wave per group -> this way: 252 -> 22, 153 -> 26, 111 -> 20 us.
+// rows fill the waves one after the other.  Bound by vector ALU issue and by what stores reach: 99 vector instructions per
+// 512 weights and candidate (135 with a branch and a tie measure with |t| per element, three branches a row, lane exchanges
+// apart from the maxima, two conversions and an OR per pair), and five candidates a wave (see launch_quant).  20
+// candidates of 4096 x 4096 (0.7 GB written): 171 -> 142 us (4.7 TB/s), of 4096 x 11008 488 -> 398, of 13824 x 5120 757 ->
+// 650; difference form of 5120 x 5120 335 -> 256.  LPG > 0 fixes the group at compile time (16 lanes: the usual 128).
+// Groups of 24, 40 and 56 of 4096 x 4100 with every output, a wave per group -> this way: 252 -> 22, 153 -> 26, 111 -> 20 us.
 template <typename T, bool SYM, int MODE, int R, int LPG>
 __global__ __launch_bounds__(256) void quant_pow2_kernel(QuantDev a) {
   const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  // (32 bits: a wave has 512 weights, and no memory holds 2^41)
+  const uint32_t wave = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lpg = LPG > 0 ? LPG : 1 << a.shift;
-  int64_t row0, c;
+  int64_t row0;                    // the same for the whole wave unless groups are packed
+  uint32_t c;
   bool valid, active;              // the lane's channels exist; it also stores them
   if (LPG == 0 && a.packed) {
     const uint32_t groups = (uint32_t)(a.c_in / a.group);
-    const uint32_t unit = (uint32_t)wave * (64u >> a.shift) + (uint32_t)(lane >> a.shift);   // (row, group), flat
+    const uint32_t unit = wave * (64u >> a.shift) + (uint32_t)(lane >> a.shift);   // (row, group), flat
     const int chunk = lane & (lpg - 1);
     const bool spare = chunk * 8 >= a.group;
     row0 = (int64_t)(unit / groups) * R;
-    c = (int64_t)(unit % groups) * a.group + (spare ? 0 : chunk * 8);
+    c = unit % groups * (uint32_t)a.group + (spare ? 0 : chunk * 8);
     valid = row0 < a.c_out;
     active = valid && !spare;
   } else {
-    const int64_t cblocks = (a.c_in + 511) / 512;
-    row0 = wave / cblocks * R;
+    const uint32_t cblocks = ((uint32_t)a.c_in + 511) / 512, rb = wave / cblocks;
+    row0 = (int64_t)rb * R;
     if (row0 >= a.c_out) return;
-    c = (wave % cblocks) * 512 + lane * 8;
-    valid = active = c < a.c_in;
+    c = (wave - rb * cblocks) * 512 + lane * 8;
+    valid = active = c < (uint32_t)a.c_in;
   }
+  if (!valid) { row0 = 0; c = 0; }       // (reads what is there, stores nothing)
 
   float w[R][8];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (valid && row0 + r < a.c_out) v = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + c);
-    widen8<T>(v, w[r]);
+    const int64_t row = row0 + r < a.c_out ? row0 + r : row0;
+    widen8<T>(*reinterpret_cast<const uint4*>(a.W + row * a.ldw + c), w[r]);
   }
   const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
   float s[8], inv[8], cs[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) { s[j] = 1.0f; inv[j] = 1.0f; cs[j] = 1.0f; }
-  if (MODE == Q_DIFF && valid && a.col_scale) load8(a.col_scale + c, cs);
+  if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
   const int k0 = (int)blockIdx.y * a.cand_step;
   const int k1 = k0 + a.cand_step < a.n_cand ? k0 + a.cand_step : a.n_cand;
-  const float* ps = a.s_table && valid ? a.s_table + (int64_t)k0 * a.c_in + c : nullptr;
-  const float* pi = MODE != Q_AUX && a.inv_table && valid ? a.inv_table + (int64_t)k0 * a.c_in + c : nullptr;
-  uint16_t* out = MODE != Q_AUX ? a.what + (int64_t)k0 * a.what_cand_stride + row0 * a.c_in + c : nullptr;
+  const float* ps = a.s_table ? a.s_table + (int64_t)k0 * a.c_in : nullptr;
+  const float* pi = MODE != Q_AUX && a.inv_table ? a.inv_table + (int64_t)k0 * a.c_in : nullptr;
+  uint16_t* out = MODE != Q_AUX ? a.what + (int64_t)k0 * a.what_cand_stride : nullptr;
 #pragma unroll 1
   for (int k = k0; k < k1; ++k) {
-    if (ps) { load8(ps, s); ps += a.c_in; }
-    if (pi) { load8(pi, inv); pi += a.c_in; }
+    if (ps) { load8(ps + c, s); ps += a.c_in; }
+    if (pi) { load8(pi + c, inv); pi += a.c_in; }
+    // (the rows side by side, with one branch for what has to be divided in any of them)
+    float n[R][8], mx[R], mn[R];
+    Grid g[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      float ws[8];
+      mx[r] = SYM ? 0.0f : -__builtin_inff();
+      mn[r] = __builtin_inff();
+      times8(w[r], s, n[r]);
+      range8<SYM>(n[r], mx[r], mn[r]);
+    }
+    if constexpr (LPG == 16) {
+      row_ranges<SYM, R>(mx, mn);
+    } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) ws[j] = w[r][j] * s[j];
-      float mx = SYM ? fabsf(ws[0]) : ws[0], mn = ws[0];
-      range8<SYM>(ws, mx, mn);
-      mx = lanes_reduce<true>(mx, lpg);
-      if (!SYM) mn = lanes_reduce<false>(mn, lpg);
-      const Grid g = make_grid<SYM>(mx, mn, a);
-      if (!active || row0 + r >= a.c_out) continue;
-      emit8<T, SYM, MODE>(a, g, w[r], ws, inv, cs, wsub, MODE != Q_AUX ? out + r * a.c_in : nullptr, row0 + r, c);
-      if (MODE == Q_AUX && (lane & (lpg - 1)) == 0) {
-        const int64_t gidx = (row0 + r) * (a.c_in / a.group) + c / a.group;
-        if (a.zp) a.zp[gidx] = (uint8_t)g.zpf;
-        if (a.delta) a.delta[gidx] = g.delta;
+      for (int r = 0; r < R; ++r) {
+        mx[r] = lanes_reduce<true>(mx[r], lpg);
+        if (!SYM) mn[r] = lanes_reduce<false>(mn[r], lpg);
+      }
+    }
+    bool near = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float tie;
+      g[r] = make_grid<SYM>(mx[r], mn[r], a, tie);
+      near |= !(rint_quotient8(n[r], g[r], tie, n[r]) < g[r].lim);
+    }
+    if (near) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        divide_grid<SYM>(mx[r], mn[r], a, g[r]);
+        times8(w[r], s, n[r]);
+        divide8(n[r], g[r], n[r]);
+      }
+    }
+    if (active) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (row0 + r >= a.c_out) break;
+        emit8<T, SYM, MODE>(a, g[r], w[r], n[r], inv, cs, wsub, MODE != Q_AUX ? out + (row0 + r) * a.c_in + c : nullptr, row0 + r, c);
+        if (MODE == Q_AUX && (lane & (lpg - 1)) == 0) {
+          const int64_t gidx = (row0 + r) * (a.c_in / a.group) + c / a.group;
+          if (a.zp) a.zp[gidx] = (uint8_t)g[r].zpf;
+          if (a.delta) a.delta[gidx] = g[r].delta;
+        }
       }
     }
     if (MODE != Q_AUX) out += a.what_cand_stride;
@@ -265,30 +350,39 @@ __global__ __launch_bounds__(256) void quant_pow2_kernel(QuantDev a) {
 }
 
 // Any other group of up to 16384 channels, whole rows among them: NWG waves (1 or 4) own one group of R
-// rows, a lane CH chunks of 8 channels, `64 NWG` chunks apart.  The weights stay packed in registers, each
-// candidate's scales are read twice (range, then codes; the second time from L1) for R rows.  20
-// candidates of 4096 x 4096, group = row: 1143 -> 190 us (2-byte loads, two sweeps over W before).
+// rows, a lane CH chunks of 8 channels, `64 NWG` chunks apart.  The weights stay packed in registers; times a
+// candidate's scales they stay there from the range to the codes where two rows (or one of four chunks) fit, elsewhere they are
+// worked out twice.  Bound like the above; the registers decide how many waves there are (widened weights and column factors
+// that the compiler held through all candidates took 100 - 200 of them).  us, group = row, 20 candidates: 4096 x 4096 as int8
+// 131 -> 107, 5120 x 5120 290 -> 237; 12 candidates' differences of 1400 x 1096 31 -> 25; 16 candidates of 3000 x 13824 412
+// -> 383, as int8 of 3000 x 12288 265 -> 245.
 template <typename T, bool SYM, int MODE, int NWG, int CH, int R>
 __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
   __shared__ float red[2][4][2 * R];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t G = a.c_in / a.group;
-  const int64_t unit = NWG == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wv;
-  const int64_t row0 = unit / G * R, gi = unit % G;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t G = (uint32_t)(a.c_in / a.group);             // (32 bits: no memory holds 2^32 units of groups)
+  const uint32_t unit = NWG == 4 ? blockIdx.x : blockIdx.x * 4u + (uint32_t)wv;
+  const int64_t row0 = (int64_t)(unit / G) * R;
+  const uint32_t gi = unit % G;
   if (NWG == 1 && row0 >= a.c_out) return;
-  const int64_t cl = ((NWG == 4 ? wv * 64 : 0) + lane) * 8;    // channel of chunk 0 inside the group
-  const int64_t cg = gi * a.group;
-  constexpr int64_t STEP = (int64_t)NWG * 512;
+  const uint32_t group = (uint32_t)a.group, cg = gi * group;
+  const uint32_t cl = ((NWG == 4 ? wv * 64 : 0) + lane) * 8;   // channel of chunk 0 inside the group
+  constexpr uint32_t STEP = (uint32_t)NWG * 512;
+  // the weights times the scales stay in registers between the two sweeps where they fit, and are worked out twice elsewhere
+  constexpr bool KEEP = R * CH <= 4;
+  constexpr bool ANEW = KEEP || CH > 4 || MODE != Q_FOLD;     // (the widened weights of four chunks and two rows fit beside the rest)
+  // chunk i of the lane; past the group's end its first channels again, which change no range and are not stored; a wave
+  // of which nothing is left skips the chunk
+  auto chunk = [&](int i) { return cl + i * STEP < group ? cl + i * STEP : 0u; };
+  auto some = [&](int i) { return (NWG == 4 ? wv * 512u : 0u) + i * STEP < group; };
 
   uint4 wp[R][CH];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < R; ++r) {
+    const int64_t row = row0 + r < a.c_out ? row0 + r : row0;
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      wp[r][i] = make_uint4(0, 0, 0, 0);
-      if (row0 + r < a.c_out && cl + i * STEP < a.group)
-        wp[r][i] = *reinterpret_cast<const uint4*>(a.W + (row0 + r) * a.ldw + cg + cl + i * STEP);
-    }
+    for (int i = 0; i < CH; ++i) wp[r][i] = *reinterpret_cast<const uint4*>(a.W + row * a.ldw + cg + chunk(i));
+  }
   const float wsub = MODE == Q_DIFF ? diff_factor(a) : 0.0f;
   float s[8], inv[8], cs[8];
 #pragma unroll
@@ -297,19 +391,22 @@ __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
   const int k1 = k0 + a.cand_step < a.n_cand ? k0 + a.cand_step : a.n_cand;
 #pragma unroll 1
   for (int k = k0; k < k1; ++k) {
-    float mx[R], mn[R];
+    const float* ps = a.s_table ? a.s_table + (int64_t)k * a.c_in + cg : nullptr;
+    const float* pi = MODE < Q_AUX && a.inv_table ? a.inv_table + (int64_t)k * a.c_in + cg : nullptr;
+    float n[KEEP ? R : 1][KEEP ? CH : 1][8], mx[R], mn[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) { mx[r] = SYM ? 0.0f : -__builtin_inff(); mn[r] = __builtin_inff(); }
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
-      if (cl + i * STEP >= a.group) continue;
-      if (a.s_table) load8(a.s_table + (int64_t)k * a.c_in + cg + cl + i * STEP, s);
+      __builtin_amdgcn_sched_barrier(0);     // (not all chunks' scales at once)
+      if (!some(i)) continue;
+      if (ps) load8(ps + chunk(i), s);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        float ws[8];
-        widen8<T>(wp[r][i], ws);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ws[j] *= s[j];
+        float w[8], (&ws)[8] = n[KEEP ? r : 0][KEEP ? i : 0];
+        if (ANEW) anew(wp[r][i]);
+        widen8<T>(wp[r][i], w);
+        times8(w, s, ws);
         range8<SYM>(ws, mx[r], mn[r]);
       }
     }
@@ -335,34 +432,43 @@ __global__ __launch_bounds__(256) void quant_row_kernel(QuantDev a) {
     }
     Grid g[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) g[r] = make_grid<SYM>(mx[r], mn[r], a);
+    for (int r = 0; r < R; ++r) g[r] = grid_of<SYM>(mx[r], mn[r], a);
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
-      const int64_t c = cg + cl + i * STEP;
-      if constexpr (MODE == Q_INT) {       // (the group is the row)
-        if (cl + i * STEP >= a.group) {
-#pragma unroll
-          for (int r = 0; r < R; ++r)
-            if (row0 + r < a.c_out && c < a.ld8)
-              *reinterpret_cast<uint2*>(a.w8 + (int64_t)k * a.w8_cand_stride + (row0 + r) * a.ld8 + c) = make_uint2(0, 0);
-          continue;
-        }
-      }
-      if (cl + i * STEP >= a.group) continue;
-      if (a.s_table) load8(a.s_table + (int64_t)k * a.c_in + c, s);
-      if (MODE < Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
+      __builtin_amdgcn_sched_barrier(0);
+      const bool in = cl + i * STEP < group;
+      const uint32_t c = cg + chunk(i);
+      if (MODE != Q_INT && !some(i)) continue;     // (the integer rows have zeros behind the last channel)
+      if (!KEEP && ps) load8(ps + chunk(i), s);
+      if (pi) load8(pi + chunk(i), inv);
       if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
+        float w[8], (&q)[8] = n[KEEP ? r : 0][KEEP ? i : 0];
+        if (MODE != Q_INT || some(i)) {
+          if (!KEEP) {
+            if (ANEW) anew(wp[r][i]);
+            widen8<T>(wp[r][i], w);
+            times8(w, s, q);
+          }
+          if (!(rint_quotient8(q, g[r], 0.0f, q) < g[r].lim)) {
+            if (KEEP && ps) load8(ps + chunk(i), s);
+            anew(wp[r][i]);
+            widen8<T>(wp[r][i], w);
+            times8(w, s, q);
+            divide8(q, g[r], q);
+          }
+          if (MODE == Q_DIFF && (KEEP || ANEW)) { anew(wp[r][i]); widen8<T>(wp[r][i], w); }
+        }
         if (row0 + r >= a.c_out) continue;
-        float w[8], ws[8];
-        widen8<T>(wp[r][i], w);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
-        uint16_t* at = nullptr;
-        if (MODE == Q_INT) at = (uint16_t*)(a.w8 + (int64_t)k * a.w8_cand_stride + (row0 + r) * a.ld8 + c);
-        else if (MODE != Q_AUX) at = a.what + (int64_t)k * a.what_cand_stride + (row0 + r) * a.c_in + c;
-        emit8<T, SYM, MODE>(a, g[r], w, ws, inv, cs, wsub, at, row0 + r, c);
+        if (MODE == Q_INT) {               // (the group is the row)
+          int8_t* at = a.w8 + (int64_t)k * a.w8_cand_stride + (row0 + r) * a.ld8 + cl + i * STEP;
+          if (in) emit8<T, SYM, MODE>(a, g[r], w, q, inv, cs, wsub, (uint16_t*)at, row0 + r, c);
+          else if (cl + i * STEP < a.ld8) *reinterpret_cast<uint2*>(at) = make_uint2(0, 0);
+        } else if (in) {
+          emit8<T, SYM, MODE>(a, g[r], w, q, inv, cs, wsub,
+                              MODE != Q_AUX ? a.what + (int64_t)k * a.what_cand_stride + (row0 + r) * a.c_in + c : nullptr, row0 + r, c);
+        }
       }
     }
     if (MODE == Q_INT && cl == 0) {
@@ -410,16 +516,17 @@ __global__ __launch_bounds__(256) void quant_any_kernel(QuantDev a) {
     }
     mx = lanes_reduce<true>(mx, 64);
     if (!SYM) mn = lanes_reduce<false>(mn, 64);
-    const Grid g = make_grid<SYM>(mx, mn, a);
+    const Grid g = grid_of<SYM>(mx, mn, a);
     for (int64_t c = c0 + lane * 8; c < c0 + a.group; c += 512) {
-      float w[8], ws[8];
+      float w[8], ws[8], n[8];
       widen8<T>(*reinterpret_cast<const uint4*>(a.W + row * a.ldw + c), w);
       if (sk) load8(sk + c, s);
       if (MODE != Q_AUX && a.inv_table) load8(a.inv_table + (int64_t)k * a.c_in + c, inv);
       if (MODE == Q_DIFF && a.col_scale) load8(a.col_scale + c, cs);
 #pragma unroll
       for (int j = 0; j < 8; ++j) ws[j] = w[j] * s[j];
-      emit8<T, SYM, MODE>(a, g, w, ws, inv, cs, wsub,
+      if (!(rint_quotient8(ws, g, 0.0f, n) < g.lim)) divide8(ws, g, n);
+      emit8<T, SYM, MODE>(a, g, w, n, inv, cs, wsub,
                           MODE != Q_AUX ? a.what + (int64_t)k * a.what_cand_stride + row * a.c_in + c : nullptr, row, c);
     }
     if (MODE == Q_AUX && lane == 0) {
@@ -435,12 +542,12 @@ __global__ __launch_bounds__(256) void quant_any_kernel(QuantDev a) {
 //   code = clip(rint(xt / sigma), -2^(n-1), 2^(n-1) - 1).
 // A block owns eight rows, its waves strips of 512 channels.  A strip's tile (8 rows x 8 channels a lane) stays in
 // registers for all candidates: first the row maxima of every candidate, which meet in LDS, then, with the tile
-// read again (from cache), the codes.  Bound by vector ALU issue, 7 instructions an element and candidate.  The codes are
+// read again (from cache), the codes.  Bound by vector ALU issue, 7 - 8 instructions an element and candidate.  The codes are
 // fp16 integers (exact), so the contraction runs on the same MFMA path and the per-token step is applied to the
 // accumulators in its epilogue.
 // Four launches (maxima through shuffles and global atomics, one tie branch per element) -> one: one candidate
 // of 3678 x 4096 24.0 -> 13.5 us, 128 x 4096 15.2 -> 6.2, 2000 x 13824 51 -> 30, 1000000 x 8 301 -> 164; 20 candidates of
-// 3678 x 4096 250 -> 170 us (the 0.6 GB of codes at 3.5 TB/s).
+// 3678 x 4096 250 -> 170 us (the 0.6 GB of codes at 3.5 TB/s); as int8 117 -> 105 with bytes cut out of biased floats.
 constexpr int kAqRows = 8;      // rows per block
 constexpr int kAqCols = 512;    // channels per strip (64 lanes x 8)
 constexpr int kAqWaves = 8;     // waves per block at most
@@ -534,11 +641,12 @@ __global__ __launch_bounds__(kAqWaves * 64) void act_quant_kernel(const uint16_t
         Grid g;
         g.delta = step[k][r];
         g.rd = __builtin_amdgcn_rcpf(g.delta);
-        g.slow = !(g.delta < 1e36f);
+        // (the step came from a division by qa: no quotient is beyond qa and a rounding)
+        g.lim = g.delta < 1e36f ? 0.49999976f - 4.8e-7f * (qa + 1.0f) : -1.0f;
         float xt[8], n[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) xt[j] = x[r][j] * iv[j];
-        rint_quotient8(xt, g, n);
+        if (!(rint_quotient8(xt, g, 0.0f, n) < g.lim)) divide8(xt, g, n);
         if constexpr (INT) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) n[j] = __builtin_amdgcn_fmed3f(n[j], -qa - 1.0f, qa);
@@ -589,6 +697,11 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
     int64_t split = waves < 8192 ? 8192 / waves : 1;
     if (split > d.n_cand) split = d.n_cand;
     d.cand_step = (int)ceil_div(d.n_cand, split);
+    // Never more than five candidates a wave: what is written at any time are then a few stretches of memory and not
+    // twenty (stores alone, 20 x 4096 x 4096: 4.3 TB/s with all candidates in a wave, 5.6 with five, 3.9 with one, which
+    // reads W as often as it writes; this kernel, us by candidates a wave 2, 3, 5, 10, 20: 161, 148, 142, 151, 158; in cache,
+    // 16 x 3000 x 3000 in whole rows 3, 5, 10, 16: 73, 70, 73, 89)
+    if (d.cand_step > 5) d.cand_step = (int)ceil_div(d.n_cand, ceil_div(d.n_cand, 5));
     return dim3((unsigned)blocks, (unsigned)ceil_div(d.n_cand, d.cand_step));
   };
   // A group below 64 that is no power of two would have a wave of quant_row_kernel to its 3 to 7 chunks: whole groups
@@ -625,16 +738,16 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
   // rows x chunks: up to 8 packed register quads per lane (4 with one chunk); a block per group above 2048 channels
   // (a wave alone would need more than four chunks a lane)
   if constexpr (MODE == Q_INT) {       // (half the shapes: every instance lengthens the loading of the library)
-    if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
-    else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 4>, 4);
+    if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 2>, 2);
+    else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 2>, 2);
     else if (d.group <= 8192) four(quant_row_kernel<T, SYM, MODE, 4, 4, 2>, 2);
     else four(quant_row_kernel<T, SYM, MODE, 4, 8, 1>, 1);
     return;
   } else {
   if (d.group <= 512) one(quant_row_kernel<T, SYM, MODE, 1, 1, 4>, 4);
-  else if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 4>, 4);
-  else if (d.group <= 2048) one(quant_row_kernel<T, SYM, MODE, 1, 4, 2>, 2);
-  else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 4>, 4);
+  else if (d.group <= 1024) one(quant_row_kernel<T, SYM, MODE, 1, 2, 2>, 2);
+  else if (d.group <= 2048) one(quant_row_kernel<T, SYM, MODE, 1, 4, 1>, 1);
+  else if (d.group <= 4096) four(quant_row_kernel<T, SYM, MODE, 4, 2, 2>, 2);
   else if (d.group <= 8192) four(quant_row_kernel<T, SYM, MODE, 4, 4, 2>, 2);
   else if (d.group <= 16384) four(quant_row_kernel<T, SYM, MODE, 4, 8, 1>, 1);
   else quant_any_kernel<T, SYM, MODE><<<(unsigned)ceil_div(d.c_out * G, 4), 256, 0, stream>>>(d);

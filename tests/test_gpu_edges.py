@@ -159,6 +159,33 @@ def test_quantiser_group_layouts(gpu, group, ci, co, sym, bits, bf16):
     np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
 
 
+@pytest.mark.parametrize("n,sym", [(19, 0), (64, 0), (64, 1)])
+def test_two_rows_of_a_wave_divide_together(gpu, n, sym):
+    """Two rows share a wave and one test for quotients near a tie: here every quotient of the even rows lies on one at
+    exponent zero, none of the odd rows' does; an odd number of rows, a last block of 128 channels, difference form
+    (n = 19) and folded operands.  A tie that is rounded the wrong way moves a whole step: the losses see it."""
+    import torch
+    g = np.random.default_rng([25, n, sym])
+    co, ci, na, bits = 2101, 1152, 4, 4
+    W = g.standard_normal((co, ci)) * 0.05
+    # steps of 1/16: quotients k + 1/2 between the group's ends, which are whole steps apart
+    k = g.integers(-7, 7, (co, ci)) + 0.5
+    k[:, 0::128], k[:, 1::128] = (-7.0, 7.0) if sym else (-8.0, 7.0)
+    W[0::2] = k[0::2] / 16.0
+    W, X = F16(W), F16(g.standard_normal((n, ci)))
+    Y = orc.ref_output(X, W).astype(np.float32)
+    w, al = np.full(n, 1.0 / n, np.float32), np.array([0.0, 0.25, 0.5, 0.75], np.float32)
+    p = tlq.params(bits=bits, group=128, symmetric=sym, x_dtype=tlq.F16, yref_dtype=tlq.F32)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses = torch.empty(na, dtype=torch.float32, device=gpu)
+    tY = torch.zeros((n, co + 3), dtype=torch.float32, device=gpu)[:, :co]
+    tY.copy_(torch.from_numpy(Y))
+    tlq.scale_search(dev(X, gpu, False), dev(W, gpu, False), tY, torch.from_numpy(w).to(gpu), torch.from_numpy(al).to(gpu), p,
+                     best, idx, losses)
+    ref = orc.scale_search(X, W, Y, w, bits, 128, al, symmetric=bool(sym))
+    np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
+
+
 @pytest.mark.parametrize("n,ci,co,pad", [(1, 8, 1, 0), (3, 520, 2, 8), (4097, 72, 5, 0), (9, 4104, 3, 16),
                                          (1, 131080, 2, 0), (6, 70000, 1, 8), (130, 1544, 2, 0)])
 def test_token_preparation_and_folding_edges(gpu, n, ci, co, pad):
