@@ -444,7 +444,8 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   } else if (inv_s) {
     // the folded operand is a computed value: with bf16 inputs keep it (and X) in fp16
     if (bf16) {
-      TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, e.xmax, e.xh, st));
+      // (the operands' place is not written yet: room for the maxima of blocks, here and below)
+      TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, e.xmax, e.xh, st, false, (uint32_t*)e.folded, (size_t)c_out * c_in * 2));
       g.X = e.xh; g.ldx = c_in; g.bf16 = false;
     }
     TLQ_HIP(launch_fold_scale(Wdq, c_out, c_in, ldw, bf16, inv_s, bf16 ? e.xmax : nullptr, bf16,
@@ -506,7 +507,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
   const bool prep = bf16 && !act && !use_prep;
   uint32_t* shift_bits = (bf16 && !act) ? s.xmax : nullptr;
   if (x_stat_in) {
-    if (prep) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
+    if (prep) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st, false, (uint32_t*)s.what, (size_t)n_alpha * c_out * c_in * 2));
     TLQ_HIP(launch_scale_table(x_stat_in, c_in, alpha_grid, n_alpha, s.s_table, s_table_out, s.inv_table, shift_bits, st));
   } else {
     // the token maximum comes with the statistic; its per-block words pass through the operands' place, not written yet
@@ -762,10 +763,9 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   if (prepared && needs_prepared(p)) {
     const Prepared v = view_prepared(prepared);
     xmax = const_cast<uint32_t*>(v.xmax); xh = const_cast<uint16_t*>(v.xh);
-  } else if (bf16 && !act) {
-    TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, xmax, xh, st));
   }
-  TLQ_HIP(launch_recip(s, c_in, (bf16 && !act) ? xmax : nullptr, inv, st));
+  if (bf16 && !act && !prepared) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, xmax, xh, st, false, (uint32_t*)what, (size_t)c_out * c_in * 2, s, inv));
+  else TLQ_HIP(launch_recip(s, c_in, (bf16 && !act) ? xmax : nullptr, inv, st));
   if (act) TLQ_HIP(launch_act_quant(X, n_tok, c_in, ldx, bf16, inv, 0, 1, p->act_bits, xh, sig, st, ld8));
   QuantArgs q{};
   q.W = W; q.c_out = c_out; q.c_in = c_in; q.ldw = ldw; q.bf16 = bf16;

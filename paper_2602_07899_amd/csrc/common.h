@@ -123,9 +123,11 @@ hipError_t launch_recip(const float* s, int64_t c_in, const uint32_t* xmax_bits,
 // the same shift from it.  The folded weights carry the factor 2^shift, so the
 // contraction is unchanged while its computed operand is rounded to 11 instead of 8
 // significant bits.
-// have_max: xmax_bits holds the maximum already
+// have_max: xmax_bits holds the maximum already.  words: scratch of `room` bytes for the maxima of blocks, which saves a launch
+// (NULL: none).  s, inv: also inv[c] = 2^shift / s[c] (NULL: not).
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
-                        void* Xh, hipStream_t stream, bool have_max = false);
+                        void* Xh, hipStream_t stream, bool have_max = false, uint32_t* words = nullptr, size_t room = 0,
+                        const float* s = nullptr, float* inv = nullptr);
 __host__ __device__ inline int shift_from_bf16_bits(uint32_t bits) {
   const int k = (int)((bits >> 7) & 0xffu) - 141;  // |x| < 2^(e-126); want < 2^15
   return k < 0 ? 0 : (k > 24 ? 24 : k);

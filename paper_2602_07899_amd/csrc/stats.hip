@@ -189,9 +189,35 @@ static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_i
   return hipGetLastError();
 }
 
+template <typename T, int KIND>
+__device__ __forceinline__ float xstat_direct(const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx,
+                                              double (&red)[kXfWaves][64]);
+template <typename T, int KIND>
+__global__ __launch_bounds__(kXfWaves * 64) void xstat_direct_kernel(const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in,
+                                                                     int64_t ldx, float* __restrict__ x_stat) {
+  __shared__ double red[kXfWaves][64];
+  const float xs = xstat_direct<T, KIND>(X, n_tok, c_in, ldx, red);
+  const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && c < c_in) x_stat[c] = xs;
+}
+
+// Rows up to which one launch is faster than two (a whole search of 20 candidates, us two launches -> one, at 512 and at
+// 4096 channels: 256 rows 39.4 -> 37.6 and 86.0 -> 84.0, 1024 rows 40.0 -> 38.8 and 87.9 -> 87.4, 2048 rows
+// 41.2 -> 41.8 and 97.8 -> 100.0; the statistic alone, calls in a row: 16 - 512 rows 7.9 -> 4.7, 1024 x 4096 7.9 -> 5.1).  Not where the token maximum is taken along: a block sees 64 channels only.
+constexpr int64_t kDirectRows = 1024;
+
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,
                         const uint8_t* pos_mask, int64_t period) {
+  if (!pos_mask && n_tok <= kDirectRows) {
+    ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
+    auto go = [&](auto kern) {
+      kern<<<(unsigned)ceil_div(c_in, 64), kXfWaves * 64, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, x_stat);
+    };
+    if (!bf16) kind == 0 ? go(xstat_direct_kernel<F16, 0>) : go(xstat_direct_kernel<F16, 1>);
+    else kind == 0 ? go(xstat_direct_kernel<BF16, 0>) : go(xstat_direct_kernel<BF16, 1>);
+    return hipGetLastError();
+  }
   const hipError_t e = launch_xstat_partial(X, n_tok, c_in, ldx, bf16, kind, partial, stream, pos_mask, period, nullptr);
   if (e != hipSuccess) return e;
   const int chunks = xstat_chunks(n_tok);
@@ -340,11 +366,6 @@ __global__ __launch_bounds__(kXfWaves * 64) void xstat_table_direct_kernel(const
     table_entry(stat[lane], t.alpha[k], up, (int64_t)k * t.c_in + c, t.s_table, t.s_copy, t.inv_table);
 }
 
-// Rows up to which one launch is faster than two (a whole search of 20 candidates, us two launches -> one, at 512 and at
-// 4096 channels: 256 rows 39.4 -> 37.6 and 86.0 -> 84.0, 1024 rows 40.0 -> 38.8 and 87.9 -> 87.4, 2048 rows
-// 41.2 -> 41.8 and 97.8 -> 100.0).  Not where the token maximum is taken along: a block sees 64 channels only.
-constexpr int64_t kDirectRows = 1024;
-
 size_t xstat_block_max_words(int64_t n_tok, int64_t c_in) { return (size_t)xstat_chunks(n_tok) * (size_t)ceil_div(c_in, kXsCols); }
 
 hipError_t launch_xstat_table(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16, int kind, double* partial,
@@ -396,7 +417,7 @@ __global__ void zero_u32_kernel(uint32_t* p) { *p = 0u; }
 constexpr int kPrepBlocks = 1024;   // 4 per CU
 __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
                                                           int64_t c_in, int64_t ldx, int64_t per,
-                                                          uint32_t* __restrict__ out) {
+                                                          uint32_t* __restrict__ out, bool words) {
   __shared__ uint32_t red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t chunks = c_in / 8, i0 = blockIdx.y * per, i1 = i0 + per < chunks ? i0 + per : chunks;
@@ -420,38 +441,114 @@ __global__ __launch_bounds__(256) void absmax_bits_kernel(const uint16_t* __rest
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int i = 1; i < 4; ++i) m = m > red[i] ? m : red[i];
-    atomicMax(out, m);
+    if (words) out[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = m;
+    else atomicMax(out, m);
   }
 }
 
-// NT, NTS: loads and stores past the caches
+__device__ __forceinline__ float down_scale(uint32_t top) {
+  return __builtin_bit_cast(float, (uint32_t)(127 - shift_from_bf16_bits(top)) << 23);
+}
+__device__ __forceinline__ uint4 bf16x8_to_f16(const uint4& v, float scale) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float lo = BF16::to_float((uint16_t)w[j]) * scale, hi = BF16::to_float((uint16_t)(w[j] >> 16)) * scale;
+    o[j] = (uint32_t)F16::from_float(lo) | ((uint32_t)F16::from_float(hi) << 16);
+  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+// the reciprocals of a scale vector for the tokens' shift, dealt over the blocks of a launch
+__device__ __forceinline__ void recip_share(const float* __restrict__ s, int64_t n, uint32_t top, float* __restrict__ inv) {
+  const double up = pow2(shift_from_bf16_bits(top));
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    inv[i] = (float)(up / (double)s[i]);
+}
+
+// All of it in one launch for few tokens: every block reads them all for the maximum (from L2 but for the first time) and
+// converts its share.  Latency-bound, see kPrepWhole.
+__global__ __launch_bounds__(1024) void xprep_whole_kernel(const uint16_t* __restrict__ X, uint32_t pieces, uint32_t chunks,
+                                                           int64_t ldx, uint32_t* __restrict__ xmax, uint16_t* __restrict__ Xh,
+                                                           const float* __restrict__ s, float* __restrict__ inv) {
+  __shared__ uint32_t red[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t row = threadIdx.x / chunks, col = threadIdx.x - row * chunks;
+  const uint32_t drow = 1024 / chunks, dcol = 1024 - drow * chunks;
+  u16x2 m = {0, 0};
+#pragma unroll 8
+  for (uint32_t i = threadIdx.x; i < pieces; i += 1024) {
+    const uint4 v = *reinterpret_cast<const uint4*>(X + row * ldx + col * 8);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
+    col += dcol;
+    row += drow;
+    if (col >= chunks) { col -= chunks; ++row; }
+  }
+  uint32_t top = wave_max(m[0] > m[1] ? m[0] : m[1]);
+  if (lane == 0) red[wave] = top;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) top = top > red[w] ? top : red[w];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *xmax = top;
+  const uint32_t i = blockIdx.x * 1024 + threadIdx.x;
+  if (i < pieces) {
+    row = i / chunks;
+    col = i - row * chunks;
+    const uint4 v = *reinterpret_cast<const uint4*>(X + row * ldx + col * 8);
+    *reinterpret_cast<uint4*>(Xh + (int64_t)i * 8) = bf16x8_to_f16(v, down_scale(top));
+  }
+  if (s) recip_share(s, (int64_t)chunks * 8, top, inv);
+}
+
+// NT, NTS: loads and stores past the caches.  n_words: the maximum is that of so many words (then it is stored in *xmax),
+// 0: it is in *xmax.
 template <bool NT, bool NTS>
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __restrict__ X, int64_t n_tok,
                                                           int64_t c_in, int64_t ldx, int64_t per,
-                                                          const uint32_t* __restrict__ xmax_bits,
-                                                          uint16_t* __restrict__ Xh) {
+                                                          const uint32_t* __restrict__ words, int n_words,
+                                                          uint32_t* __restrict__ xmax, uint16_t* __restrict__ Xh,
+                                                          const float* __restrict__ s, float* __restrict__ inv) {
+  __shared__ uint32_t red[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t chunks = c_in / 8, i0 = blockIdx.y * per, i1 = i0 + per < chunks ? i0 + per : chunks;
-  const float scale = __builtin_bit_cast(float, (uint32_t)(127 - shift_from_bf16_bits(*xmax_bits)) << 23);
+  uint32_t top;
+  if (n_words) {
+    top = 0;
+    for (int i = threadIdx.x; i < n_words; i += 256) top = top > words[i] ? top : words[i];
+    top = wave_max(top);
+    if (lane == 0) red[wave] = top;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) top = top > red[w] ? top : red[w];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *xmax = top;
+  } else {
+    top = *xmax;
+  }
+  const float scale = down_scale(top);
   for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n_tok; r += (int64_t)gridDim.x * 4) {
 #pragma unroll 4
-    for (int64_t i = i0 + lane; i < i1; i += 64) {
-      const uint4 v = load16<NT>(X + r * ldx + i * 8);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-      uint32_t o[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float lo = BF16::to_float((uint16_t)w[j]) * scale, hi = BF16::to_float((uint16_t)(w[j] >> 16)) * scale;
-        o[j] = (uint32_t)F16::from_float(lo) | ((uint32_t)F16::from_float(hi) << 16);
-      }
-      store16<NTS>(Xh + r * c_in + i * 8, make_uint4(o[0], o[1], o[2], o[3]));
-    }
+    for (int64_t i = i0 + lane; i < i1; i += 64)
+      store16<NTS>(Xh + r * c_in + i * 8, bf16x8_to_f16(load16<NT>(X + r * ldx + i * 8), scale));
   }
+  if (s && blockIdx.y == 0) recip_share(s, c_in, top, inv);
 }
 
+// Tokens up to this size go through one launch (calls in a row, us, three launches -> one: 8 - 256 KB 10.4 -> 4.9, 512 KB 10.5
+// -> 7.1; at 1 MB every block would read as much as 64 KB cost in launches).  Beyond it, with room for words, two: products
+// of bf16 tokens with their own reciprocals, 4000 x 640 x 600 36.4 -> 23.4, 1200 x 5120 x 13824 205 -> 200.
+constexpr int64_t kPrepWhole = 512 << 10;    // bytes
+
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
-                        void* Xh, hipStream_t stream, bool have_max) {
+                        void* Xh, hipStream_t stream, bool have_max, uint32_t* words, size_t room, const float* s, float* inv) {
   ProfScope ps("bf16_to_f16", stream, 6.0 * (double)n_tok * (double)c_in);
+  const int64_t pieces = n_tok * (c_in / 8);
+  if (!have_max && pieces * 16 <= kPrepWhole) {
+    xprep_whole_kernel<<<(unsigned)ceil_div(pieces, 1024), 1024, 0, stream>>>((const uint16_t*)X, (uint32_t)pieces, (uint32_t)(c_in / 8),
+                                                                              ldx, xmax_bits, (uint16_t*)Xh, s, inv);
+    return hipGetLastError();
+  }
   const int64_t rows = ceil_div(n_tok, 4);
   // Few rows: split them into as many stretches (of 512 channels at least) as give every CU a block (us for the
   // three launches, a wave a row -> split: 4 x 131072 45.5 -> 12.6, 1 x 65536 23.7 -> 12.5, 64 x 65536
@@ -459,12 +556,15 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   const int64_t per = ceil_div(ceil_div(c_in, 512), rows < 256 ? 256 / rows : 1) * 64;   // in chunks of 8 channels
   const unsigned split = (unsigned)ceil_div(c_in / 8, per);
   const dim3 mgrid((unsigned)(rows < kPrepBlocks ? rows : kPrepBlocks), split), cgrid((unsigned)(rows < 8192 ? rows : 8192), split);
+  const size_t n_words = (size_t)mgrid.x * mgrid.y;
+  const bool by_words = !have_max && words && n_words * sizeof(uint32_t) <= room && n_words <= 4096;
   if (!have_max) {
-    zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
-    absmax_bits_kernel<<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits);
+    if (!by_words) zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
+    absmax_bits_kernel<<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, by_words ? words : xmax_bits, by_words);
   }
   auto go = [&](auto kern) {
-    kern<<<cgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, xmax_bits, (uint16_t*)Xh);
+    kern<<<cgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, words, by_words ? (int)n_words : 0, xmax_bits,
+                                    (uint16_t*)Xh, s, inv);
   };
   const double bytes = (double)n_tok * (double)c_in;
   if (!streams_past(4.0 * bytes)) go(bf16_to_f16_kernel<false, false>);

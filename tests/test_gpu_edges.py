@@ -159,6 +159,33 @@ def test_quantiser_group_layouts(gpu, group, ci, co, sym, bits, bf16):
     np.testing.assert_allclose(losses.cpu().numpy(), ref["losses"], rtol=1e-3)   # the parity bar of the search
 
 
+@pytest.mark.parametrize("n,ci", [(1, 8), (255, 1024), (256, 1024), (257, 1024), (1030, 264), (4097, 72), (3, 131072), (1025, 512)])
+def test_token_preparation_by_one_two_and_three_launches(gpu, n, ci):
+    """Tokens up to 512 KB are prepared in one launch, larger ones in two where the call has scratch for the maxima of
+    blocks (here with the reciprocals of the scales) and in three elsewhere: the same bits, with the largest
+    magnitude in the last token's last channel.  The statistic of up to 1024 rows is one launch too."""
+    import torch
+    g = np.random.default_rng([26, n, ci])
+    co = 40
+    X, W = BF(g.standard_normal((n, ci)) * 3.0), BF(g.standard_normal((co, ci)) * 0.05)
+    X[n - 1, ci - 1] = BF(np.array([3.0e5]))[0]
+    tX, tW = dev(X, gpu, True), dev(W, gpu, True)
+    s = torch.from_numpy(np.exp(g.standard_normal(ci)).astype(np.float32)).to(gpu)
+    p = tlq.params(bits=4, group=8, x_dtype=tlq.BF16, yref_dtype=tlq.BF16)
+    prepared = torch.zeros(tlq.prepared_tokens_bytes(n, ci, p), dtype=torch.uint8, device=gpu)
+    tlq.prepare_tokens(tX, p, prepared)
+    k = max(0, int(np.floor(np.log2(3.0e5))) + 1 - 15)          # the shift that brings the largest below 2^15
+    body = prepared[256:256 + 2 * n * ci].view(torch.float16).view(n, ci)
+    np.testing.assert_array_equal(host(body), F16(X * 2.0 ** -k).astype(np.float64))    # (subnormals round to fp16's grid)
+    out = [torch.empty((n, co), dtype=torch.bfloat16, device=gpu) for _ in range(2)]
+    tlq.apply_best(tX, tW, s, p, out[0])
+    tlq.apply_best(tX, tW, s, p, out[1], prepared=prepared)
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    xs = torch.empty(ci, dtype=torch.float32, device=gpu)
+    tlq.x_stat(tX, p, xs)
+    np.testing.assert_array_equal(host(xs), np.abs(X).mean(0).astype(np.float32).astype(np.float64))
+
+
 @pytest.mark.parametrize("n,sym", [(19, 0), (64, 0), (64, 1)])
 def test_two_rows_of_a_wave_divide_together(gpu, n, sym):
     """Two rows share a wave and one test for quotients near a tie: here every quotient of the even rows lies on one at
