@@ -183,7 +183,7 @@ def test_token_preparation_by_one_two_and_three_launches(gpu, n, ci):
     assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
     xs = torch.empty(ci, dtype=torch.float32, device=gpu)
     tlq.x_stat(tX, p, xs)
-    np.testing.assert_array_equal(host(xs), np.abs(X).mean(0).astype(np.float32).astype(np.float64))
+    np.testing.assert_array_equal(host(xs), np.abs(X.astype(np.float64)).mean(0).astype(np.float32).astype(np.float64))
 
 
 @pytest.mark.parametrize("n,sym", [(19, 0), (64, 0), (64, 1)])
