@@ -9,6 +9,7 @@
 namespace tlq {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
@@ -21,6 +22,13 @@ template <> __device__ __forceinline__ f32x4 mma32<F16>(u16x8 a, u16x8 b, f32x4 
 }
 template <> __device__ __forceinline__ f32x4 mma32<BF16>(u16x8 a, u16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+template <typename T> __device__ __forceinline__ f32x16 mma16(u16x8 a, u16x8 b, f32x16 c);
+template <> __device__ __forceinline__ f32x16 mma16<F16>(u16x8 a, u16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+template <> __device__ __forceinline__ f32x16 mma16<BF16>(u16x8 a, u16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 // 16-bit transposing LDS read: 16 lanes address four rows of 16 elements (four lanes x 8 bytes a row) and
 // lane i of the sixteen receives column i of those four rows
@@ -385,6 +393,226 @@ __global__ __launch_bounds__(256, 3) void causal_attention_kernel(
 #endif
 }
 
+[[maybe_unused]] constexpr int kShortBk = 32;                         // keys per step
+[[maybe_unused]] constexpr int kShortTile = kShortBk * kAttRow;       // bytes of one K or V tile
+
+// The same for short sequences and for launches that leave CUs without a block (short_attention): 32 keys a step, S^T = K Q^T
+// and O^T = V^T P^T in 32x32x16 products, a lane owns one query column, its running reference and sum are shared only with
+// lane ^ 32.  The accumulator registers of S^T, taken in order, are the keys 16 sl + 8 (e / 4) + 4 (lane / 32) + e % 4 of a
+// 16-key step, and V^T is read in that order.  Two stages of K and V: the next 32 keys are on their way for a whole step.
+// Latency-bound in such launches: 4.7 us for one step, 0.8 us for every further 64 keys.
+// LDS rows are 256 B; the 16-byte chunks of a K row are XORed with row % 16, the 32-byte pairs of a V
+// row with a permutation of row % 8: fragment reads and transposing reads hit each bank once.
+template <typename T, bool WIDE>
+__global__ __launch_bounds__(256, 3) void short_attention_kernel(
+    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
+    const uint16_t* __restrict__ V, int64_t ldv, uint16_t* __restrict__ O, int64_t ldo, int seq_len,
+    int n_heads, int64_t n_hs, unsigned ways, unsigned members, int n_qblocks, float scale) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  // two stages of one step's K and V, apart from each other so that the compiler sees that the loads into one do not
+  // touch what is read from the other
+  __shared__ __attribute__((aligned(1024))) unsigned char stage0[2 * kShortTile], stage1[2 * kShortTile];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  // blockIdx.x = ways * (members * query block + member) + pair
+  unsigned pair = blockIdx.x & 7, rest = blockIdx.x >> 3;
+  if (ways != 8) {
+    rest = blockIdx.x / ways;
+    pair = blockIdx.x - rest * ways;
+  }
+  const unsigned qblock = rest / members, member = rest - qblock * members;
+  const int64_t hs = (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * members + member) * ways + pair;
+  if (hs >= n_hs) return;
+  const int qb = n_qblocks - 1 - (int)qblock;    // longest rows first
+  const int64_t row0 = (hs / n_heads) * seq_len;
+  const int64_t col0 = (hs % n_heads) * kAttDh;
+  const int q0 = qb * kAttBq + wave * 32;
+  const int q = q0 + l32;                      // may lie past the end of the sample: computed, never stored
+  const int qc = q < seq_len ? q : seq_len - 1;
+
+  u16x8 qf[8];
+  {
+    const uint16_t* qp = Q + (row0 + qc) * ldq + col0 + 8 * h;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const u16x8*>(qp + 16 * s);
+  }
+  f32x16 acc[4];
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[dt][v] = 0.0f;
+  float m_run = -INFINITY, l_run = 0.0f;
+
+  int last_q = qb * kAttBq + kAttBq - 1;
+  if (last_q > seq_len - 1) last_q = seq_len - 1;
+  const int n_kt = last_q / kShortBk + 1;
+  int wave_last_q = q0 + 31;
+  if (wave_last_q > seq_len - 1) wave_last_q = seq_len - 1;
+  // steps of this wave; none if it lies past the end: then it only helps to load
+  const int n_mine = q0 <= wave_last_q ? wave_last_q / kShortBk + 1 : 0;
+
+  // global -> LDS without registers: a wave-wide load fills four rows of 256 bytes, so the swizzle is on the global
+  // side; a wave loads rows 8 wave + 4 i + lane / 16, i < 2, of K and of V.  Its descriptors begin at the first of
+  // the eight rows and end with the sample: rows past it arrive as zeros (masked below).
+  const int drow = lane >> 4, dch = lane & 15;
+  const uint16_t* kn = K + (row0 + 8 * wave) * ldk + col0;     // of the next tile
+  const uint16_t* vn = V + (row0 + 8 * wave) * ldv + col0;
+  int left = seq_len - 8 * wave;                               // rows of the sample from there on
+  auto fetch = [&](unsigned char* at) __attribute__((always_inline)) {
+    unsigned char *ak = at + 2 * wave * 1024, *av = ak + kShortTile;
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int64_t r = 4 * i + drow < left ? 4 * i + drow : left - 1;     // (left - 1 may lie before kn, not the sample)
+        const int kc = (dch ^ ((8 * wave + 4 * i + drow) & 15)) * 8;
+        const int vc = ((((dch >> 1) ^ ((drow << 1) | (i & 1))) << 1) | (dch & 1)) * 8;
+        *reinterpret_cast<u16x8*>(ak + i * 1024 + lane * 16) = *reinterpret_cast<const u16x8*>(kn + r * ldk + kc);
+        *reinterpret_cast<u16x8*>(av + i * 1024 + lane * 16) = *reinterpret_cast<const u16x8*>(vn + r * ldv + vc);
+      }
+    } else {
+      const int rows = left < 8 ? left : 8;
+      const int kbytes = rows > 0 ? ((rows - 1) * (int)ldk + kAttDh) * 2 : 0;
+      const int vbytes = rows > 0 ? ((rows - 1) * (int)ldv + kAttDh) * 2 : 0;
+      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)kn, 0, kbytes, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)vn, 0, vbytes, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = 4 * i + drow;
+        const int kvo = r * (int)ldk * 2 + (dch ^ ((8 * wave + r) & 15)) * 16;
+        const int vvo = r * (int)ldv * 2 + ((((dch >> 1) ^ ((drow << 1) | (i & 1))) << 1) | (dch & 1)) * 16;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_ptr_t)(ak + i * 1024), 16, kvo, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr_t)(av + i * 1024), 16, vvo, 0, 0, 0);
+      }
+    }
+    kn += kShortBk * ldk;
+    vn += kShortBk * ldv;
+    left -= kShortBk;
+  };
+  const int kbase = l32 * kAttRow + ((h ^ (l32 & 15)) << 4);
+  const int r4 = (lane & 15) >> 2, vg = (lane >> 4) & 1;
+  const int vbase = (h * 4 + r4) * kAttRow + (((vg ^ h) << 1 | ((lane >> 1) & 1)) << 4) + (lane & 1) * 8;
+  int ka[8], va[4];
+#pragma unroll
+  for (int st = 0; st < 8; ++st) ka[st] = kbase ^ (st << 5);
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) va[dt] = kShortTile + (vbase ^ ((dt ^ r4) << 6));
+
+  // 32 keys; mask: some of them lie beyond some query of the wave
+  auto step = [&](const unsigned char* kv, bool mask, int kt) __attribute__((always_inline)) {
+    f32x16 s;
+    u16x8 kf[4];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+#pragma unroll
+    for (int st = 0; st < 4; ++st) kf[st] = *reinterpret_cast<const u16x8*>(kv + ka[st]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      s = mma16<T>(kf[st & 3], qf[st], s);
+      if (st < 4) kf[st] = *reinterpret_cast<const u16x8*>(kv + ka[st + 4]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    u16x8 vf[4];
+    auto read_v = [&](int sl) __attribute__((always_inline)) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const unsigned char* p = kv + va[dt] + sl * 16 * kAttRow;
+        const u16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * kAttRow);
+        vf[dt] = u16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      }
+    };
+    read_v(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] *= scale;
+    if (mask) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int key = kt * kShortBk + 8 * (v >> 2) + 4 * h + (v & 3);
+        s[v] = key <= q ? s[v] : -INFINITY;
+      }
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+    // key 0 is visible to every query and is part of the first step, so m_run becomes finite there; only the lanes
+    // whose query meets a new maximum take part in the rescaling, elsewhere the factor is exactly 1
+    float alpha = 1.0f;
+    const float m_new = fmaxf(m_run, swap32_max(mx, mx));
+    if (m_new > m_run) {
+      alpha = __expf(m_run - m_new);
+      m_run = m_new;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[dt][v] *= alpha;
+    }
+    float ps = 0.0f;
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) {
+      u16x8 pf;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float pv = __expf(s[8 * sl + e] - m_run);
+        ps += pv;
+        pf[e] = T::from_float(pv);
+      }
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) acc[dt] = mma16<T>(vf[dt], pf, acc[dt]);
+      if (sl == 0) read_v(1);
+    }
+    l_run = __builtin_fmaf(l_run, alpha, ps);
+  };
+  // one barrier a step: behind it the next tile has landed (each wave has waited for its own loads) and the stage
+  // read last may be refilled
+  auto turn = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+  auto walk = [&](unsigned char* here, unsigned char* next, int kt) __attribute__((always_inline)) {
+    turn();
+    if (kt + 1 < n_kt) fetch(next);
+    // a wave's queries start at a multiple of 32, so only its last 32 visible keys are masked
+    if (kt < n_mine) step(here, kt == n_mine - 1, kt);
+  };
+  fetch(stage0);
+  for (int kt = 0; kt < n_kt; kt += 2) {
+    walk(stage0, stage1, kt);
+    if (kt + 1 < n_kt) walk(stage1, stage0, kt + 1);
+  }
+  __syncthreads();
+  l_run += __shfl_xor(l_run, 32, 64);
+  // the wave's 32 x 128 outputs leave as whole rows through its own quarter of the (now free) stages
+  const float inv = 1.0f / l_run;
+  unsigned char* ol = (wave < 2 ? stage0 : stage1) + (wave & 1) * 32 * kAttRow;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      u16x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = T::from_float(acc[dt][4 * j + i] * inv);
+      *reinterpret_cast<u16x4*>(ol + l32 * kAttRow + (((dt * 4 + j) ^ (l32 & 15)) << 4) + h * 8) = o;
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = i * 4 + (lane >> 4), c = lane & 15;
+    const u16x8 o = *reinterpret_cast<const u16x8*>(ol + r * kAttRow + ((c ^ (r & 15)) << 4));
+    if (q0 + r < seq_len) *reinterpret_cast<u16x8*>(O + (row0 + q0 + r) * ldo + col0 + c * 8) = o;
+  }
+#endif
+}
+
+// Where the 32-key form stays.  Up to two query blocks a sequence neither form is ahead (us, 32 keys a step -> 64: 32 x 100 x 16
+// 12.1 -> 11.5, 32 x 100 x 32 19.7 -> 20.7, 32 x 200 x 16 22.5 -> 23.0).  A launch of at most one block a CU waits for latencies
+// in both (4 x 300 x 6 10.8 -> 10.1, 8 x 512 x 8 17.0 -> 15.9): searches of a short chain of blocks decide near ties by the last
+// bits of these outputs, and less than a microsecond does not pay for other ones.  Beyond, 3 - 13 %: 16 x 300 x 8 14.8 -> 13.1,
+// 16 x 512 x 8 23.5 -> 20.5, 16 x 1024 x 8 50.8 -> 45.2.
+static bool short_attention(int64_t n_hs, int n_qblocks) { return n_qblocks <= 2 || n_hs * n_qblocks <= 256; }
+
 hipError_t launch_causal_attention(const void* Q, int64_t ldq, const void* K, int64_t ldk, const void* V,
                                    int64_t ldv, int64_t n_tok, int n_heads, int seq_len, bool bf16, void* O,
                                    int64_t ldo, hipStream_t stream) {
@@ -398,14 +626,18 @@ hipError_t launch_causal_attention(const void* Q, int64_t ldq, const void* K, in
   const int n_qblocks = (int)ceil_div(seq_len, kAttBq);
   const int64_t chunks = ceil_div(groups, members), gy = chunks < 32768 ? chunks : 32768;
   const dim3 grid(ways * members * (unsigned)n_qblocks, (unsigned)gy, (unsigned)ceil_div(chunks, gy));
-  const float scale = (float)(0.08838834764831845 * 1.4426950408889634);  // log2(e) / sqrt(128)
   const bool wide = ldk >= kAttWide || ldv >= kAttWide;
-  auto go = [&](auto kern) {
+  auto go = [&](auto kern, double scale) {
     kern<<<grid, 256, 0, stream>>>((const uint16_t*)Q, ldq, (const uint16_t*)K, ldk, (const uint16_t*)V, ldv, (uint16_t*)O,
-                                   ldo, seq_len, n_heads, n_hs, ways, members, n_qblocks, scale);
+                                   ldo, seq_len, n_heads, n_hs, ways, members, n_qblocks, (float)scale);
   };
-  if (!bf16) wide ? go(causal_attention_kernel<F16, true>) : go(causal_attention_kernel<F16, false>);
-  else wide ? go(causal_attention_kernel<BF16, true>) : go(causal_attention_kernel<BF16, false>);
+  auto pick = [&](auto t) {
+    using T = decltype(t);
+    const double scale = 0.08838834764831845, log2e = 1.4426950408889634;  // 1 / sqrt(128); the longer form takes powers of two
+    if (short_attention(n_hs, n_qblocks)) wide ? go(short_attention_kernel<T, true>, scale) : go(short_attention_kernel<T, false>, scale);
+    else wide ? go(causal_attention_kernel<T, true>, scale * log2e) : go(causal_attention_kernel<T, false>, scale * log2e);
+  };
+  bf16 ? pick(BF16{}) : pick(F16{});
   return hipGetLastError();
 }
 

@@ -45,10 +45,12 @@ def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("seq,heads,samples", [(1, 1, 1), (15, 2, 1), (17, 1, 5), (48, 1, 2), (79, 3, 1), (80, 1, 1), (95, 1, 1),
-                                               (97, 2, 1), (127, 1, 2), (129, 1, 1), (191, 1, 1), (193, 2, 1), (321, 1, 1)])
+                                               (97, 2, 1), (127, 1, 2), (129, 1, 1), (191, 1, 1), (193, 2, 1), (321, 1, 1),
+                                               (257, 43, 2), (271, 86, 1), (273, 29, 3), (304, 86, 1), (321, 43, 2), (335, 29, 3),
+                                               (383, 86, 1), (385, 65, 1)])
 def test_attention_tile_remainders(gpu, bf16, seq, heads, samples):
-    """64-key tiles of two 32-key blocks, of which a wave's last may be the first or the second; 16-query tiles that are
-    rescaled apart: scores that grow with the key make every step meet new maxima in some queries."""
+    """Steps of 32 keys (one sequence or few); 64-key tiles of two 32-key blocks, of which a wave's last may be the first or the
+    second, with 16-query tiles that are rescaled apart (more than 256 blocks): scores that grow with the key make every step meet new maxima in some queries."""
     import torch
     g = np.random.default_rng([24, seq, heads])
     n, width = seq * samples, heads * 128
@@ -63,7 +65,8 @@ def test_attention_tile_remainders(gpu, bf16, seq, heads, samples):
     assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
 
 
-@pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, "")])
+@pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, ""),
+                                                        (True, 259, 87, 1, "K"), (False, 257, 87, 1, "V")])
 def test_attention_far_rows_and_partial_groups(gpu, bf16, seq, heads, samples, far):
     """Row strides of 2^27 elements and more (beyond 32-bit offsets inside a wave's rows) give the bits of dense rows;
     75 (sample, head) pairs leave the second group of pairs partly filled."""
@@ -87,14 +90,15 @@ def test_attention_far_rows_and_partial_groups(gpu, bf16, seq, heads, samples, f
         assert torch.equal(out.view(torch.int16), again.view(torch.int16))
 
 
-def test_attention_infinite_value_stays_behind_its_key(gpu):
+@pytest.mark.parametrize("seq,heads", [(200, 1), (300, 86)])
+def test_attention_infinite_value_stays_behind_its_key(gpu, seq, heads):
     """An infinite V row reaches only the queries of its own 32-query block and later ones."""
     import torch
     g = np.random.default_rng(22)
-    q, k, v = (F16(g.standard_normal((200, 128))).astype(np.float64) for _ in range(3))
+    q, k, v = (F16(g.standard_normal((seq, heads * 128))).astype(np.float64) for _ in range(3))
     v[170] = np.inf
-    out = torch.empty((200, 128), dtype=torch.float16, device=gpu)
-    tlq.causal_attention(dev(q, gpu, False), dev(k, gpu, False), dev(v, gpu, False), 1, 200, tlq.params(), out)
+    out = torch.empty((seq, heads * 128), dtype=torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, False), dev(k, gpu, False), dev(v, gpu, False), heads, seq, tlq.params(), out)
     got = host(out)
     assert np.all(np.isfinite(got[:160])) and np.all(np.isinf(got[170:]))
 
