@@ -455,11 +455,8 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   g.Yref = Y_ref; g.ldy = ldy; g.yref_dtype = p->yref_dtype; g.token_w = token_w;
   g.tile() = e.tile; g.partial = e.partial; g.tok_partial = per_token_err ? e.tok_partial : nullptr;
   TLQ_HIP(launch_gemm_loss(g, st));
-  TLQ_HIP(launch_finalize(e.partial, 1, e.tiles_o * e.tiles_t, c_out, nullptr, c_in, loss, nullptr,
-                          nullptr, st));
-  if (per_token_err)
-    TLQ_HIP(launch_token_err_reduce(e.tok_partial, e.tiles_o, n_tok, c_out, per_token_err, st));
-  return TLQ_OK;
+  const FinalDev f{e.partial, 1, e.tiles_o * e.tiles_t, 1.0 / (double)c_out, nullptr, nullptr, c_in, loss, nullptr, nullptr};
+  return hip_status(per_token_err ? launch_layer_err(f, e.tok_partial, e.tiles_o, n_tok, per_token_err, st) : launch_finalize(f, st));
 }
 
 // ------------------------------------------------------------------- S0 .. S5
@@ -511,7 +508,8 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     TLQ_HIP(launch_scale_table(x_stat_in, c_in, alpha_grid, n_alpha, s.s_table, s_table_out, s.inv_table, shift_bits, st));
   } else {
     // the token maximum comes with the statistic; its per-block words pass through the operands' place, not written yet
-    uint32_t* block_max = prep && xstat_block_max_words(n_tok, c_in) * sizeof(uint32_t) <=
+    // (few tokens: prepared in one launch, and the statistic and the table in another, instead of three)
+    uint32_t* block_max = prep && !(xprep_whole(n_tok, c_in) && n_tok <= kDirectRows) && xstat_block_max_words(n_tok, c_in) * sizeof(uint32_t) <=
                                       (size_t)n_alpha * c_out * c_in * sizeof(uint16_t) ? (uint32_t*)s.what : nullptr;
     if (prep && !block_max) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
     TLQ_HIP(launch_xstat_table(X, n_tok, c_in, ldx, bf16, p->xstat_kind, s.xs_partial, alpha_grid, n_alpha, s.s_table,
@@ -574,9 +572,8 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     }
   }
   // S4 combine + S5
-  TLQ_HIP(launch_finalize(s.partial, n_alpha, s.tiles_o * s.tiles_t, c_out, s.s_table, c_in, losses,
-                          best_idx, best_scales, st));
-  return TLQ_OK;
+  const FinalDev f{s.partial, n_alpha, s.tiles_o * s.tiles_t, 1.0 / (double)c_out, nullptr, s.s_table, c_in, losses, best_idx, best_scales};
+  return hip_status(launch_finalize(f, st));
 }
 
 tlq_status tlq_scale_search(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
@@ -698,10 +695,9 @@ tlq_status tlq_scale_search_gram(const void* gram, int64_t c_in, const void* W, 
   g.Wh = v.C; g.ldw = c_in; g.w_cand_stride = 0; g.bf16 = false;
   g.Yref = s.dq; g.ldy = c_in; g.yref_dtype = TLQ_F16; g.y_cand_stride = c_out * c_in;
   g.partial = s.partial; g.tile() = s.tile;
+  const FinalDev f{s.partial, n_alpha, s.tiles_o * s.tiles_t, 1.0 / (double)c_out, v.factor, s.s_table, c_in, losses, best_idx, best_scales};
   TLQ_HIP(launch_gemm_dot(g, st));
-  TLQ_HIP(launch_finalize(s.partial, n_alpha, s.tiles_o * s.tiles_t, c_out, s.s_table, c_in, losses,
-                          best_idx, best_scales, st, v.factor));
-  return TLQ_OK;
+  return hip_status(launch_finalize(f, st));
 }
 
 // ---------------------------------------------------------------- f_fp output

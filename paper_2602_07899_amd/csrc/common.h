@@ -92,6 +92,11 @@ struct ProfScope {
 // ---- kernel launchers (each enqueues on `stream`, returns hipGetLastError) --
 // S0: column mean/max of |X|; partial: double [n_chunks, c_in]
 int xstat_chunks(int64_t n_tok);
+// Rows up to which one launch is faster than two (a whole search of 20 candidates, us two launches -> one, at 512 and at
+// 4096 channels: 256 rows 39.4 -> 37.6 and 86.0 -> 84.0, 1024 rows 40.0 -> 38.8 and 87.9 -> 87.4, 2048 rows
+// 41.2 -> 41.8 and 97.8 -> 100.0; the statistic alone, calls in a row: 16 - 512 rows 7.9 -> 4.7, 1024 x 4096 7.9 -> 5.1).  Not
+// where the token maximum is taken along: a block sees 64 channels only.
+constexpr int64_t kDirectRows = 1024;
 // pos_mask (optional): only rows r with pos_mask[r % period] != 0 take part
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,
@@ -123,6 +128,10 @@ hipError_t launch_recip(const float* s, int64_t c_in, const uint32_t* xmax_bits,
 // the same shift from it.  The folded weights carry the factor 2^shift, so the
 // contraction is unchanged while its computed operand is rounded to 11 instead of 8
 // significant bits.
+// Tokens up to this size go through one launch (calls in a row, us, three launches -> one: 8 - 256 KB 10.4 -> 4.9, 512 KB 10.5
+// -> 7.1; at 1 MB every block would read as much as 64 KB cost in launches).  Beyond it, with room for words, two: products
+// of bf16 tokens with their own reciprocals, 4000 x 640 x 600 36.4 -> 23.4, 1200 x 5120 x 13824 205 -> 200.
+inline bool xprep_whole(int64_t n_tok, int64_t c_in) { return n_tok * c_in * 2 <= 512 << 10; }
 // have_max: xmax_bits holds the maximum already.  words: scratch of `room` bytes for the maxima of blocks, which saves a launch
 // (NULL: none).  s, inv: also inv[c] = 2^shift / s[c] (NULL: not).
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
@@ -165,6 +174,13 @@ hipError_t launch_act_quant(const void* X, int64_t n_tok, int64_t c_in, int64_t 
 hipError_t launch_fold_scale(const void* Win, int64_t c_out, int64_t c_in, int64_t ldw, bool bf16,
                              const float* inv_s, const uint32_t* xmax_bits, bool out_f16, void* Wout,
                              hipStream_t stream);
+
+// S4 final combine + S5 selection: losses[k] = inv_c_out * factor * the sum of partial[k, 0 .. tiles), the first
+// smallest of them, its row of the table.  best_idx, best_scales and factor (then 1) may be NULL.
+struct FinalDev {
+  const float* partial; int n_cand; int64_t tiles; double inv_c_out; const double* factor;
+  const float* s_table; int64_t c_in; float* losses; int32_t* best_idx; float* best_scales;
+};
 
 // Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
 // or 128 x 128 (stores without tri, and fp16 losses without tok_partial).  gemm_tile says which is the fastest.
@@ -221,13 +237,9 @@ hipError_t launch_gram_operand(const void* X, int64_t n_tok, int64_t c_in, int64
 hipError_t launch_gram_finish(float* H, int64_t c_in, int n_split, int64_t split_stride, const float* wmax,
                               int* e, double* factor, float* col_scale, void* C, hipStream_t stream);
 
-// S4 final combine + S5 selection.
-// `factor` (optional): device double multiplied into every loss
-hipError_t launch_finalize(const float* partial, int n_cand, int64_t tiles_per_cand, int64_t c_out,
-                           const float* s_table, int64_t c_in, float* losses, int32_t* best_idx,
-                           float* best_scales, hipStream_t stream, const double* factor = nullptr);
-hipError_t launch_token_err_reduce(const float* tok_partial, int64_t tiles_o, int64_t n_tok,
-                                   int64_t c_out, float* per_token_err, hipStream_t stream);
+hipError_t launch_finalize(const FinalDev& f, hipStream_t stream);
+// the same with one candidate and no selection, and err[t] = inv_c_out * the sum of column t of tok_partial [tiles_o, n_tok]
+hipError_t launch_layer_err(const FinalDev& f, const float* tok_partial, int64_t tiles_o, int64_t n_tok, float* err, hipStream_t stream);
 
 
 // chain glue (glue.hip)

@@ -201,11 +201,6 @@ __global__ __launch_bounds__(kXfWaves * 64) void xstat_direct_kernel(const uint1
   if (threadIdx.x < 64 && c < c_in) x_stat[c] = xs;
 }
 
-// Rows up to which one launch is faster than two (a whole search of 20 candidates, us two launches -> one, at 512 and at
-// 4096 channels: 256 rows 39.4 -> 37.6 and 86.0 -> 84.0, 1024 rows 40.0 -> 38.8 and 87.9 -> 87.4, 2048 rows
-// 41.2 -> 41.8 and 97.8 -> 100.0; the statistic alone, calls in a row: 16 - 512 rows 7.9 -> 4.7, 1024 x 4096 7.9 -> 5.1).  Not where the token maximum is taken along: a block sees 64 channels only.
-constexpr int64_t kDirectRows = 1024;
-
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,
                         const uint8_t* pos_mask, int64_t period) {
@@ -467,7 +462,7 @@ __device__ __forceinline__ void recip_share(const float* __restrict__ s, int64_t
 }
 
 // All of it in one launch for few tokens: every block reads them all for the maximum (from L2 but for the first time) and
-// converts its share.  Latency-bound, see kPrepWhole.
+// converts its share.  Latency-bound, see xprep_whole.
 __global__ __launch_bounds__(1024) void xprep_whole_kernel(const uint16_t* __restrict__ X, uint32_t pieces, uint32_t chunks,
                                                            int64_t ldx, uint32_t* __restrict__ xmax, uint16_t* __restrict__ Xh,
                                                            const float* __restrict__ s, float* __restrict__ inv) {
@@ -535,16 +530,11 @@ __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t* __rest
   if (s && blockIdx.y == 0) recip_share(s, c_in, top, inv);
 }
 
-// Tokens up to this size go through one launch (calls in a row, us, three launches -> one: 8 - 256 KB 10.4 -> 4.9, 512 KB 10.5
-// -> 7.1; at 1 MB every block would read as much as 64 KB cost in launches).  Beyond it, with room for words, two: products
-// of bf16 tokens with their own reciprocals, 4000 x 640 x 600 36.4 -> 23.4, 1200 x 5120 x 13824 205 -> 200.
-constexpr int64_t kPrepWhole = 512 << 10;    // bytes
-
 hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, uint32_t* xmax_bits,
                         void* Xh, hipStream_t stream, bool have_max, uint32_t* words, size_t room, const float* s, float* inv) {
   ProfScope ps("bf16_to_f16", stream, 6.0 * (double)n_tok * (double)c_in);
   const int64_t pieces = n_tok * (c_in / 8);
-  if (!have_max && pieces * 16 <= kPrepWhole) {
+  if (!have_max && xprep_whole(n_tok, c_in)) {
     xprep_whole_kernel<<<(unsigned)ceil_div(pieces, 1024), 1024, 0, stream>>>((const uint16_t*)X, (uint32_t)pieces, (uint32_t)(c_in / 8),
                                                                               ldx, xmax_bits, (uint16_t*)Xh, s, inv);
     return hipGetLastError();
@@ -574,81 +564,106 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
 }
 
 // ------------------------------------------- final combine (S4) + select (S5)
-// One block.  Wave k sums candidate k's tile partials in double in a fixed
-// order (lane-strided, then a fixed butterfly), scales by 1/c_out, and stores
-// the loss as float (+inf if not finite).  Thread 0 then picks the first
-// minimum (Sec. 3.2.1 argmin) and the block copies that row of the table.  The partials are loaded 16 at a
-// time and added in order: latency-bound, 20 candidates of 12000 tiles 167 -> 25 us, of 640 tiles 13 -> 8.
-__global__ __launch_bounds__(1024) void finalize_kernel(
-    const float* __restrict__ partial, int n_cand, int64_t tiles_per_cand, double inv_c_out,
-    const double* __restrict__ factor, const float* __restrict__ s_table, int64_t c_in, float* __restrict__ losses,
-    int32_t* __restrict__ best_idx, float* __restrict__ best_scales) {
-  __shared__ float sl[TLQ_MAX_ALPHA];
-  __shared__ int sbest;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  for (int k = wave; k < n_cand; k += nwaves) {
-    double acc = 0.0;
-    const float* p = partial + (int64_t)k * tiles_per_cand;
-    for (int64_t i = lane; i < tiles_per_cand; i += 16 * 64) {   // 16 loads in flight, added in order
-      float v[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = p[i + j * 64 < tiles_per_cand ? i + j * 64 : lane];   // (no branch)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc += i + j * 64 < tiles_per_cand ? (double)v[j] : 0.0;
-    }
+// Wave k of the block sums candidate k's tile partials in double in a fixed order (lane-strided, then a fixed
+// butterfly), scales by 1/c_out, and stores the loss as float (+inf if not finite).  Wave 0 then picks the first
+// minimum (Sec. 3.2.1 argmin) and the block copies that row of the table.  The order does not depend on the number of
+// waves.  The partials are loaded 16 at a time and added in order (latency-bound, 20 candidates of 12000 tiles 167 -> 25 us, of
+// 640 tiles 13 -> 8), up to 64 of them those of eight candidates at a time.  sl: TLQ_MAX_ALPHA floats of LDS and one int.
+__device__ __forceinline__ void finalize_block(const FinalDev& f, float* sl) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+  const double scale = f.inv_c_out;
+  auto finish = [&](int k, double acc) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane == 0) {
-      float l = (float)(acc * inv_c_out * (factor ? *factor : 1.0));
+      float l = (float)(acc * scale * (f.factor ? *f.factor : 1.0));
       if (!(l == l) || l == __builtin_inff() || l == -__builtin_inff()) l = __builtin_inff();
       sl[k] = l;
-      losses[k] = l;
+      f.losses[k] = l;
+    }
+  };
+  if (f.tiles <= 64) {
+    for (int k0 = wave; k0 < f.n_cand; k0 += 8 * nwaves) {
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = k0 + j * nwaves < f.n_cand ? k0 + j * nwaves : k0;
+        v[j] = f.partial[(int64_t)k * f.tiles + (lane < f.tiles ? lane : 0)];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (k0 + j * nwaves < f.n_cand) finish(k0 + j * nwaves, lane < f.tiles ? (double)v[j] : 0.0);
+    }
+  } else {
+    for (int k = wave; k < f.n_cand; k += nwaves) {
+      double acc = 0.0;
+      const float* p = f.partial + (int64_t)k * f.tiles;
+      for (int64_t i = lane; i < f.tiles; i += 16 * 64) {   // 16 loads in flight, added in order
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = p[i + j * 64 < f.tiles ? i + j * 64 : lane];   // (no branch)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc += i + j * 64 < f.tiles ? (double)v[j] : 0.0;
+      }
+      finish(k, acc);
+    }
+  }
+  if (!f.best_idx && !f.best_scales) return;
+  int* sbest = reinterpret_cast<int*>(sl + TLQ_MAX_ALPHA);
+  __syncthreads();
+  if (wave == 0) {
+    float bl = lane < f.n_cand ? sl[lane] : __builtin_inff();     // (n_cand <= TLQ_MAX_ALPHA = 64)
+    int b = bl < __builtin_inff() ? lane : -1;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const float ol = __shfl_xor(bl, off, 64);
+      const int ob = __shfl_xor(b, off, 64);
+      if (ob >= 0 && (b < 0 || ol < bl || (ol == bl && ob < b))) { bl = ol; b = ob; }
+    }
+    if (lane == 0) {
+      *sbest = b;
+      if (f.best_idx) *f.best_idx = b;
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int b = -1;
-    float bl = __builtin_inff();
-    for (int k = 0; k < n_cand; ++k)
-      if (sl[k] < bl) { bl = sl[k]; b = k; }
-    sbest = b;
-    if (best_idx) *best_idx = b;
-  }
-  __syncthreads();
-  if (best_scales) {
-    const int b = sbest;
-    for (int64_t c = threadIdx.x; c < c_in; c += blockDim.x)
-      best_scales[c] = b >= 0 ? s_table[(int64_t)b * c_in + c] : __builtin_nanf("");
+  if (f.best_scales) {
+    const int b = *sbest;
+    for (int64_t c = threadIdx.x; c < f.c_in; c += blockDim.x)
+      f.best_scales[c] = b >= 0 ? f.s_table[(int64_t)b * f.c_in + c] : __builtin_nanf("");
   }
 }
 
-hipError_t launch_finalize(const float* partial, int n_cand, int64_t tiles_per_cand, int64_t c_out,
-                           const float* s_table, int64_t c_in, float* losses, int32_t* best_idx,
-                           float* best_scales, hipStream_t stream, const double* factor) {
-  ProfScope ps("finalize", stream, 4.0 * (double)n_cand * (double)tiles_per_cand);
-  finalize_kernel<<<1, 1024, 0, stream>>>(partial, n_cand, tiles_per_cand, 1.0 / (double)c_out,
-                                          factor, s_table, c_in, losses, best_idx, best_scales);
+__global__ __launch_bounds__(1024) void finalize_kernel(FinalDev f) {
+  __shared__ float sl[TLQ_MAX_ALPHA + 1];
+  finalize_block(f, sl);
+}
+
+hipError_t launch_finalize(const FinalDev& f, hipStream_t stream) {
+  ProfScope ps("finalize", stream, 4.0 * (double)f.n_cand * (double)f.tiles);
+  finalize_kernel<<<1, 1024, 0, stream>>>(f);
   return hipGetLastError();
 }
 
-// per_token_err[t] = (1/c_out) * sum over o-tiles of the tile row sums
-__global__ void token_err_reduce_kernel(const float* __restrict__ tok_partial, int64_t tiles_o,
-                                        int64_t n_tok, double inv_c_out, float* __restrict__ out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Block 0 combines the loss, the others the errors of 256 tokens each: one launch instead of two of 4 us.
+__global__ __launch_bounds__(256) void layer_err_kernel(FinalDev f, const float* __restrict__ tok_partial, int64_t tiles_o,
+                                                        int64_t n_tok, float* __restrict__ out) {
+  __shared__ float sl[TLQ_MAX_ALPHA + 1];
+  if (blockIdx.x == 0) {
+    finalize_block(f, sl);
+    return;
+  }
+  const int64_t t = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
   if (t >= n_tok) return;
   double acc = 0.0;
 #pragma unroll 8
   for (int64_t i = 0; i < tiles_o; ++i) acc += (double)tok_partial[i * n_tok + t];
-  out[t] = (float)(acc * inv_c_out);
+  out[t] = (float)(acc * f.inv_c_out);
 }
 
-hipError_t launch_token_err_reduce(const float* tok_partial, int64_t tiles_o, int64_t n_tok,
-                                   int64_t c_out, float* per_token_err, hipStream_t stream) {
+hipError_t launch_layer_err(const FinalDev& f, const float* tok_partial, int64_t tiles_o, int64_t n_tok, float* err, hipStream_t stream) {
   ProfScope ps("token_err_reduce", stream, 4.0 * (double)tiles_o * (double)n_tok);
-  token_err_reduce_kernel<<<(unsigned)ceil_div(n_tok, 256), 256, 0, stream>>>(
-      tok_partial, tiles_o, n_tok, 1.0 / (double)c_out, per_token_err);
+  layer_err_kernel<<<(unsigned)ceil_div(n_tok, 256) + 1, 256, 0, stream>>>(f, tok_partial, tiles_o, n_tok, err);
   return hipGetLastError();
 }
 
 }  // namespace tlq
-

@@ -848,3 +848,31 @@ def test_losses_where_half_a_tile_lies_past_the_edge(gpu, n, co, kind):
         if tok:
             # one output: a residual near zero keeps the absolute error of its product
             np.testing.assert_allclose(err.cpu().numpy(), e.cpu().numpy(), rtol=2e-5, atol=2e-6)
+
+
+@pytest.mark.parametrize("n,co,na", [(40, 72, 1), (40, 72, 17), (300, 600, 64), (2100, 1300, 33)])
+def test_selection_of_few_and_many_partial_sums(gpu, n, co, na):
+    """Up to 64 partial sums a candidate are read for eight candidates at a time, more one candidate after the other; equal
+    losses select the first of them; the errors of the tokens come from the launch that combines the loss."""
+    import torch
+    g = np.random.default_rng([27, n, na])
+    ci = 64
+    X, W = F16(g.standard_normal((n, ci))), F16(g.standard_normal((co, ci)) * 0.05)
+    Y = orc.ref_output(X, W).astype(np.float32)
+    al = np.repeat(g.uniform(0.0, 1.0, (na + 1) // 2), 2)[:na].astype(np.float32)       # every strength twice
+    w = np.full(n, 1.0 / n, np.float32)
+    p = tlq.params(bits=4, group=32, x_dtype=tlq.F16, yref_dtype=tlq.F32)
+    tX, tW, tY, tw = dev(X, gpu, False), dev(W, gpu, False), torch.from_numpy(Y).to(gpu), torch.from_numpy(w).to(gpu)
+    best, idx = torch.empty(ci, dtype=torch.float32, device=gpu), torch.empty(1, dtype=torch.int32, device=gpu)
+    losses, table = (torch.empty(s, dtype=torch.float32, device=gpu) for s in ((na,), (na, ci)))
+    tlq.scale_search(tX, tW, tY, tw, torch.from_numpy(al).to(gpu), p, best, idx, losses, s_table_out=table)
+    got = host(losses)
+    assert int(idx) == int(np.argmin(got)) and int(idx) % 2 == 0
+    assert np.array_equal(got[0:na - na % 2:2], got[1::2]) and torch.equal(best, table[int(idx)])
+    loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+    Wq = F16(W + g.standard_normal(W.shape) * 0.01)
+    tlq.weighted_layer_err(tX, dev(Wq, gpu, False), None, tY, tw, p, loss, per_token_err=err)
+    ref = ((Y.astype(np.float64) - X.astype(np.float64) @ Wq.astype(np.float64).T) ** 2).mean(1)
+    # squares are added in 32 bits inside a tile: at most 320 in a chain, so 320 x 2^-24, and the products' own rounding
+    np.testing.assert_allclose(host(err), ref, rtol=1e-4, atol=1e-9)
+    assert abs(float(loss) - ref.mean()) <= 1e-4 * ref.mean()
