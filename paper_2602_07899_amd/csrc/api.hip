@@ -147,27 +147,26 @@ struct ErrPlan {
   float* partial; float* tok_partial; uint16_t* folded; uint32_t* xmax; uint16_t* xh; float* sig;
   size_t bytes; int64_t tiles_o, tiles_t; GemmTile tile;   // xh doubles as the code matrix in act mode
 };
-// fp16: fp16 operands for the pipelined kernel
+// fp16: fp16 operands for the pipelined kernel.  The workspace has room for the tiles of either
 ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act, bool fp16 = false) {
   ErrPlan e;
   Carver c(ws);
-  gemm_tile_counts(n_tok, c_out, GemmTile{}, &e.tiles_o, &e.tiles_t);
-  e.partial = c.take<float>((size_t)e.tiles_o * e.tiles_t);
-  e.tok_partial = c.take<float>((size_t)e.tiles_o * n_tok);
+  int64_t big_o, big_t;
+  gemm_tile_counts(n_tok, c_out, GemmTile{}, &big_o, &big_t);
+  GemmArgs g{};
+  g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
+  // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
+  // 2048 76 -> 66)
+  e.tile = gemm_tile(g, kTileSmall | kTileWide, INT64_MAX);
+  gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
+  e.partial = c.take<float>((size_t)std::max(big_o * big_t, e.tiles_o * e.tiles_t));
+  e.tok_partial = c.take<float>((size_t)std::max(big_o, e.tiles_o) * n_tok);
   e.folded = c.take<uint16_t>((size_t)c_out * c_in);
   e.xmax = c.take<uint32_t>(1);
   e.xh = (bf16 || act) ? c.take<uint16_t>((size_t)n_tok * c_in) : nullptr;
   e.sig = act ? c.take<float>((size_t)n_tok) : nullptr;
   e.bytes = c.off;
-  e.tile = GemmTile{};
-  if (fp16) {
-    GemmArgs g{};
-    g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
-    // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
-    // 2048 76 -> 66)
-    e.tile = gemm_tile(g, kTileWide, e.tiles_o * e.tiles_t);
-  }
-  gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
+  if (!fp16) e.tile = GemmTile{}, e.tiles_o = big_o, e.tiles_t = big_t;
   return e;
 }
 

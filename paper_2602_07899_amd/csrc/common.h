@@ -183,7 +183,7 @@ struct FinalDev {
 };
 
 // Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
-// or 128 x 128 (stores without tri, and fp16 losses without tok_partial).  gemm_tile says which is the fastest.
+// or 128 x 128 (stores without tri, and fp16 losses).  gemm_tile says which is the fastest.
 struct GemmTile { bool small; int tok_blocks; };
 // S3+S4 / plain GEMM with store epilogue.
 struct GemmArgs : GemmTile {
@@ -212,7 +212,7 @@ struct GemmArgs : GemmTile {
 };
 void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tiles_o, int64_t* tiles_t);
 // The tile for a launch of g's sizes, candidates and order.  kinds: tiles besides 256 x 256 that the launch has (stores and
-// fp16 losses: all; fp16 losses with tok_partial and the quadratic form: the wide one); max_tiles: tiles per candidate
+// fp16 losses: all; fp16 losses with tok_partial: not the narrow one; the quadratic form: the wide one); max_tiles: tiles per candidate
 // that the caller has room for, at least those of 256 x 256
 enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7 };
 GemmTile gemm_tile(const GemmArgs& g, int kinds, int64_t max_tiles);

@@ -22,12 +22,13 @@
 // pipelined kernels (16x16x32 MFMA, operands brought into LDS by LDS-DMA loads, two 64 KB stages, hand-placed waits):
 //   gemm_dma_kernel    (gemm.hip) tiles of 256 x 256 and 128 x 128;
 //   gemm_width_kernel  (gemm_width.hip) 256 x 192 and 256 x 320, for launches that they suit better (gemm_tile);
+//   gemm_small_tok_kernel  (gemm_tok.hip) 128 x 128 with the errors of tokens;
 //   gemm_i8_kernel     (gemm_i8.hip) integer codes, all four tiles;
 //   gemm_kernel        (gemm.hip) for row strides of 2^21 elements and more (beyond the 32-bit offsets of the others):
 //                      32x32x16 MFMA, register-staged loads.
-// They are three files because the kernels of a file are loaded together, by the first call that needs one of them, and
+// They are four files because the kernels of a file are loaded together, by the first call that needs one of them, and
 // few programs need all (library, first product and first small search of a process: 9.7 ms from one file, 7.6
-// from three; without the tiles of the other two files it was 6.6).
+// from three; without the tiles of the other files it was 6.6).
 // Tiling (wave64): block tile 256 x 256 outputs, k-tile 64; waves own 128 x 64
 // sub-tiles.  Both operands are K-contiguous in memory, so a fragment is one
 // 16-byte LDS read per lane.  LDS rows are 128 B (64 halves) and the eight
@@ -945,8 +946,9 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
 }
 
 constexpr int kDmaBK = 64;                   // k-tile depth of the pipelined kernels
-// Launches of the kernels of gemm_width.hip and gemm_i8.hip: `epi` is the epilogue; combinations that no call makes are refused.
+// Launches of the kernels of gemm_width.hip, gemm_tok.hip and gemm_i8.hip: `epi` is the epilogue; combinations that no call makes are refused.
 hipError_t launch_dma_width(const GemmDev& d, int epi, bool bf16, int tok_blocks, unsigned blocks, hipStream_t stream);
+hipError_t launch_dma_small_tok(const GemmDev& d, bool deep, unsigned blocks, hipStream_t stream);
 hipError_t launch_dma_i8(const GemmDev& d, int epi, GemmTile tile, unsigned blocks, hipStream_t stream);
 
 }  // namespace tlq

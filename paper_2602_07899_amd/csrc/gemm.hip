@@ -297,7 +297,7 @@ static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ld
 
 // Only the instances that some launch reaches are compiled: the loading of the code object is part of a
 // program's first call.  The searches' operands are fp16 in every form, so bf16 operands meet the loss only
-// in the single-candidate call, which keeps the big tiles (as does its per-token variant); the quadratic
+// in the single-candidate call, which keeps the big tiles; the quadratic
 // form is fp16, big and symmetric.
 template <typename T, int EPI>
 static hipError_t launch_dma(const GemmDev& d, GemmTile tile, unsigned blocks, hipStream_t stream) {
@@ -311,9 +311,10 @@ static hipError_t launch_dma(const GemmDev& d, GemmTile tile, unsigned blocks, h
     else gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
     return hipGetLastError();
   }
+  // one block per CU at most: four LDS stages hide the latency that a second block would
+  const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
+  if constexpr (EPI == EPI_LOSS_TOK && std::is_same<T, F16>::value) return launch_dma_small_tok(d, deep, blocks, stream);
   if constexpr (SMALL) {
-    // one block per CU at most: four LDS stages hide the latency that a second block would
-    const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
     if (!tail && deep) gemm_dma_kernel<T, 4, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
     else if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
     else if (deep) gemm_dma_kernel<T, 4, EPI, SYMK, true, 1><<<blocks, 256, 0, stream>>>(d);

@@ -876,3 +876,29 @@ def test_selection_of_few_and_many_partial_sums(gpu, n, co, na):
     # squares are added in 32 bits inside a tile: at most 320 in a chain, so 320 x 2^-24, and the products' own rounding
     np.testing.assert_allclose(host(err), ref, rtol=1e-4, atol=1e-9)
     assert abs(float(loss) - ref.mean()) <= 1e-4 * ref.mean()
+
+
+@pytest.mark.parametrize("n,ci,co", [(1, 8, 1), (129, 72, 127), (256, 320, 128), (511, 1096, 385), (2100, 200, 2100), (2048, 192, 2176)])
+@pytest.mark.parametrize("bf16,float_target", [(False, False), (False, True), (True, False)])
+def test_token_errors_in_small_tiles(gpu, n, ci, co, bf16, float_target):
+    """Losses with token errors of up to 512 tiles of 128 x 128: two and four k-tiles in flight (more than 256 tiles and up to
+    there), contractions that end inside a k-tile, tiles inside the matrix and at its edges."""
+    import torch
+    g = np.random.default_rng([28, n, ci])
+    rnd = BF if bf16 else F16
+    X, Wq = (np.asarray(rnd(g.standard_normal(s) * f), np.float64) for s, f in (((n, ci), 1.0), ((co, ci), 0.05)))
+    Y = X @ (Wq + g.standard_normal((co, ci)) * 0.01).T
+    tY = torch.zeros((n, co + -co % 8), dtype=torch.float32 if float_target else torch.bfloat16 if bf16 else torch.float16, device=gpu)[:, :co]
+    tY.copy_(torch.from_numpy(Y))
+    w = g.uniform(0.0, 2.0 / n, n).astype(np.float32)
+    p = tlq.params(bits=4, group=8, x_dtype=tlq.BF16 if bf16 else tlq.F16, yref_dtype=tlq.F32 if float_target else tlq.BF16 if bf16 else tlq.F16)
+    loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+    inv = torch.ones(ci, dtype=torch.float32, device=gpu)
+    tlq.weighted_layer_err(dev(X, gpu, bf16), dev(Wq, gpu, bf16), inv, tY, torch.from_numpy(w).to(gpu), p, loss, per_token_err=err)
+    ref = ((host(tY).astype(np.float64) - X @ Wq.T) ** 2).mean(1)
+    # (ci <= 1096 products in 32 bits, of sums about 20 times the residual; 64 squares in a chain)
+    np.testing.assert_allclose(host(err), ref, rtol=2e-3, atol=1e-12)
+    np.testing.assert_allclose(float(loss), (w.astype(np.float64) * ref).sum(), rtol=1e-3)
+    alone = torch.empty_like(loss)
+    tlq.weighted_layer_err(dev(X, gpu, bf16), dev(Wq, gpu, bf16), inv, tY, torch.from_numpy(w).to(gpu), p, alone)
+    np.testing.assert_allclose(float(alone), float(loss), rtol=1e-5)
