@@ -158,6 +158,7 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
   // 2048 76 -> 66)
   e.tile = gemm_tile(g, kTileSmall | kTileWide, INT64_MAX);
+  if (e.tile.small && !e.tile.tok_blocks) e.tile.tok_blocks = 4;     // (there is room for their token sums)
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
   e.partial = c.take<float>((size_t)std::max(big_o * big_t, e.tiles_o * e.tiles_t));
   e.tok_partial = c.take<float>((size_t)std::max(big_o, e.tiles_o) * n_tok);

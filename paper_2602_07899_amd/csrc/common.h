@@ -183,7 +183,8 @@ struct FinalDev {
 };
 
 // Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
-// or 128 x 128 (stores without tri, and fp16 losses).  gemm_tile says which is the fastest.
+// or 128 x 128 (stores without tri, and fp16 losses, with tok_partial
+// only if tok_blocks is 4).  gemm_tile says which is the fastest.
 struct GemmTile { bool small; int tok_blocks; };
 // S3+S4 / plain GEMM with store epilogue.
 struct GemmArgs : GemmTile {

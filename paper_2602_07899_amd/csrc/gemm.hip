@@ -313,7 +313,9 @@ static hipError_t launch_dma(const GemmDev& d, GemmTile tile, unsigned blocks, h
   }
   // one block per CU at most: four LDS stages hide the latency that a second block would
   const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
-  if constexpr (EPI == EPI_LOSS_TOK && std::is_same<T, F16>::value) return launch_dma_small_tok(d, deep, blocks, stream);
+  // (a caller has to say that its token sums have rows for these tiles)
+  if constexpr (EPI == EPI_LOSS_TOK && std::is_same<T, F16>::value)
+    return tile.tok_blocks != 4 ? hipErrorInvalidValue : launch_dma_small_tok(d, deep, blocks, stream);
   if constexpr (SMALL) {
     if (!tail && deep) gemm_dma_kernel<T, 4, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
     else if (!tail) gemm_dma_kernel<T, 2, EPI, SYMK, false, 1><<<blocks, 256, 0, stream>>>(d);
