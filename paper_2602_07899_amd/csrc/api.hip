@@ -157,7 +157,7 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
   // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
   // 2048 76 -> 66)
-  e.tile = gemm_tile(g, kTileSmall | kTileWide, INT64_MAX);
+  e.tile = gemm_tile(g, kTileSmall | kTileHalf | kTileWide, INT64_MAX);
   if (e.tile.small && !e.tile.tok_blocks) e.tile.tok_blocks = 4;     // (there is room for their token sums)
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
   e.partial = c.take<float>((size_t)std::max(big_o * big_t, e.tiles_o * e.tiles_t));
@@ -298,7 +298,7 @@ int64_t tlq_selftest_tile_map(int64_t n_tok, int64_t c_in, int64_t c_out, int32_
   p.bits = 4;
   if (n_cand > 1) g = search_args(n_tok, c_in, c_out, n_cand, false, false);
   else g.wide_patch = true;
-  g.tile() = n_cand > 1 ? search_tile(g, c_in, n_cand, use_diff_form(&p, n_tok, c_out)) : gemm_tile(g, kTileAll, INT64_MAX);
+  g.tile() = n_cand > 1 ? search_tile(g, c_in, n_cand, use_diff_form(&p, n_tok, c_out)) : gemm_tile(g, kTileAll | kTileHalf, INT64_MAX);
   if (blocks) *blocks = gemm_blocks(g);
   return tile_map_defects(n_tok, c_in, c_out, n_cand);
 }
@@ -536,7 +536,7 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     // few channels: the wide tile's subtraction, which stages the target in three goes, outweighs its products (two
     // candidates' searches without and with it, us: 5000 x 128 x 13824 292 and 328, 20,000 x 512 x 2048 with a 16-bit
     // target 243 and 252, a float one 293 and 285, 40,000 x 768 x 1000 381 and 363)
-    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(r, c_in >= 512 ? kTileAll : kTileSmall | kTileNarrow, INT64_MAX);
+    if (gemm_strides_ok(ldx, ldw)) r.tile() = gemm_tile(r, kTileHalf | (c_in >= 512 ? kTileAll : kTileSmall | kTileNarrow), INT64_MAX);
     r.Yref = Y_ref; r.ldy = ldy; r.yref_dtype = p->yref_dtype;   // subtracted in the epilogue (float output)
     TLQ_HIP(launch_gemm_store(r, st));
   }
@@ -717,7 +717,7 @@ tlq_status tlq_ref_output(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   g.bf16 = p->x_dtype == TLQ_BF16;
   g.Yout = Y; g.ldo = ldy; g.yout_dtype = p->yref_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, kTileAll, INT64_MAX);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, kTileAll | kTileHalf, INT64_MAX);
   return hip_status(launch_gemm_store(g, (hipStream_t)stream));
 }
 
@@ -776,7 +776,7 @@ static tlq_status apply_best_impl(const void* X, int64_t n_tok, int64_t c_in, in
   if (ld8) { g.i8_k = c_in; g.c_in = g.ldx = g.ldw = ld8 / 2; g.row_scale = steps; }      // (in units of 16 bits)
   g.Yout = X_next; g.ldo = ld_next; g.yout_dtype = p->x_dtype;
   g.wide_patch = true;   // one candidate: 8 weight panels stay per patch row, 4 token panels change (+1 .. +4 % measured)
-  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, kTileAll, INT64_MAX);
+  if (gemm_strides_ok(g.ldx, g.ldw)) g.tile() = gemm_tile(g, g.i8_k ? kTileAll : kTileAll | kTileHalf, INT64_MAX);
   return hip_status(launch_gemm_store(g, st));
 }
 

@@ -183,8 +183,9 @@ struct FinalDev {
 };
 
 // Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
-// or 128 x 128 (stores without tri, and fp16 losses, with tok_partial
-// only if tok_blocks is 4).  gemm_tile says which is the fastest.
+// or small: 128 rows x 32 tok_blocks (0 = 4, or 2: 128 x 64, not of integer codes), for stores without tri and fp16 losses
+// (128 x 128 with tok_partial: tok_blocks has to say 4).
+// gemm_tile says which is the fastest.
 struct GemmTile { bool small; int tok_blocks; };
 // S3+S4 / plain GEMM with store epilogue.
 struct GemmArgs : GemmTile {
@@ -215,7 +216,7 @@ void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tile
 // The tile for a launch of g's sizes, candidates and order.  kinds: tiles besides 256 x 256 that the launch has (stores and
 // fp16 losses: all; fp16 losses with tok_partial: not the narrow one; the quadratic form: the wide one); max_tiles: tiles per candidate
 // that the caller has room for, at least those of 256 x 256
-enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7 };
+enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7, kTileHalf = 8 };
 GemmTile gemm_tile(const GemmArgs& g, int kinds, int64_t max_tiles);
 // row strides that the pipelined kernel (and with it any tile but 256 x 256) takes
 bool gemm_strides_ok(int64_t ldx, int64_t ldw);

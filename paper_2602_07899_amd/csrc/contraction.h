@@ -22,11 +22,12 @@
 // pipelined kernels (16x16x32 MFMA, operands brought into LDS by LDS-DMA loads, two 64 KB stages, hand-placed waits):
 //   gemm_dma_kernel    (gemm.hip) tiles of 256 x 256 and 128 x 128;
 //   gemm_width_kernel  (gemm_width.hip) 256 x 192 and 256 x 320, for launches that they suit better (gemm_tile);
+//   gemm_half_kernel   (gemm_half.hip) 128 x 64, for launches of at most one of them a CU;
 //   gemm_small_tok_kernel  (gemm_tok.hip) 128 x 128 with the errors of tokens;
 //   gemm_i8_kernel     (gemm_i8.hip) integer codes, all four tiles;
 //   gemm_kernel        (gemm.hip) for row strides of 2^21 elements and more (beyond the 32-bit offsets of the others):
 //                      32x32x16 MFMA, register-staged loads.
-// They are four files because the kernels of a file are loaded together, by the first call that needs one of them, and
+// They are five files because the kernels of a file are loaded together, by the first call that needs one of them, and
 // few programs need all (library, first product and first small search of a process: 9.7 ms from one file, 7.6
 // from three; without the tiles of the other files it was 6.6).
 // Tiling (wave64): block tile 256 x 256 outputs, k-tile 64; waves own 128 x 64
@@ -685,8 +686,10 @@ __device__ __forceinline__ void lds_wait(u32x4 (&a)[4]) {
 }
 template <int N>
 __device__ __forceinline__ void lds_wait(u32x4 (&a)[4], u32x4 (&b)[N]) {
-  static_assert(N >= 3 && N <= 5, "token fragments of a wave tile");
-  if constexpr (N == 3)
+  static_assert(N >= 2 && N <= 5, "token fragments of a wave tile");
+  if constexpr (N == 2)
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]) : : "memory");
+  else if constexpr (N == 3)
     asm volatile("s_waitcnt lgkmcnt(0)"
                  : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]) : : "memory");
   else if constexpr (N == 4)
@@ -730,7 +733,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // JB = 3 or 5: the wave tile is 128 x 48 or 128 x 80 tokens (twelve or twenty MFMAs a phase); 80 take 252 registers and 144 KB
 // of LDS, the most that two waves a SIMD and one block a CU can have.
 // HALVES = 1: a block of 4 waves computes 128 x 128 outputs, a wave 64 x 64 (a phase per k32 step, all of
-// its eight fragments read one phase ahead); two blocks share a CU.  For launches whose 256 x 256 tiles
+// its eight fragments read one phase ahead); two blocks share a CU.  JB = 2: 128 x 64, a wave 64 x 32.  For launches whose 256 x 256 tiles
 // would leave CUs idle, see gemm_small_tiles.
 template <typename T, int NSTAGE, int EPI, bool SYMK, bool TAIL, int HALVES, int JB>
 __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
@@ -946,8 +949,9 @@ __device__ __forceinline__ void gemm_dma_body(const GemmDev& a) {
 }
 
 constexpr int kDmaBK = 64;                   // k-tile depth of the pipelined kernels
-// Launches of the kernels of gemm_width.hip, gemm_tok.hip and gemm_i8.hip: `epi` is the epilogue; combinations that no call makes are refused.
+// Launches of the kernels of gemm_width.hip, gemm_half.hip, gemm_tok.hip and gemm_i8.hip: `epi` is the epilogue; combinations that no call makes are refused.
 hipError_t launch_dma_width(const GemmDev& d, int epi, bool bf16, int tok_blocks, unsigned blocks, hipStream_t stream);
+hipError_t launch_dma_half(const GemmDev& d, int epi, bool bf16, unsigned blocks, hipStream_t stream);
 hipError_t launch_dma_small_tok(const GemmDev& d, bool deep, unsigned blocks, hipStream_t stream);
 hipError_t launch_dma_i8(const GemmDev& d, int epi, GemmTile tile, unsigned blocks, hipStream_t stream);
 

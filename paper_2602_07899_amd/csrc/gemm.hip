@@ -127,7 +127,7 @@ constexpr int64_t kChunkBytes = (int64_t)128 << 20;
 // 308, 960 428 -> 401; 1080 664 -> 667, 1720 762 -> 815: there a strip no longer fits an L2).
 constexpr int64_t kStripTiles = 1024;
 
-static int64_t tile_tokens(GemmTile t) { return t.small ? kSmall : 64 * (t.tok_blocks ? t.tok_blocks : 4); }
+static int64_t tile_tokens(GemmTile t) { return (t.small ? 32 : 64) * (t.tok_blocks ? t.tok_blocks : 4); }
 void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tiles_o, int64_t* tiles_t) {
   *tiles_o = ceil_div(c_out, tile.small ? kSmall : kBO);
   *tiles_t = ceil_div(n_tok, tile_tokens(tile));
@@ -271,6 +271,9 @@ GemmTile gemm_tile(const GemmArgs& args, int kinds, int64_t max_tiles) {
   int64_t to, tt;
   gemm_tile_counts(g.n_tok, g.c_out, best, &to, &tt);
   const bool few = to * tt * g.n_cand <= 512;
+  // at most one tile of 128 x 64 a CU (gemm_half.hip)
+  gemm_tile_counts(g.n_tok, g.c_out, GemmTile{true, 2}, &to, &tt);
+  if ((kinds & kTileHalf) && to * tt * g.n_cand <= 256 && to * tt <= max_tiles) return GemmTile{true, 2};
   auto consider = [&](GemmTile t, double first, double each) {
     gemm_tile_counts(g.n_tok, g.c_out, t, &to, &tt);
     if (to * tt > max_tiles) return;
@@ -311,6 +314,7 @@ static hipError_t launch_dma(const GemmDev& d, GemmTile tile, unsigned blocks, h
     else gemm_dma_kernel<T, 2, EPI, SYMK, true, 2><<<blocks, 512, 0, stream>>>(d);
     return hipGetLastError();
   }
+  if (tile.tok_blocks == 2) return launch_dma_half(d, EPI, std::is_same<T, BF16>::value, blocks, stream);
   // one block per CU at most: four LDS stages hide the latency that a second block would
   const bool deep = (int64_t)d.tiles_o * d.tiles_t * d.n_cand <= 256;
   // (a caller has to say that its token sums have rows for these tiles)
@@ -331,6 +335,7 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
   const bool dma = pipelined_ok(g);
   constexpr bool kHasInt = std::is_same<T, F16>::value && (EPI == EPI_LOSS || EPI == EPI_STORE);
   if (g.i8_k && (!kHasInt || !dma || !g.row_scale || (g.c_in % kDmaBK) != 0)) return hipErrorInvalidValue;
+  if (g.small && g.tok_blocks != 0 && g.tok_blocks != 4 && (g.tok_blocks != 2 || g.i8_k || g.tri)) return hipErrorInvalidValue;
   if (!dma && (g.small || (g.tok_blocks && g.tok_blocks != 4))) return hipErrorInvalidValue;   // (the callers ask gemm_strides_ok first)
   const GemmDev d = make_dev(g);
   const int64_t blocks = dev_blocks(d);
@@ -360,10 +365,10 @@ static hipError_t launch_gemm(const GemmArgs& g, const char* name, hipStream_t s
 // exactly once (0 = all maps are bijections onto the tiles), or -1 if memory runs out.
 int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand) {
   int64_t bad = 0;
-  // walks 0 - 15: bit 0 the order, bit 1 the patch shape, bits 2 and 3 the tile
-  const GemmTile tiles_of[4] = {{false, 0}, {true, 0}, {false, 3}, {false, 5}};
-  const int side_of[4] = {256, 128, 192, 320};
-  enum { kQuadratic = 16, kTriOut, kTriIn, kWalks };
+  // walks 0 - 19: bit 0 the order, bit 1 the patch shape, the others the tile
+  const GemmTile tiles_of[5] = {{false, 0}, {true, 0}, {false, 3}, {false, 5}, {true, 2}};
+  const int side_of[5] = {256, 128, 192, 320, 64};
+  enum { kQuadratic = 20, kTriOut, kTriIn, kWalks };
   for (int walk = 0; walk < kWalks; ++walk) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;

@@ -878,11 +878,12 @@ def test_selection_of_few_and_many_partial_sums(gpu, n, co, na):
     assert abs(float(loss) - ref.mean()) <= 1e-4 * ref.mean()
 
 
-@pytest.mark.parametrize("n,ci,co", [(1, 8, 1), (129, 72, 127), (256, 320, 128), (511, 1096, 385), (2100, 200, 2100), (2048, 192, 2176)])
+@pytest.mark.parametrize("n,ci,co", [(1, 8, 1), (129, 72, 127), (256, 320, 128), (511, 1096, 385), (1100, 136, 2000), (1152, 128, 2048),
+                                      (2100, 200, 2100), (2048, 192, 2176)])
 @pytest.mark.parametrize("bf16,float_target", [(False, False), (False, True), (True, False)])
 def test_token_errors_in_small_tiles(gpu, n, ci, co, bf16, float_target):
-    """Losses with token errors of up to 512 tiles of 128 x 128: two and four k-tiles in flight (more than 256 tiles and up to
-    there), contractions that end inside a k-tile, tiles inside the matrix and at its edges."""
+    """Losses with token errors in tiles of 128 x 64 (up to 256 of them) and 128 x 128 (up to 512): two and four k-tiles in
+    flight (more than 256 tiles and up to there), contractions that end inside a k-tile, tiles inside the matrix and at its edges."""
     import torch
     g = np.random.default_rng([28, n, ci])
     rnd = BF if bf16 else F16
@@ -902,3 +903,21 @@ def test_token_errors_in_small_tiles(gpu, n, ci, co, bf16, float_target):
     alone = torch.empty_like(loss)
     tlq.weighted_layer_err(dev(X, gpu, bf16), dev(Wq, gpu, bf16), inv, tY, torch.from_numpy(w).to(gpu), p, alone)
     np.testing.assert_allclose(float(alone), float(loss), rtol=1e-5)
+
+
+@pytest.mark.parametrize("n,ci,co", [(1, 8, 8), (63, 72, 128), (64, 64, 136), (65, 320, 248), (128, 128, 384), (1000, 1096, 2000), (64, 200, 16384)])
+@pytest.mark.parametrize("bf16,float_out", [(False, False), (False, True), (True, False)])
+def test_products_in_tiles_of_one_a_unit(gpu, n, ci, co, bf16, float_out):
+    """Stores in tiles of 128 x 64 (up to 256 of them): one k-tile and several, ends inside a k-tile, a ring, a tile."""
+    import torch
+    g = np.random.default_rng([29, n, ci])
+    rnd = BF if bf16 else F16
+    X, W = (np.asarray(rnd(g.standard_normal(s)), np.float64) for s in ((n, ci), (co, ci)))
+    dt = torch.float32 if float_out else torch.bfloat16 if bf16 else torch.float16
+    p = tlq.params(bits=4, group=8, x_dtype=tlq.BF16 if bf16 else tlq.F16, yref_dtype=tlq.F32 if float_out else tlq.BF16 if bf16 else tlq.F16)
+    Y = torch.full((n, co + 8), 7.0, dtype=dt, device=gpu)
+    tlq.ref_output(dev(X, gpu, bf16), dev(W, gpu, bf16), Y[:, :co], p)
+    want, mag = X @ W.T, np.abs(X) @ np.abs(W).T
+    eps = 0.0 if float_out else 2.0 ** -8 if bf16 else 2.0 ** -11     # the output's rounding, and ci additions in 32 bits
+    assert np.all(np.abs(host(Y[:, :co]) - want) <= eps * np.abs(want) + ci * 2.0 ** -24 * mag)
+    assert torch.all(Y[:, co:] == 7.0)
