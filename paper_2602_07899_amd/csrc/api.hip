@@ -652,9 +652,10 @@ tlq_status tlq_token_gram(const void* X, int64_t n_tok, int64_t c_in, int64_t ld
   r.X = g.xst; r.n_tok = c_in; r.c_in = g.kc; r.ldx = g.kp; r.x_cand_stride = g.kc;
   r.Wh = g.xst; r.c_out = c_in; r.ldw = g.kp; r.w_cand_stride = g.kc; r.n_cand = g.n_split; r.bf16 = false;
   r.Yout = g.H; r.ldo = c_in; r.yout_dtype = TLQ_F32; r.o_cand_stride = c_in * c_in; r.tri = true;
+  r.small = gemm_small_triangle(r);
   TLQ_HIP(launch_gemm_store(r, st));
   return hip_status(launch_gram_finish(g.H, c_in, g.n_split, c_in * c_in, g.wmax, g.e, v.factor, v.col_scale,
-                                       v.C, st));
+                                       v.C, r.small ? 128 : 256, st));
 }
 
 size_t tlq_scale_search_gram_workspace_bytes(int64_t c_in, int64_t c_out, int32_t n_alpha,

@@ -183,7 +183,7 @@ struct FinalDev {
 };
 
 // Output tile of the pipelined contraction: 256 rows x 64 tok_blocks tokens (3, 4 or 5 blocks of 16 tokens a wave; 0 = 4),
-// or small: 128 rows x 32 tok_blocks (0 = 4, or 2: 128 x 64, not of integer codes), for stores without tri and fp16 losses
+// or small: 128 rows x 32 tok_blocks (0 = 4, or 2: 128 x 64, not of integer codes), for stores (with tri only 128 x 128) and fp16 losses
 // (128 x 128 with tok_partial: tok_blocks has to say 4).
 // gemm_tile says which is the fastest.
 struct GemmTile { bool small; int tok_blocks; };
@@ -218,6 +218,7 @@ void gemm_tile_counts(int64_t n_tok, int64_t c_out, GemmTile tile, int64_t* tile
 // that the caller has room for, at least those of 256 x 256
 enum { kTileSmall = 1, kTileNarrow = 2, kTileWide = 4, kTileAll = 7, kTileHalf = 8 };
 GemmTile gemm_tile(const GemmArgs& g, int kinds, int64_t max_tiles);
+bool gemm_small_triangle(const GemmArgs& g);   // whether a store with tri is faster in tiles of 128 x 128
 // row strides that the pipelined kernel (and with it any tile but 256 x 256) takes
 bool gemm_strides_ok(int64_t ldx, int64_t ldw);
 int64_t gemm_blocks(const GemmArgs& g);   // workgroups of the launch (sizes, tile and order are read, no pointer)
@@ -237,7 +238,7 @@ hipError_t launch_gram_operand(const void* X, int64_t n_tok, int64_t c_in, int64
 // balanced fp16 matrix C, the per-channel factors of the weight errors and the factor that turns
 // d'^T C d' into the loss; e is scratch [c_in].
 hipError_t launch_gram_finish(float* H, int64_t c_in, int n_split, int64_t split_stride, const float* wmax,
-                              int* e, double* factor, float* col_scale, void* C, hipStream_t stream);
+                              int* e, double* factor, float* col_scale, void* C, int side, hipStream_t stream);
 
 hipError_t launch_finalize(const FinalDev& f, hipStream_t stream);
 // the same with one candidate and no selection, and err[t] = inv_c_out * the sum of column t of tok_partial [tiles_o, n_tok]

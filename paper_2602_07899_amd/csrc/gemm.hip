@@ -298,6 +298,14 @@ int64_t gemm_blocks(const GemmArgs& g) { return dev_blocks(make_dev(g)); }
 bool gemm_strides_ok(int64_t ldx, int64_t ldw) { return ldw < (1 << 21) && ldx < (1 << 21); }
 static bool pipelined_ok(const GemmArgs& g) { return gemm_strides_ok(g.ldx, g.ldw); }
 
+// Up to two small tiles a CU, as in gemm_small_tiles: few channels have few big tiles, with a long contraction each (the whole
+// token product, us big -> small, tokens x channels: 600 x 256 38 -> 27, 10,640 x 896 135 -> 71, 64,699 x 640 151 -> 120, 465
+// tiles of 4096 x 3840 137 -> 112; beyond, 528 tiles of 4200 x 4096 146 -> 156, 780 of 44,166 x 1536 197 -> 220).
+bool gemm_small_triangle(const GemmArgs& g) {
+  const int64_t side = ceil_div(g.c_out, kSmall);
+  return pipelined_ok(g) && side * (side + 1) / 2 * g.n_cand <= 512;
+}
+
 // Only the instances that some launch reaches are compiled: the loading of the code object is part of a
 // program's first call.  The searches' operands are fp16 in every form, so bf16 operands meet the loss only
 // in the single-candidate call, which keeps the big tiles; the quadratic
@@ -368,7 +376,7 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand)
   // walks 0 - 19: bit 0 the order, bit 1 the patch shape, the others the tile
   const GemmTile tiles_of[5] = {{false, 0}, {true, 0}, {false, 3}, {false, 5}, {true, 2}};
   const int side_of[5] = {256, 128, 192, 320, 64};
-  enum { kQuadratic = 20, kTriOut, kTriIn, kWalks };
+  enum { kQuadratic = 20, kTriOut, kTriIn, kSmallTriOut, kSmallTriIn, kWalks };
   for (int walk = 0; walk < kWalks; ++walk) {
     GemmArgs g{};
     g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = n_cand;
@@ -380,10 +388,11 @@ int64_t tile_map_defects(int64_t n_tok, int64_t c_in, int64_t c_out, int n_cand)
       g.cand_outer = g.wide_patch = g.sym_k = true;
     } else {
       g.tri = true;
-      g.n_tok = g.c_out = walk == kTriOut ? c_out : c_in;
+      g.small = walk >= kSmallTriOut;
+      g.n_tok = g.c_out = walk == kTriOut || walk == kSmallTriOut ? c_out : c_in;
     }
     const GemmDev d = make_dev(g);
-    const int64_t side_t = walk < kQuadratic ? side_of[walk >> 2] : 256, side_o = g.small ? 128 : 256;
+    const int64_t side_o = g.small ? 128 : 256, side_t = walk < kQuadratic ? side_of[walk >> 2] : side_o;
     if (d.tiles_o != (g.c_out + side_o - 1) / side_o || d.tiles_t != (g.n_tok + side_t - 1) / side_t) ++bad;
     const int64_t blocks = dev_blocks(d);
     const int64_t tiles = (int64_t)n_cand * d.tiles_o * d.tiles_t;

@@ -126,9 +126,9 @@ __global__ __launch_bounds__(1024) void gram_diag_kernel(const float* __restrict
 // H[0] += H[1] + ... + H[n_split - 1] in that order, over the 64 x 64 blocks of the computed
 // triangle (split-k partial products, each [c_in, c_in] float, `stride` elements apart).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(float* __restrict__ H, int64_t c_in, int n_split,
-                                                          int64_t stride) {
+                                                          int64_t stride, int side) {
   const int64_t a0 = (int64_t)blockIdx.y * GT, b0 = (int64_t)blockIdx.x * GT;
-  if ((b0 / 256) > (a0 / 256)) return;
+  if ((b0 / side) > (a0 / side)) return;
   for (int i = threadIdx.x; i < GT * GT / 4; i += 256) {
     const int64_t a = a0 + i / (GT / 4), b = b0 + (i % (GT / 4)) * 4;
     if (a >= c_in || b >= c_in) continue;     // c_in % 4 == 0: whole groups of four
@@ -141,14 +141,14 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(float* __restrict__ H,
   }
 }
 
-// C[a,b] = fp16(H[a,b] * 2^-(e_a + e_b)).  H holds the 256 x 256 tiles whose column tile is not
-// beyond their row tile; the others are read from the mirrored position.  A 64 x 64 block lies
+// C[a,b] = fp16(H[a,b] * 2^-(e_a + e_b)).  H holds the side x side tiles (256 or 128) whose column tile is
+// not beyond their row tile; the others are read from the mirrored position.  A 64 x 64 block lies
 // inside one such tile, so the choice is uniform per block.
 __global__ __launch_bounds__(256) void gram_convert_kernel(const float* __restrict__ H, int64_t c_in,
-                                                           const int* __restrict__ e, uint16_t* __restrict__ C) {
+                                                           const int* __restrict__ e, uint16_t* __restrict__ C, int side) {
   __shared__ float tile[GT][GT + 1];
   const int64_t a0 = (int64_t)blockIdx.y * GT, b0 = (int64_t)blockIdx.x * GT;
-  const bool direct = (b0 / 256) <= (a0 / 256);
+  const bool direct = (b0 / side) <= (a0 / side);
   const int64_t r0 = direct ? a0 : b0, q0 = direct ? b0 : a0;    // source rows / columns
   for (int i = threadIdx.x; i < GT * GT; i += 256) {
     const int r = i / GT, q = i % GT;
@@ -186,14 +186,14 @@ hipError_t launch_gram_operand(const void* X, int64_t n_tok, int64_t c_in, int64
 }
 
 hipError_t launch_gram_finish(float* H, int64_t c_in, int n_split, int64_t split_stride, const float* wmax,
-                              int* e, double* factor, float* col_scale, void* C, hipStream_t stream) {
+                              int* e, double* factor, float* col_scale, void* C, int side, hipStream_t stream) {
   const int64_t b = ceil_div(c_in, GT);
   if (b > 65535) return hipErrorInvalidValue;
   ProfScope ps("gram_scale", stream, (6.0 + 2.0 * n_split) * (double)c_in * (double)c_in);
   if (n_split > 1)
-    gram_reduce_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, n_split, split_stride);
+    gram_reduce_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, n_split, split_stride, side);
   gram_diag_kernel<<<1, 1024, 0, stream>>>(H, c_in, wmax, e, col_scale, factor);
-  gram_convert_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, e, (uint16_t*)C);
+  gram_convert_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, e, (uint16_t*)C, side);
   return hipGetLastError();
 }
 

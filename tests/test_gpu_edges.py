@@ -921,3 +921,22 @@ def test_products_in_tiles_of_one_a_unit(gpu, n, ci, co, bf16, float_out):
     eps = 0.0 if float_out else 2.0 ** -8 if bf16 else 2.0 ** -11     # the output's rounding, and ci additions in 32 bits
     assert np.all(np.abs(host(Y[:, :co]) - want) <= eps * np.abs(want) + ci * 2.0 ** -24 * mag)
     assert torch.all(Y[:, co:] == 7.0)
+
+
+@pytest.mark.parametrize("n,ci", [(40, 8), (300, 136), (700, 264), (9000, 392), (600, 4096)])
+def test_token_product_in_small_tiles(gpu, n, ci):
+    """The triangle of the token product in tiles of 128 x 128 (up to 512 of them; 4096 channels have 528 and big tiles): the
+    matrix is symmetric to the bit, whichever side of the diagonal a block of it came from."""
+    import torch
+    g = np.random.default_rng([30, n, ci])
+    X, w = F16(g.standard_normal((n, ci))), g.uniform(0.5, 1.0, n).astype(np.float32)
+    gram = torch.zeros(tlq.token_gram_bytes(ci), dtype=torch.uint8, device=gpu)
+    tlq.token_gram(dev(X, gpu, False), torch.from_numpy(w).to(gpu), tlq.params(), gram)
+    C = host(gram[256 + -(-4 * ci // 256) * 256:][:2 * ci * ci].view(torch.float16).view(ci, ci)).astype(np.float64)
+    assert np.array_equal(C, C.T)
+    Xs = F16(X.astype(np.float64) * np.sqrt(w / w.max())[:, None]).astype(np.float64)
+    G = Xs.T @ Xs
+    e = np.rint(np.log2(np.diag(G)) / 2)
+    want = G * 2.0 ** -(e[:, None] + e[None, :])
+    # one rounding to 16 bits, n additions in 32 bits; the tokens' own rounding may fall the other way at a tie of sqrt
+    np.testing.assert_allclose(C, want, rtol=2.0 ** -10, atol=4e-3)
