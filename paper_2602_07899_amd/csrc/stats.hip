@@ -34,7 +34,11 @@ int xstat_chunks(int64_t n_tok) {
 }
 
 // NW waves per block: 16 where a chunk has 128 rows at most (8 a wave; with 4 waves the two blocks of a
-// 256 x 512 input walked 32 rows each wave, 11 us against 4), 4 on longer chunks.
+// 256 x 512 input walked 32 rows each wave, 11 us against 4) and where few channels make few blocks, whose 4 waves with a
+// row each in flight leave memory idle: up to 2048 channels, and without a mask up to 5120 on chunks of more than 256 rows (us, 4
+// waves -> 16 with four rows each in flight: 24,000 x 312 13.6 -> 9.8, 64,699 x 640 46.6 -> 19.2, 153,600 x 1024 154 -> 52,
+// 44,166 x 1536 38 -> 24, 17,000 x 2048 18.8 -> 15.1, 60,000 x 4096 92 -> 79, 153,600 x 5120 247 -> 240).  Elsewhere 4, with as
+// many blocks as it takes (20,000 x 4096 27.7 and 28.3, 40,000 x 13,824 181 and 185, masked 153,600 x 5120 129 and 132).
 // NT: rows that come past the caches (153,600 x 5120: 265 -> 244 us, 6.4 TB/s).
 // MAXBITS: every block also leaves the largest magnitude (as bits) that it has seen in block_max, for the fp16
 // re-expression of bf16 tokens, which would read them all once more for it.
@@ -69,7 +73,17 @@ __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
   };
   if (MASKED || c0 < c_in) {
     if constexpr (!MASKED) {
-      for (int64_t r = r0 + wave; r < r1; r += NW) add(load16<NT>(X + r * ldx + c0));
+      constexpr int U = NW == 16 ? 4 : 1;                       // rows of a wave that are loaded together
+      int64_t r = r0 + wave;
+      for (; r + (U - 1) * NW < r1; r += U * NW) {
+        uint4 v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = load16<NT>(X + (r + i * NW) * ldx + c0);
+#pragma unroll
+        for (int i = 0; i < U; ++i) add(v[i]);
+      }
+      if constexpr (U > 1)
+        for (; r < r1; r += NW) add(load16<NT>(X + r * ldx + c0));
     } else {
       const int64_t cr = c0 < c_in ? c0 : 0;     // (every lane takes part in the look-up)
       // rows that are not selected are not read: the lanes look 64 of the wave's rows up at once, the set
@@ -166,7 +180,8 @@ static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_i
   const dim3 grid((unsigned)ceil_div(c_in, kXsCols), (unsigned)chunks);
   const uint16_t* x = (const uint16_t*)X;
   ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
-  const bool shallow = rows <= 128, nt = streams_past(2.0 * (double)n_tok * (double)c_in);
+  const bool wide = rows <= 128 || grid.x <= 4 || (!pos_mask && grid.x <= 10 && rows > 256);
+  const bool nt = streams_past(2.0 * (double)n_tok * (double)c_in);
   auto go = [&](auto kern, int waves) {
     kern<<<grid, waves * 64, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period, block_max);
   };
@@ -174,7 +189,8 @@ static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_i
     using T = decltype(t);
     constexpr int KIND = decltype(kind_c)::value;
     constexpr bool MASKED = decltype(masked_c)::value, MAXBITS = decltype(max_c)::value;
-    if (shallow) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, false>, 16);
+    if (wide && nt) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, true>, 16);
+    else if (wide) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, false>, 16);
     else if (nt) go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, true>, 4);
     else go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, false>, 4);
   };

@@ -940,3 +940,26 @@ def test_token_product_in_small_tiles(gpu, n, ci):
     want = G * 2.0 ** -(e[:, None] + e[None, :])
     # one rounding to 16 bits, n additions in 32 bits; the tokens' own rounding may fall the other way at a tie of sqrt
     np.testing.assert_allclose(C, want, rtol=2.0 ** -10, atol=4e-3)
+
+
+@pytest.mark.parametrize("n,c", [(16389, 8), (16500, 520), (33001, 2056), (30000, 5128)])
+@pytest.mark.parametrize("bf16,masked", [(False, False), (True, False), (True, True)])
+def test_statistic_of_long_chunks(gpu, n, c, bf16, masked):
+    """Chunks of more than 128 rows in blocks of 16 waves (up to 2048 channels, 5120 without a mask) and of 4: rows in fours
+    and the rest of a chunk, rows apart from each other."""
+    import torch
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(31 + n)
+    X = torch.randn((n, c + 8), generator=gen, device=gpu).to(torch.bfloat16 if bf16 else torch.float16)[:, :c]
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    out = torch.empty(c, dtype=torch.float32, device=gpu)
+    if masked:
+        mask = (torch.rand(n, generator=gen, device=gpu) < 0.3).to(torch.uint8)
+        tlq.x_stat_masked(X, mask, p, out)
+        want = X[mask.bool()].abs().amax(0).float()
+        assert torch.equal(out, want)
+    else:
+        tlq.x_stat(X, p, out)
+        want = torch.stack([part.double().abs().sum(0) for part in X.split(4096)]).sum(0) / n
+        # sums in 64 bits on both sides, one rounding to 32
+        assert torch.all((out.double() - want).abs() <= want * (2.0 ** -24 + 1e-12))
