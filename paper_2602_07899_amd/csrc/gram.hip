@@ -124,21 +124,26 @@ __global__ __launch_bounds__(1024) void gram_diag_kernel(const float* __restrict
 }
 
 // H[0] += H[1] + ... + H[n_split - 1] in that order, over the 64 x 64 blocks of the computed
-// triangle (split-k partial products, each [c_in, c_in] float, `stride` elements apart).
+// triangle (split-k partial products, each [c_in, c_in] float, `stride` elements apart).  Bound by memory at thousands of
+// channels and by latency at hundreds: a group of four a thread, eight partial products in flight (us, 640 x 640 x 15, four
+// groups a thread one after the other -> this: 17 -> 5).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(float* __restrict__ H, int64_t c_in, int n_split,
                                                           int64_t stride, int side) {
   const int64_t a0 = (int64_t)blockIdx.y * GT, b0 = (int64_t)blockIdx.x * GT;
   if ((b0 / side) > (a0 / side)) return;
-  for (int i = threadIdx.x; i < GT * GT / 4; i += 256) {
-    const int64_t a = a0 + i / (GT / 4), b = b0 + (i % (GT / 4)) * 4;
-    if (a >= c_in || b >= c_in) continue;     // c_in % 4 == 0: whole groups of four
-    float4 acc = *reinterpret_cast<const float4*>(H + a * c_in + b);
-    for (int k = 1; k < n_split; ++k) {
-      const float4 v = *reinterpret_cast<const float4*>(H + k * stride + a * c_in + b);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-    *reinterpret_cast<float4*>(H + a * c_in + b) = acc;
+  const int i = blockIdx.z * 256 + threadIdx.x;
+  const int64_t a = a0 + i / (GT / 4), b = b0 + (i % (GT / 4)) * 4;
+  if (a >= c_in || b >= c_in) return;         // c_in % 4 == 0: whole groups of four
+  float4 acc = *reinterpret_cast<const float4*>(H + a * c_in + b);
+  for (int k = 1; k < n_split; k += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4*>(H + (k + j < n_split ? k + j : k) * stride + a * c_in + b);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k + j < n_split) { acc.x += v[j].x; acc.y += v[j].y; acc.z += v[j].z; acc.w += v[j].w; }
   }
+  *reinterpret_cast<float4*>(H + a * c_in + b) = acc;
 }
 
 // C[a,b] = fp16(H[a,b] * 2^-(e_a + e_b)).  H holds the side x side tiles (256 or 128) whose column tile is
@@ -150,11 +155,18 @@ __global__ __launch_bounds__(256) void gram_convert_kernel(const float* __restri
   const int64_t a0 = (int64_t)blockIdx.y * GT, b0 = (int64_t)blockIdx.x * GT;
   const bool direct = (b0 / side) <= (a0 / side);
   const int64_t r0 = direct ? a0 : b0, q0 = direct ? b0 : a0;    // source rows / columns
-  for (int i = threadIdx.x; i < GT * GT; i += 256) {
-    const int r = i / GT, q = i % GT;
-    float v = 0.0f;
-    if (r0 + r < c_in && q0 + q < c_in) v = H[(r0 + r) * c_in + q0 + q];
-    tile[r][q] = v;
+  // (all of a thread's loads in flight, c_in % 4 == 0: 640 channels 8.4 -> 5.2 us)
+  float4 in[GT * GT / 4 / 256];
+#pragma unroll
+  for (int j = 0; j < GT * GT / 4 / 256; ++j) {
+    const int i = j * 256 + threadIdx.x, r = i / (GT / 4), q = i % (GT / 4) * 4;
+    in[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (r0 + r < c_in && q0 + q < c_in) in[j] = *reinterpret_cast<const float4*>(H + (r0 + r) * c_in + q0 + q);
+  }
+#pragma unroll
+  for (int j = 0; j < GT * GT / 4 / 256; ++j) {
+    const int i = j * 256 + threadIdx.x, r = i / (GT / 4), q = i % (GT / 4) * 4;
+    tile[r][q] = in[j].x; tile[r][q + 1] = in[j].y; tile[r][q + 2] = in[j].z; tile[r][q + 3] = in[j].w;
   }
   __syncthreads();
   for (int i = threadIdx.x; i < GT * GT; i += 256) {
@@ -191,7 +203,7 @@ hipError_t launch_gram_finish(float* H, int64_t c_in, int n_split, int64_t split
   if (b > 65535) return hipErrorInvalidValue;
   ProfScope ps("gram_scale", stream, (6.0 + 2.0 * n_split) * (double)c_in * (double)c_in);
   if (n_split > 1)
-    gram_reduce_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, n_split, split_stride, side);
+    gram_reduce_kernel<<<dim3((unsigned)b, (unsigned)b, GT * GT / 4 / 256), 256, 0, stream>>>(H, c_in, n_split, split_stride, side);
   gram_diag_kernel<<<1, 1024, 0, stream>>>(H, c_in, wmax, e, col_scale, factor);
   gram_convert_kernel<<<dim3((unsigned)b, (unsigned)b), 256, 0, stream>>>(H, c_in, e, (uint16_t*)C, side);
   return hipGetLastError();
