@@ -101,9 +101,11 @@ constexpr int64_t kAttWide = 1LL << 27;   // row strides from which eight rows n
 // - 64 keys a step: the accumulators of a query are rescaled where it meets a new maximum, and some query of a wave
 //   does so in most steps, so half the steps need little more than half of those 64 multiplications.  The two query tiles
 //   are rescaled apart, and in the first step there is nothing to rescale.
-// - Scores go into one FMA with the factor of the exponential; the sum of the probabilities is taken over their 16-bit
-//   values, two in an instruction (error against 64 bits before the output is rounded, bf16: 8.1e-4 -> 7.9e-4).
-//   Together 38 % fewer vector instructions than one multiplication, subtraction, multiplication and addition a score.
+// - A score less the maximum, times the factor of the exponential (before: two multiplications and a subtraction); the sum of
+//   the probabilities is taken over their 16-bit values, two in an instruction (error against 64 bits before the output is
+//   rounded, bf16: 8.1e-4 -> 7.9e-4).  Fewer vector instructions, 2.68 -> 2.45 ms with the steps above.  (One FMA of the score
+//   with the factor and the rounded product of maximum and factor takes 1.4 % off the whole, but the largest score's exponent is
+//   then the rounding of that product and not 0: at scores of 2^30 finite inputs gave infinities and NaN.)
 // - 16x16x32 products: half the accumulator traffic of the 32x32x16 shape for the same operands (2.45 -> 2.38 ms).
 // - A wave in its products goes first (s_setprio): the others of its SIMD fill in the softmax (2.38 -> 2.33 ms).
 // - One K and one V tile in LDS, three waves per SIMD (<= 168 registers, 32 KB of LDS a block).  The next K tile is on its
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256, 3) void causal_attention_kernel(
   for (int d = 0; d < 8; ++d)
 #pragma unroll
     for (int u = 0; u < 2; ++u) acc[d][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  // the running maximum of q . k times `scale` (of tile 0 in the even rows of lanes, of tile 1 in the odd ones), the sums of
+  // the running maximum of q . k (of tile 0 in the even rows of lanes, of tile 1 in the odd ones), the sums of
   // the probabilities as they are rounded
   float mc = -INFINITY, l_run[2] = {0.0f, 0.0f};
 
@@ -277,13 +279,13 @@ __global__ __launch_bounds__(256, 3) void causal_attention_kernel(
     }
     const float both = swap16_max(mx[0], mx[1]);
     // (key 0 is visible to every query; elsewhere than at a new maximum the factor is exactly 1)
-    const float top = swap32_max(both, both) * scale;
+    const float top = swap32_max(both, both);
     const uint64_t up = __builtin_amdgcn_ballot_w64(top > mc);
     if (kt == 0) {
       mc = top;
     } else if (up) {
       const float to = top > mc ? top : mc;
-      float al[2] = {__builtin_amdgcn_exp2f(mc - to), 0.0f};
+      float al[2] = {__builtin_amdgcn_exp2f((mc - to) * scale), 0.0f};
       al[1] = al[0];
       mc = to;
       swap16(al[0], al[1]);
@@ -303,11 +305,12 @@ __global__ __launch_bounds__(256, 3) void causal_attention_kernel(
     __builtin_amdgcn_sched_barrier(0);
     float ref[2] = {mc, mc};
     swap16(ref[0], ref[1]);
-    // probabilities of keys 2 e, 2 e + 1 (of eight) of a lane in block w, tile u
+    // probabilities of keys 2 e, 2 e + 1 (of eight) of a lane in block w, tile u.  The difference first: the largest score's is
+    // exactly 0, whatever its size
     auto pair_of = [&](int w, int u, int e) __attribute__((always_inline)) {
       const f32x4& x = s[2 * w + (e >> 1)][u];
-      const uint32_t v = pack2<T>(__builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * (e & 1)], scale, -ref[u])),
-                                  __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * (e & 1) + 1], scale, -ref[u])));
+      const uint32_t v = pack2<T>(__builtin_amdgcn_exp2f((x[2 * (e & 1)] - ref[u]) * scale),
+                                  __builtin_amdgcn_exp2f((x[2 * (e & 1) + 1] - ref[u]) * scale));
       l_run[u] = add2<T>(v, l_run[u]);
       asm volatile("" : "+v"(l_run[u]));     // (now, not when its operands have been held to the end)
       return v;

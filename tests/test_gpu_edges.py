@@ -65,6 +65,28 @@ def test_attention_tile_remainders(gpu, bf16, seq, heads, samples):
     assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
 
 
+@pytest.mark.parametrize("seq,heads", [(200, 2), (300, 86)])
+@pytest.mark.parametrize("bf16,size", [(False, 8192.0), (False, 65504.0), (True, 2.0 ** 15), (True, 2.0 ** 18), (True, 2.0 ** 40)])
+def test_attention_scores_of_any_size(gpu, bf16, size, seq, heads):
+    """Scores up to 2^80: a query gives all its weight to its largest key, or shares it evenly among equal ones.  One channel of
+    q and k is not zero, so the products are exact in 32 bits, and different ones are at least 1/128 apart, thousands in the exponent."""
+    import torch
+    g = np.random.default_rng([32, seq, int(np.log2(size))])
+    width = heads * 128
+    rnd = BF if bf16 else F16
+    q, k = np.zeros((seq, width)), np.zeros((seq, width))
+    at = np.arange(heads) * 128 + g.integers(0, 128, heads)
+    q[:, at] = rnd(g.choice([-1.0, 1.0], (seq, heads)) * size * g.uniform(0.5, 1.0, (seq, heads)))
+    k[:, at] = rnd(size * g.integers(-64, 65, (seq, heads)) / 64.0)
+    v = np.asarray(rnd(g.standard_normal((seq, width))), np.float64)
+    want, mag = ost.causal_attention(q, k, v, heads, seq), ost.causal_attention(q, k, np.abs(v), heads, seq)
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    out = torch.empty((seq, width), dtype=torch.bfloat16 if bf16 else torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
+    eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # as above
+    assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+
+
 @pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, ""),
                                                         (True, 259, 87, 1, "K"), (False, 257, 87, 1, "V")])
 def test_attention_far_rows_and_partial_groups(gpu, bf16, seq, heads, samples, far):
