@@ -49,8 +49,8 @@ def test_attention_step_and_block_edges(gpu, bf16, seq, heads, samples):
                                                (257, 43, 2), (271, 86, 1), (273, 29, 3), (304, 86, 1), (321, 43, 2), (335, 29, 3),
                                                (383, 86, 1), (385, 65, 1)])
 def test_attention_tile_remainders(gpu, bf16, seq, heads, samples):
-    """Steps of 32 keys (one sequence or few); 64-key tiles of two 32-key blocks, of which a wave's last may be the first or the
-    second, with 16-query tiles that are rescaled apart (more than 256 blocks): scores that grow with the key make every step meet new maxima in some queries."""
+    """Sequences that end inside 16, 32, 64 and 128 keys and just behind them, in launches of few blocks and of more than one a
+    unit; scores that grow with the key make every step meet new maxima in some queries."""
     import torch
     g = np.random.default_rng([24, seq, heads])
     n, width = seq * samples, heads * 128
@@ -85,6 +85,47 @@ def test_attention_scores_of_any_size(gpu, bf16, size, seq, heads):
     tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
     eps = 2.0 ** -8 if bf16 else 2.0 ** -11       # as above
     assert np.all(np.abs(host(out) - want) <= eps * (mag + np.abs(want)) + 2e-6)
+
+
+@pytest.mark.parametrize("seq,heads", [(200, 2), (300, 86)])
+@pytest.mark.parametrize("bf16,gap", [(False, 7.671875), (False, 7.78125), (True, 7.28125), (True, 7.625)])
+def test_attention_divides_by_the_sum_in_32_bits(gpu, bf16, gap, seq, heads):
+    """The probabilities are rounded to 16 bits for the product with V, not for their sum.  Key 0 has weight 1, all others
+    exp(-gap / sqrt(128)), just above 1/2 and nearly half a unit of the last place off its rounding: dividing by the sum of
+    the rounded ones would be off by 2^-11 (bf16: 2^-8), almost a unit of an output just below 2."""
+    import torch
+    g = np.random.default_rng([33, seq, int(gap * 64)])
+    width = heads * 128
+    rnd = BF if bf16 else F16
+    q, k = np.zeros((seq, width)), np.zeros((seq, width))
+    q[:, ::128], k[0, ::128] = 1.0, gap
+    assert float(rnd(np.array([gap]))[0]) == gap
+    v = np.asarray(rnd(np.broadcast_to(g.uniform(1.5, 2.0, width), (seq, width))), np.float64)
+    weight = np.exp(-gap / np.sqrt(128.0))
+    rounded = float(rnd(np.array([weight]))[0])
+    n = np.arange(seq)[:, None]
+    want = v * (1.0 + n * rounded) / (1.0 + n * weight)
+    p = tlq.params(x_dtype=tlq.BF16 if bf16 else tlq.F16)
+    out = torch.empty((seq, width), dtype=torch.bfloat16 if bf16 else torch.float16, device=gpu)
+    tlq.causal_attention(dev(q, gpu, bf16), dev(k, gpu, bf16), dev(v, gpu, bf16), heads, seq, p, out)
+    half = 2.0 ** (np.floor(np.log2(want)) - (8 if bf16 else 11))      # the output's rounding; sums of up to 300 terms in 32 bits
+    assert np.all(np.abs(host(out) - want) <= half + want * (seq + 8) * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("bf16,seq,heads,samples", [(False, 72, 8, 40), (True, 300, 8, 16), (True, 513, 6, 11)])
+def test_attention_of_a_sample_does_not_depend_on_its_neighbours(gpu, bf16, seq, heads, samples):
+    """A calibration set may be split into any batches: a sample's outputs have the same bits alone and beside others."""
+    import torch
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(34 + seq)
+    dt, p = (torch.bfloat16, tlq.params(x_dtype=tlq.BF16)) if bf16 else (torch.float16, tlq.params())
+    q, k, v = ((torch.randn((seq * samples, heads * 128), generator=gen, device=gpu) * 1.4).to(dt) for _ in range(3))
+    out, one = torch.empty_like(q), torch.empty_like(q)
+    tlq.causal_attention(q, k, v, heads, seq, p, out)
+    for b in range(samples):
+        r = slice(b * seq, (b + 1) * seq)
+        tlq.causal_attention(q[r], k[r], v[r], heads, seq, p, one[r])
+    assert torch.equal(out.view(torch.int16), one.view(torch.int16))
 
 
 @pytest.mark.parametrize("bf16,seq,heads,samples,far", [(False, 40, 1, 1, "K"), (True, 35, 1, 1, "V"), (True, 33, 25, 3, ""),
