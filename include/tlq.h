@@ -177,7 +177,10 @@ tlq_status tlq_act_fake_quant(const void* X, int64_t n_tok, int64_t c_in, int64_
  * loss: out float [1]; per_token_err: out float [n_tok] or NULL.
  * The operand that enters the matrix cores is round16(Wdq * inv_s); on problems with only a
  * handful of outputs that rounding can show in the loss beyond 1e-3 (tlq_scale_search, which
- * also sees W, avoids it there). */
+ * also sees W, avoids it there).
+ * Where the outputs are few tiles the query asks for the room of tiles of 128 rows; a
+ * workspace with room for those of 256 rows (4 bytes for each of them and for n_tok of every 256
+ * outputs instead of every 128) is taken too, and the call is slower. */
 size_t tlq_weighted_layer_err_workspace_bytes(int64_t n_tok, int64_t c_in, int64_t c_out,
                                               const tlq_params* p);
 tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,

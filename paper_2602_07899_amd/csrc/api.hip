@@ -147,8 +147,9 @@ struct ErrPlan {
   float* partial; float* tok_partial; uint16_t* folded; uint32_t* xmax; uint16_t* xh; float* sig;
   size_t bytes; int64_t tiles_o, tiles_t; GemmTile tile;   // xh doubles as the code matrix in act mode
 };
-// fp16: fp16 operands for the pipelined kernel.  The workspace has room for the tiles of either
-ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act, bool fp16 = false) {
+// fp16: fp16 operands for the pipelined kernel; small: there is room for the tiles of 128 rows, which the workspace query asks
+// for: up to twice the token sums, and partials.  Less is enough for the others.
+ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16, bool act, bool fp16, bool small) {
   ErrPlan e;
   Carver c(ws);
   int64_t big_o, big_t;
@@ -157,7 +158,7 @@ ErrPlan plan_err(void* ws, int64_t n_tok, int64_t c_in, int64_t c_out, bool bf16
   g.n_tok = n_tok; g.c_in = c_in; g.c_out = c_out; g.n_cand = 1;
   // (also with a float target, which no tile stages: 10,240 x 4096 x 4096 fp16 us 256 -> 320: 338 -> 297, 20,000 x 512 x
   // 2048 76 -> 66)
-  e.tile = gemm_tile(g, kTileSmall | kTileHalf | kTileWide, INT64_MAX);
+  e.tile = gemm_tile(g, small ? kTileSmall | kTileHalf | kTileWide : kTileWide, small ? INT64_MAX : big_o * big_t);
   if (e.tile.small && !e.tile.tok_blocks) e.tile.tok_blocks = 4;     // (there is room for their token sums)
   gemm_tile_counts(n_tok, c_out, e.tile, &e.tiles_o, &e.tiles_t);
   e.partial = c.take<float>((size_t)std::max(big_o * big_t, e.tiles_o * e.tiles_t));
@@ -408,7 +409,7 @@ tlq_status tlq_act_fake_quant(const void* X, int64_t n_tok, int64_t c_in, int64_
 size_t tlq_weighted_layer_err_workspace_bytes(int64_t n_tok, int64_t c_in, int64_t c_out,
                                               const tlq_params* p) {
   if (n_tok <= 0 || c_in <= 0 || c_out <= 0 || check_params(p) != TLQ_OK) return 0;
-  return plan_err(nullptr, n_tok, c_in, c_out, p->x_dtype == TLQ_BF16, p->act_bits != 0).bytes;
+  return plan_err(nullptr, n_tok, c_in, c_out, p->x_dtype == TLQ_BF16, p->act_bits != 0, true, true).bytes;
 }
 
 tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
@@ -424,12 +425,13 @@ tlq_status tlq_weighted_layer_err(const void* X, int64_t n_tok, int64_t c_in, in
   if ((c_in % 8) != 0) return TLQ_ERR_SHAPE;
   if (!mat16_aligned(X, ldx) || !mat16_aligned(Wdq, ldw) || !mat_aligned(Y_ref, ldy, p->yref_dtype))
     return TLQ_ERR_ALIGN;
-  TLQ_TRY(check_ws(workspace, workspace_bytes,
-                   tlq_weighted_layer_err_workspace_bytes(n_tok, c_in, c_out, p)));
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = p->x_dtype == TLQ_BF16;
   const bool act = p->act_bits != 0;
-  ErrPlan e = plan_err(workspace, n_tok, c_in, c_out, bf16, act, gemm_strides_ok(ldx, ldw) && (!bf16 || act || inv_s));
+  const bool fp16 = gemm_strides_ok(ldx, ldw) && (!bf16 || act || inv_s);
+  ErrPlan e = plan_err(workspace, n_tok, c_in, c_out, bf16, act, fp16, true);
+  if (workspace_bytes < e.bytes) e = plan_err(workspace, n_tok, c_in, c_out, bf16, act, fp16, false);
+  TLQ_TRY(check_ws(workspace, workspace_bytes, e.bytes));
   GemmArgs g{};
   g.X = X; g.n_tok = n_tok; g.c_in = c_in; g.ldx = ldx;
   g.Wh = Wdq; g.c_out = c_out; g.ldw = ldw; g.w_cand_stride = 0; g.n_cand = 1; g.bf16 = bf16;

@@ -968,6 +968,44 @@ def test_token_errors_in_small_tiles(gpu, n, ci, co, bf16, float_target):
     np.testing.assert_allclose(float(alone), float(loss), rtol=1e-5)
 
 
+def _layer_err_room(n, ci, co, bf16):
+    """Bytes of a workspace of tlq_weighted_layer_err for tiles of 256 x 256: partial sums, token sums, folded weights, a word,
+    tokens in fp16, each in whole units of 256 bytes."""
+    to, tt = -(-co // 256), -(-n // 256)
+    return sum(-(-b // 256) * 256 for b in (4 * to * tt, 4 * to * n, 2 * co * ci, 4, 2 * n * ci if bf16 else 0))
+
+
+@pytest.mark.parametrize("n,ci,co,bf16", [(1, 8, 1, True), (129, 72, 1000, False), (1948, 32, 10145, True), (1100, 136, 2000, False)])
+def test_layer_error_with_the_room_of_big_tiles(gpu, n, ci, co, bf16):
+    """A workspace that holds the sums of 256 x 256 tiles only, less than the query asks for where smaller ones are
+    faster, is enough, and nothing behind it is written."""
+    import torch
+    g = np.random.default_rng([35, n, ci])
+    rnd = BF if bf16 else F16
+    X, Wq = (np.asarray(rnd(g.standard_normal(s) * f), np.float64) for s, f in (((n, ci), 1.0), ((co, ci), 0.05)))
+    dt, code = (torch.bfloat16, tlq.BF16) if bf16 else (torch.float16, tlq.F16)
+    tY = torch.zeros((n, co + -co % 8), dtype=dt, device=gpu)[:, :co]
+    tY.copy_(torch.from_numpy(X @ (Wq + g.standard_normal((co, ci)) * 0.01).T))
+    w = torch.from_numpy(g.uniform(0.0, 2.0 / n, n).astype(np.float32)).to(gpu)
+    p = tlq.params(bits=4, group=8, x_dtype=code, yref_dtype=code)
+    inv = torch.ones(ci, dtype=torch.float32, device=gpu)
+    room = _layer_err_room(n, ci, co, bf16)
+    assert room <= tlq.weighted_layer_err_workspace_bytes(n, ci, co, p)
+    buf = torch.full((room + 4096,), 0xA5, dtype=torch.uint8, device=gpu)
+    got = []
+    for ws in (None, buf[:room]):
+        loss, err = torch.empty(1, dtype=torch.float32, device=gpu), torch.empty(n, dtype=torch.float32, device=gpu)
+        tlq.weighted_layer_err(dev(X, gpu, bf16), dev(Wq, gpu, bf16), inv, tY, w, p, loss, per_token_err=err, workspace=ws)
+        got.append((float(loss), host(err)))
+    assert torch.all(buf[room:] == 0xA5)
+    # the same products; squares are added in another order, at most 320 in a chain of 32 bits
+    np.testing.assert_allclose(got[1][1], got[0][1], rtol=320 * 2.0 ** -24, atol=1e-12)
+    np.testing.assert_allclose(got[1][0], got[0][0], rtol=320 * 2.0 ** -24)
+    with pytest.raises(tlq.TlqError) as e:
+        tlq.weighted_layer_err(dev(X, gpu, bf16), dev(Wq, gpu, bf16), inv, tY, w, p, loss, workspace=buf[:room - 1])
+    assert e.value.status == tlq.ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("n,ci,co", [(1, 8, 8), (63, 72, 128), (64, 64, 136), (65, 320, 248), (128, 128, 384), (1000, 1096, 2000), (64, 200, 16384)])
 @pytest.mark.parametrize("bf16,float_out", [(False, False), (False, True), (True, False)])
 def test_products_in_tiles_of_one_a_unit(gpu, n, ci, co, bf16, float_out):
