@@ -22,6 +22,10 @@ def host(t):
     return t.detach().float().cpu().numpy().astype(np.float64)
 
 
+def host64(t):
+    return t.detach().double().cpu().numpy()
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("seq,heads,samples", [(31, 9, 1), (33, 1, 9), (63, 3, 3), (64, 2, 1), (65, 1, 1), (96, 1, 2),
                                                (128, 1, 1), (160, 2, 1), (257, 1, 1), (1100, 1, 1), (400, 7, 1),
@@ -1024,23 +1028,27 @@ def test_products_in_tiles_of_one_a_unit(gpu, n, ci, co, bf16, float_out):
     assert torch.all(Y[:, co:] == 7.0)
 
 
-@pytest.mark.parametrize("n,ci", [(40, 8), (300, 136), (700, 264), (9000, 392), (600, 4096)])
+@pytest.mark.parametrize("n,ci", [(40, 8), (300, 136), (700, 264), (9000, 392), (45000, 264), (600, 4096)])
 def test_token_product_in_small_tiles(gpu, n, ci):
-    """The triangle of the token product in tiles of 128 x 128 (up to 512 of them; 4096 channels have 528 and big tiles): the
-    matrix is symmetric to the bit, whichever side of the diagonal a block of it came from."""
+    """The triangle of the token product in tiles of 128 x 128 (up to 512 of them; 4096 channels have 528 and big tiles), in
+    one, two and ten parts of the tokens: the matrix is symmetric to the bit, whichever side of the diagonal a block of it
+    came from.  The weights' square roots are exact, and so are the weighted tokens in 16 bits."""
     import torch
     g = np.random.default_rng([30, n, ci])
-    X, w = F16(g.standard_normal((n, ci))), g.uniform(0.5, 1.0, n).astype(np.float32)
+    X, w = F16(g.standard_normal((n, ci))), g.choice([1.0, 0.25], n).astype(np.float32)
+    w[0] = 1.0
     gram = torch.zeros(tlq.token_gram_bytes(ci), dtype=torch.uint8, device=gpu)
-    tlq.token_gram(dev(X, gpu, False), torch.from_numpy(w).to(gpu), tlq.params(), gram)
-    C = host(gram[256 + -(-4 * ci // 256) * 256:][:2 * ci * ci].view(torch.float16).view(ci, ci)).astype(np.float64)
-    assert np.array_equal(C, C.T)
-    Xs = F16(X.astype(np.float64) * np.sqrt(w / w.max())[:, None]).astype(np.float64)
-    G = Xs.T @ Xs
+    tX, tw = dev(X, gpu, False), torch.from_numpy(w).to(gpu)
+    tlq.token_gram(tX, tw, tlq.params(), gram)
+    C = gram[256 + -(-4 * ci // 256) * 256:][:2 * ci * ci].view(torch.float16).view(ci, ci)
+    assert torch.equal(C, C.t())
+    Xs = (tX.float() * tw.sqrt()[:, None]).half().double()
+    Xt = Xs.t().contiguous()
+    G, mag = host64(Xt @ Xs), host64(Xt.abs() @ Xs.abs())
     e = np.rint(np.log2(np.diag(G)) / 2)
-    want = G * 2.0 ** -(e[:, None] + e[None, :])
-    # one rounding to 16 bits, n additions in 32 bits; the tokens' own rounding may fall the other way at a tie of sqrt
-    np.testing.assert_allclose(C, want, rtol=2.0 ** -10, atol=4e-3)
+    unit = 2.0 ** -(e[:, None] + e[None, :])
+    # one rounding to 16 bits; in 32 bits 32 products to an accumulator at a time, and up to 16 parts
+    assert np.all(np.abs(host64(C) - G * unit) <= 2.0 ** -11 * np.abs(G) * unit + 2.0 ** -25 + (n / 32 + 32 + 16) * 2.0 ** -24 * mag * unit)
 
 
 @pytest.mark.parametrize("n,c", [(16389, 8), (16500, 520), (33001, 2056), (30000, 5128)])
