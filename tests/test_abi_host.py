@@ -227,8 +227,8 @@ def test_only_reachable_contraction_kernels_are_compiled():
     """The library holds the contraction kernels that some call launches and no others (every one lengthens
     the loading of the library): operand type, LDS stages, epilogue (loss, loss with per-token
     errors, store, quadratic form), symmetric form, k tail, 64-row halves of a wave tile; of the wider and narrower tiles
-    operand type, epilogue, symmetric form, k tail and token blocks; of the integer ones LDS stages, epilogue, halves
-    and token blocks."""
+    operand type, epilogue, symmetric form, k tail and token blocks; of the 128 x 64 ones operand type, epilogue and k tail; of
+    the 128 x 128 ones with token errors LDS stages and k tail; of the integer ones LDS stages, epilogue, halves and token blocks."""
     blob = open(tlq.LIB_PATH, "rb").read()
 
     def found(pattern):
@@ -248,15 +248,22 @@ def test_only_reachable_contraction_kernels_are_compiled():
     want |= {("F16", epi, 0, tail, jb) for tail in (0, 1) for epi, jb in ((LOSS, 3), (LOSS, 5), (TOK, 5))}
     want |= {("F16", DOT, 1, tail, 5) for tail in (0, 1)}
     assert have == want, (sorted(have - want), sorted(want - have))
+    have = found(rb"gemm_half_kernel" + ty + rb"Li(\d)ELb(\d)")
+    want = {(t, epi, tail) for tail in (0, 1) for t, epi in (("F16", LOSS), ("F16", TOK), ("F16", STORE), ("BF16", STORE))}
+    assert have == want, (sorted(have - want), sorted(want - have))
+    have = found(rb"gemm_small_tok_kernelILi(\d)ELb(\d)")
+    want = {(st, tail) for st in (2, 4) for tail in (0, 1)}
+    assert have == want, (sorted(have - want), sorted(want - have))
     have = found(rb"gemm_i8_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)")
     want = {(2, epi, 2, jb) for epi in (LOSS, STORE) for jb in (3, 4, 5)} | {(st, epi, 1, 4) for epi in (LOSS, STORE) for st in (2, 4)}
     assert have == want, (sorted(have - want), sorted(want - have))
 
 
-def test_contraction_kernels_are_loaded_in_three_parts():
-    """A code object is loaded as a whole by the first call that needs one of its kernels: square, wider and narrower, and
-    integer tiles are one each, and the other kernels of the library are in none of them."""
-    families = [rb"gemm_dma_kernel", rb"gemm_width_kernel", rb"gemm_i8_kernel", rb"quant_row_kernel", rb"xstat_partial_kernel"]
+def test_contraction_kernels_are_loaded_in_five_parts():
+    """A code object is loaded as a whole by the first call that needs one of its kernels: square, wider and narrower, 128 x 64,
+    128 x 128 with token errors, and integer tiles are one each, and the other kernels of the library are in none of them."""
+    families = [rb"gemm_dma_kernel", rb"gemm_width_kernel", rb"gemm_half_kernel", rb"gemm_small_tok_kernel", rb"gemm_i8_kernel",
+                rb"quant_row_kernel", rb"xstat_partial_kernel"]
     objects = list(code_objects(open(tlq.LIB_PATH, "rb").read()))
     where = [[i for i, o in enumerate(objects) if f in o] for f in families]
     assert all(len(w) == 1 for w in where) and len({w[0] for w in where}) == len(families), where
