@@ -28,8 +28,9 @@
 //   gemm_kernel        (gemm.hip) for row strides of 2^21 elements and more (beyond the 32-bit offsets of the others):
 //                      32x32x16 MFMA, register-staged loads.
 // They are five files because the kernels of a file are loaded together, by the first call that needs one of them, and
-// few programs need all (library, first product and first small search of a process: 9.7 ms from one file, 7.6
-// from three; without the tiles of the other files it was 6.6).
+// few programs need all (library, first product and first small search of a process: 9.7 ms with all that there were in one file, 7.6
+// in the first three; on another box 7.5 in those three and 7.9 in five, where the first product, in tiles of 128 x 64, takes 2.2
+// instead of 3.3 and the search loads the square tiles).
 // Tiling (wave64): block tile 256 x 256 outputs, k-tile 64; waves own 128 x 64
 // sub-tiles.  Both operands are K-contiguous in memory, so a fragment is one
 // 16-byte LDS read per lane.  LDS rows are 128 B (64 halves) and the eight

@@ -37,8 +37,12 @@ int xstat_chunks(int64_t n_tok) {
 // 256 x 512 input walked 32 rows each wave, 11 us against 4) and where few channels make few blocks, whose 4 waves with a
 // row each in flight leave memory idle: up to 2048 channels, and without a mask up to 5120 on chunks of more than 256 rows (us, 4
 // waves -> 16 with four rows each in flight: 24,000 x 312 13.6 -> 9.8, 64,699 x 640 46.6 -> 19.2, 153,600 x 1024 154 -> 52,
-// 44,166 x 1536 38 -> 24, 17,000 x 2048 18.8 -> 15.1, 60,000 x 4096 92 -> 79, 153,600 x 5120 247 -> 240).  Elsewhere 4, with as
-// many blocks as it takes (20,000 x 4096 27.7 and 28.3, 40,000 x 13,824 181 and 185, masked 153,600 x 5120 129 and 132).
+// 44,166 x 1536 38 -> 24, 17,000 x 2048 18.8 -> 15.1, 60,000 x 4096 91 -> 79, 33,000 x 5120 62 -> 56, 153,600 x 5120 244 -> 241).
+// Elsewhere 4, with as many blocks as it takes (4 and 16: 20,000 x 4096 27.4 and 28.4, masked 153,600 x 5120 129 and 132; 44,000 x
+// 5632 78.8 and 82.6, 60,000 x 6144 112.8 and 117.9, 100,000 x 7168 212 and 224, 153,600 x 5632 264 and 269, x 6144 276 and 290, x
+// 8192 380 and 390).  The line misses that 16 are ahead again from 10,240 channels on (60,000 x 10,240 215 and 197, 44,000 x
+// 13,824 220 and 204) and up to 33,000 rows (x 8192 110 and 94).
+// The order of a channel's sums follows the number of waves; where it shows see above.
 // NT: rows that come past the caches (153,600 x 5120: 265 -> 244 us, 6.4 TB/s).
 // MAXBITS: every block also leaves the largest magnitude (as bits) that it has seen in block_max, for the fp16
 // re-expression of bf16 tokens, which would read them all once more for it.
