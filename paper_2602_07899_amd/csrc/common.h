@@ -97,6 +97,10 @@ int xstat_chunks(int64_t n_tok);
 // 41.2 -> 41.8 and 97.8 -> 100.0; the statistic alone, calls in a row: 16 - 512 rows 7.9 -> 4.7, 1024 x 4096 7.9 -> 5.1).  Not
 // where the token maximum is taken along: a block sees 64 channels only.
 constexpr int64_t kDirectRows = 1024;
+// Channels up to which that holds for the statistic alone: one block a CU, a second round of them costs more than the other launch
+// (us two -> one, mean and maximum: 64 x 16,384 6.2 -> 5.4 and 6.7 -> 5.7, 1000 x 16,384 8.5 -> 6.4 and 9.5 -> 7.6; 64 x 18,432 6.3 -> 7.5
+// and 6.8 -> 8.7, 1000 x 18,432 10.4 -> 10.8 and 12.2 -> 14.2, 64 x 131,072 9.3 -> 21.6 and 10.2 -> 28.2).
+constexpr int64_t kDirectCols = 64 * 256;
 // pos_mask (optional): only rows r with pos_mask[r % period] != 0 take part
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kXfWaves * 64) void xstat_direct_kernel(const uint1
 hipError_t launch_xstat(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx, bool bf16,
                         int kind, double* partial, float* x_stat, hipStream_t stream,
                         const uint8_t* pos_mask, int64_t period) {
-  if (!pos_mask && n_tok <= kDirectRows) {
+  if (!pos_mask && n_tok <= kDirectRows && c_in <= kDirectCols) {
     ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
     auto go = [&](auto kern) {
       kern<<<(unsigned)ceil_div(c_in, 64), kXfWaves * 64, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, x_stat);

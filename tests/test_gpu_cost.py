@@ -55,6 +55,19 @@ def test_token_preparation_of_few_long_rows(gpu):
     assert few < 2.0 * many, (few, many)
 
 
+def test_statistic_of_few_long_rows(gpu):
+    """Rows of 262,144 channels or sixteen times as many of 16,384: twice the cost in two launches, five times where every 64
+    channels have a block of their own."""
+    import torch
+    X = torch.randn((64, 262144), device=gpu).to(torch.float16)
+    p = tlq.params(xstat_kind=1)
+    out = torch.empty(262144, dtype=torch.float32, device=gpu)
+    ws = torch.empty(tlq.x_stat_workspace_bytes(64, 262144), dtype=torch.uint8, device=gpu)
+    few, many = micros(lambda: tlq.x_stat(X, p, out, workspace=ws),
+                       lambda: tlq.x_stat(X.view(1024, 16384), p, out[:16384], workspace=ws), reps=30)
+    assert few < 3.0 * many, (few, many)
+
+
 def shifted(x):
     """A copy of x that starts one element off the 16-byte alignment of the wide paths."""
     import torch
