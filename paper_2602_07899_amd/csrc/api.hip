@@ -510,8 +510,12 @@ static tlq_status scale_search_impl(const void* X, int64_t n_tok, int64_t c_in, 
     TLQ_HIP(launch_scale_table(x_stat_in, c_in, alpha_grid, n_alpha, s.s_table, s_table_out, s.inv_table, shift_bits, st));
   } else {
     // the token maximum comes with the statistic; its per-block words pass through the operands' place, not written yet
-    // (few tokens: prepared in one launch, and the statistic and the table in another, instead of three)
-    uint32_t* block_max = prep && !(xprep_whole(n_tok, c_in) && n_tok <= kDirectRows) && xstat_block_max_words(n_tok, c_in) * sizeof(uint32_t) <=
+    // (few tokens: prepared in one launch, and the statistic and the table in another, instead of three.  A search of 264 outputs and 20
+    // candidates, us three -> two: 64 rows of 64 to 192 KB 38.7 -> 38.3, 47.9 -> 47.8, 60.2 -> 60.7; 256 rows of 128, 192, 256, 384, 512
+    // KB 28.5 -> 27.6, 31.4 -> 30.8, 31.9 -> 32.0, 35.9 -> 37.0, 39.8 -> 41.9; 1024 rows of 128, 192, 256, 512 KB 29.0 -> 26.2, 29.7 -> 29.2,
+    // 28.4 -> 28.5, 30.5 -> 33.2)
+    const bool apart = n_tok <= kDirectRows && n_tok * c_in * 2 <= 192 << 10;
+    uint32_t* block_max = prep && !apart && xstat_block_max_words(n_tok, c_in) * sizeof(uint32_t) <=
                                       (size_t)n_alpha * c_out * c_in * sizeof(uint16_t) ? (uint32_t*)s.what : nullptr;
     if (prep && !block_max) TLQ_HIP(launch_xprep(X, n_tok, c_in, ldx, s.xmax, s.xh, st));
     TLQ_HIP(launch_xstat_table(X, n_tok, c_in, ldx, bf16, p->xstat_kind, s.xs_partial, alpha_grid, n_alpha, s.s_table,
