@@ -46,7 +46,8 @@ int xstat_chunks(int64_t n_tok) {
 // NT: rows that come past the caches (153,600 x 5120: 265 -> 244 us, 6.4 TB/s).
 // MAXBITS: every block also leaves the largest magnitude (as bits) that it has seen in block_max, for the fp16
 // re-expression of bf16 tokens, which would read them all once more for it.
-template <typename T, int KIND, bool MASKED, int NW, bool MAXBITS, bool NT>
+// U: rows of a wave that are loaded together (the masked form takes four).
+template <typename T, int KIND, bool MASKED, int NW, bool MAXBITS, bool NT, int U>
 __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
     const uint16_t* __restrict__ X, int64_t n_tok, int64_t c_in, int64_t ldx, int rows_per_chunk,
     double* __restrict__ partial, const uint8_t* __restrict__ pos_mask, int64_t period, uint32_t* __restrict__ block_max) {
@@ -77,7 +78,6 @@ __global__ __launch_bounds__(NW * 64) void xstat_partial_kernel(
   };
   if (MASKED || c0 < c_in) {
     if constexpr (!MASKED) {
-      constexpr int U = NW == 16 ? 4 : 1;                       // rows of a wave that are loaded together
       int64_t r = r0 + wave;
       for (; r + (U - 1) * NW < r1; r += U * NW) {
         uint4 v[U];
@@ -185,6 +185,10 @@ static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_i
   const uint16_t* x = (const uint16_t*)X;
   ProfScope ps("xstat_partial", stream, 2.0 * (double)n_tok * (double)c_in);
   const bool wide = rows <= 128 || grid.x <= 4 || (!pos_mask && grid.x <= 10 && rows > 256);
+  // Chunks of 128 rows at most: a row a wave at a time, but the mean of many chunks of many channels four (us, one -> four, mean: 6000 x 4096
+  // 13.6 -> 13.1, 12,000 x 8192 43.4 -> 39.1, 16,384 x 8192 56.5 -> 50.5, but 6000 x 3072 11.1 -> 11.7, 12,000 x 2048 14.5 -> 15.4, 3000 x 8192
+  // 13.9 -> 14.4; maximum: 3000 x 8192 14.1 -> 16.0, 6000 x 4096 13.7 -> 15.2, 16,384 x 5120 30.2 -> 32.9, but 6000 x 8192 27.0 -> 25.2)
+  const bool shallow = rows <= 128 && (kind != 0 || chunks <= 32 || grid.x < 8);
   const bool nt = streams_past(2.0 * (double)n_tok * (double)c_in);
   auto go = [&](auto kern, int waves) {
     kern<<<grid, waves * 64, 0, stream>>>(x, n_tok, c_in, ldx, rows, partial, pos_mask, period, block_max);
@@ -193,10 +197,12 @@ static hipError_t launch_xstat_partial(const void* X, int64_t n_tok, int64_t c_i
     using T = decltype(t);
     constexpr int KIND = decltype(kind_c)::value;
     constexpr bool MASKED = decltype(masked_c)::value, MAXBITS = decltype(max_c)::value;
-    if (wide && nt) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, true>, 16);
-    else if (wide) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, false>, 16);
-    else if (nt) go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, true>, 4);
-    else go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, false>, 4);
+    constexpr int FOUR = MASKED ? 1 : 4;
+    if (shallow) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, false, 1>, 16);
+    else if (wide && nt) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, true, FOUR>, 16);
+    else if (wide) go(xstat_partial_kernel<T, KIND, MASKED, 16, MAXBITS, false, FOUR>, 16);
+    else if (nt) go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, true, 1>, 4);
+    else go(xstat_partial_kernel<T, KIND, MASKED, 4, MAXBITS, false, 1>, 4);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
