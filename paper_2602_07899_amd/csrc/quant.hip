@@ -701,7 +701,7 @@ template <typename T, bool SYM, int MODE>
 static void launch_quant(QuantDev d, hipStream_t stream) {
   // Enough blocks to fill the chip: the candidates of small matrices are split over blockIdx.y (W is
   // read again per stretch, from L2).  `waves` counts the waves of one stretch; 8192 = 8 per SIMD.
-  auto grid = [&](int64_t blocks, int64_t waves) {
+  auto grid = [&](int64_t blocks, int64_t waves, int most = 5) {
     int64_t split = waves < 8192 ? 8192 / waves : 1;
     if (split > d.n_cand) split = d.n_cand;
     d.cand_step = (int)ceil_div(d.n_cand, split);
@@ -709,7 +709,7 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
     // twenty (stores alone, 20 x 4096 x 4096: 4.3 TB/s with all candidates in a wave, 5.6 with five, 3.9 with one, which
     // reads W as often as it writes; this kernel, us by candidates a wave 2, 3, 5, 10, 20: 161, 148, 142, 151, 158; in cache,
     // 16 x 3000 x 3000 in whole rows 3, 5, 10, 16: 73, 70, 73, 89)
-    if (d.cand_step > 5) d.cand_step = (int)ceil_div(d.n_cand, ceil_div(d.n_cand, 5));
+    if (d.cand_step > most) d.cand_step = (int)ceil_div(d.n_cand, ceil_div(d.n_cand, 5));
     return dim3((unsigned)blocks, (unsigned)ceil_div(d.n_cand, d.cand_step));
   };
   // A group below 64 that is no power of two would have a wave of quant_row_kernel to its 3 to 7 chunks: whole groups
@@ -725,7 +725,10 @@ static void launch_quant(QuantDev d, hipStream_t stream) {
     };
     const bool two = R == 2 && waves_of(ceil_div(d.c_out, 2)) * d.n_cand >= 8192;
     const int64_t waves = waves_of(ceil_div(d.c_out, two ? 2 : 1));
-    const dim3 g = grid(ceil_div(waves, 4), waves);
+    // Up to nine stay together here while they fit the last-level cache, more or less: then it is the second reading of W that counts (a
+    // search, us five at most -> nine: 4096 x 4096 in groups of 128, 6 candidates (201 MB) 112.3 -> 109.3, 9 (302 MB) 238.3 -> 234.5, in
+    // groups of 40, 7 candidates 194 -> 187; 11,008 x 4096, 6 candidates (541 MB) 317 -> 347)
+    const dim3 g = grid(ceil_div(waves, 4), waves, d.n_cand <= 9 && 2.0 * d.n_cand * d.c_out * d.c_in <= 400e6 ? 9 : 5);
     if (two && d.group == 128) quant_pow2_kernel<T, SYM, MODE, R, 16><<<g, 256, 0, stream>>>(d);
     else if (two) quant_pow2_kernel<T, SYM, MODE, R, 0><<<g, 256, 0, stream>>>(d);
     else if (d.group == 128) quant_pow2_kernel<T, SYM, MODE, 1, 16><<<g, 256, 0, stream>>>(d);
