@@ -576,7 +576,7 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
   const bool by_words = !have_max && words && n_words * sizeof(uint32_t) <= room && n_words <= 4096;
   if (!have_max) {
     if (!by_words) zero_u32_kernel<<<1, 1, 0, stream>>>(xmax_bits);
-    absmax_bits_kernel<<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, by_words ? words : xmax_bits, by_words);
+    absmax_bits_kernel<<<mgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, words, by_words);
   }
   auto go = [&](auto kern) {
     kern<<<cgrid, 256, 0, stream>>>((const uint16_t*)X, n_tok, c_in, ldx, per, words, by_words ? (int)n_words : 0, xmax_bits,
@@ -592,7 +592,7 @@ hipError_t launch_xprep(const void* X, int64_t n_tok, int64_t c_in, int64_t ldx,
 // ------------------------------------------- final combine (S4) + select (S5)
 // Wave k of the block sums candidate k's tile partials in double in a fixed order (lane-strided, then a fixed
 // butterfly), scales by 1/c_out, and stores the loss as float (+inf if not finite).  Wave 0 then picks the first
-// minimum (Sec. 3.2.1 argmin) and the block copies that row of the table.  The order does not depend on the number of
+// minimum (Sec. 3.2.1 argmin, in as many exchanges as the candidates need: six for one of them were 0.5 us) and the block copies that row of the table.  The order does not depend on the number of
 // waves.  The partials are loaded 16 at a time and added in order (latency-bound, 20 candidates of 12000 tiles 167 -> 25 us, of
 // 640 tiles 13 -> 8), up to 64 of them those of eight candidates at a time.  sl: TLQ_MAX_ALPHA floats of LDS and one int.
 __device__ __forceinline__ void finalize_block(const FinalDev& f, float* sl) {
@@ -640,8 +640,7 @@ __device__ __forceinline__ void finalize_block(const FinalDev& f, float* sl) {
   if (wave == 0) {
     float bl = lane < f.n_cand ? sl[lane] : __builtin_inff();     // (n_cand <= TLQ_MAX_ALPHA = 64)
     int b = bl < __builtin_inff() ? lane : -1;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
+    for (int off = 1; off < f.n_cand; off <<= 1) {
       const float ol = __shfl_xor(bl, off, 64);
       const int ob = __shfl_xor(b, off, 64);
       if (ob >= 0 && (b < 0 || ol < bl || (ol == bl && ob < b))) { bl = ol; b = ob; }
